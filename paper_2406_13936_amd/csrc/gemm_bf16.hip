@@ -21,12 +21,14 @@
 //     8-byte vectors addressed by lanes i/4, i/4 + 4, i/4 + 8, i/4 + 12 -- i.e. four
 //     consecutive k for its own row when lane j addresses (k = j / 4, rows 4 (j % 4) ..+3).
 //   * one s_barrier per k-tile; s_waitcnt vmcnt(n) lets the younger stages stay in flight.
+//   * the 256 x 256 tile has a main loop of its own (see the note above the kernel).
 //
 // Tiling: BM x BN x BK block tile, WM x WN wavefronts of 64 lanes, each a grid of 32x32x16
 // bf16 MFMAs with fp32 accumulators.  Work-group ids are remapped so that each XCD (ids are
 // dealt round-robin to the 8 XCDs) works on a contiguous range of tiles and its L2 sees one
 // replica's operands at a time.
 #include <mutex>
+#include <utility>
 #include "abs_internal.h"
 #include "device_utils.h"
 
@@ -89,14 +91,18 @@ struct Operand {
   uint32_t voff[NI];     // per-lane byte offset of its chunk at k0 = 0 (OOB if the row is outside)
   int kofs[NI];          // k (relative to k0) of the chunk, for the ragged last k-tile
 
+  // SPREAD (k-contiguous only): stage row u holds matrix row row0 + 64 (u / 32) + u % 32, i.e. every second group of 32
+  template <bool SPREAD = false>
   __device__ __forceinline__ void init(int wave, int lane, int row0, int rows, int ld) {
+    static_assert(!(SPREAD && TRANS), "row-contiguous stages keep their rows in order");
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       const int c = (wave * NI + i) * 64 + lane;          // linear 16-byte chunk index in the stage
       if (!TRANS) {
         const int row = c / CPR, kc = (c % CPR) ^ ((row >> SWS) & (CPR - 1));
+        const int mrow = row0 + (SPREAD ? (row >> 5) * 64 + (row & 31) : row);
         kofs[i] = kc * 8;
-        voff[i] = (row0 + row < rows) ? (uint32_t)((row0 + row) * ld + kc * 8) * 2u : OOB;
+        voff[i] = (mrow < rows) ? (uint32_t)(mrow * ld + kc * 8) * 2u : OOB;
       } else {
         const int kq = c / CH, ch = (c % CH) ^ ((4 * (kq & 3)) & (CH - 1));
         kofs[i] = kq;
@@ -115,6 +121,18 @@ struct Operand {
     if (!full && kt * BK + kofs[i] >= K) v = OOB;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void *)(stage + (wave * NI + i) * 512), 16, v,
                                              soff(kt, ld), 0, 0);
+  }
+  // The whole stage from k = kbeg on, for callers that keep the number of loads in flight constant: chunks at or
+  // beyond K come back as zeros, also where the stage lies wholly beyond it (then ksafe, a multiple of BK below K,
+  // takes the place of kbeg in the scalar offset, which the range check subtracts from the operand's extent).
+  __device__ __forceinline__ void load_all(__amdgpu_buffer_rsrc_t rsrc, bf16_t *stage, int wave, int kbeg, int ksafe, int K,
+                                           int ld) const {
+    const uint32_t so = (uint32_t)(kbeg < K ? kbeg : ksafe) * (TRANS ? (uint32_t)ld * 2u : 2u);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const uint32_t v = kofs[i] < K - kbeg ? voff[i] : OOB;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void *)(stage + (wave * NI + i) * 512), 16, v, so, 0, 0);
+    }
   }
 };
 
@@ -162,6 +180,27 @@ struct Frag {
   }
 };
 
+// LDS fragment reads with the stage, row-tile and k-step as an immediate offset (inline assembly for the reason
+// given in Frag::read; the caller waits for them itself)
+template <int OFF> __device__ __forceinline__ bf16x8 lds_read_rows(uint32_t addr) {
+  bf16x8 v;
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF) : "memory");
+  return v;
+}
+template <int OFF, int NEXT4> __device__ __forceinline__ bf16x8 lds_read_cols(uint32_t addr) {
+  s16x4 lo, hi;
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(lo) : "v"(addr), "n"(OFF) : "memory");
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(hi) : "v"(addr), "n"(OFF + NEXT4) : "memory");
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+template <int V> struct Const { static constexpr int value = V; };
+template <int... I, class F> __device__ __forceinline__ void static_for_impl(std::integer_sequence<int, I...>, F &&f) {
+  (f(Const<I>{}), ...);
+}
+template <int N, class F> __device__ __forceinline__ void static_for(F &&f) {
+  static_for_impl(std::make_integer_sequence<int, N>{}, static_cast<F &&>(f));
+}
+
 // Wait until at most N LDS operations of this wave are outstanding, and make the fragments that
 // the following MFMAs read depend on that wait (needed where fragment reads are inline assembly).
 template <int N, int MI, int NI>
@@ -175,6 +214,26 @@ __device__ __forceinline__ void wait_frags(bf16x8 (&a)[MI], bf16x8 (&b)[NI]) {
 }
 
 // ---- the kernel --------------------------------------------------------------------------
+//
+// Main loop of the 256 x 256 tile.  64 KB of operands per k-tile of 64 and 256 x 256 outputs is what a CU has to take in
+// every 2048 matrix-core cycles; a fifth of it misses the XCD's L2 and comes back after 1000 to 1600 cycles, so a load that
+// is issued during the k-tile before it is needed arrives late (two 64 KB stages with one wait per k-tile: the waves
+// stood at that wait for a third of their time).  Here LDS holds the same 128 KB as eight units of 16 KB (A rows in two
+// halves h, B in two halves c, two k-tiles), each with its own life: a k-tile is four phases (h, c) of eight MFMAs per wave,
+// a phase reads one unit's fragments and refills, for the k-tile after the next, the unit that the phase before read, so every
+// load has seven phases (3500 cycles) to arrive and six units stay in flight at each wait.
+// The four waves with wm = 1 (one per SIMD) run one barrier behind those with wm = 0: while one wave of a SIMD issues its
+// MFMAs the other one reads fragments and issues loads.
+//   phase        0 (0,0)     1 (0,1)     2 (1,0)     3 (1,1)
+//   reads        A0          B1          A1          B0 of the next k-tile
+//   refills      B0          A0          B1          A1            (of k-tile + 2)
+// Why a refill cannot overtake a read: a wave waits for its own reads (lgkmcnt) before the barrier that ends its memory
+// half, and the refill is issued at the earliest one barrier after the later group's reads.  Why a read finds its data: the
+// wait in phase f covers the unit of phase f + 1, and a barrier of all waves lies between.
+// B halves: k-contiguous operands split by columns (unit c holds columns 64 j + 32 c .. + 31 of every wave column j, so that
+// a wave still owns 64 consecutive columns), row-contiguous ones by k (unit c = 32 of the 64 k: 512 bytes of a memory row).
+// Measured, 16 replicas, against the two-stage loop: inner products 8192 x 2048 x 2048 1017 -> 850 us (1.30 PFLOP/s),
+// forward 1160 -> 1043, backward-data 1110 -> 922, weight gradient with the step in its epilogue 1178 -> 993.
 template <int BM, int BN, int BK, int WM, int WN, int NS, bool AT, bool BT, int EPI, int ACT>
 __global__ void __launch_bounds__(WM * WN * 64)
 gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int nblk, const int chunk) {
@@ -189,6 +248,7 @@ gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int 
   typedef Operand<BN, BK, BT, NW> OpB;
   constexpr int NL = OpA::NI + OpB::NI;                 // load instructions per wave per stage
   static_assert((NS - 2) * NL <= 63, "vmcnt range");
+  constexpr bool PP = BM == 256 && BN == 256 && BK == 64 && WM == 2 && WN == 4;   // the pipelined main loop
 
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   bf16_t *smem = reinterpret_cast<bf16_t *>(smem_raw);
@@ -233,23 +293,6 @@ gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int 
   const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<bf16_t *>(B), 0, (int)((long long)(BT ? p.Kd : p.Nd) * p.ldb * 2), 0x00020000);
 
-  OpA oa;
-  OpB ob;
-  oa.init(wave, lane, m0, p.Md, p.lda);
-  ob.init(wave, lane, n0, p.Nd, p.ldb);
-
-  // issue the loads of stage-slot `buf` for k-tile kt whose index l satisfies l % NPART == part
-  auto issue = [&](int kt, int buf, int part) {
-    bf16_t *sa = smem + buf * STAGE, *sb = sa + BM * BK;
-    const bool full = (kt + 1) * BK <= p.Kd;
-#pragma unroll
-    for (int l = 0; l < NL; ++l) {
-      if (l % NPART != part) continue;
-      if (l < OpA::NI) oa.load(l, ra, sa, wave, kt, p.Kd, p.lda, full);
-      else ob.load(l - OpA::NI, rb, sb, wave, kt, p.Kd, p.ldb, full);
-    }
-  };
-
   f32x16 acc[MI][NI];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
@@ -258,12 +301,8 @@ gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int 
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
-  Frag<BM, BK, AT> fa[MI];
-  Frag<BN, BK, BT> fb[NI];
-#pragma unroll
-  for (int i = 0; i < MI; ++i) fa[i].init(wm * TM + i * 32, lane);
-#pragma unroll
-  for (int j = 0; j < NI; ++j) fb[j].init(wn * TN + j * 32, lane);
+  // first row of row slice i (32 rows) of this wave, relative to the tile
+  auto slice_row = [&](int i) -> int { return PP ? (i >> 1) * 128 + wm * 64 + (i & 1) * 32 : wm * TM + i * 32; };
 
   // Fused optimizer step (EPI_WGRAD_UPD): the epilogue walks this wave's slices (32 rows x TN columns) in batches of
   // UHB 16-byte chunks per lane, and the loads of batch k + 1 (parameters and optimizer state) are issued before
@@ -286,7 +325,7 @@ gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int 
   auto upd_where = [&](int bi, int u, int &m, int &n, int &row, int &cc) {
     const int c = ((bi % UBPS) * UHB + u) * 64 + lane;
     row = c / UFCPR; cc = c % UFCPR;
-    m = m0 + wm * TM + (bi / UBPS) * 32 + row;
+    m = m0 + slice_row(bi / UBPS) + row;
     n = n0 + wn * TN + cc * 4;
   };
   auto upd_prefetch = [&](int bi) {
@@ -308,69 +347,204 @@ gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int 
   if constexpr (UPD_EARLY) upd_prefetch(0);
 
   const int KT = (p.Kd + BK - 1) / BK;
+  if constexpr (PP) {
+    // ---- pipelined main loop of the 256 x 256 tile (see the note above the kernel) -----------------------------
+    typedef Operand<128, 64, AT, NW> UA;                     // A unit h: rows 128 h .. 128 h + 127 of the tile, 64 k
+    typedef Operand<BT ? 256 : 128, BT ? 32 : 64, BT, NW> UB;   // B unit c: k 32 c .. (BT), or columns 64 j + 32 c ..
+    constexpr int UNIT = 8192;                               // elements of a unit (16 KB)
+    UA ua[2];
+    UB ub[2];
 #pragma unroll
-  for (int s = 0; s < NS - 1; ++s) {
-    if (s < KT) {
-#pragma unroll
-      for (int q = 0; q < NPART; ++q) issue(s, s, q);
+    for (int h = 0; h < 2; ++h) {
+      ua[h].init(wave, lane, m0 + h * 128, p.Md, p.lda);
+      if constexpr (BT) ub[h].init(wave, lane, n0, p.Nd, p.ldb);
+      else ub[h].template init<true>(wave, lane, n0 + h * 32, p.Nd, p.ldb);
     }
-  }
-
-  for (int kt = 0; kt < KT; ++kt) {
-    // k-tile kt has landed once only the loads of the younger in-flight stages are outstanding
-    if (kt + NS - 1 <= KT) wait_vmcnt<(NS - 2) * NL>(); else wait_vmcnt<0>();
-    __builtin_amdgcn_s_barrier();      // all waves' loads of kt visible; everyone is done with kt-1
-    const bool more = kt + NS - 1 < KT;
-    const bf16_t *S = smem + (kt % NS) * STAGE;
-    // fragments are double-buffered in registers: the LDS reads of MFMA group kk+1 and this
-    // group's share of the next stage's global loads are issued before the MFMAs of group kk,
-    // which then run as one raised-priority cluster
-    bf16x8 af[2][MI], bfr[2][NI];
-    // transpose reads (untracked by the compiler's lgkmcnt accounting) go first, so that the
-    // newest outstanding reads are always the ones the compiler counts
-    if (BT && !AT) {
+    auto load_a = [&](int kt, int slot, int h) {
+      ua[h].load_all(ra, smem + (slot * 2 + h) * UNIT, wave, kt * 64, 0, p.Kd, p.lda);
+    };
+    auto load_b = [&](int kt, int slot, int c) {
+      ub[c].load_all(rb, smem + (4 + slot * 2 + c) * UNIT, wave, kt * 64 + (BT ? c * 32 : 0), 0, p.Kd, p.ldb);
+    };
+    // LDS byte addresses of this lane's fragments in unit 0; everything else is an immediate offset
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void *)smem;
+    const int half = lane >> 5, l32 = lane & 31, i16 = lane & 15, g16 = lane >> 4;
+    const int kq = (g16 >> 1) * 8 + (i16 >> 2);              // transpose reads: k within the 16-wide step
+    uint32_t aaddr[AT ? 2 : 4], baddr[BT ? 2 : 4];
+    if constexpr (AT) {
 #pragma unroll
-      for (int j = 0; j < NI; ++j) bfr[0][j] = fb[j].read(S + BM * BK, 0);
-    }
-#pragma unroll
-    for (int i = 0; i < MI; ++i) af[0][i] = fa[i].read(S, 0);
-    if (!(BT && !AT)) {
-#pragma unroll
-      for (int j = 0; j < NI; ++j) bfr[0][j] = fb[j].read(S + BM * BK, 0);
-    }
-#pragma unroll
-    for (int kk = 0; kk < NPART; ++kk) {
-      const int cur = kk & 1, nxt = cur ^ 1;
-      if (kk + 1 < NPART) {
-        if (BT && !AT) {
-#pragma unroll
-          for (int j = 0; j < NI; ++j) bfr[nxt][j] = fb[j].read(S + BM * BK, kk + 1);
-        }
-#pragma unroll
-        for (int i = 0; i < MI; ++i) af[nxt][i] = fa[i].read(S, kk + 1);
-        if (!(BT && !AT)) {
-#pragma unroll
-          for (int j = 0; j < NI; ++j) bfr[nxt][j] = fb[j].read(S + BM * BK, kk + 1);
-        }
+      for (int ii = 0; ii < 2; ++ii) {
+        const int rr = wm * 64 + ii * 32 + (g16 & 1) * 16 + 4 * (i16 & 3);
+        aaddr[ii] = lds0 + 2u * (uint32_t)(kq * 128 + ((rr >> 3) ^ (4 * (kq & 3))) * 8 + (rr & 7));
       }
-      if (more) issue(kt + NS - 1, (kt + NS - 1) % NS, kk);
-      if (AT || BT) {
-        // LDS reads issued per MFMA group (transpose reads count two per fragment); the reads of
-        // group kk + 1, if any, are the newest ones and may stay outstanding
-        constexpr int RD = (AT ? 2 : 1) * MI + (BT ? 2 : 1) * NI;
-        if (kk + 1 < NPART) wait_frags<RD>(af[cur], bfr[cur]); else wait_frags<0>(af[cur], bfr[cur]);
+    } else {
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk)
+        aaddr[kk] = lds0 + (uint32_t)((wm * 64 + l32) * 128 + (((kk * 2 + half) ^ ((l32 >> 1) & 7)) << 4));
+    }
+    if constexpr (BT) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int rr = wn * 64 + j * 32 + (g16 & 1) * 16 + 4 * (i16 & 3);
+        baddr[j] = lds0 + 65536u + 2u * (uint32_t)(kq * 256 + ((rr >> 3) ^ (4 * (kq & 3))) * 8 + (rr & 7));
       }
+    } else {
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk)
+        baddr[kk] = lds0 + 65536u + (uint32_t)((wn * 32 + l32) * 128 + (((kk * 2 + half) ^ ((l32 >> 1) & 7)) << 4));
+    }
+    bf16x8 fa[2][4], fb[2][4];                               // fa[row tile][k-step]; fb[unit][k-step (BT: 2 col tile + k-step)]
+    auto read_a = [&](auto SLOT, auto H) {
+      constexpr int U = (decltype(SLOT)::value * 2 + decltype(H)::value) * UNIT * 2;
+      static_for<8>([&](auto I) {
+        constexpr int kk = decltype(I)::value >> 1, ii = decltype(I)::value & 1;
+        if constexpr (AT) fa[ii][kk] = lds_read_cols<U + kk * 4096, 1024>(aaddr[ii]);
+        else fa[ii][kk] = lds_read_rows<U + ii * 4096>(aaddr[kk]);
+      });
+    };
+    auto read_b = [&](auto SLOT, auto C) {
+      constexpr int c = decltype(C)::value, U = (decltype(SLOT)::value * 2 + c) * UNIT * 2;
+      static_for<4>([&](auto I) {
+        constexpr int q = decltype(I)::value;
+        if constexpr (BT) fb[c][q] = lds_read_cols<U + (q & 1) * 8192, 2048>(baddr[q >> 1]);
+        else fb[c][q] = lds_read_rows<U>(baddr[q]);
+      });
+    };
+    auto close_reads = [&]() {                               // this wave's fragment reads are done
+      __builtin_amdgcn_s_waitcnt(0xC07F);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) asm volatile("" : "+v"(fa[0][q]), "+v"(fa[1][q]), "+v"(fb[0][q]), "+v"(fb[1][q]));
+    };
+    auto phase = [&](auto SLOT, auto F, int kt) {
+      constexpr int f = decltype(F)::value, h = f >> 1, c = f & 1;
+      // memory half: this phase's fragments, and the unit two k-tiles ahead that takes the place read last phase
+      if constexpr (f == 0) { read_a(SLOT, Const<0>{}); load_b(kt + 2, SLOT.value, 0); }
+      if constexpr (f == 1) { read_b(SLOT, Const<1>{}); load_a(kt + 2, SLOT.value, 0); }
+      if constexpr (f == 2) { read_a(SLOT, Const<1>{}); load_b(kt + 2, SLOT.value, 1); }
+      if constexpr (f == 3) { read_b(Const<1 - decltype(SLOT)::value>{}, Const<0>{}); load_a(kt + 2, SLOT.value, 1); }
+      wait_vmcnt<12>();                                      // the unit read next phase has landed; six more stay in flight
+      close_reads();
+      __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
       __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-      for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NI; ++j)
-          // operands swapped: the accumulator tile is C^T, so a lane owns one row m of C and
-          // groups of four consecutive columns n (see the epilogue)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[cur][j], af[cur][i], acc[i][j], 0, 0, 0);
+      static_for<8>([&](auto I) {
+        constexpr int q = decltype(I)::value;
+        if constexpr (BT) {
+          constexpr int kk = q >> 2, ii = (q >> 1) & 1, j = q & 1;
+          acc[2 * h + ii][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[c][2 * j + kk], fa[ii][2 * c + kk], acc[2 * h + ii][j], 0, 0, 0);
+        } else {
+          constexpr int kk = q >> 1, ii = q & 1;
+          acc[2 * h + ii][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[c][kk], fa[ii][kk], acc[2 * h + ii][c], 0, 0, 0);
+        }
+      });
       __builtin_amdgcn_s_setprio(0);
       __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_barrier();
+    };
+    auto ktile = [&](auto SLOT, int kt) { static_for<4>([&](auto F) { phase(SLOT, F, kt); }); };
+#pragma unroll
+    for (int s = 0; s < 2; ++s) { load_b(s, s, 0); load_a(s, s, 0); load_b(s, s, 1); load_a(s, s, 1); }
+    wait_vmcnt<12>();
+    __builtin_amdgcn_s_barrier();
+    read_b(Const<0>{}, Const<0>{});
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    __builtin_amdgcn_s_barrier();
+    if (wm == 1) __builtin_amdgcn_s_barrier();               // these four waves run half a phase behind
+    for (int kt = 0; kt < KT; kt += 2) {
+      ktile(Const<0>{}, kt);
+      if (kt + 1 < KT) ktile(Const<1>{}, kt + 1);
+    }
+    if (wm == 0) __builtin_amdgcn_s_barrier();
+    wait_vmcnt<0>();                                         // (zeros beyond K still on their way to LDS)
+  } else {
+    OpA oa;
+    OpB ob;
+    oa.init(wave, lane, m0, p.Md, p.lda);
+    ob.init(wave, lane, n0, p.Nd, p.ldb);
+
+    // issue the loads of stage-slot `buf` for k-tile kt whose index l satisfies l % NPART == part
+    auto issue = [&](int kt, int buf, int part) {
+      bf16_t *sa = smem + buf * STAGE, *sb = sa + BM * BK;
+      const bool full = (kt + 1) * BK <= p.Kd;
+#pragma unroll
+      for (int l = 0; l < NL; ++l) {
+        if (l % NPART != part) continue;
+        if (l < OpA::NI) oa.load(l, ra, sa, wave, kt, p.Kd, p.lda, full);
+        else ob.load(l - OpA::NI, rb, sb, wave, kt, p.Kd, p.ldb, full);
+      }
+    };
+
+    Frag<BM, BK, AT> fa[MI];
+    Frag<BN, BK, BT> fb[NI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) fa[i].init(wm * TM + i * 32, lane);
+#pragma unroll
+    for (int j = 0; j < NI; ++j) fb[j].init(wn * TN + j * 32, lane);
+
+#pragma unroll
+    for (int s = 0; s < NS - 1; ++s) {
+      if (s < KT) {
+#pragma unroll
+        for (int q = 0; q < NPART; ++q) issue(s, s, q);
+      }
+    }
+
+    for (int kt = 0; kt < KT; ++kt) {
+      // k-tile kt has landed once only the loads of the younger in-flight stages are outstanding
+      if (kt + NS - 1 <= KT) wait_vmcnt<(NS - 2) * NL>(); else wait_vmcnt<0>();
+      __builtin_amdgcn_s_barrier();      // all waves' loads of kt visible; everyone is done with kt-1
+      const bool more = kt + NS - 1 < KT;
+      const bf16_t *S = smem + (kt % NS) * STAGE;
+      // fragments are double-buffered in registers: the LDS reads of MFMA group kk+1 and this
+      // group's share of the next stage's global loads are issued before the MFMAs of group kk,
+      // which then run as one raised-priority cluster
+      bf16x8 af[2][MI], bfr[2][NI];
+      // transpose reads (untracked by the compiler's lgkmcnt accounting) go first, so that the
+      // newest outstanding reads are always the ones the compiler counts
+      if (BT && !AT) {
+#pragma unroll
+        for (int j = 0; j < NI; ++j) bfr[0][j] = fb[j].read(S + BM * BK, 0);
+      }
+#pragma unroll
+      for (int i = 0; i < MI; ++i) af[0][i] = fa[i].read(S, 0);
+      if (!(BT && !AT)) {
+#pragma unroll
+        for (int j = 0; j < NI; ++j) bfr[0][j] = fb[j].read(S + BM * BK, 0);
+      }
+#pragma unroll
+      for (int kk = 0; kk < NPART; ++kk) {
+        const int cur = kk & 1, nxt = cur ^ 1;
+        if (kk + 1 < NPART) {
+          if (BT && !AT) {
+#pragma unroll
+            for (int j = 0; j < NI; ++j) bfr[nxt][j] = fb[j].read(S + BM * BK, kk + 1);
+          }
+#pragma unroll
+          for (int i = 0; i < MI; ++i) af[nxt][i] = fa[i].read(S, kk + 1);
+          if (!(BT && !AT)) {
+#pragma unroll
+            for (int j = 0; j < NI; ++j) bfr[nxt][j] = fb[j].read(S + BM * BK, kk + 1);
+          }
+        }
+        if (more) issue(kt + NS - 1, (kt + NS - 1) % NS, kk);
+        if (AT || BT) {
+          // LDS reads issued per MFMA group (transpose reads count two per fragment); the reads of
+          // group kk + 1, if any, are the newest ones and may stay outstanding
+          constexpr int RD = (AT ? 2 : 1) * MI + (BT ? 2 : 1) * NI;
+          if (kk + 1 < NPART) wait_frags<RD>(af[cur], bfr[cur]); else wait_frags<0>(af[cur], bfr[cur]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+          for (int j = 0; j < NI; ++j)
+            // operands swapped: the accumulator tile is C^T, so a lane owns one row m of C and
+            // groups of four consecutive columns n (see the epilogue)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[cur][j], af[cur][i], acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_s_setprio(0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
   }
 
@@ -428,7 +602,7 @@ gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int 
   uint4 ereg[2][SIT];
   const bf16_t *Eg = p.E ? static_cast<const bf16_t *>(p.E) + (long long)g * p.sEg : nullptr;
   constexpr bool USES_E = EPI == EPI_IPDOT || (EPI == EPI_BWD && ACT != ACT_NONE);
-  if (USES_E) load_slice(Eg, p.lde, m0 + wm * TM, p.Nd, ereg[0]);
+  if (USES_E) load_slice(Eg, p.lde, m0 + slice_row(0), p.Nd, ereg[0]);
   // staging -> global
   auto stage_out = [&](bf16_t *dst, int ld, int mrow0, int ncols) {
 #pragma unroll
@@ -466,8 +640,8 @@ gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int 
   if (EPI == EPI_IPDOT) {
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-      const int mrow0 = m0 + wm * TM + i * 32;
-      if (i + 1 < MI) load_slice(Eg, p.lde, mrow0 + 32, p.Nd, ereg[(i + 1) & 1]);
+      const int mrow0 = m0 + slice_row(i);
+      if (i + 1 < MI) load_slice(Eg, p.lde, m0 + slice_row(i + 1), p.Nd, ereg[(i + 1) & 1]);
       put_slice(ereg[i & 1]);
       float rs = 0.0f;
 #pragma unroll
@@ -483,7 +657,7 @@ gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int 
           }
         }
       rs += __shfl_xor(rs, 32, 64);                               // the two column halves of the row
-      if (lhalf == 0) red[wn * BM + wm * TM + i * 32 + lcol] = rs;
+      if (lhalf == 0) red[wn * BM + slice_row(i) + lcol] = rs;
     }
     finish_rows();
     return;
@@ -495,7 +669,7 @@ gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int 
     const int ncols = p.pad_to_ld ? p.ldc : p.Nd;           // pad columns are written as zeros
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-      const int mrow0 = m0 + wm * TM + i * 32;
+      const int mrow0 = m0 + slice_row(i);
       uint2 dpk[NI][4];
       float rs = 0.0f;
 #pragma unroll
@@ -517,7 +691,7 @@ gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int 
         }
       if (p.part) {
         rs += __shfl_xor(rs, 32, 64);
-        if (lhalf == 0) red[wn * BM + wm * TM + i * 32 + lcol] = rs;
+        if (lhalf == 0) red[wn * BM + slice_row(i) + lcol] = rs;
       }
       stage_out(C, p.ldc, mrow0, ncols);
       if (ACT == ACT_GELU && C2) {
@@ -541,9 +715,9 @@ gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int 
     for (int c = 0; c < (TN + 63) / 64; ++c) cs[c] = 0.0f;
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-      const int mrow0 = m0 + wm * TM + i * 32;
+      const int mrow0 = m0 + slice_row(i);
       if (ACT != ACT_NONE) {
-        if (i + 1 < MI) load_slice(Eg, p.lde, mrow0 + 32, p.Nd, ereg[(i + 1) & 1]);
+        if (i + 1 < MI) load_slice(Eg, p.lde, m0 + slice_row(i + 1), p.Nd, ereg[(i + 1) & 1]);
         put_slice(ereg[i & 1]);
       }
       float rs = 0.0f;
@@ -571,7 +745,7 @@ gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int 
         }
       if (p.part) {
         rs += __shfl_xor(rs, 32, 64);
-        if (lhalf == 0) red[wn * BM + wm * TM + i * 32 + lcol] = rs;
+        if (lhalf == 0) red[wn * BM + slice_row(i) + lcol] = rs;
       }
       stage_out(C, p.ldc, mrow0, ncols);
       if (p.cpart) {
@@ -682,7 +856,7 @@ gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int 
   }
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
-    const int mrow0 = m0 + wm * TM + i * 32;
+    const int mrow0 = m0 + slice_row(i);
 #pragma unroll
     for (int j = 0; j < NI; ++j)
 #pragma unroll

@@ -1,0 +1,75 @@
+"""GPU parity of single kernels at the sizes where their tiling can go wrong, against fp64 arithmetic or the CPU oracle."""
+import numpy as np
+import pytest
+
+from oracle import abs_oracle as O
+from paper_2406_13936_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+EPS32 = 2.0 ** -24      # half a unit in the last place of fp32 (round to nearest), relative
+EPSBF = 2.0 ** -9       # the same for bf16
+
+
+def _A():
+    import paper_2406_13936_amd as A
+    return A
+
+
+# The 256 x 256 tile's pipelined main loop reads two k-tiles of 64 ahead: reductions of one, two, three, an odd number of
+# k-tiles and ragged last k-tiles, with row and column remainders (K of the inner products = fin, of the gradient = b).
+@pytest.mark.parametrize("b,fin,fout", [(1030, 8, 1032), (1024, 64, 1024), (1025, 72, 1100 // 8 * 8), (1100, 136, 1048),
+                                        (1031, 264, 1024), (257, 1032, 1040), (330, 1024, 1096), (1027, 1088, 1160)])
+def test_large_tile_contractions_at_the_edges_of_the_reduction(b, fin, fout):
+    import torch
+    A = _A()
+    M = 16 if b < 1024 else 2        # (the large tile is taken for short reductions only if it fills the chip)
+    g = torch.Generator().manual_seed(b + fin)
+    a = torch.randn((M, b, fin), generator=g).to(torch.bfloat16)
+    d = torch.randn((M, b, fout), generator=g).to(torch.bfloat16)
+    res, n, q, gbar = A.layer_stats([a.cuda()], [d.cuda()], want_per_sample=True, want_gbar=True)
+    for m in (0, M - 1):
+        a64, d64 = a[m].double().numpy(), d[m].double().numpy()
+        G, Gabs = d64.T @ a64 / b, np.abs(d64).T @ np.abs(a64) / b
+        # a sum of b products in fp32, any order: (b + 1) roundings of at most the sum of magnitudes; one more for 1 / b
+        err = np.abs(gbar[m].cpu().numpy().reshape(fout, fin) - G)
+        assert (err <= (b + 2) * EPS32 * Gabs).all(), (m, err.max())
+        want = (d64 * (a64 @ G.T)).sum(1)
+        # Gbar rounded to bf16 as the operand, then fin products and fout products summed in fp32
+        bound = (EPSBF * (1 + 2 ** -8) + (b + fin + fout + 4) * EPS32) * (np.abs(d64) * (np.abs(a64) @ Gabs.T)).sum(1)
+        assert (np.abs(q[m].cpu().numpy() - want) <= bound).all(), m
+        # (the bound above cannot tell a wrong entry of a long sum: the spread of the differences does)
+        assert np.linalg.norm(q[m].cpu().numpy() - want) <= 1e-3 * np.linalg.norm(want), m
+        np.testing.assert_allclose(n[m].cpu().numpy(), (a64 ** 2).sum(1) * (d64 ** 2).sum(1), rtol=(fin + fout + 4) * EPS32)
+        assert abs(res[m].gbar_sq - (G ** 2).sum()) <= 1e-5 * (G ** 2).sum()
+
+
+# Forward and backward-data in the same tile: reductions of 72 (two k-tiles, ragged), 1032 (17 k-tiles) and 10 / 130 classes.
+@pytest.mark.parametrize("dims,act", [((72, 1032, 1040, 130), W.ACT_GELU), ((64, 1048, 1024, 10), W.ACT_RELU)])
+def test_large_tile_step_at_the_edges_of_the_reduction(dims, act):
+    A = _A()
+    b, M = 1030, 2
+    w = W.Workload("edges", dims, act, True, W.PREC_BF16, N=2048, M=M, H=1, rounds=1, b0=b, b_cap=b, opt=W.OPT_SHB, lr=0.05,
+                   momentum=0.9, test=W.TEST_IP, theta=0.9, data="teacher_mlp", seed=5)
+    X, y = W.make_dataset(w)
+    x0 = W.make_x0(w)
+    rep = A.Replicas.from_workload(w, X, y, x0)
+    orc = O.Replicas(O.Net(w.dims, w.act, True), x0, X, y, M, opt=w.opt, momentum=w.momentum, mixed=True, want_ip=True)
+    try:
+        for h in range(2):
+            idx = W.step_indices(w, 0, h, b)
+            rep.local_step(idx, w.lr)
+            g = rep.inner_product_test(w.theta)
+            orc.local_step(idx, w.lr)
+            for m in range(M):
+                s = orc.stats[m]
+                for got, want in ((g[m].sum_sq, s["S1"]), (g[m].gbar_sq, s["S2"]), (g[m].sum_q, s["S4"]),
+                                  (g[m].sum_q2, s["S3"]), (g[m].loss_sum, s["loss_sum"])):
+                    assert abs(got - want) <= 2e-3 * abs(want), (h, m, got, want)
+                grad = rep.get_grad(m).astype(np.float64)
+                assert np.linalg.norm(grad - orc.grads[m]) <= 2e-3 * np.linalg.norm(orc.grads[m]), (h, m)
+                p = rep.get_params(m).astype(np.float64)
+                assert np.abs(p - orc.x[m]).max() <= 1e-3 * np.abs(orc.x[m]).max()
+        assert rep.guard_intact()
+    finally:
+        rep.close()
