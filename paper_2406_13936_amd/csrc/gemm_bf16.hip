@@ -234,7 +234,7 @@ __device__ __forceinline__ void wait_frags(bf16x8 (&a)[MI], bf16x8 (&b)[NI]) {
 // a wave still owns 64 consecutive columns), row-contiguous ones by k (unit c = 32 of the 64 k: 512 bytes of a memory row).
 // Measured, 16 replicas, against the two-stage loop: inner products 8192 x 2048 x 2048 1017 -> 850 us (1.30 PFLOP/s),
 // forward 1160 -> 1043, backward-data 1110 -> 922, weight gradient with the step in its epilogue 1178 -> 993.
-template <int BM, int BN, int BK, int WM, int WN, int NS, bool AT, bool BT, int EPI, int ACT>
+template <int BM, int BN, int BK, int WM, int WN, int NS, bool PP, bool AT, bool BT, int EPI, int ACT>
 __global__ void __launch_bounds__(WM * WN * 64)
 gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int nblk, const int chunk) {
   constexpr int NW = WM * WN, NT = NW * 64;
@@ -248,7 +248,7 @@ gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int 
   typedef Operand<BN, BK, BT, NW> OpB;
   constexpr int NL = OpA::NI + OpB::NI;                 // load instructions per wave per stage
   static_assert((NS - 2) * NL <= 63, "vmcnt range");
-  constexpr bool PP = BM == 256 && BN == 256 && BK == 64 && WM == 2 && WN == 4;   // the pipelined main loop
+  static_assert(!PP || (BM == 256 && BN == 256 && BK == 64 && WM == 2 && WN == 4 && NS == 2), "the pipelined main loop");
 
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   bf16_t *smem = reinterpret_cast<bf16_t *>(smem_raw);
@@ -902,7 +902,7 @@ gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int 
   }
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int NS, bool AT, bool BT, int EPI, int ACT>
+template <int BM, int BN, int BK, int WM, int WN, int NS, bool PP, bool AT, bool BT, int EPI, int ACT>
 hipError_t launch_cfg(const GemmP &p, hipStream_t s) {
   constexpr int NT = WM * WN * 64;
   constexpr size_t tile_bytes = (size_t)NS * (BM + BN) * BK * sizeof(bf16_t);
@@ -911,7 +911,7 @@ hipError_t launch_cfg(const GemmP &p, hipStream_t s) {
   constexpr size_t epi_bytes = epi_bf16 > epi_f32 ? epi_bf16 : epi_f32;
   constexpr size_t lds = tile_bytes > epi_bytes ? tile_bytes : epi_bytes;
   static_assert(lds <= 160 * 1024, "LDS budget");
-  auto kern = gemm_bf16_kernel<BM, BN, BK, WM, WN, NS, AT, BT, EPI, ACT>;
+  auto kern = gemm_bf16_kernel<BM, BN, BK, WM, WN, NS, PP, AT, BT, EPI, ACT>;
   // once per kernel variant, also when several host threads (each with a context of its own) launch it first together
   static std::once_flag attr_once;
   static hipError_t attr_err = hipSuccess;
@@ -928,19 +928,27 @@ hipError_t launch_cfg(const GemmP &p, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Reductions up to this length keep the two-stage loop in 256 x 256 tiles: the pipelined loop fetches two k-tiles beyond the
+// last one and starts later, which a handful of k-tiles does not pay back (784-512-512-10, 8 replicas, b = 4096, one tile
+// per CU: 285.7 us per step with the pipelined loop everywhere, 281.9 with this line at 512, 283.0 at 1024; 1024-wide
+// layers, K = 1024, b = 4096: 2184 us with the two-stage loop, 2006 with the pipelined one).
+constexpr int PIPE_MIN_K = 512;
+
 // Tile shape by problem size: the large shape when both output extents fill it,
 // otherwise a 128x128 (or 128x64 for narrow outputs, 64x128 for outputs of at most 64 rows) tile.
 template <bool AT, bool BT, int EPI, int ACT>
 hipError_t launch_shape(const GemmP &p, hipStream_t s) {
   constexpr bool IS_WGRAD = EPI == EPI_WGRAD || EPI == EPI_WGRAD_UPD;
   switch (IS_WGRAD ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr) : gemm_bf16_tile_shape(p.Md, p.Nd, p.groups)) {
-    case 0: return launch_cfg<128, 64, 64, 4, 1, 3, AT, BT, EPI, ACT>(p, s);
+    case 0: return launch_cfg<128, 64, 64, 4, 1, 3, false, AT, BT, EPI, ACT>(p, s);
     case 3:
-      if constexpr (IS_WGRAD) return launch_cfg<64, 256, 32, 1, 4, 2, AT, BT, EPI, ACT>(p, s);
+      if constexpr (IS_WGRAD) return launch_cfg<64, 256, 32, 1, 4, 2, false, AT, BT, EPI, ACT>(p, s);
       else return hipErrorInvalidValue;
-    case 2: return launch_cfg<256, 256, 64, 2, 4, 2, AT, BT, EPI, ACT>(p, s);
+    case 2:
+      if constexpr (!IS_WGRAD) if (p.Kd <= PIPE_MIN_K) return launch_cfg<256, 256, 64, 2, 4, 2, false, AT, BT, EPI, ACT>(p, s);
+      return launch_cfg<256, 256, 64, 2, 4, 2, true, AT, BT, EPI, ACT>(p, s);
     case 4:
-      if constexpr (!IS_WGRAD) return launch_cfg<64, 128, 64, 2, 2, 6, AT, BT, EPI, ACT>(p, s);
+      if constexpr (!IS_WGRAD) return launch_cfg<64, 128, 64, 2, 2, 6, false, AT, BT, EPI, ACT>(p, s);
       else return hipErrorInvalidValue;
     default: {
       // Two stages (64 KB) let two work-groups share a CU; a deeper ring keeps one work-group fed through a long
@@ -950,8 +958,8 @@ hipError_t launch_shape(const GemmP &p, hipStream_t s) {
       // flight: such launches are bound by the latency of their operand stream) otherwise.
       const long long nblk = (long long)((p.Md + 127) / 128) * ((p.Nd + 127) / 128) * p.groups *
                              ((EPI == EPI_WGRAD && p.ksplit > 1) ? p.ksplit : 1);
-      if (p.Kd <= 1024 || nblk > 256) return launch_cfg<128, 128, 64, 2, 2, 2, AT, BT, EPI, ACT>(p, s);
-      return launch_cfg<128, 128, 64, 2, 2, 4, AT, BT, EPI, ACT>(p, s);
+      if (p.Kd <= 1024 || nblk > 256) return launch_cfg<128, 128, 64, 2, 2, 2, false, AT, BT, EPI, ACT>(p, s);
+      return launch_cfg<128, 128, 64, 2, 2, 4, false, AT, BT, EPI, ACT>(p, s);
     }
   }
 }
