@@ -39,7 +39,7 @@ struct Plan {
   size_t colpart_per = 0;              // floats of column-partial scratch per replica (fp32 mode: one piece for all layers)
   size_t o_colpart_l[MAXL + 1] = {0};  // bf16 mode: one piece per layer, so that one launch can finish all bias gradients
   size_t colpart_l_per[MAXL + 1] = {0};
-  int rparts[MAXL + 1] = {0};          // partial vectors kept for the row norms of width dims[l]
+  size_t rpart_floats[MAXL + 1] = {0}; // floats per replica for the partial row norms of width dims[l]
   // byte offsets into the workspace
   size_t o_xm = 0, o_xs = 0, o_grad = 0, o_gradbf = 0, o_v = 0, o_m = 0, o_Xbf = 0;
   size_t o_A[MAXL] = {0}, o_Dact[MAXL] = {0}, o_Dl[MAXL + 1] = {0};
@@ -121,9 +121,9 @@ void make_plan(const abs_config *c, long long N, Plan &pl) {
     pl.o_U = take(MB * mx * 4);
   }
   for (int l = 0; l <= pl.L; ++l)
-    pl.rparts[l] = (pl.bf16 && l >= 1 && l < pl.L) ? gemm_bf16_ipdot_parts(pl.dims[l]) : 1;
-  for (int l = 0; l < pl.L; ++l) pl.o_an[l] = take(MB * 4 * pl.rparts[l]);
-  for (int l = 1; l <= pl.L; ++l) pl.o_dn[l] = take(MB * 4 * pl.rparts[l]);
+    pl.rpart_floats[l] = (pl.bf16 && l >= 1 && l < pl.L) ? gemm_bf16_row_part_floats(pl.dims[l], pl.M, pl.cap) : (size_t)pl.cap;
+  for (int l = 0; l < pl.L; ++l) pl.o_an[l] = take(4 * (size_t)pl.M * pl.rpart_floats[l]);
+  for (int l = 1; l <= pl.L; ++l) pl.o_dn[l] = take(4 * (size_t)pl.M * pl.rpart_floats[l]);
   pl.o_loss = take(MB * 4);
   pl.o_nout = take(MB * 4);
   pl.o_qout = take(MB * 4);
@@ -200,17 +200,17 @@ int choose_ksplit(int shape, long long tiles, int KT, double outputs, size_t kpa
 // Event-timed launch classes (abs_profile_*): one entry per kernel symbol of interest.
 enum {
   T_GATHER = 0, T_SOFTMAX, T_ROWNORM, T_COLSUM, T_STATS, T_UPDATE, T_AVERAGE, T_ROWDOT, T_GRAM,
-  T_GEMM0,                       // + epi * 5 + tile shape (bf16) ; fp32 family uses shape 1
-  T_GEMM_KINDS = 5 * 5, T_LAYERS = 17,   // GEMM classes are resolved per layer
+  T_GEMM0,                       // + epi * 6 + tile shape (bf16) ; fp32 family uses shape 1
+  T_GEMM_KINDS = 5 * 6, T_LAYERS = 17,   // GEMM classes are resolved per layer
   T_COUNT = T_GEMM0 + T_GEMM_KINDS * T_LAYERS
 };
 static const char *const kTagNames[T_GEMM0 + T_GEMM_KINDS] = {
   "gather_rows", "softmax_ce", "row_sqnorm", "col_sum", "stats", "update", "average", "rowdot", "gram_ip",
-  "gemm_fwd_128x64", "gemm_fwd_128x128", "gemm_fwd_256x256", "gemm_fwd_64x256", "gemm_fwd_64x128",
-  "gemm_logits_128x64", "gemm_logits_128x128", "gemm_logits_256x256", "gemm_logits_64x256", "gemm_logits_64x128",
-  "gemm_bwd_128x64", "gemm_bwd_128x128", "gemm_bwd_256x256", "gemm_bwd_64x256", "gemm_bwd_64x128",
-  "gemm_wgrad_128x64", "gemm_wgrad_128x128", "gemm_wgrad_256x256", "gemm_wgrad_64x256", "gemm_wgrad_64x128",
-  "gemm_ipdot_128x64", "gemm_ipdot_128x128", "gemm_ipdot_256x256", "gemm_ipdot_64x256", "gemm_ipdot_64x128"};
+  "gemm_fwd_128x64", "gemm_fwd_128x128", "gemm_fwd_256x256", "gemm_fwd_64x256", "gemm_fwd_64x128", "gemm_fwd_32x32",
+  "gemm_logits_128x64", "gemm_logits_128x128", "gemm_logits_256x256", "gemm_logits_64x256", "gemm_logits_64x128", "gemm_logits_32x32",
+  "gemm_bwd_128x64", "gemm_bwd_128x128", "gemm_bwd_256x256", "gemm_bwd_64x256", "gemm_bwd_64x128", "gemm_bwd_32x64",
+  "gemm_wgrad_128x64", "gemm_wgrad_128x128", "gemm_wgrad_256x256", "gemm_wgrad_64x256", "gemm_wgrad_64x128", "gemm_wgrad_32x32",
+  "gemm_ipdot_128x64", "gemm_ipdot_128x128", "gemm_ipdot_256x256", "gemm_ipdot_64x256", "gemm_ipdot_64x128", "gemm_ipdot_32x32"};
 
 struct ProfRec { int tag; hipEvent_t e0, e1; double flops, bytes; };
 
@@ -312,7 +312,7 @@ struct ProfScope {
 
 hipError_t gemm(abs_ctx *c, const GemmP &p, int epi, int layer) {
   int shape = !c->pl.bf16 ? 1 : (epi == EPI_WGRAD ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr)
-                                                   : gemm_bf16_tile_shape(p.Md, p.Nd, p.groups));
+                                                   : gemm_bf16_tile_shape(epi, p.Md, p.Nd, p.groups));
   // algorithmic bytes of the launch: both operands once, the outputs once, the epilogue's elementwise operand once
   const double e = c->pl.esz, mn = (double)p.Md * p.Nd;
   double bytes = ((double)p.Md + p.Nd) * p.Kd * e;
@@ -322,7 +322,7 @@ hipError_t gemm(abs_ctx *c, const GemmP &p, int epi, int layer) {
   else if (epi == EPI_IPDOT) bytes += mn * e;
   else if (p.upd_x) bytes += mn * (8 + (p.upd_v ? 8 : 0) + (p.upd_m ? 8 : 0) + (p.upd_shadow ? 2 : 0) + (p.C2 ? 2 : 0));
   else bytes += mn * (4 + (p.C2 ? 2 : 0) + (p.accumulate ? 4 : 0));
-  ProfScope ps(c, T_GEMM0 + (epi * 5 + shape) * T_LAYERS + layer, 2.0 * p.Md * p.Nd * p.Kd * p.groups, bytes * p.groups);
+  ProfScope ps(c, T_GEMM0 + (epi * 6 + shape) * T_LAYERS + layer, 2.0 * p.Md * p.Nd * p.Kd * p.groups, bytes * p.groups);
   return c->pl.bf16 ? launch_gemm_bf16(p, epi, c->stream) : launch_gemm_f32(p, epi, c->stream);
 }
 
@@ -590,6 +590,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
   for (int l = 0; l <= MAXL; ++l) an_parts[l] = dn_parts[l] = 1;
   dn_parts[MAXL + 1] = 1;
   const long long cap = pl.cap;
+  const long long part_ld = rup(b, 64);   // distance between two partial vectors of the row norms
   hipStream_t s = c->stream;
   const bool hb = c->cfg.has_bias != 0;
   float *xm = c->at<float>(pl.o_xm);
@@ -629,9 +630,9 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
         if (pl.gelu) { p.C2 = act_ptr(pl.o_Dact[l]); p.sC2g = cap * pl.ld[l]; p.ldc2 = pl.ld[l]; }
         if (pl.bf16) {
           // ||a_i^l||^2 as per-tile partials out of the GEMM epilogue (summed by the statistics kernel)
-          an_parts[l] = gemm_bf16_row_parts(b, pl.dims[l], M);
-          if (an_parts[l] > pl.rparts[l]) return cfail(c, ABS_ENOMEM, "row-partial scratch too small for this tile shape");
-          if (want_parts) { p.part = c->at<float>(pl.o_an[l]); p.sPartg = cap * pl.rparts[l]; p.sPartTile = cap; }
+          an_parts[l] = gemm_bf16_row_parts(EPI_FWD_ACT, b, pl.dims[l], M);
+          if ((size_t)(an_parts[l] * part_ld) > pl.rpart_floats[l]) return cfail(c, ABS_ENOMEM, "row-partial scratch too small for this tile shape");
+          if (want_parts) { p.part = c->at<float>(pl.o_an[l]); p.sPartg = (long long)pl.rpart_floats[l]; p.sPartTile = part_ld; }
           HIPCHK(c, gemm(c, p, EPI_FWD_ACT, l));
         } else {
           HIPCHK(c, gemm(c, p, EPI_FWD_ACT, l));
@@ -662,17 +663,17 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       p.sEg = cap * pl.ld[l - 1]; p.lde = pl.ld[l - 1];
       if (pl.bf16) {
         // ||delta_i^{l-1}||^2 and (with biases) the column sums of delta^{l-1} as epilogue partials
-        dn_parts[l - 1] = gemm_bf16_row_parts(b, pl.dims[l - 1], M);
-        if (dn_parts[l - 1] > pl.rparts[l - 1]) return cfail(c, ABS_ENOMEM, "row-partial scratch too small for this tile shape");
-        if (want_parts) { p.part = c->at<float>(pl.o_dn[l - 1]); p.sPartg = cap * pl.rparts[l - 1]; p.sPartTile = cap; }
+        dn_parts[l - 1] = gemm_bf16_row_parts(EPI_BWD, b, pl.dims[l - 1], M);
+        if ((size_t)(dn_parts[l - 1] * part_ld) > pl.rpart_floats[l - 1]) return cfail(c, ABS_ENOMEM, "row-partial scratch too small for this tile shape");
+        if (want_parts) { p.part = c->at<float>(pl.o_dn[l - 1]); p.sPartg = (long long)pl.rpart_floats[l - 1]; p.sPartTile = part_ld; }
         if (hb && ph.wgrad) {
           p.cpart = c->at<float>(pl.o_colpart_l[l - 1]);
-          p.sCpartg = (long long)gemm_bf16_col_parts(b, pl.dims[l - 1], M) * pl.dims[l - 1];
+          p.sCpartg = (long long)gemm_bf16_col_parts(EPI_BWD, b, pl.dims[l - 1], M) * pl.dims[l - 1];
           if ((size_t)p.sCpartg > pl.colpart_l_per[l - 1]) return cfail(c, ABS_ENOMEM, "column-partial scratch too small for this tile shape");
           // the partials are added up for all layers at once after the weight gradients
           const int e = cf.n++;
-          cf.part[e] = p.cpart; cf.cols[e] = pl.dims[l - 1]; cf.nsplit[e] = gemm_bf16_col_parts(b, pl.dims[l - 1], M);
-          gemm_bf16_col_part_shape(gemm_bf16_tile_shape(b, pl.dims[l - 1], M), &cf.tile_m[e], &cf.parts_per_tile[e]);
+          cf.part[e] = p.cpart; cf.cols[e] = pl.dims[l - 1]; cf.nsplit[e] = gemm_bf16_col_parts(EPI_BWD, b, pl.dims[l - 1], M);
+          gemm_bf16_col_part_shape(EPI_BWD, b, pl.dims[l - 1], M, &cf.tile_m[e], &cf.parts_per_tile[e]);
           cf.out_off[e] = pl.offB[l - 1];
           cf_bytes += 4.0 * M * cf.nsplit[e] * cf.cols[e];
         }
@@ -850,7 +851,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
         p.part = c->at<float>(pl.o_qpart[l - 1]);
         p.sPartg = cap * pl.qparts[l - 1]; p.sPartTile = cap;
         HIPCHK(c, gemm(c, p, EPI_IPDOT, l));
-        sp.qpart[l - 1] = p.part; sp.nparts[l - 1] = gemm_bf16_row_parts(b, pl.dims[l], M);
+        sp.qpart[l - 1] = p.part; sp.nparts[l - 1] = gemm_bf16_row_parts(EPI_IPDOT, b, pl.dims[l], M);
         if (sp.nparts[l - 1] > pl.qparts[l - 1]) return cfail(c, ABS_ENOMEM, "inner-product scratch too small for this tile shape");
         sp.sQg[l - 1] = p.sPartg; sp.sQpart[l - 1] = cap;
       } else {
@@ -871,10 +872,10 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
   sp.do_n = ph.nstats ? 1 : 0; sp.do_q = do_ip ? 1 : 0; sp.acc_n = ph.acc_n ? 1 : 0; sp.acc_q = ph.acc_q ? 1 : 0;
   for (int l = 0; l < L; ++l) {
     sp.an[l] = c->at<float>(pl.o_an[l]); sp.dn[l] = c->at<float>(pl.o_dn[l + 1]);
-    sp.an_parts[l] = an_parts[l]; sp.an_sg[l] = cap * pl.rparts[l];
-    sp.dn_parts[l] = dn_parts[l + 1]; sp.dn_sg[l] = cap * pl.rparts[l + 1];
+    sp.an_parts[l] = an_parts[l]; sp.an_sg[l] = (long long)pl.rpart_floats[l];
+    sp.dn_parts[l] = dn_parts[l + 1]; sp.dn_sg[l] = (long long)pl.rpart_floats[l + 1];
   }
-  sp.sNg = cap;
+  sp.sNg = cap; sp.sPart = part_ld;
   sp.loss = c->at<float>(pl.o_loss);
   if (ph.ps_off >= 0) { sp.n_out = c->at<float>(pl.o_nout) + ph.ps_off; sp.q_out = c->at<float>(pl.o_qout) + ph.ps_off; }
   sp.Ppad = pl.Ppad;
@@ -1436,11 +1437,11 @@ abs_status abs_layer_stats(int L, const int *in_dims, const int *out_dims, int M
     p.E = delta_dev[l]; p.sEg = sd; p.lde = out_dims[l];
     p.part = reinterpret_cast<float *>(ws + off[9 + l]); p.sPartg = (long long)b * np; p.sPartTile = b;
     HIPCHK(nc, launch_gemm_bf16(p, EPI_IPDOT, s));
-    sp.qpart[l] = p.part; sp.nparts[l] = gemm_bf16_row_parts(b, out_dims[l], M); sp.sQg[l] = p.sPartg; sp.sQpart[l] = b;
+    sp.qpart[l] = p.part; sp.nparts[l] = gemm_bf16_row_parts(EPI_IPDOT, b, out_dims[l], M); sp.sQg[l] = p.sPartg; sp.sQpart[l] = b;
     sp.an[l] = an + (size_t)l * M * b; sp.dn[l] = dn + (size_t)l * M * b;
     sp.an_parts[l] = sp.dn_parts[l] = 1; sp.an_sg[l] = sp.dn_sg[l] = b;
   }
-  sp.L = L; sp.has_bias = 0; sp.groups = M; sp.b = b; sp.want_ip = 1; sp.sNg = b;
+  sp.L = L; sp.has_bias = 0; sp.groups = M; sp.b = b; sp.want_ip = 1; sp.sNg = sp.sPart = b;
   sp.do_n = sp.do_q = 1;
   sp.loss = loss;
   sp.n_out = n_out_dev ? n_out_dev : reinterpret_cast<float *>(ws + off[5]);

@@ -74,12 +74,19 @@ struct GemmP {
 hipError_t launch_gemm_bf16(const GemmP &p, int epi, hipStream_t s);
 int gemm_bf16_ipdot_parts(int Nd);
 // Exact number of row partials (tiles along n) and of column-partial rows (tiles along m times
-// wave rows) that the bf16 family writes for an Md x Nd output.
-int gemm_bf16_row_parts(int Md, int Nd, int groups);
-int gemm_bf16_col_parts(int Md, int Nd, int groups);
+// wave rows) that launch_gemm_bf16 writes for epilogue epi (forward, logits, backward-data, inner products) of an
+// Md x Nd output; the rows of a column partial's tile and the partials per tile.
+int gemm_bf16_row_parts(int epi, int Md, int Nd, int groups);
+int gemm_bf16_col_parts(int epi, int Md, int Nd, int groups);
+void gemm_bf16_col_part_shape(int epi, int Md, int Nd, int groups, int *tile_m, int *parts_per_tile);
+// Floats per group that hold the row partials of forward / backward-data launches over any b <= cap rows when
+// partials lie b (rounded up to 64) apart.
+size_t gemm_bf16_row_part_floats(int Nd, int groups, int cap);
 // Tile shape the bf16 family uses for an Md x Nd output over `groups` replicas: 0 = 128x64, 1 = 128x128, 2 = 256x256,
-// 4 = 64x128 with a six-stage ring (outputs of at most 64 rows; 3 is a weight-gradient shape, see below).
-int gemm_bf16_tile_shape(int Md, int Nd, int groups);
+// 4 = 64x128 with a six-stage ring (outputs of at most 64 rows; 3 is a weight-gradient shape, see below),
+// 5 = 32-row tiles of gemm_small.hip (forward, logits and backward-data launches that would leave most CUs idle).
+int gemm_bf16_tile_shape(int epi, int Md, int Nd, int groups);
+hipError_t launch_gemm_small(const GemmP &p, int epi, hipStream_t s);
 // Tile shape of an EPI_WGRAD launch whose reduction runs over Kd samples: as above, or 3 = 64x256 with a k-step of
 // 32 and several work-groups per CU while the batch is short and the launch is bound by its epilogue's memory traffic;
 // fused != 0: the launch carries the optimizer step in its epilogue (GemmP::upd_x), which keeps medium batches on
@@ -162,9 +169,10 @@ hipError_t launch_rowdot_f32(const float *D, long long sDg, int ldd, const float
 struct StatsP {
   int L, has_bias, groups, b, want_ip;
   const float *an[16];      // layer-input squared norms as an_parts[l] partial vectors:
-  const float *dn[16];      //   an[l][g * an_sg[l] + part * sNg + i]; likewise the backprop-signal norms
+  const float *dn[16];      //   an[l][g * an_sg[l] + part * sPart + i]; likewise the backprop-signal norms
   int an_parts[16], dn_parts[16];
   long long an_sg[16], dn_sg[16];
+  long long sPart;          // distance between two partial vectors of the norms
   long long sNg;
   const float *qpart[16];   // per layer: [g][part][i]
   int nparts[16];
@@ -257,8 +265,6 @@ hipError_t launch_stage_step_inputs(const int32_t *idx_src, int32_t *idx_dst, lo
 // dst[0..n) = v[0..n): the values travel as kernel arguments, so the host array may be reused at once
 enum { SET_INTS_MAX = 64 };
 hipError_t launch_set_ints(const int *v_host, int n, int *dst, hipStream_t s);
-// tile extent along m and column partials per tile of the bf16 family's tile shape `shape`
-void gemm_bf16_col_part_shape(int shape, int *tile_m, int *parts_per_tile);
 hipError_t launch_copy_probe(const void *src, void *dst, long long bytes, hipStream_t s);
 
 }  // namespace absk

@@ -376,8 +376,8 @@ __device__ __forceinline__ void stats_samples_block(const StatsP &p, int g, int 
     if (p.do_n) {
       float n = 0.0f;
       for (int l = 0; l < p.L; ++l) {
-        const float a = sum_strided(0.0f, p.an[l] + (long long)g * p.an_sg[l] + i, p.an_parts[l], p.sNg);
-        const float d = sum_strided(0.0f, p.dn[l] + (long long)g * p.dn_sg[l] + i, p.dn_parts[l], p.sNg);
+        const float a = sum_strided(0.0f, p.an[l] + (long long)g * p.an_sg[l] + i, p.an_parts[l], p.sPart);
+        const float d = sum_strided(0.0f, p.dn[l] + (long long)g * p.dn_sg[l] + i, p.dn_parts[l], p.sPart);
         n = fmaf(d, a + hb, n);
       }
       if (p.n_out) p.n_out[o] = n;

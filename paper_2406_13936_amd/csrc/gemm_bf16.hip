@@ -27,6 +27,7 @@
 // bf16 MFMAs with fp32 accumulators.  Work-group ids are remapped so that each XCD (ids are
 // dealt round-robin to the 8 XCDs) works on a contiguous range of tiles and its L2 sees one
 // replica's operands at a time.
+#include <algorithm>
 #include <mutex>
 #include <utility>
 #include "abs_internal.h"
@@ -928,6 +929,7 @@ hipError_t launch_cfg(const GemmP &p, hipStream_t s) {
   return hipGetLastError();
 }
 
+int tiled_shape(int Md, int Nd, int groups);
 // Reductions up to this length keep the two-stage loop in 256 x 256 tiles: the pipelined loop fetches two k-tiles beyond the
 // last one and starts later, which a handful of k-tiles does not pay back (784-512-512-10, 8 replicas, b = 4096, one tile
 // per CU: 285.7 us per step with the pipelined loop everywhere, 281.9 with this line at 512, 283.0 at 1024; 1024-wide
@@ -939,7 +941,7 @@ constexpr int PIPE_MIN_K = 512;
 template <bool AT, bool BT, int EPI, int ACT>
 hipError_t launch_shape(const GemmP &p, hipStream_t s) {
   constexpr bool IS_WGRAD = EPI == EPI_WGRAD || EPI == EPI_WGRAD_UPD;
-  switch (IS_WGRAD ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr) : gemm_bf16_tile_shape(p.Md, p.Nd, p.groups)) {
+  switch (IS_WGRAD ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr) : tiled_shape(p.Md, p.Nd, p.groups)) {
     case 0: return launch_cfg<128, 64, 64, 4, 1, 3, false, AT, BT, EPI, ACT>(p, s);
     case 3:
       if constexpr (IS_WGRAD) return launch_cfg<64, 256, 32, 1, 4, 2, false, AT, BT, EPI, ACT>(p, s);
@@ -985,9 +987,7 @@ hipError_t launch_act(const GemmP &p, hipStream_t s) {
   return launch_shape<AT, BT, EPI, ACT_NONE>(p, s);
 }
 
-}  // namespace
-
-int gemm_bf16_tile_shape(int Md, int Nd, int groups) {
+int tiled_shape(int Md, int Nd, int groups) {
   if (Nd <= 64) return 0;
   // up to 64 rows (the first local batch sizes): the launch streams its B operand (the weights) once and is bound by
   // that stream; a 64-row tile leaves LDS for a ring of six stages, five k-tiles of B in flight per work-group
@@ -1006,6 +1006,21 @@ int gemm_bf16_tile_shape(int Md, int Nd, int groups) {
   return 1;
 }
 
+// Launches of at most this many 32 x 32 tiles go to gemm_small.hip (half as many for outputs of at most 64 columns, whose
+// 128 x 64 tiles read A once as well).  Whole steps, tiled -> small: 784-512-512-10, 8 replicas, b = 32 (128 tiles) 102 ->
+// 91 us, b = 128 (512) 117 -> 105, b = 256 (1024) 130 -> 126, b = 501 (2048) 147 -> 163 with the line at 2048;
+// 784-768-768-768-100, 16 replicas, b = 16 (384) 221 -> 203; config 3 at b = 64 only its logits (128 tiles) 21 -> 14 us.
+constexpr long long SMALL_TILES = 1024;
+long long small_tiles(int Md, int Nd, int groups) { return (long long)((Md + 31) / 32) * ((Nd + 31) / 32) * groups; }
+
+}  // namespace
+
+int gemm_bf16_tile_shape(int epi, int Md, int Nd, int groups) {
+  if ((epi == EPI_FWD_ACT || epi == EPI_LOGITS || epi == EPI_BWD) && small_tiles(Md, Nd, groups) <= (Nd <= 64 ? SMALL_TILES / 2 : SMALL_TILES))
+    return 5;
+  return tiled_shape(Md, Nd, groups);
+}
+
 // Weight gradients reduce over the local batch (Kd = b).  While the batch is short the launch is all epilogue
 // (one or a few k-tiles, then 4 to 20 bytes of stores and loads per output entry): a 64 x 256 x 32 tile with two
 // 20 KB stages lets several work-groups share a CU, which keeps far more memory requests in flight than one
@@ -1013,7 +1028,7 @@ int gemm_bf16_tile_shape(int Md, int Nd, int groups) {
 // bytes in each of its 64 rows (measured against a 128 x 128 tile, 512 bytes in each of 128 rows, on config 3 at
 // b = 64: 2 to 2.5 % faster with the optimizer step in the epilogue, equal at b = 256).
 int gemm_bf16_wgrad_shape(int Md, int Nd, int Kd, int groups, int fused) {
-  int sh = gemm_bf16_tile_shape(Md, Nd, groups);
+  int sh = tiled_shape(Md, Nd, groups);
   if (sh == 4) sh = 1;                       // (the short-batch tile of the other contractions)
   if (sh != 0 && Kd <= 256) return 3;        // (measured on config 3: at b = 384 and above the large tiles are faster)
   // with the optimizer step in the epilogue a medium batch is still mostly epilogue: two or three 128 x 128
@@ -1029,22 +1044,31 @@ int gemm_bf16_upd_slots(int Md, int Nd, int Kd, int groups) {   // (always with 
   return ((Md + bm[sh] - 1) / bm[sh]) * ((Nd + bn[sh] - 1) / bn[sh]) * nw[sh];
 }
 
-int gemm_bf16_row_parts(int Md, int Nd, int groups) {
-  const int bn[5] = {64, 128, 256, 0, 128};
-  const int sh = gemm_bf16_tile_shape(Md, Nd, groups);
+int gemm_bf16_row_parts(int epi, int Md, int Nd, int groups) {
+  const int bn[6] = {64, 128, 256, 0, 128, epi == EPI_BWD ? 64 : 32};
+  const int sh = gemm_bf16_tile_shape(epi, Md, Nd, groups);
   return (Nd + bn[sh] - 1) / bn[sh];
 }
 
-int gemm_bf16_col_parts(int Md, int Nd, int groups) {
-  const int bm[5] = {128, 128, 256, 0, 64}, wm[5] = {4, 2, 2, 0, 2};
-  const int sh = gemm_bf16_tile_shape(Md, Nd, groups);
-  return (Md + bm[sh] - 1) / bm[sh] * wm[sh];
+void gemm_bf16_col_part_shape(int epi, int Md, int Nd, int groups, int *tile_m, int *parts_per_tile) {
+  const int bm[6] = {128, 128, 256, 0, 64, 32}, wm[6] = {4, 2, 2, 0, 2, 1};
+  const int sh = gemm_bf16_tile_shape(epi, Md, Nd, groups);
+  *tile_m = bm[sh];
+  *parts_per_tile = wm[sh];
 }
 
-void gemm_bf16_col_part_shape(int shape, int *tile_m, int *parts_per_tile) {
-  const int bm[5] = {128, 128, 256, 0, 64}, wm[5] = {4, 2, 2, 0, 2};
-  *tile_m = bm[shape];
-  *parts_per_tile = wm[shape];
+int gemm_bf16_col_parts(int epi, int Md, int Nd, int groups) {
+  int bm, wm;
+  gemm_bf16_col_part_shape(epi, Md, Nd, groups, &bm, &wm);
+  return (Md + bm - 1) / bm * wm;
+}
+
+size_t gemm_bf16_row_part_floats(int Nd, int groups, int cap) {
+  const size_t rows = ((size_t)cap + 63) / 64 * 64;
+  const size_t tiled = rows * gemm_bf16_ipdot_parts(Nd);
+  // a launch of gemm_small.hip has at most SMALL_TILES tiles over all groups: 32 rows each, partials 64-rounded rows apart
+  const size_t small = std::min(rows * (size_t)((Nd + 31) / 32), (size_t)(SMALL_TILES * 64 / groups));
+  return std::max(tiled, small);
 }
 
 int gemm_bf16_ipdot_parts(int Nd) {
@@ -1072,6 +1096,7 @@ hipError_t launch_gemm_bf16(const GemmP &p, int epi, hipStream_t s) {
                   (p.sCg & 3) || (reinterpret_cast<uintptr_t>(p.upd_x) & 15) || (p.C2 && ((p.ldc2 & 3) || p.ldc2 != p.ldc)) ||
                   (p.upd_opt != OPT_SGD && !p.upd_v) || (p.upd_opt == OPT_ADAMW && !p.upd_m)))
     return hipErrorInvalidValue;
+  if (epi != EPI_WGRAD && gemm_bf16_tile_shape(epi, p.Md, p.Nd, p.groups) == 5) return launch_gemm_small(p, epi, s);
   if (!p.a_trans && !p.b_trans) {
     if (epi == EPI_FWD_ACT) return launch_act<false, false, EPI_FWD_ACT>(p, s);
     if (epi == EPI_LOGITS) return launch_act<false, false, EPI_LOGITS>(p, s);

@@ -73,3 +73,36 @@ def test_large_tile_step_at_the_edges_of_the_reduction(dims, act):
         assert rep.guard_intact()
     finally:
         rep.close()
+
+
+# Launches of few 32 x 32 tiles: row and column remainders of the 32 x 32 (forward, logits) and 32 x 64 (backward-data)
+# tiles, reductions shorter than a wave's first chunk (8), a chunk with a remainder (72, 264) and more than one trip (1096).
+@pytest.mark.parametrize("dims,act,b", [((8, 40, 3), W.ACT_RELU, 2), ((72, 8, 16, 2), W.ACT_GELU, 31),
+                                        ((264, 72, 104, 130), W.ACT_GELU, 33), ((1096, 136, 10), W.ACT_NONE, 65),
+                                        ((40, 1096, 64, 33), W.ACT_RELU, 32)])
+def test_small_launches_at_the_edges_of_their_tiles(dims, act, b):
+    A = _A()
+    M = 3
+    w = W.Workload("edges", dims, act, True, W.PREC_BF16, N=512, M=M, H=1, rounds=1, b0=b, b_cap=b, opt=W.OPT_SGD, lr=0.05,
+                   test=W.TEST_IP, theta=0.9, data="teacher_mlp", seed=7)
+    X, y = W.make_dataset(w)
+    x0 = W.make_x0(w)
+    rep = A.Replicas.from_workload(w, X, y, x0)
+    orc = O.Replicas(O.Net(w.dims, w.act, True), x0, X, y, M, opt=w.opt, mixed=True, want_ip=True, gram_max_b=256)
+    try:
+        for h in range(2):
+            idx = W.step_indices(w, 0, h, b)
+            rep.local_step(idx, w.lr)
+            g = rep.inner_product_test(w.theta)
+            orc.local_step(idx, w.lr)
+            for m in range(M):
+                s = orc.stats[m]
+                for got, want in ((g[m].sum_sq, s["S1"]), (g[m].gbar_sq, s["S2"]), (g[m].loss_sum, s["loss_sum"])):
+                    assert abs(got - want) <= 2e-3 * abs(want), (h, m, got, want)
+                grad = rep.get_grad(m).astype(np.float64)
+                assert np.linalg.norm(grad - orc.grads[m]) <= 2e-3 * np.linalg.norm(orc.grads[m]), (h, m)
+                p = rep.get_params(m).astype(np.float64)
+                assert np.abs(p - orc.x[m]).max() <= 1e-3 * np.abs(orc.x[m]).max()
+        assert rep.guard_intact()
+    finally:
+        rep.close()
