@@ -44,7 +44,7 @@ struct Plan {
   size_t o_xm = 0, o_xs = 0, o_grad = 0, o_gradbf = 0, o_v = 0, o_m = 0, o_Xbf = 0;
   size_t o_A[MAXL] = {0}, o_Dact[MAXL] = {0}, o_Dl[MAXL + 1] = {0};
   size_t o_Z = 0, o_U = 0, o_gram = 0, o_an[MAXL] = {0}, o_dn[MAXL + 1] = {0}, o_loss = 0, o_nout = 0, o_qout = 0;
-  size_t o_qpart[MAXL] = {0}, o_partials = 0, o_stats = 0, o_cw = 0, o_colpart = 0, o_rows = 0, o_sqwave = 0, o_idx = 0, o_scal = 0, o_mean = 0;
+  size_t o_qpart[MAXL] = {0}, o_partials = 0, o_stats = 0, o_done = 0, o_cw = 0, o_colpart = 0, o_rows = 0, o_sqwave = 0, o_idx = 0, o_scal = 0, o_mean = 0;
   size_t o_kpart_l[MAXL + 1] = {0};    // per layer: partial products of a split weight-gradient reduction
   size_t kpart_floats_l[MAXL + 1] = {0};
   size_t total = 0;
@@ -152,6 +152,7 @@ void make_plan(const abs_config *c, long long N, Plan &pl) {
   }
   pl.o_partials = take((size_t)pl.M * 5 * STATS_PBLK * 8);
   pl.o_stats = take((size_t)pl.M * 8 * 8);
+  pl.o_done = take((size_t)pl.M * sizeof(int));
   pl.o_rows = take((size_t)2 * pl.M * sizeof(int));          // per-group row counts, then the launch order
   pl.o_sqwave = take((size_t)pl.M * (pl.Ppad / 256) * sizeof(float));
   for (int l = 1; l <= pl.L; ++l) {
@@ -456,6 +457,7 @@ abs_status abs_init_replicas(const abs_config *cfg, const float *x0_host, const 
   void *hs_dev = nullptr;
   if (hipHostGetDevicePointer(&hs_dev, c->host_stats, 0) == hipSuccess) c->host_stats_dev = static_cast<double *>(hs_dev);
   else (void)hipGetLastError();                   // no mapping: read_stats copies instead
+  if ((e = launch_fill_zero(c->at<void>(pl.o_done), rup((long long)pl.M * 4, 16), c->stream)) != hipSuccess) return bail(hipGetErrorString(e));
   // zero parameters, gradient and optimizer state (including their padding)
   const size_t MP = (size_t)pl.M * pl.Ppad;
   if ((e = launch_fill_zero(c->at<void>(pl.o_xm), MP * 4, c->stream)) != hipSuccess) return bail(hipGetErrorString(e));
@@ -608,6 +610,8 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
   SplitKFinishMany kf;                    // split weight-gradient reductions, finished together
   std::memset(&kf, 0, sizeof(kf));
   double kf_bytes = 0.0;
+  int max_width = 0;
+  for (int l = 1; l <= L; ++l) max_width = std::max(max_width, pl.dims[l]);
   const float inv_b = 1.0f / (float)(ph.b_total > 0 ? ph.b_total : b);
   if (ph.passes) {
     // batch gather (Alg. 1: "sample the local batch")
@@ -713,7 +717,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       slots += bf16_ksplit(l) > 1 ? splitk_finish_slots((long long)pl.dims[l] * pl.dims[l - 1])
                                   : gemm_bf16_upd_slots(pl.dims[l], pl.dims[l - 1], b, M);
     }
-    if (hb) { int mx = 0; for (int l = 1; l <= L; ++l) mx = std::max(mx, pl.dims[l]); slots += (long long)L * ((mx + 255) / 256); }
+    if (hb) slots += col_finish_slots(L, max_width);
     if (slots > pl.Ppad / 256) fused = false;
   }
   int fused_slots = 0;
@@ -782,14 +786,19 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
                                  c->at<float>(pl.o_colpart), rows, ph.acc_grad ? 1 : 0, s));
       }
       if (hb && pl.bf16 && l == L) {      // bf16 mode: layers below L got their partials from the backward epilogue
-        ProfScope ps_(c, T_COLSUM, 0.0, 1.0 * M * b * pl.ld[l] * pl.esz);
-        float *scr = c->at<float>(pl.o_colpart_l[L]);
         const int e = cf.n++;
-        cf.part[e] = scr; cf.cols[e] = pl.dims[L]; cf.nsplit[e] = (b + COLSUM_ROWS - 1) / COLSUM_ROWS;
+        cf.cols[e] = pl.dims[L]; cf.nsplit[e] = (b + COLSUM_ROWS - 1) / COLSUM_ROWS;
         cf.tile_m[e] = 0; cf.parts_per_tile[e] = 0; cf.out_off[e] = pl.offB[L];
-        if ((size_t)cf.nsplit[e] * cf.cols[e] > pl.colpart_l_per[L]) return cfail(c, ABS_ENOMEM, "column-sum scratch too small");
-        cf_bytes += 4.0 * M * cf.nsplit[e] * cf.cols[e];
-        HIPCHK(c, launch_col_sum_partials(isb, p.A, p.sAg, pl.ld[l], pl.dims[l], M, b, scr, rows, s));
+        if (b <= COLSUM_ROWS) {           // one partial per column would be the sum itself
+          cf.src[e] = static_cast<const bf16_t *>(p.A); cf.sXg[e] = p.sAg; cf.ldx[e] = pl.ld[l];
+        } else {
+          float *scr = c->at<float>(pl.o_colpart_l[L]);
+          cf.part[e] = scr;
+          if ((size_t)cf.nsplit[e] * cf.cols[e] > pl.colpart_l_per[L]) return cfail(c, ABS_ENOMEM, "column-sum scratch too small");
+          cf_bytes += 4.0 * M * cf.nsplit[e] * cf.cols[e];
+          ProfScope ps_(c, T_COLSUM, 0.0, 1.0 * M * b * pl.ld[l] * pl.esz);
+          HIPCHK(c, launch_col_sum_partials(isb, p.A, p.sAg, pl.ld[l], pl.dims[l], M, b, scr, rows, s));
+        }
       }
     }
     if (kf.n > 0) {                        // all split reductions of the step in one launch
@@ -809,9 +818,20 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       }
       HIPCHK(c, launch_splitk_finish(kf, M, s));
     }
-    if (cf.n > 0) {                        // all bias gradients of the step in one launch
+    if (cf.n > 0) {                        // all bias gradients of the step in one launch, with the biases' step if the weights take theirs
       ProfScope ps_(c, T_COLSUM, 0.0, cf_bytes);
-      cf.alpha = inv_b; cf.out = grad; cf.sOg = pl.Ppad; cf.rows = rows; cf.accumulate = ph.acc_grad ? 1 : 0;
+      cf.alpha = inv_b; cf.out = grad; cf.sOg = pl.Ppad; cf.rows = rows; cf.accumulate = ph.acc_grad ? 1 : 0; cf.b = b;
+      if (fused) {
+        cf.upd_x = xm;
+        cf.upd_v = c->cfg.opt != ABS_OPT_SGD ? c->at<float>(pl.o_v) : nullptr;
+        cf.upd_m = c->cfg.opt == ABS_OPT_ADAMW ? c->at<float>(pl.o_m) : nullptr;
+        cf.upd_shadow = c->at<bf16_t>(pl.o_xs);
+        cf.upd_opt = c->cfg.opt; cf.upd_lr = lr; cf.upd_momentum = c->cfg.momentum; cf.upd_beta1 = c->cfg.beta1;
+        cf.upd_beta2 = c->cfg.beta2; cf.upd_eps = c->cfg.eps; cf.upd_wd = c->cfg.weight_decay;
+        cf.upd_c1 = ph.c1; cf.upd_c2 = ph.c2; cf.upd_scal = ph.scal;
+        cf.sq = c->at<float>(pl.o_sqwave); cf.sSqg = pl.Ppad / 256; cf.slot0 = fused_slots;
+        fused_slots += col_finish_slots(cf.n, max_width);
+      }
       HIPCHK(c, launch_col_sum_finish_many(cf, M, s));
     }
   }
@@ -881,6 +901,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
   sp.Ppad = pl.Ppad;
   sp.partials = c->at<double>(pl.o_partials); sp.stats = c->at<double>(pl.o_stats);
   sp.stats_host = c->host_stats_dev;
+  sp.done = c->at<int>(pl.o_done);
   if (sp.stats_host) { c->ticket += 1.0; sp.ticket = c->ticket; c->ticket_live = true; }
   // When this call both finishes the gradient and updates, the update kernel gathers ||gbar||^2 on
   // its way through the gradient (none of the statistics depends on the parameters, so the update
@@ -888,25 +909,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
   const bool s2_in_update = ph.s2 && ph.update;
   sp.grad = (ph.s2 && !s2_in_update) ? grad : nullptr;
   if (fused) {
-    // the weights have taken their step in the epilogues; the biases take theirs here, and ||gbar||^2 is the sum
-    // of the slots the epilogues and this launch left
-    if (hb) {
-      BiasUpdateP bu;
-      std::memset(&bu, 0, sizeof(bu));
-      bu.n = L;
-      for (int l = 1; l <= L; ++l) { bu.width[l - 1] = pl.dims[l]; bu.off[l - 1] = pl.offB[l]; }
-      bu.stride = pl.Ppad;
-      bu.x = xm; bu.g = grad;
-      bu.v = c->cfg.opt != ABS_OPT_SGD ? c->at<float>(pl.o_v) : nullptr;
-      bu.m = c->cfg.opt == ABS_OPT_ADAMW ? c->at<float>(pl.o_m) : nullptr;
-      bu.shadow = c->at<bf16_t>(pl.o_xs);
-      bu.opt = c->cfg.opt; bu.lr = lr; bu.momentum = c->cfg.momentum; bu.beta1 = c->cfg.beta1; bu.beta2 = c->cfg.beta2;
-      bu.eps = c->cfg.eps; bu.wd = c->cfg.weight_decay; bu.c1 = ph.c1; bu.c2 = ph.c2; bu.scal = ph.scal;
-      bu.sq = c->at<float>(pl.o_sqwave); bu.sSqg = pl.Ppad / 256; bu.slot0 = fused_slots;
-      fused_slots += update_bias_slots(bu);
-      ProfScope ps_(c, T_UPDATE, 0.0, 0.0);
-      HIPCHK(c, launch_update_bias(bu, M, s));
-    }
+    // every parameter has taken its step; ||gbar||^2 is the sum of the slots that the launches which did it left
     sp.sq_wave = c->at<float>(pl.o_sqwave); sp.n_sq_wave = fused_slots;
     sp.sq_stride = pl.Ppad / 256;
     ProfScope ps_(c, T_STATS, 0.0, 4.0 * M * fused_slots);
@@ -1361,7 +1364,7 @@ static abs_status ls_plan(int L, const int *in_dims, const int *out_dims, int M,
   off.push_back(take((size_t)M * Wtot * 2));                 // 1: grad bf16
   off.push_back(take((size_t)M * b * 4 * L));                // 2: an
   off.push_back(take((size_t)M * b * 4 * L));                // 3: dn
-  off.push_back(take((size_t)M * b * 4));                    // 4: loss (zeros)
+  off.push_back(take((size_t)M * 4));                        // 4: block counters of the statistics (zeros)
   off.push_back(take((size_t)M * b * 4));                    // 5: n_out
   off.push_back(take((size_t)M * b * 4));                    // 6: q_out
   off.push_back(take((size_t)M * 5 * STATS_PBLK * 8));       // 7: partials
@@ -1399,9 +1402,9 @@ abs_status abs_layer_stats(int L, const int *in_dims, const int *out_dims, int M
   bf16_t *gradbf = reinterpret_cast<bf16_t *>(ws + off[1]);
   float *an = reinterpret_cast<float *>(ws + off[2]);
   float *dn = reinterpret_cast<float *>(ws + off[3]);
-  float *loss = reinterpret_cast<float *>(ws + off[4]);
+  int *done = reinterpret_cast<int *>(ws + off[4]);
   abs_ctx *nc = nullptr;
-  HIPCHK(nc, launch_fill_zero(loss, (long long)M * b * 4, s));
+  HIPCHK(nc, launch_fill_zero(done, rup((long long)M * 4, 16), s));
   {
     // the weight gradients overwrite every entry of their layers; only the padding behind the last layer,
     // which the ||gbar||^2 pass reads too, has to be cleared
@@ -1443,7 +1446,7 @@ abs_status abs_layer_stats(int L, const int *in_dims, const int *out_dims, int M
   }
   sp.L = L; sp.has_bias = 0; sp.groups = M; sp.b = b; sp.want_ip = 1; sp.sNg = sp.sPart = b;
   sp.do_n = sp.do_q = 1;
-  sp.loss = loss;
+  sp.done = done;
   sp.n_out = n_out_dev ? n_out_dev : reinterpret_cast<float *>(ws + off[5]);
   sp.q_out = q_out_dev ? q_out_dev : reinterpret_cast<float *>(ws + off[6]);
   sp.grad = grad; sp.Ppad = Wtot;

@@ -149,9 +149,23 @@ hipError_t launch_col_sum_partials(int is_bf16, const void *X, long long sXg, in
 // out[g][out_off_l + j] = alpha * sum_r part_l[g][r][j], r < nsplit_l (partials from a GEMM epilogue or from
 // launch_col_sum_partials).  With rows: alpha = 1 / rows[g] and, where tile_m_l > 0, only the first
 // ceil(rows[g] / tile_m_l) * parts_per_tile_l partials of group g exist.
+// A layer with src_l set has no partials: its b <= COLSUM_ROWS signals src_l[g][i][j] (bf16, group stride sXg_l, row stride
+// ldx_l) are added up directly.
+// With upd_x the biases take their optimizer step in the same launch (accumulate == 0): parameters, state and shadow lie at
+// out_off_l + j of every group's vector (group stride sOg), and block (x, layer l) of group g leaves its squared gradient
+// entries' sum in sq[g * sSqg + slot0 + l * gridDim.x + x] (col_finish_slots of them).
 struct ColFinishMany {
   enum { MAXN = 16 };
   int n;                         // layers
+  const bf16_t *src[MAXN];
+  long long sXg[MAXN];
+  int ldx[MAXN], b;
+  float *upd_x, *upd_v, *upd_m;
+  bf16_t *upd_shadow;
+  int upd_opt;
+  float upd_lr, upd_momentum, upd_beta1, upd_beta2, upd_eps, upd_wd, upd_c1, upd_c2;
+  const float *upd_scal;
+  float *sq; long long sSqg; int slot0;
   const float *part[MAXN];       // partials [groups][nsplit][cols]
   int cols[MAXN], nsplit[MAXN], tile_m[MAXN], parts_per_tile[MAXN];
   long long out_off[MAXN];       // offset of the layer's sums inside a group's output vector
@@ -161,6 +175,7 @@ struct ColFinishMany {
   int accumulate;
 };
 hipError_t launch_col_sum_finish_many(const ColFinishMany &p, int groups, hipStream_t s);
+inline int col_finish_slots(int layers, int max_cols) { return layers * ((max_cols + 63) / 64); }
 // q[g][i] += sum_j D[g][i][j] * U[g][i][j]  (fp32 path of the inner products)
 hipError_t launch_rowdot_f32(const float *D, long long sDg, int ldd, const float *U,
                              long long sUg, int ldu, int cols, int groups, int b, float *q,
@@ -177,11 +192,12 @@ struct StatsP {
   const float *qpart[16];   // per layer: [g][part][i]
   int nparts[16];
   long long sQg[16], sQpart[16];
-  const float *loss;        // [g][i]
+  const float *loss;        // [g][i] (null: zeros)
   float *n_out, *q_out;     // [g][i] (stride sNg)
   const float *grad;        // [g][Ppad]
   long long Ppad;
   double *partials;         // scratch: [groups][5][PBLK]
+  int *done;                // [groups] block counters, zero before the launch and after it
   double *stats;            // out: [groups][8] = S1, S2, S3, S4, loss, 0,0,0
   double ticket;            // with stats_host: written to stats_host[g * 8 + 7] after group g's sums have been
                             //   made visible to the host (a host that polls that word needs no stream synchronisation)
@@ -207,21 +223,6 @@ struct UpdateP {
                             //   that a captured launch can be replayed with new values
 };
 hipError_t launch_update(const UpdateP &p, hipStream_t s);
-// The optimizer step of the bias vectors alone (layers l < n: width[l] entries at offset off[l] of every group's
-// vector of `stride` elements), with per-block sums of their squared gradient entries into sq.
-struct BiasUpdateP {
-  enum { MAXN = 16 };
-  int n;
-  int width[MAXN];
-  long long off[MAXN];
-  long long stride;
-  float *x; const float *g; float *v; float *m; bf16_t *shadow;
-  int opt; float lr, momentum, beta1, beta2, eps, wd, c1, c2;
-  const float *scal;
-  float *sq; long long sSqg; int slot0;
-};
-int update_bias_slots(const BiasUpdateP &p);
-hipError_t launch_update_bias(const BiasUpdateP &p, int groups, hipStream_t s);
 hipError_t launch_average_f32(float *x, bf16_t *shadow, float *mean, int groups, long long Ppad, hipStream_t s);
 hipError_t launch_average_bf16(bf16_t *x, bf16_t *mean, int groups, long long n, hipStream_t s);
 // cross-worker statistics: out[0] = sum_m ||g^m||^2, out[1] = ||mean_m g^m||^2;

@@ -2,6 +2,7 @@
 // row / column reductions, the test statistics, the fused optimizer update, the replica
 // average.  All reductions run in a fixed order (no floating-point atomics), so a step is
 // bit-reproducible.  Wavefronts are 64 lanes; rows are read with 16-byte loads.
+#include <algorithm>
 #include "abs_internal.h"
 #include "device_utils.h"
 
@@ -292,29 +293,64 @@ __global__ void __launch_bounds__(256) col_sum_stage2(const float *__restrict__ 
   }
 }
 
-__global__ void __launch_bounds__(256) col_sum_stage2_many(const ColFinishMany p) {
-  __shared__ float red[4][64];
-  const int l = blockIdx.z, g = blockIdx.y, cl = threadIdx.x & 63, rl = threadIdx.x >> 6;
+// One launch for the bias gradients of all layers and, with OPT >= 0, their optimizer step (a launch of its own costs as much
+// as its work: 784-512-512-10, b = 32: 3.0 + 3.2 us apart, and 3.4 us for the first stage of the last layer's sums).
+template <int OPT>
+__global__ void __launch_bounds__(256) col_finish_many_kernel(const ColFinishMany p) {
+  __shared__ float red[256];
+  const int l = blockIdx.z, g = blockIdx.y;
   const int cols = p.cols[l];
-  if (blockIdx.x * 64 >= cols) return;             // uniform over the block
-  const int c = blockIdx.x * 64 + cl;
-  int ns = p.nsplit[l];
-  float alpha = p.alpha;
-  if (p.rows) {
-    alpha = 1.0f / (float)p.rows[g];
-    if (p.tile_m[l] > 0) ns = (p.rows[g] + p.tile_m[l] - 1) / p.tile_m[l] * p.parts_per_tile[l];
+  const bf16_t *src = p.src[l];
+  // 64 columns x 4 row-lanes per block; 16 x 16 for a narrow layer summed directly (a shorter serial walk per lane)
+  const int CL = src && cols <= 16 ? 16 : 64, RL = 256 / CL;
+  const int cl = threadIdx.x & (CL - 1), rl = threadIdx.x / CL;
+  const int c = blockIdx.x * CL + cl;
+  float gg = 0.0f;
+  if (blockIdx.x * CL < cols) {                    // uniform over the block
+    float alpha = p.alpha;
+    int ns = src ? p.b : p.nsplit[l];
+    if (p.rows) {
+      alpha = 1.0f / (float)p.rows[g];
+      if (src) ns = p.rows[g];
+      else if (p.tile_m[l] > 0) ns = (p.rows[g] + p.tile_m[l] - 1) / p.tile_m[l] * p.parts_per_tile[l];
+    }
+    float s = 0.0f;
+    if (c < cols) {
+      if (src) {
+        const bf16_t *q = src + (long long)g * p.sXg[l] + c;
+#pragma unroll 8
+        for (int r = rl; r < ns; r += RL) s += bf2f(q[(long long)r * p.ldx[l]]);
+      } else {
+        const float *q = p.part[l] + (long long)g * p.nsplit[l] * cols + c;
+#pragma unroll 4
+        for (int r = rl; r < ns; r += RL) s += q[(long long)r * cols];
+      }
+    }
+    red[threadIdx.x] = s;
+    __syncthreads();
+    if (rl == 0 && c < cols) {
+      float t = red[cl];
+      for (int k = 1; k < RL; ++k) t += red[k * CL + cl];
+      const long long off = (long long)g * p.sOg + p.out_off[l] + c;
+      float *o = p.out + off;
+      const float gr = p.accumulate ? fmaf(alpha, t, *o) : alpha * t;
+      *o = gr;
+      if constexpr (OPT >= 0) {
+        OptHyper h = {p.upd_lr, p.upd_momentum, p.upd_beta1, p.upd_beta2, p.upd_eps, p.upd_wd, p.upd_c1, p.upd_c2};
+        if (p.upd_scal) { h.lr = p.upd_scal[0]; h.c1 = p.upd_scal[1]; h.c2 = p.upd_scal[2]; }
+        float x = p.upd_x[off], v = OPT != OPT_SGD ? p.upd_v[off] : 0.0f, m = OPT == OPT_ADAMW ? p.upd_m[off] : 0.0f;
+        opt_step_elem<OPT>(x, gr, v, m, h);
+        p.upd_x[off] = x;
+        if (OPT != OPT_SGD) p.upd_v[off] = v;
+        if (OPT == OPT_ADAMW) p.upd_m[off] = m;
+        if (p.upd_shadow) p.upd_shadow[off] = f2bf(x);
+        gg = gr * gr;
+      }
+    }
   }
-  float s = 0.0f;
-  if (c < cols) {
-    const float *q = p.part[l] + (long long)g * p.nsplit[l] * cols + c;
-    for (int r = rl; r < ns; r += 4) s += q[(long long)r * cols];
-  }
-  red[rl][cl] = s;
-  __syncthreads();
-  if (rl == 0 && c < cols) {
-    const float t = ((red[0][cl] + red[1][cl]) + red[2][cl]) + red[3][cl];
-    float *o = p.out + (long long)g * p.sOg + p.out_off[l] + c;
-    *o = p.accumulate ? fmaf(alpha, t, *o) : alpha * t;
+  if constexpr (OPT >= 0) {                        // columns sit in the first wavefront; blocks beyond the layer leave zeros
+    const double r = wave_sum((double)gg);
+    if (threadIdx.x == 0) p.sq[(long long)g * p.sSqg + p.slot0 + l * gridDim.x + blockIdx.x] = (float)r;
   }
 }
 
@@ -382,7 +418,7 @@ __device__ __forceinline__ void stats_samples_block(const StatsP &p, int g, int 
       }
       if (p.n_out) p.n_out[o] = n;
       s1 += (double)n;
-      sl += (double)p.loss[o];
+      if (p.loss) sl += (double)p.loss[o];
     }
     if (p.do_q) {
       float q = 0.0f;
@@ -403,20 +439,53 @@ __device__ __forceinline__ void stats_samples_block(const StatsP &p, int g, int 
 }
 __device__ __forceinline__ void stats_gradsq_parts_block(const float *__restrict__ sq_wave, long long per_group,
                                                          long long stride, double *__restrict__ partials, int g, int blk,
-                                                         double *red) {
+                                                         int nb, double *red) {
   const float *p = sq_wave + (long long)g * (stride ? stride : per_group);
   double s = 0.0;
-  for (long long i = blk * 256LL + threadIdx.x; i < per_group; i += 256LL * STATS_PBLK) s += (double)p[i];
+  for (long long i = blk * 256LL + threadIdx.x; i < per_group; i += 256LL * nb) s += (double)p[i];
   const double r = block_sum<4>(s, red);
   if (threadIdx.x == 0) partials[((long long)g * 5 + 1) * STATS_PBLK + blk] = r;
 }
-// grid (nb_samples + nb_parts) x groups: the first nb_samples blocks of a group take the per-sample sums,
-// the other PBLK blocks (present when the update kernel left per-wavefront partials) the ||gbar||^2 partials.
-__global__ void __launch_bounds__(256) stats_samples_kernel(const StatsP p, int nb_samples) {
+// grid (nb_samples + nb_parts) x groups: the first nb_samples blocks of a group take the per-sample sums, the others (present
+// when the gradient's squares were left as partial sums) the ||gbar||^2 partials.  The block of a group that finishes last
+// adds the partials of each of the five sums in index order and delivers them: a launch of its own for that (5 blocks sums
+// one after the other) took 3.6 to 5.8 us of every step.
+// sel / acc: bit k set = sum k is produced by this launch / is added to the stored value.  n2: ||gbar||^2 partials.
+__global__ void __launch_bounds__(256) stats_kernel(const StatsP p, const int nb_samples, const int n2, const int sel, const int acc) {
   __shared__ double red[4];
+  __shared__ double fin[5][4];
+  __shared__ int last;
   const int g = blockIdx.y, blk = blockIdx.x;
   if (blk < nb_samples) stats_samples_block(p, g, blk, nb_samples, red);
-  else stats_gradsq_parts_block(p.sq_wave, p.n_sq_wave, p.sq_stride, p.partials, g, blk - nb_samples, red);
+  else if (p.sq_wave) stats_gradsq_parts_block(p.sq_wave, p.n_sq_wave, p.sq_stride, p.partials, g, blk - nb_samples, n2, red);
+  if (threadIdx.x == 0) {                         // (this thread has written the block's partials itself)
+    __threadfence();
+    last = atomicAdd(p.done + g, 1) == (int)gridDim.x - 1;
+    __threadfence();
+  }
+  __syncthreads();
+  if (!last) return;
+  static_assert(STATS_PBLK == 256, "one partial per thread");
+  const int t = threadIdx.x;
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+    double v = 0.0;
+    if (((sel >> k) & 1) && t < (k == 1 ? n2 : nb_samples)) v = p.partials[((long long)g * 5 + k) * STATS_PBLK + t];
+    v = wave_sum(v);
+    if ((t & 63) == 0) fin[k][t >> 6] = v;
+  }
+  __syncthreads();
+  if (t < 5 && ((sel >> t) & 1)) {
+    const double r = ((fin[t][0] + fin[t][1]) + fin[t][2]) + fin[t][3];
+    const double v = ((acc >> t) & 1) ? p.stats[g * 8 + t] + r : r;
+    p.stats[g * 8 + t] = v;
+    if (p.stats_host) p.stats_host[g * 8 + t] = v;
+  }
+  if (t < 64 && p.stats_host) __threadfence_system();   // the sums above reach host memory before the ticket does
+  if (t == 0) {
+    p.done[g] = 0;
+    if (p.stats_host) *reinterpret_cast<volatile double *>(p.stats_host + g * 8 + 7) = p.ticket;
+  }
 }
 
 // Stage 1b (grid: PBLK x groups): ||gbar||^2 over the padded gradient vector.
@@ -434,32 +503,6 @@ __global__ void __launch_bounds__(256) stats_gradsq_kernel(const float *__restri
   }
   const double r = block_sum<4>(s, red);
   if (threadIdx.x == 0) partials[((long long)g * 5 + 1) * STATS_PBLK + blockIdx.x] = r;
-}
-
-// Stage 2 (grid: groups): add the PBLK partials of each of the five sums in index order.
-// sel / acc: bit k set = sum k is produced by this launch / is added to the stored value.
-// nb_samples: how many partials of the per-sample sums (all but k = 1) this step wrote; the rest count as zero.
-__global__ void __launch_bounds__(256) stats_final_kernel(const double *__restrict__ partials,
-                                                          double *__restrict__ stats, double *__restrict__ stats_host,
-                                                          int sel, int acc, int nb_samples, double ticket) {
-  __shared__ double red[4];
-  const int g = blockIdx.x;
-  static_assert(STATS_PBLK == 256, "one partial per thread");
-  for (int k = 0; k < 5; ++k) {
-    if (!((sel >> k) & 1)) continue;
-    const bool live = k == 1 || (int)threadIdx.x < nb_samples;
-    const double v = live ? partials[((long long)g * 5 + k) * STATS_PBLK + threadIdx.x] : 0.0;
-    const double r = block_sum<4>(v, red);
-    if (threadIdx.x == 0) {
-      const double v = ((acc >> k) & 1) ? stats[g * 8 + k] + r : r;
-      stats[g * 8 + k] = v;
-      if (stats_host) stats_host[g * 8 + k] = v;
-    }
-  }
-  if (stats_host && threadIdx.x == 0) {
-    __threadfence_system();                       // the sums above reach host memory before the ticket does
-    *reinterpret_cast<volatile double *>(stats_host + g * 8 + 7) = ticket;
-  }
 }
 
 // ---- optimizer update ------------------------------------------------------------------------
@@ -503,31 +546,6 @@ __global__ void __launch_bounds__(256) update_kernel(const UpdateP pin) {
       st_stream(reinterpret_cast<uint2 *>(p.shadow) + i, o);
     }
   }
-}
-
-// The step of the bias vectors alone, for steps whose weights were updated inside the weight-gradient epilogue.
-// grid (ceil(max width / 256), groups, layers); one bias per thread; each block also leaves the sum of its
-// squared gradient entries in sq[g * sSqg + slot0 + (layer * gridDim.x + blockIdx.x)] (their share of ||gbar||^2).
-template <int OPT>
-__global__ void __launch_bounds__(256) update_bias_kernel(const BiasUpdateP p) {
-  __shared__ double red[4];
-  const int l = blockIdx.z, g = blockIdx.y, j = blockIdx.x * 256 + threadIdx.x;
-  OptHyper h = {p.lr, p.momentum, p.beta1, p.beta2, p.eps, p.wd, p.c1, p.c2};
-  if (p.scal) { h.lr = p.scal[0]; h.c1 = p.scal[1]; h.c2 = p.scal[2]; }
-  float gg = 0.0f;
-  if (j < p.width[l]) {
-    const long long o = (long long)g * p.stride + p.off[l] + j;
-    const float gr = p.g[o];
-    float x = p.x[o], v = OPT != OPT_SGD ? p.v[o] : 0.0f, m = OPT == OPT_ADAMW ? p.m[o] : 0.0f;
-    opt_step_elem<OPT>(x, gr, v, m, h);
-    p.x[o] = x;
-    if (OPT != OPT_SGD) p.v[o] = v;
-    if (OPT == OPT_ADAMW) p.m[o] = m;
-    if (p.shadow) p.shadow[o] = f2bf(x);
-    gg = gr * gr;
-  }
-  const double r = block_sum<4>((double)gg, red);
-  if (threadIdx.x == 0) p.sq[(long long)g * p.sSqg + p.slot0 + l * gridDim.x + blockIdx.x] = (float)r;
 }
 
 // ---- replica average ------------------------------------------------------------------------
@@ -915,8 +933,18 @@ hipError_t launch_col_sum_partials(int is_bf16, const void *X, long long sXg, in
 hipError_t launch_col_sum_finish_many(const ColFinishMany &p, int groups, hipStream_t s) {
   if (p.n < 1 || p.n > ColFinishMany::MAXN) return hipErrorInvalidValue;
   int mx = 0;
-  for (int l = 0; l < p.n; ++l) mx = p.cols[l] > mx ? p.cols[l] : mx;
-  hipLaunchKernelGGL(col_sum_stage2_many, dim3((mx + 63) / 64, groups, p.n), dim3(256), 0, s, p);
+  for (int l = 0; l < p.n; ++l) {
+    if (!p.src[l] && !p.part[l]) return hipErrorInvalidValue;
+    mx = p.cols[l] > mx ? p.cols[l] : mx;
+  }
+  const dim3 grid((mx + 63) / 64, groups, p.n), blk(256);
+  if (!p.upd_x) { hipLaunchKernelGGL(col_finish_many_kernel<-1>, grid, blk, 0, s, p); return hipGetLastError(); }
+  if (p.accumulate || !p.sq || (p.upd_opt != OPT_SGD && !p.upd_v) || (p.upd_opt == OPT_ADAMW && !p.upd_m))
+    return hipErrorInvalidValue;
+  if (p.upd_opt == OPT_SGD) hipLaunchKernelGGL(col_finish_many_kernel<OPT_SGD>, grid, blk, 0, s, p);
+  else if (p.upd_opt == OPT_SHB) hipLaunchKernelGGL(col_finish_many_kernel<OPT_SHB>, grid, blk, 0, s, p);
+  else if (p.upd_opt == OPT_ADAGRAD) hipLaunchKernelGGL(col_finish_many_kernel<OPT_ADAGRAD>, grid, blk, 0, s, p);
+  else hipLaunchKernelGGL(col_finish_many_kernel<OPT_ADAMW>, grid, blk, 0, s, p);
   return hipGetLastError();
 }
 
@@ -941,14 +969,16 @@ hipError_t launch_stats(const StatsP &p, hipStream_t s) {
     nb_samples = (p.b + 255) / 256;
     nb_samples = nb_samples < 1 ? 1 : (nb_samples > STATS_PBLK ? STATS_PBLK : nb_samples);
   }
-  const int nb_parts = p.sq_wave ? STATS_PBLK : 0;
-  if (nb_samples + nb_parts > 0)
-    hipLaunchKernelGGL(stats_samples_kernel, dim3(nb_samples + nb_parts, p.groups), dim3(256), 0, s, p, nb_samples);
-  if (p.grad)
+  // ||gbar||^2: from partial sums (256 per block, at most PBLK blocks), or a pass over the gradient by PBLK blocks
+  int n2 = 0;
+  if (p.sq_wave) n2 = (int)std::min<long long>(STATS_PBLK, std::max<long long>(1, (p.n_sq_wave + 255) / 256));
+  if (p.grad) {
     hipLaunchKernelGGL(stats_gradsq_kernel, dim3(STATS_PBLK, p.groups), dim3(256), 0, s, p.grad, p.Ppad,
                        p.partials);
-  hipLaunchKernelGGL(stats_final_kernel, dim3(p.groups), dim3(256), 0, s, p.partials, p.stats, p.stats_host, sel, acc,
-                     nb_samples, p.ticket);
+    n2 = STATS_PBLK;
+  }
+  const int blocks = std::max(1, nb_samples + (p.sq_wave ? n2 : 0));
+  hipLaunchKernelGGL(stats_kernel, dim3(blocks, p.groups), dim3(256), 0, s, p, nb_samples, n2, sel, acc);
   return hipGetLastError();
 }
 
@@ -969,24 +999,6 @@ hipError_t launch_update(const UpdateP &p, hipStream_t s) {
   else if (p.opt == OPT_ADAGRAD) ABS_UPD(OPT_ADAGRAD);
   else ABS_UPD(OPT_ADAMW);
 #undef ABS_UPD
-  return hipGetLastError();
-}
-
-int update_bias_slots(const BiasUpdateP &p) {
-  int mx = 0;
-  for (int l = 0; l < p.n; ++l) mx = p.width[l] > mx ? p.width[l] : mx;
-  return p.n * ((mx + 255) / 256);
-}
-
-hipError_t launch_update_bias(const BiasUpdateP &p, int groups, hipStream_t s) {
-  if (p.n < 1 || p.n > BiasUpdateP::MAXN) return hipErrorInvalidValue;
-  int mx = 0;
-  for (int l = 0; l < p.n; ++l) mx = p.width[l] > mx ? p.width[l] : mx;
-  const dim3 grid((mx + 255) / 256, groups, p.n), blk(256);
-  if (p.opt == OPT_SGD) hipLaunchKernelGGL(update_bias_kernel<OPT_SGD>, grid, blk, 0, s, p);
-  else if (p.opt == OPT_SHB) hipLaunchKernelGGL(update_bias_kernel<OPT_SHB>, grid, blk, 0, s, p);
-  else if (p.opt == OPT_ADAGRAD) hipLaunchKernelGGL(update_bias_kernel<OPT_ADAGRAD>, grid, blk, 0, s, p);
-  else hipLaunchKernelGGL(update_bias_kernel<OPT_ADAMW>, grid, blk, 0, s, p);
   return hipGetLastError();
 }
 

@@ -79,7 +79,10 @@ def test_large_tile_step_at_the_edges_of_the_reduction(dims, act):
 # tiles, reductions shorter than a wave's first chunk (8), a chunk with a remainder (72, 264) and more than one trip (1096).
 @pytest.mark.parametrize("dims,act,b", [((8, 40, 3), W.ACT_RELU, 2), ((72, 8, 16, 2), W.ACT_GELU, 31),
                                         ((264, 72, 104, 130), W.ACT_GELU, 33), ((1096, 136, 10), W.ACT_NONE, 65),
-                                        ((40, 1096, 64, 33), W.ACT_RELU, 32)])
+                                        ((40, 1096, 64, 33), W.ACT_RELU, 32),
+                                        # the last layer's bias gradient: summed in one launch up to b = 128, 16 columns a block
+                                        ((64, 72, 16), W.ACT_RELU, 128), ((64, 72, 17), W.ACT_GELU, 128),
+                                        ((64, 72, 16), W.ACT_GELU, 129), ((64, 72, 100), W.ACT_RELU, 129)])
 def test_small_launches_at_the_edges_of_their_tiles(dims, act, b):
     A = _A()
     M = 3
@@ -101,6 +104,8 @@ def test_small_launches_at_the_edges_of_their_tiles(dims, act, b):
                     assert abs(got - want) <= 2e-3 * abs(want), (h, m, got, want)
                 grad = rep.get_grad(m).astype(np.float64)
                 assert np.linalg.norm(grad - orc.grads[m]) <= 2e-3 * np.linalg.norm(orc.grads[m]), (h, m)
+                K = dims[-1]
+                assert np.linalg.norm(grad[-K:] - orc.grads[m][-K:]) <= 2e-3 * np.linalg.norm(orc.grads[m][-K:]), (h, m)
                 p = rep.get_params(m).astype(np.float64)
                 assert np.abs(p - orc.x[m]).max() <= 1e-3 * np.abs(orc.x[m]).max()
         assert rep.guard_intact()
