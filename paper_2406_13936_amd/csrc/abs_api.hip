@@ -311,9 +311,8 @@ struct ProfScope {
   ~ProfScope() { if (r) (void)hipEventRecord(r->e1, c->stream); }
 };
 
-hipError_t gemm(abs_ctx *c, const GemmP &p, int epi, int layer) {
-  int shape = !c->pl.bf16 ? 1 : (epi == EPI_WGRAD ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr)
-                                                   : gemm_bf16_tile_shape(epi, p.Md, p.Nd, p.groups));
+double gemm_flops(const GemmP &p) { return 2.0 * p.Md * p.Nd * p.Kd * p.groups; }
+double gemm_bytes(const abs_ctx *c, const GemmP &p, int epi) {
   // algorithmic bytes of the launch: both operands once, the outputs once, the epilogue's elementwise operand once
   const double e = c->pl.esz, mn = (double)p.Md * p.Nd;
   double bytes = ((double)p.Md + p.Nd) * p.Kd * e;
@@ -323,7 +322,15 @@ hipError_t gemm(abs_ctx *c, const GemmP &p, int epi, int layer) {
   else if (epi == EPI_IPDOT) bytes += mn * e;
   else if (p.upd_x) bytes += mn * (8 + (p.upd_v ? 8 : 0) + (p.upd_m ? 8 : 0) + (p.upd_shadow ? 2 : 0) + (p.C2 ? 2 : 0));
   else bytes += mn * (4 + (p.C2 ? 2 : 0) + (p.accumulate ? 4 : 0));
-  ProfScope ps(c, T_GEMM0 + (epi * 6 + shape) * T_LAYERS + layer, 2.0 * p.Md * p.Nd * p.Kd * p.groups, bytes * p.groups);
+  return bytes * p.groups;
+}
+double gemm_flops(const std::vector<GemmP> &v) { double s = 0.0; for (const GemmP &p : v) s += gemm_flops(p); return s; }
+double gemm_bytes(const abs_ctx *c, const std::vector<GemmP> &v, int epi) { double s = 0.0; for (const GemmP &p : v) s += gemm_bytes(c, p, epi); return s; }
+
+hipError_t gemm(abs_ctx *c, const GemmP &p, int epi, int layer) {
+  int shape = !c->pl.bf16 ? 1 : (epi == EPI_WGRAD ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr)
+                                                   : gemm_bf16_tile_shape(epi, p.Md, p.Nd, p.groups));
+  ProfScope ps(c, T_GEMM0 + (epi * 6 + shape) * T_LAYERS + layer, gemm_flops(p), gemm_bytes(c, p, epi));
   return c->pl.bf16 ? launch_gemm_bf16(p, epi, c->stream) : launch_gemm_f32(p, epi, c->stream);
 }
 
@@ -728,6 +735,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
                         ph.b_total == 0 && b <= c->gram_ip_max_b && b <= GRAM_MAX_B;
   // local batch gradient, eq. (batch_grad): Gbar_l = delta^T a / b, betabar_l = mean_i delta_i
   if (ph.wgrad) {
+    std::vector<GemmP> many;               // short batches: the layers share a launch
     for (int l = 1; l <= L; ++l) {
       GemmP p;
       std::memset(&p, 0, sizeof(p));
@@ -773,7 +781,8 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
         p.upd_sq = c->at<float>(pl.o_sqwave); p.upd_sSqg = pl.Ppad / 256; p.upd_slot0 = fused_slots;
         fused_slots += gemm_bf16_upd_slots(p.Md, p.Nd, b, M);
       }
-      HIPCHK(c, gemm(c, p, EPI_WGRAD, l));
+      if (pl.bf16 && gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, M, p.upd_x != nullptr) == 3) many.push_back(p);
+      else HIPCHK(c, gemm(c, p, EPI_WGRAD, l));
       if (p.ksplit > 1) {                    // its slices are added up after the loop, with those of the other layers
         const int e = kf.n++;
         kf.kpart[e] = p.kpart; kf.ksplit[e] = p.ksplit; kf.mn[e] = (long long)p.Md * p.Nd; kf.c_off[e] = pl.offW[l];
@@ -800,6 +809,10 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
           HIPCHK(c, launch_col_sum_partials(isb, p.A, p.sAg, pl.ld[l], pl.dims[l], M, b, scr, rows, s));
         }
       }
+    }
+    if (!many.empty()) {
+      ProfScope ps_(c, T_GEMM0 + (EPI_WGRAD * 6 + 3) * T_LAYERS, gemm_flops(many), gemm_bytes(c, many, EPI_WGRAD));
+      HIPCHK(c, launch_wgrad_many(many.data(), (int)many.size(), s));
     }
     if (kf.n > 0) {                        // all split reductions of the step in one launch
       ProfScope ps_(c, T_COLSUM, 0.0, kf_bytes);

@@ -235,9 +235,9 @@ __device__ __forceinline__ void wait_frags(bf16x8 (&a)[MI], bf16x8 (&b)[NI]) {
 // a wave still owns 64 consecutive columns), row-contiguous ones by k (unit c = 32 of the 64 k: 512 bytes of a memory row).
 // Measured, 16 replicas, against the two-stage loop: inner products 8192 x 2048 x 2048 1017 -> 850 us (1.30 PFLOP/s),
 // forward 1160 -> 1043, backward-data 1110 -> 922, weight gradient with the step in its epilogue 1178 -> 993.
+// (the work of one work-group: tile lb of the tilesM x tilesN x groups of a launch)
 template <int BM, int BN, int BK, int WM, int WN, int NS, bool PP, bool AT, bool BT, int EPI, int ACT>
-__global__ void __launch_bounds__(WM * WN * 64)
-gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int nblk, const int chunk) {
+__device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tilesM, const int tilesN, const int lb) {
   constexpr int NW = WM * WN, NT = NW * 64;
   constexpr int TM = BM / WM, TN = BN / WN;
   constexpr bool IS_WGRAD = EPI == EPI_WGRAD || EPI == EPI_WGRAD_UPD;   // _UPD: ACT carries the optimizer
@@ -254,10 +254,6 @@ gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int 
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   bf16_t *smem = reinterpret_cast<bf16_t *>(smem_raw);
 
-  // XCD-aware remap of the flat work-group id
-  const int bid = blockIdx.x;
-  const int lb = (bid & 7) * chunk + (bid >> 3);
-  if (lb >= nblk) return;
   const int per_g = tilesM * tilesN;
   const int vg = lb / per_g;                      // group, or (group, k-slice) pair of a split reduction
   const int t = lb - vg * per_g;
@@ -904,6 +900,37 @@ gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int 
 }
 
 template <int BM, int BN, int BK, int WM, int WN, int NS, bool PP, bool AT, bool BT, int EPI, int ACT>
+__global__ void __launch_bounds__(WM * WN * 64)
+gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int nblk, const int chunk) {
+  // XCD-aware remap of the flat work-group id
+  const int bid = blockIdx.x;
+  const int lb = (bid & 7) * chunk + (bid >> 3);
+  if (lb >= nblk) return;
+  gemm_bf16_tile<BM, BN, BK, WM, WN, NS, PP, AT, BT, EPI, ACT>(pin, tilesM, tilesN, lb);
+}
+
+// Short-batch weight gradients of several layers in one launch (64 x 256 x 32 tiles): each is a few microseconds of
+// streaming, so what separate launches add is their starts and their nearly empty last waves.  The tiles of the layers
+// lie one behind the other; the launch picks the layer by the tile number.
+struct WgradMany {
+  enum { MAXN = 8 };
+  int n, nblk, chunk;
+  int end[MAXN], tilesM[MAXN], tilesN[MAXN];
+  GemmP p[MAXN];
+};
+static_assert(sizeof(WgradMany) <= 4096, "kernel arguments");
+template <int EPI, int ACT>
+__global__ void __launch_bounds__(256) wgrad_many_kernel(const WgradMany q) {
+  const int bid = blockIdx.x;
+  int lb = (bid & 7) * q.chunk + (bid >> 3);
+  if (lb >= q.nblk) return;
+  int l = 0;
+  while (lb >= q.end[l]) ++l;                     // uniform; end[n - 1] == nblk
+  if (l > 0) lb -= q.end[l - 1];
+  gemm_bf16_tile<64, 256, 32, 1, 4, 2, false, true, true, EPI, ACT>(q.p[l], q.tilesM[l], q.tilesN[l], lb);
+}
+
+template <int BM, int BN, int BK, int WM, int WN, int NS, bool PP, bool AT, bool BT, int EPI, int ACT>
 hipError_t launch_cfg(const GemmP &p, hipStream_t s) {
   constexpr int NT = WM * WN * 64;
   constexpr size_t tile_bytes = (size_t)NS * (BM + BN) * BK * sizeof(bf16_t);
@@ -943,9 +970,7 @@ hipError_t launch_shape(const GemmP &p, hipStream_t s) {
   constexpr bool IS_WGRAD = EPI == EPI_WGRAD || EPI == EPI_WGRAD_UPD;
   switch (IS_WGRAD ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr) : tiled_shape(p.Md, p.Nd, p.groups)) {
     case 0: return launch_cfg<128, 64, 64, 4, 1, 3, false, AT, BT, EPI, ACT>(p, s);
-    case 3:
-      if constexpr (IS_WGRAD) return launch_cfg<64, 256, 32, 1, 4, 2, false, AT, BT, EPI, ACT>(p, s);
-      else return hipErrorInvalidValue;
+    case 3: return hipErrorInvalidValue;         // (launch_wgrad_many)
     case 2:
       if constexpr (!IS_WGRAD) if (p.Kd <= PIPE_MIN_K) return launch_cfg<256, 256, 64, 2, 4, 2, false, AT, BT, EPI, ACT>(p, s);
       return launch_cfg<256, 256, 64, 2, 4, 2, true, AT, BT, EPI, ACT>(p, s);
@@ -1013,6 +1038,37 @@ int tiled_shape(int Md, int Nd, int groups) {
 constexpr long long SMALL_TILES = 1024;
 long long small_tiles(int Md, int Nd, int groups) { return (long long)((Md + 31) / 32) * ((Nd + 31) / 32) * groups; }
 
+template <int EPI, int ACT>
+hipError_t launch_many(const WgradMany &q, hipStream_t s) {
+  // dynamic LDS of the 64 x 256 x 32 tile: two stages of 20 KB, or the epilogue's fp32 staging slices
+  constexpr size_t lds = std::max<size_t>((size_t)2 * (64 + 256) * 32 * sizeof(bf16_t), (size_t)4 * 32 * (256 / 4 + 4) * sizeof(float));
+  static_assert(lds <= 64 * 1024, "no attribute needed");
+  hipLaunchKernelGGL((wgrad_many_kernel<EPI, ACT>), dim3(q.chunk * 8), dim3(256), lds, s, q);
+  return hipGetLastError();
+}
+
+// operand checks that every launch relies on: 16-byte aligned rows, operands below 2 GiB per replica
+bool operands_ok(const GemmP &p, int epi) {
+  if ((p.lda & 7) || (p.ldb & 7)) return false;
+  if ((reinterpret_cast<uintptr_t>(p.A) & 15) || (reinterpret_cast<uintptr_t>(p.B) & 15)) return false;
+  if ((p.sAg & 7) || (p.sBg & 7)) return false;
+  if (!p.a_trans && (p.Kd > p.lda)) return false;
+  if (!p.b_trans && (p.Kd > p.ldb)) return false;
+  if (p.a_trans && (p.Md > p.lda)) return false;
+  if (p.b_trans && (p.Nd > p.ldb)) return false;
+  const long long abytes = (long long)(p.a_trans ? p.Kd : p.Md) * p.lda * 2;
+  const long long bbytes = (long long)(p.b_trans ? p.Kd : p.Nd) * p.ldb * 2;
+  if (abytes >= (1LL << 31) || bbytes >= (1LL << 31)) return false;
+  if (p.ksplit > 1 && (epi != EPI_WGRAD || !p.kpart || p.kchunk <= 0 || (p.kchunk & 63) ||
+                       (long long)p.kchunk * p.ksplit < p.Kd || (p.Nd & 3)))
+    return false;
+  if (p.upd_x && (epi != EPI_WGRAD || p.ksplit > 1 || p.accumulate || !p.upd_sq || (p.ldc & 3) || (p.Nd & 3) ||
+                  (p.sCg & 3) || (reinterpret_cast<uintptr_t>(p.upd_x) & 15) || (p.C2 && ((p.ldc2 & 3) || p.ldc2 != p.ldc)) ||
+                  (p.upd_opt != OPT_SGD && !p.upd_v) || (p.upd_opt == OPT_ADAMW && !p.upd_m)))
+    return false;
+  return true;
+}
+
 }  // namespace
 
 int gemm_bf16_tile_shape(int epi, int Md, int Nd, int groups) {
@@ -1077,25 +1133,43 @@ int gemm_bf16_ipdot_parts(int Nd) {
   return (Nd + 127) / 128;
 }
 
+hipError_t launch_wgrad_many(const GemmP *p, int n, hipStream_t s) {
+  for (int at = 0; at < n;) {
+    WgradMany q;
+    q.n = 0;
+    long long blocks = 0;
+    const bool upd = p[at].upd_x != nullptr;
+    for (; at < n && q.n < WgradMany::MAXN; ++at) {
+      const GemmP &c = p[at];
+      // one kernel variant for all: every layer carries the same optimizer step, or none
+      if (!operands_ok(c, EPI_WGRAD) || !c.a_trans || !c.b_trans || c.ksplit > 1 || (c.upd_x != nullptr) != upd ||
+          (upd && c.upd_opt != p[0].upd_opt) ||
+          gemm_bf16_wgrad_shape(c.Md, c.Nd, c.Kd, c.groups, upd) != 3)
+        return hipErrorInvalidValue;
+      q.tilesM[q.n] = (c.Md + 63) / 64; q.tilesN[q.n] = (c.Nd + 255) / 256;
+      blocks += (long long)q.tilesM[q.n] * q.tilesN[q.n] * c.groups;
+      if (blocks > 0x3fffffff) return hipErrorInvalidValue;
+      q.end[q.n] = (int)blocks;
+      q.p[q.n++] = c;
+    }
+    if (blocks <= 0) continue;
+    q.nblk = (int)blocks;
+    q.chunk = (q.nblk + 7) / 8;
+    hipError_t e;
+    if (!upd) e = launch_many<EPI_WGRAD, ACT_NONE>(q, s);
+    else if (p[0].upd_opt == OPT_SGD) e = launch_many<EPI_WGRAD_UPD, OPT_SGD>(q, s);
+    else if (p[0].upd_opt == OPT_SHB) e = launch_many<EPI_WGRAD_UPD, OPT_SHB>(q, s);
+    else if (p[0].upd_opt == OPT_ADAMW) e = launch_many<EPI_WGRAD_UPD, OPT_ADAMW>(q, s);
+    else if (p[0].upd_opt == OPT_ADAGRAD) e = launch_many<EPI_WGRAD_UPD, OPT_ADAGRAD>(q, s);
+    else return hipErrorInvalidValue;
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 hipError_t launch_gemm_bf16(const GemmP &p, int epi, hipStream_t s) {
-  // operand checks the kernels rely on: 16-byte aligned rows, operands below 2 GiB per replica
-  if ((p.lda & 7) || (p.ldb & 7)) return hipErrorInvalidValue;
-  if ((reinterpret_cast<uintptr_t>(p.A) & 15) || (reinterpret_cast<uintptr_t>(p.B) & 15)) return hipErrorInvalidValue;
-  if ((p.sAg & 7) || (p.sBg & 7)) return hipErrorInvalidValue;
-  if (!p.a_trans && (p.Kd > p.lda)) return hipErrorInvalidValue;
-  if (!p.b_trans && (p.Kd > p.ldb)) return hipErrorInvalidValue;
-  if (p.a_trans && (p.Md > p.lda)) return hipErrorInvalidValue;
-  if (p.b_trans && (p.Nd > p.ldb)) return hipErrorInvalidValue;
-  const long long abytes = (long long)(p.a_trans ? p.Kd : p.Md) * p.lda * 2;
-  const long long bbytes = (long long)(p.b_trans ? p.Kd : p.Nd) * p.ldb * 2;
-  if (abytes >= (1LL << 31) || bbytes >= (1LL << 31)) return hipErrorInvalidValue;
-  if (p.ksplit > 1 && (epi != EPI_WGRAD || !p.kpart || p.kchunk <= 0 || (p.kchunk & 63) ||
-                       (long long)p.kchunk * p.ksplit < p.Kd || (p.Nd & 3)))
-    return hipErrorInvalidValue;
-  if (p.upd_x && (epi != EPI_WGRAD || p.ksplit > 1 || p.accumulate || !p.upd_sq || (p.ldc & 3) || (p.Nd & 3) ||
-                  (p.sCg & 3) || (reinterpret_cast<uintptr_t>(p.upd_x) & 15) || (p.C2 && ((p.ldc2 & 3) || p.ldc2 != p.ldc)) ||
-                  (p.upd_opt != OPT_SGD && !p.upd_v) || (p.upd_opt == OPT_ADAMW && !p.upd_m)))
-    return hipErrorInvalidValue;
+  if (!operands_ok(p, epi)) return hipErrorInvalidValue;
+  if (epi == EPI_WGRAD && gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr) == 3) return launch_wgrad_many(&p, 1, s);
   if (epi != EPI_WGRAD && gemm_bf16_tile_shape(epi, p.Md, p.Nd, p.groups) == 5) return launch_gemm_small(p, epi, s);
   if (!p.a_trans && !p.b_trans) {
     if (epi == EPI_FWD_ACT) return launch_act<false, false, EPI_FWD_ACT>(p, s);
