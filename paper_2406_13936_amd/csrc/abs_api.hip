@@ -44,7 +44,7 @@ struct Plan {
   size_t o_xm = 0, o_xs = 0, o_grad = 0, o_gradbf = 0, o_v = 0, o_m = 0, o_Xbf = 0;
   size_t o_A[MAXL] = {0}, o_Dact[MAXL] = {0}, o_Dl[MAXL + 1] = {0};
   size_t o_Z = 0, o_U = 0, o_gram = 0, o_an[MAXL] = {0}, o_dn[MAXL + 1] = {0}, o_loss = 0, o_nout = 0, o_qout = 0;
-  size_t o_qpart[MAXL] = {0}, o_partials = 0, o_stats = 0, o_done = 0, o_cw = 0, o_colpart = 0, o_rows = 0, o_sqwave = 0, o_idx = 0, o_scal = 0, o_mean = 0;
+  size_t o_qpart[MAXL] = {0}, o_partials = 0, o_stats = 0, o_cw = 0, o_colpart = 0, o_rows = 0, o_sqwave = 0, o_idx = 0, o_scal = 0, o_mean = 0;
   size_t o_kpart_l[MAXL + 1] = {0};    // per layer: partial products of a split weight-gradient reduction
   size_t kpart_floats_l[MAXL + 1] = {0};
   size_t total = 0;
@@ -152,7 +152,6 @@ void make_plan(const abs_config *c, long long N, Plan &pl) {
   }
   pl.o_partials = take((size_t)pl.M * 5 * STATS_PBLK * 8);
   pl.o_stats = take((size_t)pl.M * 8 * 8);
-  pl.o_done = take((size_t)pl.M * sizeof(int));
   pl.o_rows = take((size_t)2 * pl.M * sizeof(int));          // per-group row counts, then the launch order
   pl.o_sqwave = take((size_t)pl.M * (pl.Ppad / 256) * sizeof(float));
   for (int l = 1; l <= pl.L; ++l) {
@@ -464,7 +463,6 @@ abs_status abs_init_replicas(const abs_config *cfg, const float *x0_host, const 
   void *hs_dev = nullptr;
   if (hipHostGetDevicePointer(&hs_dev, c->host_stats, 0) == hipSuccess) c->host_stats_dev = static_cast<double *>(hs_dev);
   else (void)hipGetLastError();                   // no mapping: read_stats copies instead
-  if ((e = launch_fill_zero(c->at<void>(pl.o_done), rup((long long)pl.M * 4, 16), c->stream)) != hipSuccess) return bail(hipGetErrorString(e));
   // zero parameters, gradient and optimizer state (including their padding)
   const size_t MP = (size_t)pl.M * pl.Ppad;
   if ((e = launch_fill_zero(c->at<void>(pl.o_xm), MP * 4, c->stream)) != hipSuccess) return bail(hipGetErrorString(e));
@@ -914,7 +912,6 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
   sp.Ppad = pl.Ppad;
   sp.partials = c->at<double>(pl.o_partials); sp.stats = c->at<double>(pl.o_stats);
   sp.stats_host = c->host_stats_dev;
-  sp.done = c->at<int>(pl.o_done);
   if (sp.stats_host) { c->ticket += 1.0; sp.ticket = c->ticket; c->ticket_live = true; }
   // When this call both finishes the gradient and updates, the update kernel gathers ||gbar||^2 on
   // its way through the gradient (none of the statistics depends on the parameters, so the update
@@ -1377,12 +1374,11 @@ static abs_status ls_plan(int L, const int *in_dims, const int *out_dims, int M,
   off.push_back(take((size_t)M * Wtot * 2));                 // 1: grad bf16
   off.push_back(take((size_t)M * b * 4 * L));                // 2: an
   off.push_back(take((size_t)M * b * 4 * L));                // 3: dn
-  off.push_back(take((size_t)M * 4));                        // 4: block counters of the statistics (zeros)
-  off.push_back(take((size_t)M * b * 4));                    // 5: n_out
-  off.push_back(take((size_t)M * b * 4));                    // 6: q_out
-  off.push_back(take((size_t)M * 5 * STATS_PBLK * 8));       // 7: partials
-  off.push_back(take((size_t)M * 8 * 8));                    // 8: stats
-  for (int l = 0; l < L; ++l) off.push_back(take((size_t)M * b * 4 * gemm_bf16_ipdot_parts(out_dims[l])));  // 9+l
+  off.push_back(take((size_t)M * b * 4));                    // 4: n_out
+  off.push_back(take((size_t)M * b * 4));                    // 5: q_out
+  off.push_back(take((size_t)M * 5 * STATS_PBLK * 8));       // 6: partials
+  off.push_back(take((size_t)M * 8 * 8));                    // 7: stats
+  for (int l = 0; l < L; ++l) off.push_back(take((size_t)M * b * 4 * gemm_bf16_ipdot_parts(out_dims[l])));  // 8+l
   total = o;
   return ABS_OK;
 }
@@ -1415,9 +1411,7 @@ abs_status abs_layer_stats(int L, const int *in_dims, const int *out_dims, int M
   bf16_t *gradbf = reinterpret_cast<bf16_t *>(ws + off[1]);
   float *an = reinterpret_cast<float *>(ws + off[2]);
   float *dn = reinterpret_cast<float *>(ws + off[3]);
-  int *done = reinterpret_cast<int *>(ws + off[4]);
   abs_ctx *nc = nullptr;
-  HIPCHK(nc, launch_fill_zero(done, rup((long long)M * 4, 16), s));
   {
     // the weight gradients overwrite every entry of their layers; only the padding behind the last layer,
     // which the ||gbar||^2 pass reads too, has to be cleared
@@ -1451,7 +1445,7 @@ abs_status abs_layer_stats(int L, const int *in_dims, const int *out_dims, int M
     p.B = gradbf + woff[l]; p.sBg = Wtot; p.ldb = in_dims[l];
     p.Md = b; p.Nd = out_dims[l]; p.Kd = in_dims[l]; p.groups = M;
     p.E = delta_dev[l]; p.sEg = sd; p.lde = out_dims[l];
-    p.part = reinterpret_cast<float *>(ws + off[9 + l]); p.sPartg = (long long)b * np; p.sPartTile = b;
+    p.part = reinterpret_cast<float *>(ws + off[8 + l]); p.sPartg = (long long)b * np; p.sPartTile = b;
     HIPCHK(nc, launch_gemm_bf16(p, EPI_IPDOT, s));
     sp.qpart[l] = p.part; sp.nparts[l] = gemm_bf16_row_parts(EPI_IPDOT, b, out_dims[l], M); sp.sQg[l] = p.sPartg; sp.sQpart[l] = b;
     sp.an[l] = an + (size_t)l * M * b; sp.dn[l] = dn + (size_t)l * M * b;
@@ -1459,12 +1453,11 @@ abs_status abs_layer_stats(int L, const int *in_dims, const int *out_dims, int M
   }
   sp.L = L; sp.has_bias = 0; sp.groups = M; sp.b = b; sp.want_ip = 1; sp.sNg = sp.sPart = b;
   sp.do_n = sp.do_q = 1;
-  sp.done = done;
-  sp.n_out = n_out_dev ? n_out_dev : reinterpret_cast<float *>(ws + off[5]);
-  sp.q_out = q_out_dev ? q_out_dev : reinterpret_cast<float *>(ws + off[6]);
+  sp.n_out = n_out_dev ? n_out_dev : reinterpret_cast<float *>(ws + off[4]);
+  sp.q_out = q_out_dev ? q_out_dev : reinterpret_cast<float *>(ws + off[5]);
   sp.grad = grad; sp.Ppad = Wtot;
-  sp.partials = reinterpret_cast<double *>(ws + off[7]);
-  sp.stats = reinterpret_cast<double *>(ws + off[8]);
+  sp.partials = reinterpret_cast<double *>(ws + off[6]);
+  sp.stats = reinterpret_cast<double *>(ws + off[7]);
   HIPCHK(nc, launch_stats(sp, s));
   if (gbar_out_dev) {
     long long Wsum = 0;

@@ -199,7 +199,6 @@ struct StatsP {
   const float *grad;        // [g][Ppad]
   long long Ppad;
   double *partials;         // scratch: [groups][5][PBLK]
-  int *done;                // [groups] block counters, zero before the launch and after it
   double *stats;            // out: [groups][8] = S1, S2, S3, S4, loss, 0,0,0
   double ticket;            // with stats_host: written to stats_host[g * 8 + 7] after group g's sums have been
                             //   made visible to the host (a host that polls that word needs no stream synchronisation)

@@ -374,118 +374,154 @@ __global__ void rowdot_f32_kernel(const float *__restrict__ D, long long sDg, in
 }
 
 // ---- statistics ---------------------------------------------------------------------------
-// Stage 1a (grid: PBLK x groups): per-sample squared gradient norms
-//   n_i = sum_l ||delta_i^l||^2 (||a_i^{l-1}||^2 + [bias])   and   q_i = sum_l sum_parts ...
-// with block partial sums of n_i, q_i, q_i^2 and the loss, in double.
-// s = (((s0 + base[0]) + base[stride]) + base[2 stride]) + ... over n entries: the additions keep their order, the
-// loads go out eight at a time (one at a time, n dependent round trips to memory dominate the kernel).
-__device__ __forceinline__ float sum_strided(float s0, const float *__restrict__ base, int n, long long stride) {
-  float s = s0;
-  int k = 0;
-  for (; k + 8 <= n; k += 8) {
-    float v[8];
+// Per-sample squared gradient norms  n_i = sum_l ||delta_i^l||^2 (||a_i^{l-1}||^2 + [bias])  and inner products
+// q_i = sum_l sum_parts ..., their sums (n, q, q^2, the loss) and ||gbar||^2, in double.
+//
+// What bounds these launches is the chain of dependent loads per sample (a norm is the sum of up to 64 tile partials),
+// so four thread groups of a block share a sample: group j takes the layers j, j + 4, ..., with both norms' partials eight
+// at a time in flight (b = 64 of config 3, one thread per sample: 12.6 us, of which 11 were these chains).
+// Summation order: partials in index order, a group's layers in order, the four groups in order.
+__device__ __forceinline__ void sum_partials2(const float *__restrict__ a, int na, const float *__restrict__ d, int nd,
+                                              long long stride, float &sa, float &sd) {
+  sa = sd = 0.0f;
+  for (int k = 0; k < na || k < nd; k += 8) {
+    float va[8], vd[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = base[(long long)(k + u) * stride];
+    for (int u = 0; u < 8; ++u) va[u] = k + u < na ? a[(long long)(k + u) * stride] : 0.0f;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) s += v[u];
+    for (int u = 0; u < 8; ++u) vd[u] = k + u < nd ? d[(long long)(k + u) * stride] : 0.0f;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) { sa += va[u]; sd += vd[u]; }
   }
-  if (k + 4 <= n) {
-    float v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = base[(long long)(k + u) * stride];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) s += v[u];
-    k += 4;
-  }
-  for (; k < n; ++k) s += base[(long long)k * stride];
-  return s;
 }
 
-// Blocks 0 .. nb-1 of a group share its samples (block j owns samples 256 j + t, then strides of 256 nb);
-// the launch uses nb = min(PBLK, ceil(b / 256)) blocks and stage 2 takes the other partials as zero.
-__device__ __forceinline__ void stats_samples_block(const StatsP &p, int g, int blk, int nb, double *red) {
-  double s1 = 0.0, s3 = 0.0, s4 = 0.0, sl = 0.0;
+struct StatsSums { double s[5]; };      // n, ||gbar||^2, q^2, q, loss
+
+// Blocks 0 .. nb-1 of a group share its samples: block j owns samples (NT / 4) j + t, then strides of nb NT / 4.
+template <int NT>
+__device__ __forceinline__ void stats_samples(const StatsP &p, int g, int blk, int nb, StatsSums &o) {
+  constexpr int SL = NT / 4;
+  __shared__ float comb[2][4][SL];
+  const int gl = threadIdx.x / SL, sl = threadIdx.x % SL;
   const float hb = p.has_bias ? 1.0f : 0.0f;
   const int bg = p.rows ? p.rows[g] : p.b;
-  for (int i = blk * 256 + threadIdx.x; i < bg; i += 256 * nb) {
-    const long long o = (long long)g * p.sNg + i;
-    if (p.do_n) {
-      float n = 0.0f;
-      for (int l = 0; l < p.L; ++l) {
-        const float a = sum_strided(0.0f, p.an[l] + (long long)g * p.an_sg[l] + i, p.an_parts[l], p.sPart);
-        const float d = sum_strided(0.0f, p.dn[l] + (long long)g * p.dn_sg[l] + i, p.dn_parts[l], p.sPart);
-        n = fmaf(d, a + hb, n);
+  for (int base = blk * SL; base < bg; base += nb * SL) {        // uniform over the block
+    const int i = base + sl;
+    const bool live = i < bg;
+    float n = 0.0f, q = 0.0f;
+    if (live) {
+      for (int l = gl; l < p.L; l += 4) {
+        if (p.do_n) {
+          float a, d;
+          sum_partials2(p.an[l] + (long long)g * p.an_sg[l] + i, p.an_parts[l], p.dn[l] + (long long)g * p.dn_sg[l] + i,
+                        p.dn_parts[l], p.sPart, a, d);
+          n = fmaf(d, a + hb, n);
+        }
+        if (p.do_q) {
+          const float *qp = p.qpart[l] + (long long)g * p.sQg[l] + i;
+          for (int k = 0; k < p.nparts[l]; k += 8) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = k + u < p.nparts[l] ? qp[(long long)(k + u) * p.sQpart[l]] : 0.0f;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) q += v[u];
+          }
+        }
       }
-      if (p.n_out) p.n_out[o] = n;
-      s1 += (double)n;
-      if (p.loss) sl += (double)p.loss[o];
     }
-    if (p.do_q) {
-      float q = 0.0f;
-      for (int l = 0; l < p.L; ++l) {
-        q = sum_strided(q, p.qpart[l] + (long long)g * p.sQg[l] + i, p.nparts[l], p.sQpart[l]);
+    comb[0][gl][sl] = n;
+    comb[1][gl][sl] = q;
+    __syncthreads();
+    if (gl == 0 && live) {
+      const long long at = (long long)g * p.sNg + i;
+      if (p.do_n) {
+        n = ((n + comb[0][1][sl]) + comb[0][2][sl]) + comb[0][3][sl];
+        if (p.n_out) p.n_out[at] = n;
+        o.s[0] += (double)n;
+        if (p.loss) o.s[4] += (double)p.loss[at];
       }
-      if (p.q_out) p.q_out[o] = q;
-      s4 += (double)q;
-      s3 += (double)q * (double)q;
+      if (p.do_q) {
+        q = ((q + comb[1][1][sl]) + comb[1][2][sl]) + comb[1][3][sl];
+        if (p.q_out) p.q_out[at] = q;
+        o.s[3] += (double)q;
+        o.s[2] += (double)q * (double)q;
+      }
     }
+    __syncthreads();
   }
-  double *out = p.partials + ((long long)g * 5) * STATS_PBLK + blk;
-  double r;
-  r = block_sum<4>(s1, red); if (threadIdx.x == 0) out[0 * STATS_PBLK] = r;
-  r = block_sum<4>(s3, red); if (threadIdx.x == 0) out[2 * STATS_PBLK] = r;
-  r = block_sum<4>(s4, red); if (threadIdx.x == 0) out[3 * STATS_PBLK] = r;
-  r = block_sum<4>(sl, red); if (threadIdx.x == 0) out[4 * STATS_PBLK] = r;
 }
-__device__ __forceinline__ void stats_gradsq_parts_block(const float *__restrict__ sq_wave, long long per_group,
-                                                         long long stride, double *__restrict__ partials, int g, int blk,
-                                                         int nb, double *red) {
-  const float *p = sq_wave + (long long)g * (stride ? stride : per_group);
-  double s = 0.0;
-  for (long long i = blk * 256LL + threadIdx.x; i < per_group; i += 256LL * nb) s += (double)p[i];
-  const double r = block_sum<4>(s, red);
-  if (threadIdx.x == 0) partials[((long long)g * 5 + 1) * STATS_PBLK + blk] = r;
+// ||gbar||^2 from the partial sums that the launches which applied or stored the gradient left (blk of nb blocks)
+template <int NT>
+__device__ __forceinline__ void stats_gradsq_parts(const StatsP &p, int g, int blk, int nb, StatsSums &o) {
+  const float *q = p.sq_wave + (long long)g * (p.sq_stride ? p.sq_stride : p.n_sq_wave);
+  const long long step = (long long)NT * nb;
+#pragma unroll 4
+  for (long long i = (long long)blk * NT + threadIdx.x; i < p.n_sq_wave; i += step) o.s[1] += (double)q[i];
 }
-// grid (nb_samples + nb_parts) x groups: the first nb_samples blocks of a group take the per-sample sums, the others (present
-// when the gradient's squares were left as partial sums) the ||gbar||^2 partials.  The block of a group that finishes last
-// adds the partials of each of the five sums in index order and delivers them: a launch of its own for that (5 blocks sums
-// one after the other) took 3.6 to 5.8 us of every step.
-// sel / acc: bit k set = sum k is produced by this launch / is added to the stored value.  n2: ||gbar||^2 partials.
-__global__ void __launch_bounds__(256) stats_kernel(const StatsP p, const int nb_samples, const int n2, const int sel, const int acc) {
-  __shared__ double red[4];
-  __shared__ double fin[5][4];
-  __shared__ int last;
-  const int g = blockIdx.y, blk = blockIdx.x;
-  if (blk < nb_samples) stats_samples_block(p, g, blk, nb_samples, red);
-  else if (p.sq_wave) stats_gradsq_parts_block(p.sq_wave, p.n_sq_wave, p.sq_stride, p.partials, g, blk - nb_samples, n2, red);
-  if (threadIdx.x == 0) {                         // (this thread has written the block's partials itself)
-    __threadfence();
-    last = atomicAdd(p.done + g, 1) == (int)gridDim.x - 1;
-    __threadfence();
-  }
-  __syncthreads();
-  if (!last) return;
-  static_assert(STATS_PBLK == 256, "one partial per thread");
-  const int t = threadIdx.x;
+// Sum over a block, fixed order; sum k ends in thread k < 5.
+template <int NT>
+__device__ __forceinline__ double stats_block_sums(const StatsSums &o) {
+  constexpr int NW = NT / 64;
+  __shared__ double fin[5][NW];
 #pragma unroll
   for (int k = 0; k < 5; ++k) {
-    double v = 0.0;
-    if (((sel >> k) & 1) && t < (k == 1 ? n2 : nb_samples)) v = p.partials[((long long)g * 5 + k) * STATS_PBLK + t];
-    v = wave_sum(v);
-    if ((t & 63) == 0) fin[k][t >> 6] = v;
+    const double v = wave_sum(o.s[k]);
+    if ((threadIdx.x & 63) == 0) fin[k][threadIdx.x >> 6] = v;
   }
   __syncthreads();
+  double r = 0.0;
+  if (threadIdx.x < 5)
+    for (int w = 0; w < NW; ++w) r += fin[threadIdx.x][w];
+  return r;
+}
+// thread k < 5 holds sum k of group g.  sel / acc: bit k set = sum k is produced by this launch / is added to the stored value.
+__device__ __forceinline__ void stats_deliver(const StatsP &p, int g, int sel, int acc, double r) {
+  const int t = threadIdx.x;
   if (t < 5 && ((sel >> t) & 1)) {
-    const double r = ((fin[t][0] + fin[t][1]) + fin[t][2]) + fin[t][3];
     const double v = ((acc >> t) & 1) ? p.stats[g * 8 + t] + r : r;
     p.stats[g * 8 + t] = v;
     if (p.stats_host) p.stats_host[g * 8 + t] = v;
   }
-  if (t < 64 && p.stats_host) __threadfence_system();   // the sums above reach host memory before the ticket does
-  if (t == 0) {
-    p.done[g] = 0;
-    if (p.stats_host) *reinterpret_cast<volatile double *>(p.stats_host + g * 8 + 7) = p.ticket;
+  if (t < 64 && p.stats_host) {
+    __threadfence_system();                       // the sums above reach host memory before the ticket does
+    if (t == 0) *reinterpret_cast<volatile double *>(p.stats_host + g * 8 + 7) = p.ticket;
   }
+}
+
+// One block per group does it all: for short batches and few partial sums, where two dependent launches cost more than
+// their work (784-512-512-10, b = 32: 8.6 + 3.9 us apart; b = 64 of config 3: 12.6 + 5.6).
+// n2: ||gbar||^2 partials left by stats_gradsq_kernel (0: none).
+__global__ void __launch_bounds__(1024) stats_one_kernel(const StatsP p, const int n2, const int sel, const int acc) {
+  const int g = blockIdx.x;
+  StatsSums o = {{0.0, 0.0, 0.0, 0.0, 0.0}};
+  if (p.sq_wave) stats_gradsq_parts<1024>(p, g, 0, 1, o);
+  else if ((int)threadIdx.x < n2) o.s[1] = p.partials[((long long)g * 5 + 1) * STATS_PBLK + threadIdx.x];
+  if (p.do_n || p.do_q) stats_samples<1024>(p, g, 0, 1, o);
+  stats_deliver(p, g, sel, acc, stats_block_sums<1024>(o));
+}
+// grid (nb_samples + nb_parts) x groups: the first nb_samples blocks of a group take the per-sample sums, the other
+// nb_parts the ||gbar||^2 partials; stats_final_kernel adds the blocks' sums in index order.
+__global__ void __launch_bounds__(256) stats_samples_kernel(const StatsP p, const int nb_samples, const int nb_parts) {
+  const int g = blockIdx.y, blk = blockIdx.x;
+  StatsSums o = {{0.0, 0.0, 0.0, 0.0, 0.0}};
+  const bool samples = blk < nb_samples;
+  if (samples) stats_samples<256>(p, g, blk, nb_samples, o);
+  else stats_gradsq_parts<256>(p, g, blk - nb_samples, nb_parts, o);
+  const double r = stats_block_sums<256>(o);
+  const int t = threadIdx.x;
+  if (t < 5 && samples == (t != 1)) p.partials[((long long)g * 5 + t) * STATS_PBLK + (samples ? blk : blk - nb_samples)] = r;
+}
+__global__ void __launch_bounds__(256) stats_final_kernel(const StatsP p, const int nb_samples, const int n2, const int sel,
+                                                          const int acc) {
+  const int g = blockIdx.x;
+  StatsSums o;
+  static_assert(STATS_PBLK == 256, "one partial per thread");
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+    const bool live = ((sel >> k) & 1) && (int)threadIdx.x < (k == 1 ? n2 : nb_samples);
+    o.s[k] = live ? p.partials[((long long)g * 5 + k) * STATS_PBLK + threadIdx.x] : 0.0;
+  }
+  stats_deliver(p, g, sel, acc, stats_block_sums<256>(o));
 }
 
 // Stage 1b (grid: PBLK x groups): ||gbar||^2 over the padded gradient vector.
@@ -956,6 +992,9 @@ hipError_t launch_rowdot_f32(const float *D, long long sDg, int ldd, const float
   return hipGetLastError();
 }
 
+static constexpr int STATS_ONE_B = 512;
+static constexpr long long STATS_ONE_SQ = 8192;
+
 hipError_t launch_stats(const StatsP &p, hipStream_t s) {
   if (p.do_q && !p.want_ip) return hipErrorInvalidValue;
   int sel = 0, acc = 0;
@@ -964,21 +1003,24 @@ hipError_t launch_stats(const StatsP &p, hipStream_t s) {
   if (p.grad && p.sq_wave) return hipErrorInvalidValue;
   if (p.grad || p.sq_wave) sel |= 2;
   if (!sel && !p.stats_host) return hipSuccess;       // (with a mirror the final kernel still delivers the ticket)
-  int nb_samples = 0;
-  if (p.do_n || p.do_q) {
-    nb_samples = (p.b + 255) / 256;
-    nb_samples = nb_samples < 1 ? 1 : (nb_samples > STATS_PBLK ? STATS_PBLK : nb_samples);
-  }
-  // ||gbar||^2: from partial sums (256 per block, at most PBLK blocks), or a pass over the gradient by PBLK blocks
+  const bool samples = p.do_n || p.do_q;
   int n2 = 0;
-  if (p.sq_wave) n2 = (int)std::min<long long>(STATS_PBLK, std::max<long long>(1, (p.n_sq_wave + 255) / 256));
   if (p.grad) {
     hipLaunchKernelGGL(stats_gradsq_kernel, dim3(STATS_PBLK, p.groups), dim3(256), 0, s, p.grad, p.Ppad,
                        p.partials);
     n2 = STATS_PBLK;
   }
-  const int blocks = std::max(1, nb_samples + (p.sq_wave ? n2 : 0));
-  hipLaunchKernelGGL(stats_kernel, dim3(blocks, p.groups), dim3(256), 0, s, p, nb_samples, n2, sel, acc);
+  // One block per group while a thread has at most two samples and eight partial sums to walk.
+  if ((!samples || p.b <= STATS_ONE_B) && (!p.sq_wave || p.n_sq_wave <= STATS_ONE_SQ)) {
+    hipLaunchKernelGGL(stats_one_kernel, dim3(p.groups), dim3(1024), 0, s, p, n2, sel, acc);
+    return hipGetLastError();
+  }
+  const int nb_samples = samples ? std::min((p.b + 63) / 64, (int)STATS_PBLK) : 0;
+  if (p.sq_wave) n2 = (int)std::min<long long>(STATS_PBLK, (p.n_sq_wave + 255) / 256);
+  const int nb_parts = p.sq_wave ? n2 : 0;
+  if (nb_samples + nb_parts > 0)
+    hipLaunchKernelGGL(stats_samples_kernel, dim3(nb_samples + nb_parts, p.groups), dim3(256), 0, s, p, nb_samples, nb_parts);
+  hipLaunchKernelGGL(stats_final_kernel, dim3(p.groups), dim3(256), 0, s, p, nb_samples, n2, sel, acc);
   return hipGetLastError();
 }
 
