@@ -744,23 +744,25 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       p.alpha = inv_b; p.accumulate = ph.acc_grad ? 1 : 0;
       if (pl.bf16 && pl.want_ip && !use_gram) { p.C2 = c->at<bf16_t>(pl.o_gradbf) + pl.offW[l]; p.sC2g = pl.Ppad; p.ldc2 = pl.dims[l - 1]; }
       if (!pl.bf16 && p.ldc == p.Nd && (((long long)p.Md * p.Nd) & 3) == 0) {
-        // fp32 mode (small problems): a block walks its reduction 32 samples at a time, about 2.7 us a step, so
-        // a long batch over few 64 x 64 output tiles is cut into up to 8 slices (finish launch: about 8 us)
-        const long long blocks = (long long)((p.Md + 63) / 64) * ((p.Nd + 63) / 64) * M;
-        const int KT = (b + 31) / 32;
+        // fp32 mode (small problems): a block of the smallest tiles walks its reduction 256 samples at a time, about
+        // 2.5 us a step, so a long batch over few tiles is cut into up to 8 slices (finish launch and the bias sums'
+        // two launches: about 10 us)
+        const long long blocks = (long long)((p.Md + 15) / 16) * ((p.Nd + 15) / 16) * M;
+        const int KT = (b + 255) / 256;
         int best = 1;
-        double best_cost = KT * 2.7;
-        for (int S = 2; S <= 8 && blocks < 256; ++S) {
+        double best_cost = KT * 2.5;
+        for (int S = 2; S <= 8 && blocks < 128; ++S) {
           if (blocks * S > 1024 || (size_t)S * M * p.Md * p.Nd > pl.kpart_floats_l[l]) break;
-          const double cost = ((KT + S - 1) / S) * 2.7 + 8.0;
+          const double cost = ((KT + S - 1) / S) * 2.5 + 10.0;
           if (cost < best_cost) { best = S; best_cost = cost; }
         }
         if (best > 1) {
           p.ksplit = best;
-          p.kchunk = ((KT + best - 1) / best) * 32;
+          p.kchunk = ((KT + best - 1) / best) * 256;
           p.kpart = c->at<float>(pl.o_kpart_l[l]);
         }
       }
+      if (hb && !pl.bf16 && p.ksplit <= 1) { p.rowsum = grad + pl.offB[l]; p.sRowsumg = pl.Ppad; }
       if (bf16_ksplit(l) > 1) {
         const int KT = (b + 63) / 64, S = bf16_ksplit(l);
         p.ksplit = S;
@@ -787,7 +789,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
         kf_bytes += (4.0 * p.ksplit + 6.0) * M * p.Md * p.Nd;
         if (fused) { kf.upd_slot0[e] = fused_slots; fused_slots += splitk_finish_slots(kf.mn[e]); }
       }
-      if (hb && !pl.bf16) {
+      if (hb && !pl.bf16 && p.ksplit > 1) {
         ProfScope ps_(c, T_COLSUM, 0.0, 1.0 * M * b * pl.ld[l] * pl.esz);
         HIPCHK(c, launch_col_sum(isb, p.A, p.sAg, pl.ld[l], pl.dims[l], M, b, inv_b, grad + pl.offB[l], pl.Ppad,
                                  c->at<float>(pl.o_colpart), rows, ph.acc_grad ? 1 : 0, s));

@@ -54,6 +54,9 @@ struct GemmP {
   // kpart[(g * ksplit + sp) * Md * Nd] (row-major, ld = Nd) and C / C2 are left to launch_splitk_finish.
   int ksplit, kchunk;
   float *kpart;
+  // fp32 family, EPI_WGRAD without a split (optional): rowsum[g * sRowsumg + m] = alpha * sum_k A[m][k] (+ the old value
+  // if accumulate): the bias gradient beside the weight gradient
+  float *rowsum; long long sRowsumg;
   // Optimizer step inside the epilogue (EPI_WGRAD of the bf16 family, optional: upd_x != null; needs ksplit <= 1,
   // accumulate == 0 and ldc, the layer offsets and the group stride multiples of 4).  The finished gradient entry
   // g = alpha * acc is not stored in C; instead the parameter at the same offset of upd_x (and its state in

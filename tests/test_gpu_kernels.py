@@ -111,3 +111,34 @@ def test_small_launches_at_the_edges_of_their_tiles(dims, act, b):
         assert rep.guard_intact()
     finally:
         rep.close()
+
+
+# fp32 contractions: 16-, 32- and 64-wide tiles with remainders, k-steps of 256 / 128 / 32 with remainders on either side of a
+# step, the bias sums beside the weight gradient, and a reduction long enough over few tiles to be split (b = 4099).
+@pytest.mark.parametrize("dims,b,M", [((33, 2), 2, 1), ((257, 17), 255, 3), ((256, 10), 257, 4), ((130, 40, 5), 513, 2),
+                                      ((520, 136, 70), 300, 8), ((31, 3), 4099, 1)])
+def test_fp32_step_at_the_edges_of_its_tiles(dims, b, M):
+    A = _A()
+    act = W.ACT_GELU if len(dims) > 2 else W.ACT_NONE
+    w = W.Workload("edges", dims, act, True, W.PREC_F32, N=512, M=M, H=1, rounds=1, b0=b, b_cap=b, opt=W.OPT_SGD, lr=0.05,
+                   test=W.TEST_IP, theta=0.9, data="teacher_mlp", seed=9)
+    X, y = W.make_dataset(w)
+    x0 = W.make_x0(w)
+    rep = A.Replicas.from_workload(w, X, y, x0)
+    orc = O.Replicas(O.Net(w.dims, w.act, True), x0, X, y, M, opt=w.opt, want_ip=True)
+    try:
+        idx = W.step_indices(w, 0, 0, b)
+        rep.local_step(idx, w.lr)
+        g = rep.inner_product_test(w.theta)
+        orc.local_step(idx, w.lr)
+        for m in range(M):
+            s = orc.stats[m]
+            # fp32 sums of up to 4099 products: (terms + layers) * 2^-24 of their magnitudes at worst, 1e-4 with room
+            for got, want in ((g[m].sum_sq, s["S1"]), (g[m].gbar_sq, s["S2"]), (g[m].sum_q2, s["S3"]), (g[m].loss_sum, s["loss_sum"])):
+                assert abs(got - want) <= 1e-4 * abs(want), (m, got, want)
+            grad, K = rep.get_grad(m).astype(np.float64), dims[-1]
+            assert np.linalg.norm(grad - orc.grads[m]) <= 1e-5 * np.linalg.norm(orc.grads[m]), m
+            assert np.linalg.norm(grad[-K:] - orc.grads[m][-K:]) <= 1e-5 * np.linalg.norm(orc.grads[m][-K:]), m
+        assert rep.guard_intact()
+    finally:
+        rep.close()
