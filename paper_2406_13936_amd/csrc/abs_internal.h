@@ -34,6 +34,7 @@ struct GemmP {
   float *part; long long sPartg; long long sPartTile; // row partials: part[g][tile_n][m]
                                //   EPI_IPDOT: the row dots; EPI_FWD_ACT / EPI_BWD (bf16 family, optional):
                                //   sum over the tile's columns of the squared stored outputs
+  float *part2;                // EPI_IPDOT (optional): likewise the sum over the tile's columns of E[m][n]^2
   float *cpart; long long sCpartg;   // EPI_BWD (bf16 family, optional): column partials
                                //   cpart[g][tile_m * WM + wave_m][n] = sum over the wave's rows of the stored outputs
   float alpha;
@@ -70,6 +71,9 @@ struct GemmP {
   float upd_lr, upd_momentum, upd_beta1, upd_beta2, upd_eps, upd_wd, upd_c1, upd_c2;
   const float *upd_scal;       // optional (device): {lr, c1, c2} read from memory (replayable launches)
   float *upd_sq; long long upd_sSqg; int upd_slot0;
+  // EPI_WGRAD of the bf16 family without a split or a step (optional): the sum of the squared entries of every wavefront's
+  // part of the output in sq64[g * sSq64g + tile * waves + wave].  C may then be null: only C2 and these sums are written.
+  double *sq64; long long sSq64g;
 };
 
 // bf16 MFMA family (gemm_bf16.hip).  Returns the number of column partials that
@@ -97,8 +101,8 @@ hipError_t launch_gemm_small(const GemmP &p, int epi, hipStream_t s);
 // fused != 0: the launch carries the optimizer step in its epilogue (GemmP::upd_x), which keeps medium batches on
 // 128x128 tiles.
 int gemm_bf16_wgrad_shape(int Md, int Nd, int Kd, int groups, int fused);
-// Number of upd_sq slots an EPI_WGRAD launch with an in-epilogue optimizer step writes per group.
-int gemm_bf16_upd_slots(int Md, int Nd, int Kd, int groups);
+// Number of upd_sq slots (fused: with the optimizer step in the epilogue) or sq64 slots an EPI_WGRAD launch writes per group.
+int gemm_bf16_upd_slots(int Md, int Nd, int Kd, int groups, int fused);
 // fp32 SIMT family (gemm_f32.hip); EPI_IPDOT is not offered (U is materialised instead).
 hipError_t launch_gemm_f32(const GemmP &p, int epi, hipStream_t s);
 
@@ -210,6 +214,7 @@ struct StatsP {
   const float *sq_wave;     // alternative source of S2 (grad must be null): per-wavefront sums of g^2 left by the
   long long n_sq_wave;      //   update kernel, n_sq_wave per group (one per 256 consecutive parameters)
   long long sq_stride;      //   distance between two groups' sums (0: n_sq_wave)
+  const double *sq_wave64;  // the same in double (one of the two; n_sq_wave and sq_stride count these)
   const int *rows;          // optional per-group sample counts (device) replacing b
   // which sums this launch produces: S1 and the loss (do_n), S3 and S4 (do_q; needs want_ip),
   // S2 (grad != null); acc_n / acc_q add to the stored sums instead of replacing them
@@ -235,7 +240,6 @@ int cross_worker_blocks(long long Ppad);
 hipError_t launch_cross_worker(const float *g, int groups, long long Ppad, double *partials,
                                double *out, hipStream_t s);
 hipError_t launch_fill_zero(void *p, long long bytes, hipStream_t s);
-hipError_t launch_zero_range(float *x, long long stride, long long from, long long to, int groups, hipStream_t s);
 // Finish of split reductions, the layers of a step in one launch: for layer l and group g
 //   C[g][c_off_l + e] = alpha * sum_sp kpart_l[(g * ksplit_l + sp) * mn_l + e]  (+ the old value if accumulate),
 // slices added in order; C2 (bf16, may be null) gets the rounded result at the same offsets; rows (may be null):

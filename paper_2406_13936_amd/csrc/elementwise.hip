@@ -453,8 +453,13 @@ __device__ __forceinline__ void stats_samples(const StatsP &p, int g, int blk, i
 // ||gbar||^2 from the partial sums that the launches which applied or stored the gradient left (blk of nb blocks)
 template <int NT>
 __device__ __forceinline__ void stats_gradsq_parts(const StatsP &p, int g, int blk, int nb, StatsSums &o) {
-  const float *q = p.sq_wave + (long long)g * (p.sq_stride ? p.sq_stride : p.n_sq_wave);
-  const long long step = (long long)NT * nb;
+  const long long at = (long long)g * (p.sq_stride ? p.sq_stride : p.n_sq_wave), step = (long long)NT * nb;
+  if (p.sq_wave64) {
+#pragma unroll 4
+    for (long long i = (long long)blk * NT + threadIdx.x; i < p.n_sq_wave; i += step) o.s[1] += p.sq_wave64[at + i];
+    return;
+  }
+  const float *q = p.sq_wave + at;
 #pragma unroll 4
   for (long long i = (long long)blk * NT + threadIdx.x; i < p.n_sq_wave; i += step) o.s[1] += (double)q[i];
 }
@@ -494,7 +499,7 @@ __device__ __forceinline__ void stats_deliver(const StatsP &p, int g, int sel, i
 __global__ void __launch_bounds__(1024) stats_one_kernel(const StatsP p, const int n2, const int sel, const int acc) {
   const int g = blockIdx.x;
   StatsSums o = {{0.0, 0.0, 0.0, 0.0, 0.0}};
-  if (p.sq_wave) stats_gradsq_parts<1024>(p, g, 0, 1, o);
+  if (p.sq_wave || p.sq_wave64) stats_gradsq_parts<1024>(p, g, 0, 1, o);
   else if ((int)threadIdx.x < n2) o.s[1] = p.partials[((long long)g * 5 + 1) * STATS_PBLK + threadIdx.x];
   if (p.do_n || p.do_q) stats_samples<1024>(p, g, 0, 1, o);
   stats_deliver(p, g, sel, acc, stats_block_sums<1024>(o));
@@ -1000,8 +1005,9 @@ hipError_t launch_stats(const StatsP &p, hipStream_t s) {
   int sel = 0, acc = 0;
   if (p.do_n) { sel |= 1 | 16; if (p.acc_n) acc |= 1 | 16; }
   if (p.do_q) { sel |= 4 | 8; if (p.acc_q) acc |= 4 | 8; }
-  if (p.grad && p.sq_wave) return hipErrorInvalidValue;
-  if (p.grad || p.sq_wave) sel |= 2;
+  const bool parts = p.sq_wave || p.sq_wave64;
+  if ((p.grad && parts) || (p.sq_wave && p.sq_wave64)) return hipErrorInvalidValue;
+  if (p.grad || parts) sel |= 2;
   if (!sel && !p.stats_host) return hipSuccess;       // (with a mirror the final kernel still delivers the ticket)
   const bool samples = p.do_n || p.do_q;
   int n2 = 0;
@@ -1011,13 +1017,13 @@ hipError_t launch_stats(const StatsP &p, hipStream_t s) {
     n2 = STATS_PBLK;
   }
   // One block per group while a thread has at most two samples and eight partial sums to walk.
-  if ((!samples || p.b <= STATS_ONE_B) && (!p.sq_wave || p.n_sq_wave <= STATS_ONE_SQ)) {
+  if ((!samples || p.b <= STATS_ONE_B) && (!parts || p.n_sq_wave <= STATS_ONE_SQ)) {
     hipLaunchKernelGGL(stats_one_kernel, dim3(p.groups), dim3(1024), 0, s, p, n2, sel, acc);
     return hipGetLastError();
   }
   const int nb_samples = samples ? std::min((p.b + 63) / 64, (int)STATS_PBLK) : 0;
-  if (p.sq_wave) n2 = (int)std::min<long long>(STATS_PBLK, (p.n_sq_wave + 255) / 256);
-  const int nb_parts = p.sq_wave ? n2 : 0;
+  if (parts) n2 = (int)std::min<long long>(STATS_PBLK, (p.n_sq_wave + 255) / 256);
+  const int nb_parts = parts ? n2 : 0;
   if (nb_samples + nb_parts > 0)
     hipLaunchKernelGGL(stats_samples_kernel, dim3(nb_samples + nb_parts, p.groups), dim3(256), 0, s, p, nb_samples, nb_parts);
   hipLaunchKernelGGL(stats_final_kernel, dim3(p.groups), dim3(256), 0, s, p, nb_samples, n2, sel, acc);
@@ -1126,18 +1132,6 @@ hipError_t launch_set_ints(const int *v_host, int n, int *dst, hipStream_t s) {
     for (int i = 0; i < SET_INTS_MAX; ++i) a.v[i] = i < m ? v_host[o + i] : 0;
     hipLaunchKernelGGL(set_ints_kernel, dim3(1), dim3(SET_INTS_MAX), 0, s, a, m, dst + o);
   }
-  return hipGetLastError();
-}
-
-// x[g * stride + i] = 0 for i in [from, to) and every group g (a short range: padding behind the data)
-__global__ void __launch_bounds__(256) zero_range_kernel(float *__restrict__ x, long long stride, long long from, long long to) {
-  float *p = x + (long long)blockIdx.x * stride;
-  for (long long i = from + threadIdx.x; i < to; i += 256) p[i] = 0.0f;
-}
-
-hipError_t launch_zero_range(float *x, long long stride, long long from, long long to, int groups, hipStream_t s) {
-  if (to <= from || groups <= 0) return hipSuccess;
-  hipLaunchKernelGGL(zero_range_kernel, dim3(groups), dim3(256), 0, s, x, stride, from, to);
   return hipGetLastError();
 }
 

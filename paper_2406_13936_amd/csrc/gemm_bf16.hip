@@ -70,6 +70,9 @@ __device__ __forceinline__ void st_once(float *p, float4 v) {
   __builtin_nontemporal_store(w, reinterpret_cast<f32x4_t *>(p));
 }
 
+// EPI_IPDOT instances whose activation slot holds this also leave the squared norms of E's rows (GemmP::part2)
+constexpr int IPDOT_NORMS = 1;
+
 constexpr uint32_t OOB = 0x80000000u;   // byte offset beyond any operand (operands are < 2 GiB)
 
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
@@ -617,15 +620,18 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
 
   float *red = reinterpret_cast<float *>(smem + NW * 32 * SLD);   // [WN][BM] row partials of the waves
   // add the WN waves' row partials in wave order and write part[g][tn][m]
-  auto finish_rows = [&]() {
-    __syncthreads();
-    float *part = p.part + (long long)g * p.sPartg + (long long)tn * p.sPartTile;
+  auto finish_rows_to = [&](const float *src, float *dst) {
+    float *part = dst + (long long)g * p.sPartg + (long long)tn * p.sPartTile;
     for (int r = tid; r < BM; r += NT) {
       float v = 0.0f;
 #pragma unroll
-      for (int w = 0; w < WN; ++w) v += red[w * BM + r];
+      for (int w = 0; w < WN; ++w) v += src[w * BM + r];
       if (m0 + r < p.Md) part[m0 + r] = v;
     }
+  };
+  auto finish_rows = [&]() {
+    __syncthreads();
+    finish_rows_to(red, p.part);
   };
   // squares of the four bf16 values packed in pk
   auto sq4 = [](uint2 pk) -> float {
@@ -640,12 +646,13 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
       const int mrow0 = m0 + slice_row(i);
       if (i + 1 < MI) load_slice(Eg, p.lde, m0 + slice_row(i + 1), p.Nd, ereg[(i + 1) & 1]);
       put_slice(ereg[i & 1]);
-      float rs = 0.0f;
+      float rs = 0.0f, es = 0.0f;
 #pragma unroll
       for (int j = 0; j < NI; ++j)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const uint2 ev = *reinterpret_cast<const uint2 *>(piece(j, q));
+          if (ACT == IPDOT_NORMS) es += sq4(ev);
           const float e4[4] = {__uint_as_float(ev.x << 16), __uint_as_float(ev.x & 0xffff0000u),
                                __uint_as_float(ev.y << 16), __uint_as_float(ev.y & 0xffff0000u)};
 #pragma unroll
@@ -655,8 +662,13 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
         }
       rs += __shfl_xor(rs, 32, 64);                               // the two column halves of the row
       if (lhalf == 0) red[wn * BM + slice_row(i) + lcol] = rs;
+      if (ACT == IPDOT_NORMS) {
+        es += __shfl_xor(es, 32, 64);
+        if (lhalf == 0) red[(WN + wn) * BM + slice_row(i) + lcol] = es;
+      }
     }
     finish_rows();
+    if (ACT == IPDOT_NORMS) finish_rows_to(red + WN * BM, p.part2);
     return;
   }
 
@@ -778,7 +790,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
   constexpr int FCPR = TN / 4;                              // float4 chunks per staged row
   constexpr int FIT = 32 * FCPR / 64;                       // chunks per lane per slice
   float *stf = reinterpret_cast<float *>(smem) + wave * (32 * FLD);
-  float *Cg = static_cast<float *>(p.C) + (long long)g * p.sCg;
+  float *Cg = p.C ? static_cast<float *>(p.C) + (long long)g * p.sCg : nullptr;   // (null: EPI_WGRAD for C2 and sq64 alone)
   bf16_t *C2g = (IS_WGRAD && p.C2) ? static_cast<bf16_t *>(p.C2) + (long long)g * p.sC2g : nullptr;
   bool accumulate = EPI == EPI_WGRAD && p.accumulate;        // micro-batch accumulation: C += alpha * acc
   if (EPI == EPI_WGRAD && ksplit > 1) {                      // raw partial product of this k-slice
@@ -787,6 +799,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
     C2g = nullptr; accumulate = false;
   }
   const bool vec_ok = (p.ldc & 3) == 0 && (!C2g || (p.ldc2 & 3) == 0);
+  double sq64 = 0.0;                                        // EPI_WGRAD: squared entries of this wave's part of Gbar
   __syncthreads();                                          // stages are dead
   if constexpr (EPI == EPI_WGRAD_UPD) {
     // The optimizer step in place of the gradient store: a lane's staged float4 holds four consecutive entries
@@ -880,7 +893,8 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
           const float4 old = *reinterpret_cast<const float4 *>(crow);
           v.x += old.x; v.y += old.y; v.z += old.z; v.w += old.w;
         }
-        st_once(crow, v);
+        if (Cg) st_once(crow, v);
+        if (EPI == EPI_WGRAD) sq64 += (double)fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, v.w * v.w)));
         if (C2g) {
           uint2 o;
           o.x = pack2bf(v.x, v.y); o.y = pack2bf(v.z, v.w);
@@ -891,11 +905,16 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
         for (int e = 0; e < 4; ++e) {
           if (n + e >= p.Nd) break;
           const float r = accumulate ? v4[e] + crow[e] : v4[e];
-          crow[e] = r;
+          if (Cg) crow[e] = r;
+          if (EPI == EPI_WGRAD) sq64 += (double)(r * r);
           if (C2g) C2g[(long long)m * p.ldc2 + n + e] = f2bf(r);
         }
       }
     }
+  }
+  if (EPI == EPI_WGRAD && p.sq64) {                         // uniform
+    sq64 = wave_sum(sq64);
+    if (lane == 0) p.sq64[(long long)g * p.sSq64g + (long long)t * NW + wave] = sq64;
   }
 }
 
@@ -934,7 +953,7 @@ template <int BM, int BN, int BK, int WM, int WN, int NS, bool PP, bool AT, bool
 hipError_t launch_cfg(const GemmP &p, hipStream_t s) {
   constexpr int NT = WM * WN * 64;
   constexpr size_t tile_bytes = (size_t)NS * (BM + BN) * BK * sizeof(bf16_t);
-  constexpr size_t epi_bf16 = (size_t)WM * WN * 32 * (BN / WN + 8) * sizeof(bf16_t) + (size_t)WN * BM * sizeof(float);
+  constexpr size_t epi_bf16 = (size_t)WM * WN * 32 * (BN / WN + 8) * sizeof(bf16_t) + (size_t)(EPI == EPI_IPDOT ? 2 : 1) * WN * BM * sizeof(float);
   constexpr size_t epi_f32 = (size_t)WM * WN * 32 * (BN / WN + 4) * sizeof(float);
   constexpr size_t epi_bytes = epi_bf16 > epi_f32 ? epi_bf16 : epi_f32;
   constexpr size_t lds = tile_bytes > epi_bytes ? tile_bytes : epi_bytes;
@@ -1009,6 +1028,7 @@ hipError_t launch_act(const GemmP &p, hipStream_t s) {
       default: return launch_shape<AT, BT, EPI, ACT_NONE>(p, s);
     }
   }
+  if constexpr (EPI == EPI_IPDOT) if (p.part2) return launch_shape<AT, BT, EPI, IPDOT_NORMS>(p, s);
   return launch_shape<AT, BT, EPI, ACT_NONE>(p, s);
 }
 
@@ -1062,6 +1082,9 @@ bool operands_ok(const GemmP &p, int epi) {
   if (p.ksplit > 1 && (epi != EPI_WGRAD || !p.kpart || p.kchunk <= 0 || (p.kchunk & 63) ||
                        (long long)p.kchunk * p.ksplit < p.Kd || (p.Nd & 3)))
     return false;
+  if (p.sq64 && (epi != EPI_WGRAD || p.ksplit > 1 || p.upd_x)) return false;
+  if (epi == EPI_WGRAD && !p.C && (!p.C2 || p.accumulate || p.ksplit > 1 || p.upd_x)) return false;
+  if (p.part2 && epi != EPI_IPDOT) return false;
   if (p.upd_x && (epi != EPI_WGRAD || p.ksplit > 1 || p.accumulate || !p.upd_sq || (p.ldc & 3) || (p.Nd & 3) ||
                   (p.sCg & 3) || (reinterpret_cast<uintptr_t>(p.upd_x) & 15) || (p.C2 && ((p.ldc2 & 3) || p.ldc2 != p.ldc)) ||
                   (p.upd_opt != OPT_SGD && !p.upd_v) || (p.upd_opt == OPT_ADAMW && !p.upd_m)))
@@ -1094,9 +1117,9 @@ int gemm_bf16_wgrad_shape(int Md, int Nd, int Kd, int groups, int fused) {
   return sh;
 }
 
-int gemm_bf16_upd_slots(int Md, int Nd, int Kd, int groups) {   // (always with the step in the epilogue)
+int gemm_bf16_upd_slots(int Md, int Nd, int Kd, int groups, int fused) {
   const int bm[4] = {128, 128, 256, 64}, bn[4] = {64, 128, 256, 256}, nw[4] = {4, 4, 8, 4};
-  const int sh = gemm_bf16_wgrad_shape(Md, Nd, Kd, groups, 1);
+  const int sh = gemm_bf16_wgrad_shape(Md, Nd, Kd, groups, fused);
   return ((Md + bm[sh] - 1) / bm[sh]) * ((Nd + bn[sh] - 1) / bn[sh]) * nw[sh];
 }
 

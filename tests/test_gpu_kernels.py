@@ -142,3 +142,51 @@ def test_fp32_step_at_the_edges_of_its_tiles(dims, b, M):
         assert rep.guard_intact()
     finally:
         rep.close()
+
+
+# Statistics alone with the batch gradient not asked for, in an aligned buffer (written by the launches that form it), in one
+# that is not 16-byte aligned and in one that overlaps an input (both filled at the end): the same values in all four.
+@pytest.mark.parametrize("M,b,ins,outs", [(1, 2, (8,), (8,)), (3, 300, (72, 136), (136, 40)), (2, 1030, (264,), (1032,))])
+def test_statistics_alone_deliver_the_same_gradient_into_any_buffer(M, b, ins, outs):
+    import ctypes as C
+    import torch
+    A = _A()
+    g = torch.Generator().manual_seed(b)
+    a = [torch.randn((M, b, i), generator=g).to(torch.bfloat16).cuda() for i in ins]
+    d = [torch.randn((M, b, o), generator=g).to(torch.bfloat16).cuda() for o in outs]
+    res0, n0, q0, _ = A.layer_stats(a, d, want_per_sample=True)
+    res1, n1, q1, gbar = A.layer_stats(a, d, want_per_sample=True, want_gbar=True)
+    key = lambda r: (r.sum_sq, r.gbar_sq, r.sum_q, r.sum_q2)  # noqa: E731
+    assert [key(r) for r in res0] == [key(r) for r in res1] and torch.equal(n0, n1) and torch.equal(q0, q1)
+    at = 0
+    for l, (i, o) in enumerate(zip(ins, outs)):
+        a64, d64 = a[l].double().cpu(), d[l].double().cpu()
+        G = d64.transpose(1, 2).contiguous() @ a64 / b
+        Gabs = d64.abs().transpose(1, 2).contiguous() @ a64.abs() / b
+        got = gbar[:, at:at + i * o].cpu().double().view(M, o, i)
+        assert ((got - G).abs() <= (b + 2) * EPS32 * Gabs).all()
+        at += i * o
+    want = (gbar.double() ** 2).sum(1).cpu().numpy()      # (fp32 sums of four squares, then double)
+    np.testing.assert_allclose([r.gbar_sq for r in res1], want, rtol=8 * EPS32)
+    lib, L = A.load_library(), len(ins)
+    Wsum = at
+    words = M * Wsum + M * b * (max(ins) + max(outs)) + 64
+    for lead in (1, 0):                                    # one float past an aligned address; in front of the first input
+        buf = torch.zeros(words, dtype=torch.float32, device="cuda")
+        ins_c, outs_c = (C.c_int * L)(*ins), (C.c_int * L)(*outs)
+        first = a[0]
+        if lead == 0:
+            first = buf[4:4 + a[0].numel() // 2 + 1].view(torch.bfloat16)[:a[0].numel()].view(a[0].shape)
+            first.copy_(a[0])
+        nbytes = C.c_size_t(0)
+        assert lib.abs_layer_stats_workspace_bytes(L, ins_c, outs_c, M, b, C.byref(nbytes)) == 0
+        ws = torch.empty(nbytes.value + 256, dtype=torch.uint8, device="cuda")
+        ap = (C.c_void_p * L)(*[t.data_ptr() for t in [first] + a[1:]])
+        dp = (C.c_void_p * L)(*[t.data_ptr() for t in d])
+        out = (A.TestResult * M)()
+        st = torch.cuda.current_stream().cuda_stream
+        assert lib.abs_layer_stats(L, ins_c, outs_c, M, b, ap, dp, (ws.data_ptr() + 255) // 256 * 256, nbytes.value, st, out,
+                                   None, None, buf.data_ptr() + 4 * lead) == 0
+        torch.cuda.synchronize()
+        assert [key(r) for r in out] == [key(r) for r in res1]
+        assert torch.equal(buf[lead:lead + M * Wsum].view(M, Wsum), gbar)
