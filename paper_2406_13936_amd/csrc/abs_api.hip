@@ -699,17 +699,25 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
   // (small layers, or any layer while b is the long side) are cut into slices so that the launch fills the chip;
   // the slices are added in order afterwards.
   const bool want_fused = c->fused_update && pl.bf16 && ph.wgrad && ph.update && ph.s2 && !ph.acc_grad;
-  auto bf16_ksplit = [&](int l) -> int {
-    const int Md = pl.dims[l], Nd = pl.dims[l - 1];
-    if (!pl.bf16 || (Nd & 3)) return 1;
-    const int sh = gemm_bf16_wgrad_shape(Md, Nd, b, M, want_fused);
-    if (sh == 3) return 1;                      // short batches: never split
+  auto wgrad_tiles = [&](int l, int sh) -> long long {
     const int te = sh == 2 ? 256 : 128, tn_e = sh == 0 ? 64 : te;
-    const long long tiles = (long long)((Md + te - 1) / te) * ((Nd + tn_e - 1) / tn_e) * M;
+    return (long long)((pl.dims[l] + te - 1) / te) * ((pl.dims[l - 1] + tn_e - 1) / tn_e) * M;
+  };
+  auto wgrad_shape = [&](int l) { return gemm_bf16_wgrad_shape(pl.dims[l], pl.dims[l - 1], b, M, want_fused); };
+  long long tiles_shared = 0;                   // 128 x 128 tiles of the layers that share a launch
+  if (pl.bf16)
+    for (int l = 1; l <= L; ++l) if (wgrad_shape(l) == 1) tiles_shared += wgrad_tiles(l, 1);
+  auto bf16_ksplit = [&](int l) -> int {
+    if (!pl.bf16 || (pl.dims[l - 1] & 3)) return 1;
+    const int sh = wgrad_shape(l);
+    if (sh == 3) return 1;                      // short batches: never split
+    const long long tiles = wgrad_tiles(l, sh);
     // with the optimizer step in the epilogue a launch that gives every CU a work-group stays whole (measured on the
-    // 100 x 2048 layer of config 3 at b = 8192: 256 tiles un-split take as long as the split launch and its finish)
-    if ((want_fused || ph.whole_launches) && tiles >= 256) return 1;
-    return choose_ksplit(sh, tiles, (b + 63) / 64, (double)M * Md * Nd, pl.kpart_floats_l[l]);
+    // 100 x 2048 layer of config 3 at b = 8192: 256 tiles un-split take as long as the split launch and its finish;
+    // 784-512-512-10, 8 replicas, b = 4096, 384 tiles in one launch: 283 -> 260 us per
+    // step against three split launches and their finish)
+    if ((want_fused || ph.whole_launches) && (sh == 1 ? tiles_shared : tiles) >= 256) return 1;
+    return choose_ksplit(sh, tiles, (b + 63) / 64, (double)M * pl.dims[l] * pl.dims[l - 1], pl.kpart_floats_l[l]);
   };
   // The optimizer step moves into the weight-gradient epilogue when the caller asked for it and this call both
   // finishes the gradient and updates, no reduction is split and the per-wavefront sums of squares fit their scratch.
@@ -733,7 +741,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
                         ph.b_total == 0 && b <= c->gram_ip_max_b && b <= GRAM_MAX_B;
   // local batch gradient, eq. (batch_grad): Gbar_l = delta^T a / b, betabar_l = mean_i delta_i
   if (ph.wgrad) {
-    std::vector<GemmP> many;               // short batches: the layers share a launch
+    std::vector<GemmP> many[2][2];         // layers that share a launch: [tile shape 1, 3][with the step in the epilogue]
     for (int l = 1; l <= L; ++l) {
       GemmP p;
       std::memset(&p, 0, sizeof(p));
@@ -781,7 +789,8 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
         p.upd_sq = c->at<float>(pl.o_sqwave); p.upd_sSqg = pl.Ppad / 256; p.upd_slot0 = fused_slots;
         fused_slots += gemm_bf16_upd_slots(p.Md, p.Nd, b, M, 1);
       }
-      if (pl.bf16 && gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, M, p.upd_x != nullptr) == 3) many.push_back(p);
+      const int wsh = pl.bf16 ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, M, p.upd_x != nullptr) : 0;
+      if (wsh == 1 || wsh == 3) many[wsh == 3][p.upd_x != nullptr].push_back(p);
       else HIPCHK(c, gemm(c, p, EPI_WGRAD, l));
       if (p.ksplit > 1) {                    // its slices are added up after the loop, with those of the other layers
         const int e = kf.n++;
@@ -810,10 +819,13 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
         }
       }
     }
-    if (!many.empty()) {
-      ProfScope ps_(c, T_GEMM0 + (EPI_WGRAD * 6 + 3) * T_LAYERS, gemm_flops(many), gemm_bytes(c, many, EPI_WGRAD));
-      HIPCHK(c, launch_wgrad_many(many.data(), (int)many.size(), s));
-    }
+    for (int sh = 0; sh < 2; ++sh)
+      for (const std::vector<GemmP> &v : many[sh]) {
+        if (sh == 0 && v.size() == 1) { HIPCHK(c, gemm(c, v[0], EPI_WGRAD, 0)); continue; }   // (may take a deeper ring)
+        if (v.empty()) continue;
+        ProfScope ps_(c, T_GEMM0 + (EPI_WGRAD * 6 + (sh ? 3 : 1)) * T_LAYERS, gemm_flops(v), gemm_bytes(c, v, EPI_WGRAD));
+        HIPCHK(c, launch_wgrad_many(v.data(), (int)v.size(), sh ? 3 : 1, s));
+      }
     if (kf.n > 0) {                        // all split reductions of the step in one launch
       ProfScope ps_(c, T_COLSUM, 0.0, kf_bytes);
       kf.alpha = inv_b; kf.rows = rows; kf.C = grad; kf.sCg = pl.Ppad;

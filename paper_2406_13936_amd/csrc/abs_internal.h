@@ -79,8 +79,9 @@ struct GemmP {
 // bf16 MFMA family (gemm_bf16.hip).  Returns the number of column partials that
 // EPI_IPDOT writes per row (tiles along n) for the tile shape it picks.
 hipError_t launch_gemm_bf16(const GemmP &p, int epi, hipStream_t s);
-// EPI_WGRAD of n layers whose tile shape is 3 (gemm_bf16_wgrad_shape), in one launch per eight layers
-hipError_t launch_wgrad_many(const GemmP *p, int n, hipStream_t s);
+// EPI_WGRAD of n layers whose tile shape (gemm_bf16_wgrad_shape) is `shape`, 1 or 3, in one launch per eight layers: all of
+// them with the optimizer step in the epilogue or none
+hipError_t launch_wgrad_many(const GemmP *p, int n, int shape, hipStream_t s);
 int gemm_bf16_ipdot_parts(int Nd);
 // Exact number of row partials (tiles along n) and of column-partial rows (tiles along m times
 // wave rows) that launch_gemm_bf16 writes for epilogue epi (forward, logits, backward-data, inner products) of an

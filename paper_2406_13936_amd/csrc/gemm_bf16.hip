@@ -928,9 +928,10 @@ gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int 
   gemm_bf16_tile<BM, BN, BK, WM, WN, NS, PP, AT, BT, EPI, ACT>(pin, tilesM, tilesN, lb);
 }
 
-// Short-batch weight gradients of several layers in one launch (64 x 256 x 32 tiles): each is a few microseconds of
-// streaming, so what separate launches add is their starts and their nearly empty last waves.  The tiles of the layers
-// lie one behind the other; the launch picks the layer by the tile number.
+// Weight gradients of several layers in one launch (64 x 256 x 32 tiles of short batches, two-stage 128 x 128 tiles of
+// narrow nets and medium batches): what separate launches add is their starts, their nearly empty last waves and, where a
+// layer alone has fewer tiles than the chip has places, idle CUs.  The tiles of the layers lie one behind the other;
+// a work-group picks its layer by the tile number.
 struct WgradMany {
   enum { MAXN = 8 };
   int n, nblk, chunk;
@@ -938,7 +939,7 @@ struct WgradMany {
   GemmP p[MAXN];
 };
 static_assert(sizeof(WgradMany) <= 4096, "kernel arguments");
-template <int EPI, int ACT>
+template <int BM, int BN, int BK, int WM, int WN, int EPI, int ACT>
 __global__ void __launch_bounds__(256) wgrad_many_kernel(const WgradMany q) {
   const int bid = blockIdx.x;
   int lb = (bid & 7) * q.chunk + (bid >> 3);
@@ -946,7 +947,7 @@ __global__ void __launch_bounds__(256) wgrad_many_kernel(const WgradMany q) {
   int l = 0;
   while (lb >= q.end[l]) ++l;                     // uniform; end[n - 1] == nblk
   if (l > 0) lb -= q.end[l - 1];
-  gemm_bf16_tile<64, 256, 32, 1, 4, 2, false, true, true, EPI, ACT>(q.p[l], q.tilesM[l], q.tilesN[l], lb);
+  gemm_bf16_tile<BM, BN, BK, WM, WN, 2, false, true, true, EPI, ACT>(q.p[l], q.tilesM[l], q.tilesN[l], lb);
 }
 
 template <int BM, int BN, int BK, int WM, int WN, int NS, bool PP, bool AT, bool BT, int EPI, int ACT>
@@ -1058,13 +1059,17 @@ int tiled_shape(int Md, int Nd, int groups) {
 constexpr long long SMALL_TILES = 1024;
 long long small_tiles(int Md, int Nd, int groups) { return (long long)((Md + 31) / 32) * ((Nd + 31) / 32) * groups; }
 
-template <int EPI, int ACT>
-hipError_t launch_many(const WgradMany &q, hipStream_t s) {
-  // dynamic LDS of the 64 x 256 x 32 tile: two stages of 20 KB, or the epilogue's fp32 staging slices
-  constexpr size_t lds = std::max<size_t>((size_t)2 * (64 + 256) * 32 * sizeof(bf16_t), (size_t)4 * 32 * (256 / 4 + 4) * sizeof(float));
-  static_assert(lds <= 64 * 1024, "no attribute needed");
-  hipLaunchKernelGGL((wgrad_many_kernel<EPI, ACT>), dim3(q.chunk * 8), dim3(256), lds, s, q);
+template <int BM, int BN, int BK, int WM, int WN, int EPI, int ACT>
+hipError_t launch_many_cfg(const WgradMany &q, hipStream_t s) {
+  // dynamic LDS: two stages, or the epilogue's fp32 staging slices
+  constexpr size_t lds = std::max<size_t>((size_t)2 * (BM + BN) * BK * sizeof(bf16_t), (size_t)4 * 32 * (BN / WN + 4) * sizeof(float));
+  static_assert(lds <= 64 * 1024 && WM * WN == 4, "no attribute needed");
+  hipLaunchKernelGGL((wgrad_many_kernel<BM, BN, BK, WM, WN, EPI, ACT>), dim3(q.chunk * 8), dim3(256), lds, s, q);
   return hipGetLastError();
+}
+template <int EPI, int ACT>
+hipError_t launch_many(const WgradMany &q, int shape, hipStream_t s) {
+  return shape == 3 ? launch_many_cfg<64, 256, 32, 1, 4, EPI, ACT>(q, s) : launch_many_cfg<128, 128, 64, 2, 2, EPI, ACT>(q, s);
 }
 
 // operand checks that every launch relies on: 16-byte aligned rows, operands below 2 GiB per replica
@@ -1156,7 +1161,9 @@ int gemm_bf16_ipdot_parts(int Nd) {
   return (Nd + 127) / 128;
 }
 
-hipError_t launch_wgrad_many(const GemmP *p, int n, hipStream_t s) {
+hipError_t launch_wgrad_many(const GemmP *p, int n, int shape, hipStream_t s) {
+  if (shape != 1 && shape != 3) return hipErrorInvalidValue;
+  const int bm = shape == 3 ? 64 : 128, bn = shape == 3 ? 256 : 128;
   for (int at = 0; at < n;) {
     WgradMany q;
     q.n = 0;
@@ -1165,12 +1172,12 @@ hipError_t launch_wgrad_many(const GemmP *p, int n, hipStream_t s) {
     for (; at < n && q.n < WgradMany::MAXN; ++at) {
       const GemmP &c = p[at];
       // one kernel variant for all: every layer carries the same optimizer step, or none
-      if (!operands_ok(c, EPI_WGRAD) || !c.a_trans || !c.b_trans || c.ksplit > 1 || (c.upd_x != nullptr) != upd ||
-          (upd && c.upd_opt != p[0].upd_opt) ||
-          gemm_bf16_wgrad_shape(c.Md, c.Nd, c.Kd, c.groups, upd) != 3)
+      if (!operands_ok(c, EPI_WGRAD) || !c.a_trans || !c.b_trans || (c.upd_x != nullptr) != upd ||
+          (upd && c.upd_opt != p[0].upd_opt) || (shape == 3 && c.ksplit > 1) ||
+          gemm_bf16_wgrad_shape(c.Md, c.Nd, c.Kd, c.groups, upd) != shape)
         return hipErrorInvalidValue;
-      q.tilesM[q.n] = (c.Md + 63) / 64; q.tilesN[q.n] = (c.Nd + 255) / 256;
-      blocks += (long long)q.tilesM[q.n] * q.tilesN[q.n] * c.groups;
+      q.tilesM[q.n] = (c.Md + bm - 1) / bm; q.tilesN[q.n] = (c.Nd + bn - 1) / bn;
+      blocks += (long long)q.tilesM[q.n] * q.tilesN[q.n] * c.groups * (c.ksplit > 1 ? c.ksplit : 1);
       if (blocks > 0x3fffffff) return hipErrorInvalidValue;
       q.end[q.n] = (int)blocks;
       q.p[q.n++] = c;
@@ -1179,11 +1186,11 @@ hipError_t launch_wgrad_many(const GemmP *p, int n, hipStream_t s) {
     q.nblk = (int)blocks;
     q.chunk = (q.nblk + 7) / 8;
     hipError_t e;
-    if (!upd) e = launch_many<EPI_WGRAD, ACT_NONE>(q, s);
-    else if (p[0].upd_opt == OPT_SGD) e = launch_many<EPI_WGRAD_UPD, OPT_SGD>(q, s);
-    else if (p[0].upd_opt == OPT_SHB) e = launch_many<EPI_WGRAD_UPD, OPT_SHB>(q, s);
-    else if (p[0].upd_opt == OPT_ADAMW) e = launch_many<EPI_WGRAD_UPD, OPT_ADAMW>(q, s);
-    else if (p[0].upd_opt == OPT_ADAGRAD) e = launch_many<EPI_WGRAD_UPD, OPT_ADAGRAD>(q, s);
+    if (!upd) e = launch_many<EPI_WGRAD, ACT_NONE>(q, shape, s);
+    else if (p[0].upd_opt == OPT_SGD) e = launch_many<EPI_WGRAD_UPD, OPT_SGD>(q, shape, s);
+    else if (p[0].upd_opt == OPT_SHB) e = launch_many<EPI_WGRAD_UPD, OPT_SHB>(q, shape, s);
+    else if (p[0].upd_opt == OPT_ADAMW) e = launch_many<EPI_WGRAD_UPD, OPT_ADAMW>(q, shape, s);
+    else if (p[0].upd_opt == OPT_ADAGRAD) e = launch_many<EPI_WGRAD_UPD, OPT_ADAGRAD>(q, shape, s);
     else return hipErrorInvalidValue;
     if (e != hipSuccess) return e;
   }
@@ -1192,7 +1199,8 @@ hipError_t launch_wgrad_many(const GemmP *p, int n, hipStream_t s) {
 
 hipError_t launch_gemm_bf16(const GemmP &p, int epi, hipStream_t s) {
   if (!operands_ok(p, epi)) return hipErrorInvalidValue;
-  if (epi == EPI_WGRAD && gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr) == 3) return launch_wgrad_many(&p, 1, s);
+  if (epi == EPI_WGRAD && gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr) == 3)
+    return launch_wgrad_many(&p, 1, 3, s);
   if (epi != EPI_WGRAD && gemm_bf16_tile_shape(epi, p.Md, p.Nd, p.groups) == 5) return launch_gemm_small(p, epi, s);
   if (!p.a_trans && !p.b_trans) {
     if (epi == EPI_FWD_ACT) return launch_act<false, false, EPI_FWD_ACT>(p, s);
