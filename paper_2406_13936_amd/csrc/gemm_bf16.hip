@@ -1033,6 +1033,8 @@ hipError_t launch_act(const GemmP &p, hipStream_t s) {
   return launch_shape<AT, BT, EPI, ACT_NONE>(p, s);
 }
 
+constexpr long long FEW_TILES = 128;
+
 int tiled_shape(int Md, int Nd, int groups) {
   if (Nd <= 64) return 0;
   // up to 64 rows (the first local batch sizes): the launch streams its B operand (the weights) once and is bound by
@@ -1049,6 +1051,9 @@ int tiled_shape(int Md, int Nd, int groups) {
     const long long tiles = tm * ((Nd + 255) / 256) * groups;
     if (tiles >= 256 && 10LL * Md >= 7LL * tm * 256) return 2;
   }
+  // 128 x 128 tiles for half of the CUs or fewer: twice as many 64 x 128 ones with a deeper ring (784-512-512-10, 8 replicas:
+  // b = 501, 128 tiles, a step 124 -> 107.5 us, forward 16.9 -> 11.7; b = 768, 192 tiles, would go from 128 to 140)
+  if ((long long)((Md + 127) / 128) * ((Nd + 127) / 128) * groups <= FEW_TILES) return 4;
   return 1;
 }
 
