@@ -704,9 +704,15 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
     return (long long)((pl.dims[l] + te - 1) / te) * ((pl.dims[l - 1] + tn_e - 1) / tn_e) * M;
   };
   auto wgrad_shape = [&](int l) { return gemm_bf16_wgrad_shape(pl.dims[l], pl.dims[l - 1], b, M, want_fused); };
-  long long tiles_shared = 0;                   // 128 x 128 tiles of the layers that share a launch
+  long long tiles_shared = 0, n_shared = 0;     // 128 x 128 tiles of the layers that share a launch
   if (pl.bf16)
-    for (int l = 1; l <= L; ++l) if (wgrad_shape(l) == 1) tiles_shared += wgrad_tiles(l, 1);
+    for (int l = 1; l <= L; ++l) if (wgrad_shape(l) == 1) { tiles_shared += wgrad_tiles(l, 1); ++n_shared; }
+  // 64 x 128 tiles level the load of the CUs where a shared launch has a place or two per CU, and stream a short reduction's
+  // epilogue better; long reductions over many tiles want the operand reuse of 128 x 128.  128 x 128 -> 64 x 128, us per step:
+  // 784-512-512-10, 8 replicas (384 tiles) b = 501 106.8 -> 105.7, b = 4096 260 -> 255; 784-256-10, 4 replicas, b = 1024 94.9 ->
+  // 90.0; 784-768-768-768-100, 16 replicas (1920 tiles) b = 512 428 -> 420, b = 1024 612 -> 611, but b = 2048 948 -> 972.  A layer alone on a long
+  // reduction keeps the deep ring of its own launch (3072-1024-1024-100, 8 replicas, b = 8192: 2151 us, 2173 with 64 x 128).
+  const int wgrad_fine = b <= 1024 || (n_shared > 1 && tiles_shared <= 512);
   auto bf16_ksplit = [&](int l) -> int {
     if (!pl.bf16 || (pl.dims[l - 1] & 3)) return 1;
     const int sh = wgrad_shape(l);
@@ -728,7 +734,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       if (pl.dims[l - 1] & 3) fused = false;
       // a layer whose reduction is split takes its step in the launch that adds the slices
       slots += bf16_ksplit(l) > 1 ? splitk_finish_slots((long long)pl.dims[l] * pl.dims[l - 1])
-                                  : gemm_bf16_upd_slots(pl.dims[l], pl.dims[l - 1], b, M, 1);
+                                  : gemm_bf16_upd_slots(pl.dims[l], pl.dims[l - 1], b, M, 1, wgrad_fine);
     }
     if (hb) slots += col_finish_slots(L, max_width);
     if (slots > pl.Ppad / 256) fused = false;
@@ -787,9 +793,10 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
         p.upd_beta2 = c->cfg.beta2; p.upd_eps = c->cfg.eps; p.upd_wd = c->cfg.weight_decay;
         p.upd_c1 = ph.c1; p.upd_c2 = ph.c2; p.upd_scal = ph.scal;
         p.upd_sq = c->at<float>(pl.o_sqwave); p.upd_sSqg = pl.Ppad / 256; p.upd_slot0 = fused_slots;
-        fused_slots += gemm_bf16_upd_slots(p.Md, p.Nd, b, M, 1);
+        fused_slots += gemm_bf16_upd_slots(p.Md, p.Nd, b, M, 1, wgrad_fine);
       }
       const int wsh = pl.bf16 ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, M, p.upd_x != nullptr) : 0;
+      p.fine = wsh == 1 ? wgrad_fine : 0;
       if (wsh == 1 || wsh == 3) many[wsh == 3][p.upd_x != nullptr].push_back(p);
       else HIPCHK(c, gemm(c, p, EPI_WGRAD, l));
       if (p.ksplit > 1) {                    // its slices are added up after the loop, with those of the other layers
@@ -821,7 +828,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
     }
     for (int sh = 0; sh < 2; ++sh)
       for (const std::vector<GemmP> &v : many[sh]) {
-        if (sh == 0 && v.size() == 1) { HIPCHK(c, gemm(c, v[0], EPI_WGRAD, 0)); continue; }   // (may take a deeper ring)
+        if (sh == 0 && v.size() == 1 && !v[0].fine) { HIPCHK(c, gemm(c, v[0], EPI_WGRAD, 0)); continue; }   // (may take a deeper ring)
         if (v.empty()) continue;
         ProfScope ps_(c, T_GEMM0 + (EPI_WGRAD * 6 + (sh ? 3 : 1)) * T_LAYERS, gemm_flops(v), gemm_bytes(c, v, EPI_WGRAD));
         HIPCHK(c, launch_wgrad_many(v.data(), (int)v.size(), sh ? 3 : 1, s));
@@ -1396,7 +1403,7 @@ static abs_status ls_plan(int L, const int *in_dims, const int *out_dims, int M,
   off.push_back(take((size_t)M * 8 * 8));                    // 7: stats
   for (int l = 0; l < L; ++l) off.push_back(take((size_t)M * b * 4 * gemm_bf16_ipdot_parts(out_dims[l])));  // 8+l
   size_t slots = 0;
-  for (int l = 0; l < L; ++l) slots += gemm_bf16_upd_slots(out_dims[l], in_dims[l], b, M, 0);
+  for (int l = 0; l < L; ++l) slots += gemm_bf16_upd_slots(out_dims[l], in_dims[l], b, M, 0, 0);
   off.push_back(take((size_t)M * slots * 8));                // 8+L: ||gbar||^2 by wavefront
   total = o;
   return ABS_OK;
@@ -1438,7 +1445,7 @@ abs_status abs_layer_stats(int L, const int *in_dims, const int *out_dims, int M
   long long Wsum = 0, n_slots = 0;
   for (int l = 0; l < L; ++l) {
     Wsum += (long long)in_dims[l] * out_dims[l];
-    n_slots += gemm_bf16_upd_slots(out_dims[l], in_dims[l], b, M, 0);
+    n_slots += gemm_bf16_upd_slots(out_dims[l], in_dims[l], b, M, 0, 0);
   }
   bool direct = gbar_out_dev && !(reinterpret_cast<uintptr_t>(gbar_out_dev) & 15);
   for (int l = 0; l < L && direct; ++l) {       // (a buffer that overlaps an input is filled last, through the workspace)
@@ -1465,7 +1472,7 @@ abs_status abs_layer_stats(int L, const int *in_dims, const int *out_dims, int M
     p.alpha = inv_b;
     p.sq64 = sq + slot0; p.sSq64g = n_slots;
     HIPCHK(nc, launch_gemm_bf16(p, EPI_WGRAD, s));
-    slot0 += gemm_bf16_upd_slots(out_dims[l], in_dims[l], b, M, 0);
+    slot0 += gemm_bf16_upd_slots(out_dims[l], in_dims[l], b, M, 0, 0);
     woff_out += (long long)in_dims[l] * out_dims[l];
   }
   for (int l = 0; l < L; ++l) {

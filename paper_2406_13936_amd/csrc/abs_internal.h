@@ -53,6 +53,7 @@ struct GemmP {
   // Split reduction (EPI_WGRAD of the bf16 family, optional): ksplit > 1 cuts k into ksplit slices of
   // kchunk elements; slice sp of group g writes its raw partial product to
   // kpart[(g * ksplit + sp) * Md * Nd] (row-major, ld = Nd) and C / C2 are left to launch_splitk_finish.
+  int fine;                    // EPI_WGRAD launches of tile shape 1: 64 x 128 tiles instead of 128 x 128 (two stages)
   int ksplit, kchunk;
   float *kpart;
   // fp32 family, EPI_WGRAD without a split (optional): rowsum[g * sRowsumg + m] = alpha * sum_k A[m][k] (+ the old value
@@ -103,7 +104,7 @@ hipError_t launch_gemm_small(const GemmP &p, int epi, hipStream_t s);
 // 128x128 tiles.
 int gemm_bf16_wgrad_shape(int Md, int Nd, int Kd, int groups, int fused);
 // Number of upd_sq slots (fused: with the optimizer step in the epilogue) or sq64 slots an EPI_WGRAD launch writes per group.
-int gemm_bf16_upd_slots(int Md, int Nd, int Kd, int groups, int fused);
+int gemm_bf16_upd_slots(int Md, int Nd, int Kd, int groups, int fused, int fine);
 // fp32 SIMT family (gemm_f32.hip); EPI_IPDOT is not offered (U is materialised instead).
 hipError_t launch_gemm_f32(const GemmP &p, int epi, hipStream_t s);
 

@@ -928,8 +928,8 @@ gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int 
   gemm_bf16_tile<BM, BN, BK, WM, WN, NS, PP, AT, BT, EPI, ACT>(pin, tilesM, tilesN, lb);
 }
 
-// Weight gradients of several layers in one launch (64 x 256 x 32 tiles of short batches, two-stage 128 x 128 tiles of
-// narrow nets and medium batches): what separate launches add is their starts, their nearly empty last waves and, where a
+// Weight gradients of several layers in one launch (64 x 256 x 32 tiles of short batches, two-stage 128 x 128 or 64 x 128
+// tiles of narrow nets and medium batches): what separate launches add is their starts, their nearly empty last waves and, where a
 // layer alone has fewer tiles than the chip has places, idle CUs.  The tiles of the layers lie one behind the other;
 // a work-group picks its layer by the tile number.
 struct WgradMany {
@@ -1074,6 +1074,7 @@ hipError_t launch_many_cfg(const WgradMany &q, hipStream_t s) {
 }
 template <int EPI, int ACT>
 hipError_t launch_many(const WgradMany &q, int shape, hipStream_t s) {
+  if (shape == 1 && q.p[0].fine) return launch_many_cfg<64, 128, 64, 2, 2, EPI, ACT>(q, s);
   return shape == 3 ? launch_many_cfg<64, 256, 32, 1, 4, EPI, ACT>(q, s) : launch_many_cfg<128, 128, 64, 2, 2, EPI, ACT>(q, s);
 }
 
@@ -1127,8 +1128,8 @@ int gemm_bf16_wgrad_shape(int Md, int Nd, int Kd, int groups, int fused) {
   return sh;
 }
 
-int gemm_bf16_upd_slots(int Md, int Nd, int Kd, int groups, int fused) {
-  const int bm[4] = {128, 128, 256, 64}, bn[4] = {64, 128, 256, 256}, nw[4] = {4, 4, 8, 4};
+int gemm_bf16_upd_slots(int Md, int Nd, int Kd, int groups, int fused, int fine) {
+  const int bm[4] = {128, fine ? 64 : 128, 256, 64}, bn[4] = {64, 128, 256, 256}, nw[4] = {4, 4, 8, 4};
   const int sh = gemm_bf16_wgrad_shape(Md, Nd, Kd, groups, fused);
   return ((Md + bm[sh] - 1) / bm[sh]) * ((Nd + bn[sh] - 1) / bn[sh]) * nw[sh];
 }
@@ -1168,7 +1169,8 @@ int gemm_bf16_ipdot_parts(int Nd) {
 
 hipError_t launch_wgrad_many(const GemmP *p, int n, int shape, hipStream_t s) {
   if (shape != 1 && shape != 3) return hipErrorInvalidValue;
-  const int bm = shape == 3 ? 64 : 128, bn = shape == 3 ? 256 : 128;
+  if (n < 1) return hipSuccess;
+  const int bm = shape == 3 || p[0].fine ? 64 : 128, bn = shape == 3 ? 256 : 128;
   for (int at = 0; at < n;) {
     WgradMany q;
     q.n = 0;
@@ -1178,7 +1180,7 @@ hipError_t launch_wgrad_many(const GemmP *p, int n, int shape, hipStream_t s) {
       const GemmP &c = p[at];
       // one kernel variant for all: every layer carries the same optimizer step, or none
       if (!operands_ok(c, EPI_WGRAD) || !c.a_trans || !c.b_trans || (c.upd_x != nullptr) != upd ||
-          (upd && c.upd_opt != p[0].upd_opt) || (shape == 3 && c.ksplit > 1) ||
+          (upd && c.upd_opt != p[0].upd_opt) || (shape == 3 && c.ksplit > 1) || c.fine != p[0].fine ||
           gemm_bf16_wgrad_shape(c.Md, c.Nd, c.Kd, c.groups, upd) != shape)
         return hipErrorInvalidValue;
       q.tilesM[q.n] = (c.Md + bm - 1) / bm; q.tilesN[q.n] = (c.Nd + bn - 1) / bn;
@@ -1206,6 +1208,7 @@ hipError_t launch_gemm_bf16(const GemmP &p, int epi, hipStream_t s) {
   if (!operands_ok(p, epi)) return hipErrorInvalidValue;
   if (epi == EPI_WGRAD && gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr) == 3)
     return launch_wgrad_many(&p, 1, 3, s);
+  if (epi == EPI_WGRAD && p.fine) return launch_wgrad_many(&p, 1, 1, s);
   if (epi != EPI_WGRAD && gemm_bf16_tile_shape(epi, p.Md, p.Nd, p.groups) == 5) return launch_gemm_small(p, epi, s);
   if (!p.a_trans && !p.b_trans) {
     if (epi == EPI_FWD_ACT) return launch_act<false, false, EPI_FWD_ACT>(p, s);
