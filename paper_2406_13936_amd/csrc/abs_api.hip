@@ -626,6 +626,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
                                  pl.ld[0], c->at<float>(pl.o_an[0]), cap, rows, s)); }
 
     // forward
+    const bool head_fused = gemm_head_fits(isb, b, pl.dims[L], M);
     for (int l = 1; l <= L; ++l) {
       GemmP p;
       std::memset(&p, 0, sizeof(p));
@@ -651,11 +652,16 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
         }
       } else {
         p.C = c->at<float>(pl.o_Z); p.sCg = cap * pl.ld[L]; p.ldc = pl.ld[L];
+        if (head_fused) {
+          p.head.y = c->y; p.head.idx = idx_dev; p.head.N = (int)c->N; p.head.ldi = ldi; p.head.ldd = pl.ld[L];
+          p.head.D = act_ptr(pl.o_Dl[L]); p.head.sDg = cap * pl.ld[L];
+          p.head.dn = c->at<float>(pl.o_dn[L]); p.head.loss = c->at<float>(pl.o_loss); p.head.sNg = cap;
+        }
         HIPCHK(c, gemm(c, p, EPI_LOGITS, l));
       }
     }
-    // loss head: per-sample backprop signal of the last layer
-    { ProfScope ps_(c, T_SOFTMAX, 0.0, 1.0 * M * b * pl.ld[L] * (4 + pl.esz));
+    // loss head: per-sample backprop signal of the last layer (few classes: out of the logits' launch)
+    if (!head_fused) { ProfScope ps_(c, T_SOFTMAX, 0.0, 1.0 * M * b * pl.ld[L] * (4 + pl.esz));
     HIPCHK(c, launch_softmax_ce(isb, c->at<float>(pl.o_Z), cap * pl.ld[L], pl.ld[L], pl.dims[L], c->y, (int)c->N, idx_dev, ldi, M, b,
                                 act_ptr(pl.o_Dl[L]), cap * pl.ld[L], pl.ld[L], c->at<float>(pl.o_dn[L]),
                                 c->at<float>(pl.o_loss), cap, rows, s)); }

@@ -21,6 +21,15 @@ enum {
   EPI_WGRAD_UPD = 5 // internal to the bf16 family: EPI_WGRAD with the optimizer step in the epilogue (GemmP::upd_x)
 };
 
+// The softmax cross-entropy head in the epilogue of an EPI_LOGITS launch (gemm_head_fits): instead of the logits the launch
+// stores delta = p - e_y (rows of ldd elements, pad columns zero), dn[g][i] = ||stored delta_i||^2 and loss[g][i].
+struct HeadP {
+  const int32_t *y, *idx;      // labels [N]; row i of group g carries label y[idx[g * ldi + i]] (null y: no head)
+  int N, ldi, ldd;
+  void *D; long long sDg;
+  float *dn, *loss; long long sNg;
+};
+
 struct GemmP {
   const void *A, *B;           // operands (bf16 bits or float, by kernel family)
   long long sAg, sBg;          // group (replica) strides in elements
@@ -31,6 +40,7 @@ struct GemmP {
   void *C2; long long sC2g; int ldc2;    // optional second output
   const float *bias; long long sBiasg;   // per-column vector (may be null)
   const void *E; long long sEg; int lde; // elementwise operand of the epilogue
+  HeadP head;                  // EPI_LOGITS (optional)
   float *part; long long sPartg; long long sPartTile; // row partials: part[g][tile_n][m]
                                //   EPI_IPDOT: the row dots; EPI_FWD_ACT / EPI_BWD (bf16 family, optional):
                                //   sum over the tile's columns of the squared stored outputs
@@ -98,6 +108,8 @@ size_t gemm_bf16_row_part_floats(int Nd, int groups, int cap);
 // 5 = 32-row tiles of gemm_small.hip (forward, logits and backward-data launches that would leave most CUs idle).
 int gemm_bf16_tile_shape(int epi, int Md, int Nd, int groups);
 hipError_t launch_gemm_small(const GemmP &p, int epi, hipStream_t s);
+// Whether an EPI_LOGITS launch can carry the softmax head: a row's classes lie in one tile, eight or sixteen lanes to the row.
+bool gemm_head_fits(int is_bf16, int Md, int Nd, int groups);
 // Tile shape of an EPI_WGRAD launch whose reduction runs over Kd samples: as above, or 3 = 64x256 with a k-step of
 // 32 and several work-groups per CU while the batch is short and the launch is bound by its epilogue's memory traffic;
 // fused != 0: the launch carries the optimizer step in its epilogue (GemmP::upd_x), which keeps medium batches on

@@ -1080,6 +1080,7 @@ hipError_t launch_many(const WgradMany &q, int shape, hipStream_t s) {
 
 // operand checks that every launch relies on: 16-byte aligned rows, operands below 2 GiB per replica
 bool operands_ok(const GemmP &p, int epi) {
+  if (p.head.y && !(epi == EPI_LOGITS && gemm_head_fits(1, p.Md, p.Nd, p.groups))) return false;
   if ((p.lda & 7) || (p.ldb & 7)) return false;
   if ((reinterpret_cast<uintptr_t>(p.A) & 15) || (reinterpret_cast<uintptr_t>(p.B) & 15)) return false;
   if ((p.sAg & 7) || (p.sBg & 7)) return false;
@@ -1109,6 +1110,11 @@ int gemm_bf16_tile_shape(int epi, int Md, int Nd, int groups) {
   if ((epi == EPI_FWD_ACT || epi == EPI_LOGITS || epi == EPI_BWD) && small_tiles(Md, Nd, groups) <= (Nd <= 64 ? SMALL_TILES / 2 : SMALL_TILES))
     return 5;
   return tiled_shape(Md, Nd, groups);
+}
+
+// (bf16: the 32-row tiles hold 32 columns; fp32: the smallest tile holds 16)
+bool gemm_head_fits(int is_bf16, int Md, int Nd, int groups) {
+  return is_bf16 ? Nd <= 32 && gemm_bf16_tile_shape(EPI_LOGITS, Md, Nd, groups) == 5 : Nd <= 16;
 }
 
 // Weight gradients reduce over the local batch (Kd = b).  While the batch is short the launch is all epilogue

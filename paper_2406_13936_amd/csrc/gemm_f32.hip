@@ -55,6 +55,15 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmP pin) {
 #pragma unroll
   for (int i = 0; i < R; ++i) rs[i] = 0.0f;
 
+  int labels[R];                                  // (two dependent loads: under way while the operands arrive)
+  if (EPI == EPI_LOGITS && p.head.y) {
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const int id = p.head.idx[(long long)g * p.head.ldi + min(m0 + ty + 16 * i, p.Md - 1)];
+      labels[i] = min(max(p.head.y[min(max(id, 0), p.head.N - 1)], 0), p.Nd - 1);
+    }
+  }
+
   float ra[PT], rb[PT];
   // element e of this thread: (row rr, k kk) of a stage; consecutive threads walk the operand's contiguous dimension
   auto where = [&](int e, bool trans, int &rr, int &kk) {
@@ -128,6 +137,33 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmP pin) {
   }
 
   const float *bias = p.bias ? p.bias + (long long)g * p.sBiasg : nullptr;
+  if (EPI == EPI_LOGITS && p.head.y) {            // uniform: softmax cross-entropy, class tx of row ty + 16 i (at most 16 classes)
+    const float bv = bias && tx < p.Nd ? bias[tx] : 0.0f;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const int m = m0 + ty + 16 * i;
+      const int label = labels[i];
+      const float z = tx < p.Nd ? acc[i][0] + bv : -INFINITY;
+      float mx = z;
+#pragma unroll
+      for (int x = 1; x < 16; x <<= 1) mx = fmaxf(mx, __shfl_xor(mx, x, 64));
+      const float ex = tx < p.Nd ? expf(z - mx) : 0.0f;
+      float se = ex;
+#pragma unroll
+      for (int x = 1; x < 16; x <<= 1) se += __shfl_xor(se, x, 64);
+      const float dl = tx < p.Nd ? ex * (1.0f / se) - (tx == label ? 1.0f : 0.0f) : 0.0f;
+      float sq = dl * dl;
+#pragma unroll
+      for (int x = 1; x < 16; x <<= 1) sq += __shfl_xor(sq, x, 64);
+      if (m < p.Md) {
+        const long long at = (long long)g * p.head.sNg + m;
+        if (tx < p.head.ldd) static_cast<float *>(p.head.D)[(long long)g * p.head.sDg + (long long)m * p.head.ldd + tx] = dl;
+        if (tx == 0) p.head.dn[at] = sq;
+        if (tx == label) p.head.loss[at] = -(z - mx - logf(se));
+      }
+    }
+    return;
+  }
 #pragma unroll
   for (int i = 0; i < R; ++i) {
     const int m = m0 + ty + 16 * i;
@@ -174,6 +210,9 @@ template <int EPI, int ACT>
 hipError_t launch1(const GemmP &p, hipStream_t s) {
   const int ks = (EPI == EPI_WGRAD && p.ksplit > 1) ? p.ksplit : 1;
   if ((p.a_trans != 0) != (EPI == EPI_WGRAD) || (p.b_trans != 0) != (EPI == EPI_WGRAD || EPI == EPI_BWD)) return hipErrorInvalidValue;
+  if (p.head.y && (EPI != EPI_LOGITS || !gemm_head_fits(0, p.Md, p.Nd, p.groups) || !p.head.idx || p.head.N < 1 || !p.head.D ||
+                   !p.head.dn || !p.head.loss || p.head.ldd < p.Nd || p.head.ldd > 16))
+    return hipErrorInvalidValue;
   if (p.rowsum && (EPI != EPI_WGRAD || ks > 1)) return hipErrorInvalidValue;
   if (ks > 1 && (!p.kpart || p.kchunk <= 0 || (p.kchunk & 31) || (long long)p.kchunk * ks < p.Kd)) return hipErrorInvalidValue;
   // 32 x 32 tiles while 64 x 64 ones would leave most CUs without a work-group, 16 x 16 while 32 x 32 ones would

@@ -190,3 +190,43 @@ def test_statistics_alone_deliver_the_same_gradient_into_any_buffer(M, b, ins, o
         torch.cuda.synchronize()
         assert [key(r) for r in out] == [key(r) for r in res1]
         assert torch.equal(buf[lead:lead + M * Wsum].view(M, Wsum), gbar)
+
+
+# The softmax head inside the logits' launch: classes at the edges of its lanes (2, 16 / 17, 32 / 33, the latter of each pair in a
+# launch of its own in one precision or both), rows beyond a tile, workers with batches of their own.
+@pytest.mark.parametrize("prec,K,sizes", [(p, K, s) for p in (W.PREC_F32, W.PREC_BF16) for K in (2, 16, 17, 32, 33)
+                                          for s in ((33, 33), (2, 47))])
+def test_softmax_head_at_the_edges_of_its_lanes(prec, K, sizes):
+    A = _A()
+    M, b, d = len(sizes), max(sizes), 40
+    w = W.Workload("head", (d, K), W.ACT_NONE, True, prec, N=256, M=M, H=1, rounds=1, b0=b, b_cap=b, opt=W.OPT_SGD, lr=0.05,
+                   test=W.TEST_NORM, data="teacher_mlp", seed=11)
+    X, y = W.make_dataset(w)
+    x0 = W.make_x0(w)
+    rep = A.Replicas.from_workload(w, X, y, x0)
+    try:
+        idx = W.step_indices(w, 0, 0, b)
+        rep.local_step_ragged([idx[m][:s] for m, s in enumerate(sizes)], 0.0)
+        res = rep.norm_test(0.5)
+        rnd = O.bf16_round if prec == W.PREC_BF16 else (lambda v: np.asarray(v, np.float64))
+        Wm, bias = x0[:d * K].reshape(K, d).astype(np.float64), x0[d * K:].astype(np.float64)
+        tol = 1e-3 if prec == W.PREC_BF16 else 1e-5      # delta rounded to bf16 near a tie: single entries move by 2^-9
+        for m, s in enumerate(sizes):
+            a = np.asarray(rnd(X[idx[m][:s]]), np.float64)
+            z = a @ np.asarray(rnd(Wm), np.float64).T + bias
+            lab = y[idx[m][:s]]
+            mx = z.max(1, keepdims=True)
+            p = np.exp(z - mx)
+            loss = (np.log(p.sum(1)) + mx[:, 0] - z[np.arange(s), lab]).sum()
+            p /= p.sum(1, keepdims=True)
+            p[np.arange(s), lab] -= 1.0
+            delta = np.asarray(rnd(p), np.float64)
+            n = (delta ** 2).sum(1) * ((a ** 2).sum(1) + 1.0)
+            assert abs(res[m].loss_sum - loss) <= 1e-5 * loss
+            assert abs(res[m].sum_sq - n.sum()) <= tol * n.sum()
+            G = np.concatenate([(delta.T @ a / s).ravel(), delta.mean(0)])
+            got = rep.get_grad(m).astype(np.float64)
+            assert np.linalg.norm(got - G) <= tol * np.linalg.norm(G)
+        assert rep.guard_intact()
+    finally:
+        rep.close()
