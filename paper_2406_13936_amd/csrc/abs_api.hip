@@ -34,6 +34,7 @@ struct Plan {
   std::vector<long long> offW, offB; // internal (padded) parameter offsets
   std::vector<long long> extW, extB; // packed external offsets
   long long P = 0, Ppad = 0;
+  long long sq_slots = 0;             // partial sums of ||gbar||^2 per replica
   int M = 0, cap = 0;
   int qparts[MAXL] = {0};
   size_t colpart_per = 0;              // floats of column-partial scratch per replica (fp32 mode: one piece for all layers)
@@ -153,7 +154,13 @@ void make_plan(const abs_config *c, long long N, Plan &pl) {
   pl.o_partials = take((size_t)pl.M * 5 * STATS_PBLK * 8);
   pl.o_stats = take((size_t)pl.M * 8 * 8);
   pl.o_rows = take((size_t)2 * pl.M * sizeof(int));          // per-group row counts, then the launch order
-  pl.o_sqwave = take((size_t)pl.M * (pl.Ppad / 256) * sizeof(float));
+  pl.sq_slots = pl.Ppad / 256;
+  if (!pl.bf16) {
+    long long blocks = 0;
+    for (int l = 1; l <= pl.L; ++l) blocks += gemm_f32_upd_slots(pl.dims[l], pl.dims[l - 1], pl.M);
+    pl.sq_slots = std::max(pl.sq_slots, blocks);
+  }
+  pl.o_sqwave = take((size_t)pl.M * pl.sq_slots * sizeof(float));
   for (int l = 1; l <= pl.L; ++l) {
     // one piece per layer, so that one launch can finish the split reductions of all layers.  bf16: a split is
     // only taken when the un-split launch has at most 256 tiles, and never makes more than 512 (tile, slice) pairs
@@ -701,6 +708,25 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       }
     }
   }   // passes
+  // fp32 mode (small problems): a block of the smallest tiles walks its reduction 256 samples at a time, about 2.5 us a step, so
+  // a long batch over few tiles is cut into up to 8 slices (finish launch and the bias sums' two launches: about 10 us)
+  auto f32_ksplit = [&](int l) -> int {
+    const long long mn = (long long)pl.dims[l] * pl.dims[l - 1];
+    const long long blocks = (long long)((pl.dims[l] + 15) / 16) * ((pl.dims[l - 1] + 15) / 16) * M;
+    const int KT = (b + 255) / 256;
+    int best = 1;
+    double best_cost = KT * 2.5;
+    for (int S = 2; S <= 8 && blocks < 128 && (mn & 3) == 0; ++S) {
+      if (blocks * S > 1024 || (size_t)S * M * mn > pl.kpart_floats_l[l]) break;
+      const double cost = ((KT + S - 1) / S) * 2.5 + 10.0;
+      if (cost < best_cost) { best = S; best_cost = cost; }
+    }
+    return best;
+  };
+  // fp32 mode: the optimizer step where the gradient is finished, one launch of the step less (logistic regression: 2.6 of
+  // 22 us), if no layer's reduction is split
+  bool f32_step = !pl.bf16 && ph.wgrad && ph.update && ph.s2 && !ph.acc_grad;
+  for (int l = 1; l <= L && f32_step; ++l) f32_step = f32_ksplit(l) <= 1;
   // Number of slices of layer l's weight-gradient reduction (bf16 mode): few output tiles and a long reduction
   // (small layers, or any layer while b is the long side) are cut into slices so that the launch fills the chip;
   // the slices are added in order afterwards.
@@ -743,7 +769,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
                                   : gemm_bf16_upd_slots(pl.dims[l], pl.dims[l - 1], b, M, 1, wgrad_fine);
     }
     if (hb) slots += col_finish_slots(L, max_width);
-    if (slots > pl.Ppad / 256) fused = false;
+    if (slots > pl.sq_slots) fused = false;
   }
   int fused_slots = 0;
   // Short batches take the inner products <g_i, gbar> from the Gram matrices of activations and backprop signals:
@@ -763,24 +789,11 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       p.C = grad + pl.offW[l]; p.sCg = pl.Ppad; p.ldc = pl.dims[l - 1];
       p.alpha = inv_b; p.accumulate = ph.acc_grad ? 1 : 0;
       if (pl.bf16 && pl.want_ip && !use_gram) { p.C2 = c->at<bf16_t>(pl.o_gradbf) + pl.offW[l]; p.sC2g = pl.Ppad; p.ldc2 = pl.dims[l - 1]; }
-      if (!pl.bf16 && p.ldc == p.Nd && (((long long)p.Md * p.Nd) & 3) == 0) {
-        // fp32 mode (small problems): a block of the smallest tiles walks its reduction 256 samples at a time, about
-        // 2.5 us a step, so a long batch over few tiles is cut into up to 8 slices (finish launch and the bias sums'
-        // two launches: about 10 us)
-        const long long blocks = (long long)((p.Md + 15) / 16) * ((p.Nd + 15) / 16) * M;
-        const int KT = (b + 255) / 256;
-        int best = 1;
-        double best_cost = KT * 2.5;
-        for (int S = 2; S <= 8 && blocks < 128; ++S) {
-          if (blocks * S > 1024 || (size_t)S * M * p.Md * p.Nd > pl.kpart_floats_l[l]) break;
-          const double cost = ((KT + S - 1) / S) * 2.5 + 10.0;
-          if (cost < best_cost) { best = S; best_cost = cost; }
-        }
-        if (best > 1) {
-          p.ksplit = best;
-          p.kchunk = ((KT + best - 1) / best) * 256;
-          p.kpart = c->at<float>(pl.o_kpart_l[l]);
-        }
+      if (!pl.bf16 && f32_ksplit(l) > 1) {
+        const int KT = (b + 255) / 256, S = f32_ksplit(l);
+        p.ksplit = S;
+        p.kchunk = ((KT + S - 1) / S) * 256;
+        p.kpart = c->at<float>(pl.o_kpart_l[l]);
       }
       if (hb && !pl.bf16 && p.ksplit <= 1) { p.rowsum = grad + pl.offB[l]; p.sRowsumg = pl.Ppad; }
       if (bf16_ksplit(l) > 1) {
@@ -789,17 +802,17 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
         p.kchunk = ((KT + S - 1) / S) * 64;
         p.kpart = c->at<float>(pl.o_kpart_l[l]);
       }
-      if (fused && p.ksplit <= 1) {
-        // the optimizer step replaces the gradient store (the fp32 gradient of the weights is never written)
+      if ((fused || f32_step) && p.ksplit <= 1) {
+        // bf16: the optimizer step replaces the gradient store (the fp32 gradient of the weights is never written)
         p.upd_x = xm + pl.offW[l];
         p.upd_v = c->cfg.opt != ABS_OPT_SGD ? c->at<float>(pl.o_v) + pl.offW[l] : nullptr;
         p.upd_m = c->cfg.opt == ABS_OPT_ADAMW ? c->at<float>(pl.o_m) + pl.offW[l] : nullptr;
-        p.upd_shadow = c->at<bf16_t>(pl.o_xs) + pl.offW[l];
+        p.upd_shadow = pl.bf16 ? c->at<bf16_t>(pl.o_xs) + pl.offW[l] : nullptr;
         p.upd_opt = c->cfg.opt; p.upd_lr = lr; p.upd_momentum = c->cfg.momentum; p.upd_beta1 = c->cfg.beta1;
         p.upd_beta2 = c->cfg.beta2; p.upd_eps = c->cfg.eps; p.upd_wd = c->cfg.weight_decay;
         p.upd_c1 = ph.c1; p.upd_c2 = ph.c2; p.upd_scal = ph.scal;
-        p.upd_sq = c->at<float>(pl.o_sqwave); p.upd_sSqg = pl.Ppad / 256; p.upd_slot0 = fused_slots;
-        fused_slots += gemm_bf16_upd_slots(p.Md, p.Nd, b, M, 1, wgrad_fine);
+        p.upd_sq = c->at<float>(pl.o_sqwave); p.upd_sSqg = pl.sq_slots; p.upd_slot0 = fused_slots;
+        fused_slots += pl.bf16 ? gemm_bf16_upd_slots(p.Md, p.Nd, b, M, 1, wgrad_fine) : gemm_f32_upd_slots(p.Md, p.Nd, M);
       }
       const int wsh = pl.bf16 ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, M, p.upd_x != nullptr) : 0;
       p.fine = wsh == 1 ? wgrad_fine : 0;
@@ -852,7 +865,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
         kf.upd_opt = c->cfg.opt; kf.upd_lr = lr; kf.upd_momentum = c->cfg.momentum; kf.upd_beta1 = c->cfg.beta1;
         kf.upd_beta2 = c->cfg.beta2; kf.upd_eps = c->cfg.eps; kf.upd_wd = c->cfg.weight_decay;
         kf.upd_c1 = ph.c1; kf.upd_c2 = ph.c2; kf.upd_scal = ph.scal;
-        kf.upd_sq = c->at<float>(pl.o_sqwave); kf.upd_sSqg = pl.Ppad / 256;
+        kf.upd_sq = c->at<float>(pl.o_sqwave); kf.upd_sSqg = pl.sq_slots;
       }
       HIPCHK(c, launch_splitk_finish(kf, M, s));
     }
@@ -867,7 +880,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
         cf.upd_opt = c->cfg.opt; cf.upd_lr = lr; cf.upd_momentum = c->cfg.momentum; cf.upd_beta1 = c->cfg.beta1;
         cf.upd_beta2 = c->cfg.beta2; cf.upd_eps = c->cfg.eps; cf.upd_wd = c->cfg.weight_decay;
         cf.upd_c1 = ph.c1; cf.upd_c2 = ph.c2; cf.upd_scal = ph.scal;
-        cf.sq = c->at<float>(pl.o_sqwave); cf.sSqg = pl.Ppad / 256; cf.slot0 = fused_slots;
+        cf.sq = c->at<float>(pl.o_sqwave); cf.sSqg = pl.sq_slots; cf.slot0 = fused_slots;
         fused_slots += col_finish_slots(cf.n, max_width);
       }
       HIPCHK(c, launch_col_sum_finish_many(cf, M, s));
@@ -945,14 +958,14 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
   // may run first); otherwise a separate pass over the gradient does.
   const bool s2_in_update = ph.s2 && ph.update;
   sp.grad = (ph.s2 && !s2_in_update) ? grad : nullptr;
-  if (fused) {
+  if (fused || f32_step) {
     // every parameter has taken its step; ||gbar||^2 is the sum of the slots that the launches which did it left
     sp.sq_wave = c->at<float>(pl.o_sqwave); sp.n_sq_wave = fused_slots;
-    sp.sq_stride = pl.Ppad / 256;
+    sp.sq_stride = pl.sq_slots;
     ProfScope ps_(c, T_STATS, 0.0, 4.0 * M * fused_slots);
     HIPCHK(c, launch_stats(sp, s));
     note_step(c, ph.b_total > 0 ? ph.b_total : b, b_host);
-    c->last_fused = true;
+    c->last_fused = fused;
     return ABS_OK;
   }
   c->last_fused = false;

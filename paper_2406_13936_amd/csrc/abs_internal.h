@@ -119,6 +119,9 @@ int gemm_bf16_wgrad_shape(int Md, int Nd, int Kd, int groups, int fused);
 int gemm_bf16_upd_slots(int Md, int Nd, int Kd, int groups, int fused, int fine);
 // fp32 SIMT family (gemm_f32.hip); EPI_IPDOT is not offered (U is materialised instead).
 hipError_t launch_gemm_f32(const GemmP &p, int epi, hipStream_t s);
+// Its EPI_WGRAD takes the optimizer step as well (GemmP::upd_x; the gradient is stored in C all the same, rowsum's entries take
+// theirs with it: rowsum and C point into the same vectors as upd_x); one upd_sq slot per block.
+int gemm_f32_upd_slots(int Md, int Nd, int groups);
 
 // ---- gram_ip.hip -----------------------------------------------------------
 // q[g][i] = (1 / b_g) sum_l sum_j (D_l D_l^T)[i][j] ((A_l A_l^T)[i][j] + [has_bias]),  i, j < b_g: the inner products

@@ -16,6 +16,9 @@
 namespace absk {
 namespace {
 
+// (EPI_WGRAD with GemmP::upd_x: ACT carries the optimizer, NO_STEP without)
+constexpr int NO_STEP = 15;
+
 template <int EPI, int ACT, int TS, int BK>
 __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmP pin) {
   constexpr int PT = TS * BK / 256;              // elements per thread, operand and k-step
@@ -127,12 +130,30 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmP pin) {
     }
     __syncthreads();
   }
+  // the optimizer step where the gradient is finished: parameter, state and squared entry of the gradient at offset o of group g
+  constexpr bool STEP = EPI == EPI_WGRAD && ACT != NO_STEP;
+  constexpr int OPT = STEP ? ACT : OPT_SGD;
+  OptHyper h = {p.upd_lr, p.upd_momentum, p.upd_beta1, p.upd_beta2, p.upd_eps, p.upd_wd, p.upd_c1, p.upd_c2};
+  if (STEP && p.upd_scal) { h.lr = p.upd_scal[0]; h.c1 = p.upd_scal[1]; h.c2 = p.upd_scal[2]; }
+  double sq = 0.0;
+  auto step = [&](long long o, float gr) {
+    float x = p.upd_x[o], v = OPT != OPT_SGD ? p.upd_v[o] : 0.0f, m = OPT == OPT_ADAMW ? p.upd_m[o] : 0.0f;
+    opt_step_elem<OPT>(x, gr, v, m, h);
+    p.upd_x[o] = x;
+    if (OPT != OPT_SGD) p.upd_v[o] = v;
+    if (OPT == OPT_ADAMW) p.upd_m[o] = m;
+    sq += (double)(gr * gr);
+  };
   if (row_sums && tx == 0) {
 #pragma unroll
     for (int i = 0; i < R; ++i) {
       const int m = m0 + ty + 16 * i;
       float *o = p.rowsum + (long long)g * p.sRowsumg + m;
-      if (m < p.Md) *o = p.accumulate ? fmaf(rs[i], p.alpha, *o) : rs[i] * p.alpha;
+      if (m < p.Md) {
+        const float gr = p.accumulate ? fmaf(rs[i], p.alpha, *o) : rs[i] * p.alpha;
+        *o = gr;
+        if (STEP) step((long long)g * p.sCg + (p.rowsum - static_cast<float *>(p.C)) + m, gr);
+      }
     }
   }
 
@@ -199,11 +220,24 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmP pin) {
           p.kpart[((long long)g * ksplit + ksl) * p.Md * p.Nd + (long long)m * p.Nd + n] = v;
         } else if (nin) {
           float *o = static_cast<float *>(p.C) + (long long)g * p.sCg + (long long)m * p.ldc + n;
-          *o = p.accumulate ? fmaf(v, p.alpha, *o) : v * p.alpha;
+          const float gr = p.accumulate ? fmaf(v, p.alpha, *o) : v * p.alpha;
+          *o = gr;
+          if (STEP) step((long long)g * p.sCg + (long long)m * p.ldc + n, gr);
         }
       }
     }
   }
+  if (STEP) {
+    __shared__ double red[4];
+    const double t = block_sum<4>(sq, red);
+    if (tid == 0) p.upd_sq[(long long)g * p.upd_sSqg + p.upd_slot0 + blockIdx.y * gridDim.x + blockIdx.x] = (float)t;
+  }
+}
+
+int tile_size(int Md, int Nd, long long groups) {
+  // 32 x 32 tiles while 64 x 64 ones would leave most CUs without a work-group, 16 x 16 while 32 x 32 ones would
+  auto blocks = [&](int ts) { return (long long)((Nd + ts - 1) / ts) * ((Md + ts - 1) / ts) * groups; };
+  return blocks(64) >= 128 ? 64 : blocks(32) >= 128 ? 32 : 16;
 }
 
 template <int EPI, int ACT>
@@ -215,9 +249,7 @@ hipError_t launch1(const GemmP &p, hipStream_t s) {
     return hipErrorInvalidValue;
   if (p.rowsum && (EPI != EPI_WGRAD || ks > 1)) return hipErrorInvalidValue;
   if (ks > 1 && (!p.kpart || p.kchunk <= 0 || (p.kchunk & 31) || (long long)p.kchunk * ks < p.Kd)) return hipErrorInvalidValue;
-  // 32 x 32 tiles while 64 x 64 ones would leave most CUs without a work-group, 16 x 16 while 32 x 32 ones would
-  auto blocks = [&](int ts) { return (long long)((p.Nd + ts - 1) / ts) * ((p.Md + ts - 1) / ts) * p.groups * ks; };
-  const int ts = blocks(64) >= 128 ? 64 : blocks(32) >= 128 ? 32 : 16;
+  const int ts = tile_size(p.Md, p.Nd, (long long)p.groups * ks);
   const dim3 grid((p.Nd + ts - 1) / ts, (p.Md + ts - 1) / ts, p.groups * ks);
   if (grid.y > 65535 || grid.z > 65535) return hipErrorInvalidValue;
   if (ts == 16) hipLaunchKernelGGL((gemm_f32_kernel<EPI, ACT, 16, 256>), grid, dim3(256), 0, s, p);
@@ -231,10 +263,28 @@ hipError_t launch_act(const GemmP &p, hipStream_t s) {
     if (p.act == ACT_RELU) return launch1<EPI, ACT_RELU>(p, s);
     if (p.act == ACT_GELU) return launch1<EPI, ACT_GELU>(p, s);
   }
-  return launch1<EPI, ACT_NONE>(p, s);
+  if constexpr (EPI == EPI_WGRAD) {
+    if (!p.upd_x) return launch1<EPI, NO_STEP>(p, s);
+    if (p.ksplit > 1 || p.accumulate || !p.upd_sq || (p.upd_opt != OPT_SGD && !p.upd_v) || (p.upd_opt == OPT_ADAMW && !p.upd_m))
+      return hipErrorInvalidValue;
+    switch (p.upd_opt) {
+      case OPT_SGD: return launch1<EPI, OPT_SGD>(p, s);
+      case OPT_SHB: return launch1<EPI, OPT_SHB>(p, s);
+      case OPT_ADAMW: return launch1<EPI, OPT_ADAMW>(p, s);
+      case OPT_ADAGRAD: return launch1<EPI, OPT_ADAGRAD>(p, s);
+      default: return hipErrorInvalidValue;
+    }
+  } else {
+    return launch1<EPI, ACT_NONE>(p, s);
+  }
 }
 
 }  // namespace
+
+int gemm_f32_upd_slots(int Md, int Nd, int groups) {
+  const int ts = tile_size(Md, Nd, groups);
+  return ((Nd + ts - 1) / ts) * ((Md + ts - 1) / ts);
+}
 
 hipError_t launch_gemm_f32(const GemmP &p, int epi, hipStream_t s) {
   if (p.Md <= 0 || p.Nd <= 0 || p.groups <= 0) return hipSuccess;
