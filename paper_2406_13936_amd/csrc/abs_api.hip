@@ -572,7 +572,6 @@ struct StepPhase {
   float c1 = 1.0f, c2 = 1.0f;   // Adam bias corrections 1 / (1 - beta^t) of this step (set by the caller)
   const float *scal = nullptr;  // device {lr, c1, c2} for replayable launches (then lr / c1 / c2 here are unused)
   long long ps_off = 0;  // offset of this call's samples in the per-sample outputs (-1: not stored)
-  bool whole_launches = false;  // take the split decisions of a step with the update in the epilogue (materialize_grad)
 };
 
 static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, int b, const int *b_host, float lr,
@@ -750,11 +749,11 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
     const int sh = wgrad_shape(l);
     if (sh == 3) return 1;                      // short batches: never split
     const long long tiles = wgrad_tiles(l, sh);
-    // with the optimizer step in the epilogue a launch that gives every CU a work-group stays whole (measured on the
+    // a launch that gives every CU a work-group stays whole, whatever form the update takes (measured on the
     // 100 x 2048 layer of config 3 at b = 8192: 256 tiles un-split take as long as the split launch and its finish;
     // 784-512-512-10, 8 replicas, b = 4096, 384 tiles in one launch: 283 -> 260 us per
     // step against three split launches and their finish)
-    if ((want_fused || ph.whole_launches) && (sh == 1 ? tiles_shared : tiles) >= 256) return 1;
+    if ((sh == 1 ? tiles_shared : tiles) >= 256) return 1;
     return choose_ksplit(sh, tiles, (b + 63) / 64, (double)M * pl.dims[l] * pl.dims[l - 1], pl.kpart_floats_l[l]);
   };
   // The optimizer step moves into the weight-gradient epilogue when the caller asked for it and this call both
@@ -1020,7 +1019,6 @@ static abs_status materialize_grad(abs_ctx *c) {
   if (!c->last_fused) return ABS_OK;
   StepPhase ph;
   ph.passes = ph.nstats = ph.s2 = ph.ip = ph.update = false;
-  ph.whole_launches = true;
   ph.ps_off = -1;
   abs_status st = local_step_impl(c, nullptr, c->last_b, c->last_b, c->last_ragged ? c->last_bm.data() : nullptr, 0.0f, ph);
   if (st != ABS_OK) return st;
