@@ -8,8 +8,10 @@
 // [row][BK + 4], so that four k of a row are one 16-byte read without bank conflicts.  Generality (arbitrary strides and
 // extents) comes before peak rate.  Measured against 32 x 32 x 32 tiles on 4 replicas, 256 features, 10 classes: logits
 // 11.1 -> 5.7 us at b = 16, 12.0 -> 6.0 at b = 512; weight gradient with the bias sums at b = 512 10.3 us in one launch, before
-// 7.8 + 4.9 (split and finish) + 3.3 + 1.9 (column sums).  1024-256-100, 8 replicas, a step: 168 -> 101 us at b = 16,
-// 458 -> 388 at b = 1024 (64 x 64 tiles, unchanged but for the LDS layout).
+// 7.8 + 4.9 (split and finish) + 3.3 + 1.9 (column sums).
+// Weight gradients on 64 x 64 tiles, whose operands both come row-contiguous, keep them so in LDS ([k][64 + 4], four rows of a
+// k per read): as [row][BK + 4] their stores met in 16 of the 64 banks and the loop took 180 registers, two waves to a SIMD
+// (86 and five now): 256 x 1024 outputs of 8 replicas, b = 8192: 683 -> 530 us.
 #include "abs_internal.h"
 #include "device_utils.h"
 
@@ -25,8 +27,12 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmP pin) {
   constexpr int R = TS / 16;                     // outputs per thread and dimension
   constexpr int LD = BK + 4;
   constexpr bool AT = EPI == EPI_WGRAD, BT = EPI == EPI_WGRAD || EPI == EPI_BWD;   // operand layouts (GemmP::a_trans, b_trans)
-  __shared__ __attribute__((aligned(16))) float As[TS * LD];
-  __shared__ __attribute__((aligned(16))) float Bs[TS * LD];
+  constexpr bool KM = EPI == EPI_WGRAD && TS == 64;   // operands in LDS as [k][TS + 4]: a thread's rows and columns are R neighbours
+  constexpr int STAGE = KM ? BK * (TS + 4) : TS * LD;
+  __shared__ __attribute__((aligned(16))) float As[STAGE];
+  __shared__ __attribute__((aligned(16))) float Bs[STAGE];
+  auto own = [](int t, int i) -> int { return KM ? t * R + i : t + 16 * i; };   // row (column) i of thread row (column) t
+  auto slot = [](int rr, int kk) -> int { return KM ? kk * (TS + 4) + rr : rr * LD + kk; };
   // blockIdx.z = group, or (group, k-slice) of a weight gradient whose reduction is split
   const int ksplit = (EPI == EPI_WGRAD && pin.ksplit > 1) ? pin.ksplit : 1;
   const int g = blockIdx.z / ksplit, ksl = blockIdx.z - g * ksplit;
@@ -93,42 +99,68 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmP pin) {
   };
   if (kbeg < p.Kd) fetch(kbeg);
   for (int k0 = kbeg; k0 < p.Kd; k0 += BK) {
+    float fs = 0.0f;
 #pragma unroll
     for (int e = 0; e < PT; ++e) {
       int rr, kk;
       where(e, AT, rr, kk);
-      As[rr * LD + kk] = m0 + rr < p.Md && k0 + kk < p.Kd ? ra[e] : 0.0f;
+      const float av = m0 + rr < p.Md && k0 + kk < p.Kd ? ra[e] : 0.0f;
+      As[slot(rr, kk)] = av;
+      if (KM) fs += av;                           // (a thread fetches PT of k of one row)
       where(e, BT, rr, kk);
-      Bs[rr * LD + kk] = n0 + rr < p.Nd && k0 + kk < p.Kd ? rb[e] : 0.0f;
+      Bs[slot(rr, kk)] = n0 + rr < p.Nd && k0 + kk < p.Kd ? rb[e] : 0.0f;
     }
     __syncthreads();
     if (k0 + BK < p.Kd) fetch(k0 + BK);
-    const int k4 = (min(BK, p.Kd - k0) + 3) / 4;
-    float4 ks[R];
+    if constexpr (KM) {
+      if (row_sums) rs[0] += fs;                 // (uniform; the four threads of a row meet below)
 #pragma unroll
-    for (int i = 0; i < R; ++i) ks[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int k = 0; k < BK; ++k) {             // (all of them: what lies beyond Kd is zero)
+        const float4 a4 = *reinterpret_cast<const float4 *>(As + k * (TS + 4) + ty * R);
+        const float4 b4 = *reinterpret_cast<const float4 *>(Bs + k * (TS + 4) + tx * R);
+        const float a[4] = {a4.x, a4.y, a4.z, a4.w}, b[4] = {b4.x, b4.y, b4.z, b4.w};
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+#pragma unroll
+          for (int j = 0; j < R; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+      }
+    } else {
+      const int k4 = (min(BK, p.Kd - k0) + 3) / 4;
+      float4 ks[R];
+#pragma unroll
+      for (int i = 0; i < R; ++i) ks[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 8
-    for (int q = 0; q < k4; ++q) {
-      float4 a[R], b[R];
+      for (int q = 0; q < k4; ++q) {
+        float4 a[R], b[R];
 #pragma unroll
-      for (int i = 0; i < R; ++i) a[i] = *reinterpret_cast<const float4 *>(As + (ty + 16 * i) * LD + q * 4);
+        for (int i = 0; i < R; ++i) a[i] = *reinterpret_cast<const float4 *>(As + (ty + 16 * i) * LD + q * 4);
 #pragma unroll
-      for (int j = 0; j < R; ++j) b[j] = *reinterpret_cast<const float4 *>(Bs + (tx + 16 * j) * LD + q * 4);
+        for (int j = 0; j < R; ++j) b[j] = *reinterpret_cast<const float4 *>(Bs + (tx + 16 * j) * LD + q * 4);
 #pragma unroll
-      for (int i = 0; i < R; ++i)
+        for (int i = 0; i < R; ++i)
 #pragma unroll
-        for (int j = 0; j < R; ++j)
-          acc[i][j] = fmaf(a[i].w, b[j].w, fmaf(a[i].z, b[j].z, fmaf(a[i].y, b[j].y, fmaf(a[i].x, b[j].x, acc[i][j]))));
+          for (int j = 0; j < R; ++j)
+            acc[i][j] = fmaf(a[i].w, b[j].w, fmaf(a[i].z, b[j].z, fmaf(a[i].y, b[j].y, fmaf(a[i].x, b[j].x, acc[i][j]))));
+        if (EPI == EPI_WGRAD) {
+#pragma unroll
+          for (int i = 0; i < R; ++i) { ks[i].x += a[i].x; ks[i].y += a[i].y; ks[i].z += a[i].z; ks[i].w += a[i].w; }
+        }
+      }
       if (EPI == EPI_WGRAD) {
 #pragma unroll
-        for (int i = 0; i < R; ++i) { ks[i].x += a[i].x; ks[i].y += a[i].y; ks[i].z += a[i].z; ks[i].w += a[i].w; }
+        for (int i = 0; i < R; ++i) rs[i] += (ks[i].x + ks[i].y) + (ks[i].z + ks[i].w);
       }
     }
-    if (EPI == EPI_WGRAD) {
-#pragma unroll
-      for (int i = 0; i < R; ++i) rs[i] += (ks[i].x + ks[i].y) + (ks[i].z + ks[i].w);
-    }
     __syncthreads();
+  }
+  if (KM && row_sums) {                           // (uniform; the last k-step ended with a barrier)
+    As[tid] = rs[0];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      const int r = own(ty, i);
+      rs[i] = (As[r] + As[TS + r]) + (As[2 * TS + r] + As[3 * TS + r]);
+    }
   }
   // the optimizer step where the gradient is finished: parameter, state and squared entry of the gradient at offset o of group g
   constexpr bool STEP = EPI == EPI_WGRAD && ACT != NO_STEP;
@@ -147,7 +179,7 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmP pin) {
   if (row_sums && tx == 0) {
 #pragma unroll
     for (int i = 0; i < R; ++i) {
-      const int m = m0 + ty + 16 * i;
+      const int m = m0 + own(ty, i);
       float *o = p.rowsum + (long long)g * p.sRowsumg + m;
       if (m < p.Md) {
         const float gr = p.accumulate ? fmaf(rs[i], p.alpha, *o) : rs[i] * p.alpha;
@@ -187,11 +219,11 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmP pin) {
   }
 #pragma unroll
   for (int i = 0; i < R; ++i) {
-    const int m = m0 + ty + 16 * i;
+    const int m = m0 + own(ty, i);
     if (m >= p.Md) continue;
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-      const int n = n0 + tx + 16 * j;
+      const int n = n0 + own(tx, j);
       const bool nin = n < p.Nd;
       const float v = acc[i][j];
       const float bv = (bias && nin) ? bias[n] : 0.0f;

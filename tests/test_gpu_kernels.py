@@ -230,3 +230,67 @@ def test_softmax_head_at_the_edges_of_its_lanes(prec, K, sizes):
         assert rep.guard_intact()
     finally:
         rep.close()
+
+
+# The optimizer step in the epilogue of the fp32 weight gradients, biases beside them: 64 x 64 tiles (136 x 520 outputs of 8
+# replicas), 32 x 32 (100 x 136) and 16 x 16 (the narrow net), with remainders; the second step starts from non-zero state.
+@pytest.mark.parametrize("opt", [W.OPT_SGD, W.OPT_SHB, W.OPT_ADAMW, W.OPT_ADAGRAD])
+@pytest.mark.parametrize("dims,sizes", [((520, 136, 100), (201,) * 8), ((520, 136, 100), (201, 2, 64, 150, 33, 201, 7, 128)),
+                                        ((37, 19, 5), (65, 40))])
+def test_fp32_step_in_the_weight_gradient_moves_every_parameter(dims, sizes, opt):
+    A = _A()
+    M, b = len(sizes), max(sizes)
+    w = W.Workload("step", dims, W.ACT_GELU, True, W.PREC_F32, N=1024, M=M, H=1, rounds=1, b0=b, b_cap=b, opt=opt, lr=0.05, momentum=0.9,
+                   weight_decay=0.05, test=W.TEST_NORM, data="teacher_mlp", seed=17)
+    X, y = W.make_dataset(w)
+    x0 = W.make_x0(w)
+    rep = A.Replicas.from_workload(w, X, y, x0)
+    try:
+        orc = _fp32_oracle(w, X, y, x0)
+        for h in range(2):
+            rows = [W.batch_indices(w.seed, h, 0, m, s, w.N) for m, s in enumerate(sizes)]
+            if len(set(sizes)) > 1:
+                rep.local_step_ragged(rows, w.lr)
+            else:
+                rep.local_step(np.stack(rows), w.lr)
+            _check_fp32_step(rep, w, orc, rows, (0, 1, M - 1))
+        assert rep.guard_intact()
+    finally:
+        rep.close()
+
+
+def _fp32_oracle(w, X, y, x0):
+    return O.Replicas(O.Net(w.dims, w.act, True), x0, X, y, w.M, opt=w.opt, momentum=w.momentum, beta1=w.beta1, beta2=w.beta2,
+                      eps=w.eps, weight_decay=w.weight_decay)
+
+
+def _check_fp32_step(rep, w, orc, idx, sampled):
+    """Gradient, ||gbar||^2, parameters and optimizer state after a step (already taken by `rep`) against the oracle, workers
+    `sampled` only; the oracle then takes over parameters and state (a sign-like step turns a last-bit difference of a gradient
+    that is noise into a step of the learning rate, which the next step's gradients would show).
+    A gradient entry is a sum of b products in fp32: (b + layers) roundings of 2^-24, random in sign, of terms that largely
+    cancel: 1e-5 of the largest entry leaves a factor of 10 at b = 2305.  The step adds one rounding of the parameter; sign-like
+    optimizers divide the gradient by its own magnitude, so their parameters are compared where that is no rounding noise."""
+    orc.local_step(idx, w.lr, only=sorted(set(sampled)))
+    res = rep.norm_test(0.5)
+    for m in sorted(set(sampled)):
+        g, K = orc.grads[m], w.dims[-1]
+        got = rep.get_grad(m).astype(np.float64)
+        assert np.abs(got - g).max() <= 1e-5 * np.abs(g).max(), m
+        assert np.abs(got - g)[-K:].max() <= 1e-5 * np.abs(g[-K:]).max(), m
+        assert abs(res[m].gbar_sq - orc.stats[m]["S2"]) <= 1e-5 * orc.stats[m]["S2"], m
+        signed = w.opt in (W.OPT_ADAMW, W.OPT_ADAGRAD)
+        sel = np.abs(g) >= 1e-2 * np.abs(g).max() if signed else slice(None)
+        p = rep.get_params(m).astype(np.float64)
+        assert np.abs(p - orc.x[m])[sel].max() <= 1e-5 * np.abs(orc.x[m]).max(), m
+        if signed:                                       # (noise or not, a step of this kind is bounded)
+            assert np.abs(p - orc.x[m]).max() <= 2.1 * w.lr, m
+        orc.x[m] = p
+        if w.opt != W.OPT_SGD:
+            v = rep.get_opt_state(m, 0).astype(np.float64)
+            assert np.abs(v - orc.st[m].v).max() <= 4e-5 * np.abs(orc.st[m].v).max(), m
+            orc.st[m].v = v
+        if w.opt == W.OPT_ADAMW:
+            mm = rep.get_opt_state(m, 1).astype(np.float64)
+            assert np.abs(mm - orc.st[m].m).max() <= 4e-5 * np.abs(orc.st[m].m).max(), m
+            orc.st[m].m = mm
