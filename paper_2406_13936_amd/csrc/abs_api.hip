@@ -157,17 +157,17 @@ void make_plan(const abs_config *c, long long N, Plan &pl) {
   pl.sq_slots = pl.Ppad / 256;
   if (!pl.bf16) {
     long long blocks = 0;
-    for (int l = 1; l <= pl.L; ++l) blocks += gemm_f32_upd_slots(pl.dims[l], pl.dims[l - 1], pl.M);
+    for (int l = 1; l <= pl.L; ++l) blocks += gemm_f32_upd_slots(pl.dims[l], pl.dims[l - 1], 16);   // (the smallest tile)
     pl.sq_slots = std::max(pl.sq_slots, blocks);
   }
   pl.o_sqwave = take((size_t)pl.M * pl.sq_slots * sizeof(float));
   for (int l = 1; l <= pl.L; ++l) {
     // one piece per layer, so that one launch can finish the split reductions of all layers.  bf16: a split is
     // only taken when the un-split launch has at most 256 tiles, and never makes more than 512 (tile, slice) pairs
-    // of at most 128 x 128 or 256 x 256 outputs each; fp32: at most 8 slices of launches of fewer than 256 tiles
-    // of 64 x 64
+    // of at most 128 x 128 or 256 x 256 outputs each; fp32: at most 8 slices and 1024 blocks of at most 64 x 64 outputs,
+    // none where the outputs are no multiple of 4
     const size_t full = (size_t)8 * pl.M * pl.dims[l] * pl.dims[l - 1];
-    pl.kpart_floats_l[l] = std::min(full, pl.bf16 ? (size_t)512 * 65536 : (size_t)8 * 256 * 4096);
+    pl.kpart_floats_l[l] = pl.bf16 ? std::min(full, (size_t)512 * 65536) : gemm_f32_kpart_floats(pl.dims[l], pl.dims[l - 1], pl.M);
     pl.o_kpart_l[l] = take(pl.kpart_floats_l[l] * sizeof(float));
   }
   pl.o_cw = take((2 * (size_t)cross_worker_blocks(pl.Ppad) + 8) * 8);
@@ -707,25 +707,12 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       }
     }
   }   // passes
-  // fp32 mode (small problems): a block of the smallest tiles walks its reduction 256 samples at a time, about 2.5 us a step, so
-  // a long batch over few tiles is cut into up to 8 slices (finish launch and the bias sums' two launches: about 10 us)
-  auto f32_ksplit = [&](int l) -> int {
-    const long long mn = (long long)pl.dims[l] * pl.dims[l - 1];
-    const long long blocks = (long long)((pl.dims[l] + 15) / 16) * ((pl.dims[l - 1] + 15) / 16) * M;
-    const int KT = (b + 255) / 256;
-    int best = 1;
-    double best_cost = KT * 2.5;
-    for (int S = 2; S <= 8 && blocks < 128 && (mn & 3) == 0; ++S) {
-      if (blocks * S > 1024 || (size_t)S * M * mn > pl.kpart_floats_l[l]) break;
-      const double cost = ((KT + S - 1) / S) * 2.5 + 10.0;
-      if (cost < best_cost) { best = S; best_cost = cost; }
-    }
-    return best;
-  };
+  // fp32 mode (small problems): the tile of a weight gradient and the slices that a long batch over few tiles is cut into
+  auto f32_plan = [&](int l) { return gemm_f32_wgrad_plan(pl.dims[l], pl.dims[l - 1], b, M, pl.kpart_floats_l[l]); };
   // fp32 mode: the optimizer step where the gradient is finished, one launch of the step less (logistic regression: 2.6 of
   // 22 us), if no layer's reduction is split
   bool f32_step = !pl.bf16 && ph.wgrad && ph.update && ph.s2 && !ph.acc_grad;
-  for (int l = 1; l <= L && f32_step; ++l) f32_step = f32_ksplit(l) <= 1;
+  for (int l = 1; l <= L && f32_step; ++l) f32_step = f32_plan(l).ksplit <= 1;
   // Number of slices of layer l's weight-gradient reduction (bf16 mode): few output tiles and a long reduction
   // (small layers, or any layer while b is the long side) are cut into slices so that the launch fills the chip;
   // the slices are added in order afterwards.
@@ -788,11 +775,14 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       p.C = grad + pl.offW[l]; p.sCg = pl.Ppad; p.ldc = pl.dims[l - 1];
       p.alpha = inv_b; p.accumulate = ph.acc_grad ? 1 : 0;
       if (pl.bf16 && pl.want_ip && !use_gram) { p.C2 = c->at<bf16_t>(pl.o_gradbf) + pl.offW[l]; p.sC2g = pl.Ppad; p.ldc2 = pl.dims[l - 1]; }
-      if (!pl.bf16 && f32_ksplit(l) > 1) {
-        const int KT = (b + 255) / 256, S = f32_ksplit(l);
-        p.ksplit = S;
-        p.kchunk = ((KT + S - 1) / S) * 256;
-        p.kpart = c->at<float>(pl.o_kpart_l[l]);
+      if (!pl.bf16) {
+        const F32WgradPlan w = f32_plan(l);
+        p.f32_tile = w.tile;
+        if (w.ksplit > 1) {
+          p.ksplit = w.ksplit;
+          p.kchunk = ((b + 255) / 256 + w.ksplit - 1) / w.ksplit * 256;
+          p.kpart = c->at<float>(pl.o_kpart_l[l]);
+        }
       }
       if (hb && !pl.bf16 && p.ksplit <= 1) { p.rowsum = grad + pl.offB[l]; p.sRowsumg = pl.Ppad; }
       if (bf16_ksplit(l) > 1) {
@@ -811,7 +801,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
         p.upd_beta2 = c->cfg.beta2; p.upd_eps = c->cfg.eps; p.upd_wd = c->cfg.weight_decay;
         p.upd_c1 = ph.c1; p.upd_c2 = ph.c2; p.upd_scal = ph.scal;
         p.upd_sq = c->at<float>(pl.o_sqwave); p.upd_sSqg = pl.sq_slots; p.upd_slot0 = fused_slots;
-        fused_slots += pl.bf16 ? gemm_bf16_upd_slots(p.Md, p.Nd, b, M, 1, wgrad_fine) : gemm_f32_upd_slots(p.Md, p.Nd, M);
+        fused_slots += pl.bf16 ? gemm_bf16_upd_slots(p.Md, p.Nd, b, M, 1, wgrad_fine) : gemm_f32_upd_slots(p.Md, p.Nd, p.f32_tile);
       }
       const int wsh = pl.bf16 ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, M, p.upd_x != nullptr) : 0;
       p.fine = wsh == 1 ? wgrad_fine : 0;

@@ -66,6 +66,7 @@ struct GemmP {
   int fine;                    // EPI_WGRAD launches of tile shape 1: 64 x 128 tiles instead of 128 x 128 (two stages)
   int ksplit, kchunk;
   float *kpart;
+  int f32_tile;                // fp32 family, EPI_WGRAD: extent of the tile, 16, 32 or 64 (0: by the number of outputs)
   // fp32 family, EPI_WGRAD without a split (optional): rowsum[g * sRowsumg + m] = alpha * sum_k A[m][k] (+ the old value
   // if accumulate): the bias gradient beside the weight gradient
   float *rowsum; long long sRowsumg;
@@ -121,7 +122,12 @@ int gemm_bf16_upd_slots(int Md, int Nd, int Kd, int groups, int fused, int fine)
 hipError_t launch_gemm_f32(const GemmP &p, int epi, hipStream_t s);
 // Its EPI_WGRAD takes the optimizer step as well (GemmP::upd_x; the gradient is stored in C all the same, rowsum's entries take
 // theirs with it: rowsum and C point into the same vectors as upd_x); one upd_sq slot per block.
-int gemm_f32_upd_slots(int Md, int Nd, int groups);
+int gemm_f32_upd_slots(int Md, int Nd, int tile);
+// Tile extent and number of slices (of a multiple of 256 samples each) of an EPI_WGRAD launch over Kd samples; floats of
+// kpart scratch, over all groups, that its slices take at most.
+struct F32WgradPlan { int tile, ksplit; };
+F32WgradPlan gemm_f32_wgrad_plan(int Md, int Nd, int Kd, int groups, size_t kpart_floats);
+size_t gemm_f32_kpart_floats(int Md, int Nd, int groups);
 
 // ---- gram_ip.hip -----------------------------------------------------------
 // q[g][i] = (1 / b_g) sum_l sum_j (D_l D_l^T)[i][j] ((A_l A_l^T)[i][j] + [has_bias]),  i, j < b_g: the inner products

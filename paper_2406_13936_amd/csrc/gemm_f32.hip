@@ -12,11 +12,14 @@
 // Weight gradients on 64 x 64 tiles, whose operands both come row-contiguous, keep them so in LDS ([k][64 + 4], four rows of a
 // k per read): as [row][BK + 4] their stores met in 16 of the 64 banks and the loop took 180 registers, two waves to a SIMD
 // (86 and five now): 256 x 1024 outputs of 8 replicas, b = 8192: 683 -> 530 us.
+#include <algorithm>
 #include "abs_internal.h"
 #include "device_utils.h"
 
 namespace absk {
 namespace {
+
+constexpr int KSTEP[5] = {0, 256, 128, 0, 32};     // k-step of the tile of 16 times the index
 
 // (EPI_WGRAD with GemmP::upd_x: ACT carries the optimizer, NO_STEP without)
 constexpr int NO_STEP = 15;
@@ -266,6 +269,8 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmP pin) {
   }
 }
 
+constexpr int F32_MAX_SPLIT = 8, F32_MAX_SPLIT_BLOCKS = 1024;   // slices of a reduction; blocks of a launch that is split
+
 int tile_size(int Md, int Nd, long long groups) {
   // 32 x 32 tiles while 64 x 64 ones would leave most CUs without a work-group, 16 x 16 while 32 x 32 ones would
   auto blocks = [&](int ts) { return (long long)((Nd + ts - 1) / ts) * ((Md + ts - 1) / ts) * groups; };
@@ -281,12 +286,13 @@ hipError_t launch1(const GemmP &p, hipStream_t s) {
     return hipErrorInvalidValue;
   if (p.rowsum && (EPI != EPI_WGRAD || ks > 1)) return hipErrorInvalidValue;
   if (ks > 1 && (!p.kpart || p.kchunk <= 0 || (p.kchunk & 31) || (long long)p.kchunk * ks < p.Kd)) return hipErrorInvalidValue;
-  const int ts = tile_size(p.Md, p.Nd, (long long)p.groups * ks);
+  const int ts = EPI == EPI_WGRAD && p.f32_tile ? p.f32_tile : tile_size(p.Md, p.Nd, (long long)p.groups * ks);
+  if (ts != 16 && ts != 32 && ts != 64) return hipErrorInvalidValue;
   const dim3 grid((p.Nd + ts - 1) / ts, (p.Md + ts - 1) / ts, p.groups * ks);
   if (grid.y > 65535 || grid.z > 65535) return hipErrorInvalidValue;
-  if (ts == 16) hipLaunchKernelGGL((gemm_f32_kernel<EPI, ACT, 16, 256>), grid, dim3(256), 0, s, p);
-  else if (ts == 32) hipLaunchKernelGGL((gemm_f32_kernel<EPI, ACT, 32, 128>), grid, dim3(256), 0, s, p);
-  else hipLaunchKernelGGL((gemm_f32_kernel<EPI, ACT, 64, 32>), grid, dim3(256), 0, s, p);
+  if (ts == 16) hipLaunchKernelGGL((gemm_f32_kernel<EPI, ACT, 16, KSTEP[1]>), grid, dim3(256), 0, s, p);
+  else if (ts == 32) hipLaunchKernelGGL((gemm_f32_kernel<EPI, ACT, 32, KSTEP[2]>), grid, dim3(256), 0, s, p);
+  else hipLaunchKernelGGL((gemm_f32_kernel<EPI, ACT, 64, KSTEP[4]>), grid, dim3(256), 0, s, p);
   return hipGetLastError();
 }
 template <int EPI>
@@ -313,9 +319,41 @@ hipError_t launch_act(const GemmP &p, hipStream_t s) {
 
 }  // namespace
 
-int gemm_f32_upd_slots(int Md, int Nd, int groups) {
-  const int ts = tile_size(Md, Nd, groups);
-  return ((Nd + ts - 1) / ts) * ((Md + ts - 1) / ts);
+int gemm_f32_upd_slots(int Md, int Nd, int tile) { return ((Nd + tile - 1) / tile) * ((Md + tile - 1) / tile); }
+
+// Tile and number of slices of a weight gradient's reduction over Kd samples.  Up to 256 samples (one k-step of the smallest
+// tile) the tile follows from the number of outputs alone and nothing is split.  Beyond, the pair of least modelled time, in
+// microseconds per 256 samples walked by a block with n blocks on its CU, measured on 64 x 12 to 1024 x 256 outputs of 1 to 16
+// replicas, b = 512 to 8192 (alone; 2, 4 and more blocks to a CU):
+//   64 x 64 tiles 14; 17, 30   32 x 32 tiles 7.0; 8.4, 14 (16: 51)   16 x 16 tiles 3.5; 3.9, 5.6 (7: 9.9, 32: 43)
+// A split adds its finish, the column sums of the bias gradient and the separate optimizer step: about 12 us and the traffic.
+// The tile that is launched decides, not the smallest one: 100 x 1024 outputs of 4 replicas, b = 8192, are 128 tiles of
+// 64 x 64, un-split 436 us on half of the CUs, 121 in eight slices (step 758 -> 339 us; 256 x 100,
+// 16 replicas: 766 -> 358); 1024-256-100, 8 replicas, a step at b = 2048 437 -> 417, at b = 8192 1515 -> 1376.
+F32WgradPlan gemm_f32_wgrad_plan(int Md, int Nd, int Kd, int groups, size_t kpart_floats) {
+  F32WgradPlan best = {tile_size(Md, Nd, groups), 1};
+  if (Kd <= 256) return best;
+  const double outputs = (double)Md * Nd * groups, split_bytes = 4.0 * groups * Kd * Md;
+  const int KT = (Kd + 255) / 256;
+  double best_cost = 0.0;
+  for (int i = 1; i <= 4; i *= 2)
+    for (int S = 1; S <= F32_MAX_SPLIT && S <= KT; ++S) {
+      const int tile = 16 * i;
+      const long long blocks = (long long)gemm_f32_upd_slots(Md, Nd, tile) * groups * S;
+      if (S > 1 && (((long long)Md * Nd & 3) || blocks > F32_MAX_SPLIT_BLOCKS || S * outputs > (double)kpart_floats)) break;
+      const int len = std::min(Kd, (KT + S - 1) / S * 256), step = KSTEP[i];
+      const double n = (double)((blocks + 255) / 256);
+      const double t = i == 4 ? std::max(14.0, 2.0 + 7.2 * n) : i == 2 ? std::max(7.0, 1.0 + 3.2 * n) : std::max(3.5, 1.35 * n);
+      double cost = (len + step - 1) / step * (step / 256.0) * t;
+      if (S > 1) cost += 12.0 + (8.0 * S * outputs + split_bytes) / 4.5e6;
+      if (best_cost == 0.0 || cost < best_cost) { best.tile = tile; best.ksplit = S; best_cost = cost; }
+    }
+  return best;
+}
+
+size_t gemm_f32_kpart_floats(int Md, int Nd, int groups) {
+  if ((long long)Md * Nd & 3) return 0;
+  return std::min((size_t)F32_MAX_SPLIT * groups * Md * Nd, (size_t)F32_MAX_SPLIT_BLOCKS * 64 * 64);
 }
 
 hipError_t launch_gemm_f32(const GemmP &p, int epi, hipStream_t s) {

@@ -232,6 +232,32 @@ def test_softmax_head_at_the_edges_of_its_lanes(prec, K, sizes):
         rep.close()
 
 
+# fp32 weight gradients of long batches over few tiles are cut into slices, whatever tile the launch takes (64 x 64: 100 x 1024
+# outputs of 4 replicas, 136 x 520 of 8; 32 x 32: 70 x 136, 60 x 200; 16 x 16: 10 x 256), slices with a remainder and empty ones
+# (b = 2305: 9 steps of 256 in 8 slices of two); the bias gradient then comes from column sums, the step from its own launch.
+@pytest.mark.parametrize("dims,b,M,opt", [((1024, 100), 2048, 4, W.OPT_SGD), ((256, 100), 2305, 16, W.OPT_SHB),
+                                          ((520, 136, 70), 2050, 8, W.OPT_SGD), ((200, 60, 12), 2305, 6, W.OPT_ADAGRAD),
+                                          ((256, 10), 2049, 4, W.OPT_ADAMW)])
+def test_fp32_long_reductions_over_few_tiles_are_split(dims, b, M, opt):
+    A = _A()
+    act = W.ACT_GELU if len(dims) > 2 else W.ACT_NONE
+    w = W.Workload("long", dims, act, True, W.PREC_F32, N=4096, M=M, H=1, rounds=1, b0=b, b_cap=b, opt=opt, lr=0.05, momentum=0.9,
+                   weight_decay=0.05, test=W.TEST_NORM, data="teacher_mlp", seed=13)
+    X, y = W.make_dataset(w)
+    x0 = W.make_x0(w)
+    rep = A.Replicas.from_workload(w, X, y, x0)
+    try:
+        rep.profile_enable(True)
+        idx = W.step_indices(w, 0, 0, b)
+        rep.local_step(idx, w.lr)
+        assert "col_sum" in rep.profile_read()            # (un-split, the bias sums come out of the weight gradient's launch)
+        rep.profile_enable(False)
+        _check_fp32_step(rep, w, _fp32_oracle(w, X, y, x0), idx, (0, M - 1))
+        assert rep.guard_intact()
+    finally:
+        rep.close()
+
+
 # The optimizer step in the epilogue of the fp32 weight gradients, biases beside them: 64 x 64 tiles (136 x 520 outputs of 8
 # replicas), 32 x 32 (100 x 136) and 16 x 16 (the narrow net), with remainders; the second step starts from non-zero state.
 @pytest.mark.parametrize("opt", [W.OPT_SGD, W.OPT_SHB, W.OPT_ADAMW, W.OPT_ADAGRAD])
