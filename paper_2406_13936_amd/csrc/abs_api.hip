@@ -202,6 +202,95 @@ int choose_ksplit(int shape, long long tiles, int KT, double outputs, size_t kpa
   return best;
 }
 
+long long wgrad_tiles(const Plan &pl, int l, int bm, int bn) {
+  return (long long)((pl.dims[l] + bm - 1) / bm) * ((pl.dims[l - 1] + bn - 1) / bn) * pl.M;
+}
+
+// How the bf16 weight gradients of a step over b samples are launched: the slices of every layer's reduction and, for the
+// layers on 128 x 128 tiles, one launch for all (shared) or one each, and 64 x 128 tiles instead (fine).  The same whatever form
+// the update takes, so that every form adds the same products in the same order.
+struct WgradPlan { int ksplit[MAXL + 1]; bool shared; int fine; };
+
+// Microseconds per k-tile of 64 for `blocks` work-groups of equal length: `places` fit on the chip, a round that fills the
+// first, second, third 256 of them takes t[0], t[1], t[2] (a last round of at most 256 behind full ones lies between the first
+// two: what is left of it shares CUs with late tiles).
+double round_cost(double blocks, int places, const double *t) {
+  const double full = std::floor(blocks / places), rem = blocks - full * places;
+  const int k = rem <= 256 ? 0 : rem <= 512 ? 1 : 2;
+  const double last = rem <= 0 ? 0.0 : k || full == 0 ? t[k] : t[0] + (t[1] - t[0]) * rem / 256;
+  return full * t[places / 256 - 1] + last;
+}
+
+// Batches up to 960 (15 k-tiles, which choose_ksplit leaves whole) are mostly epilogue: one launch of 64 x 128 tiles
+// (784-512-512-10, us per step, against 128 x 128 tiles / launches of their own: 8 replicas, b = 512 103 / 108 / 126; 4 replicas,
+// b = 768 97 / 99 / 130).
+// Beyond, the launch of least modelled time, constants from 34 nets and replica counts at b = 300 to 16384 (per k-tile of 64;
+// a split's finish 10 us and its traffic, a launch 4.5, 5 for every 512 coarse tiles' epilogues).  Either shared form un-split
+// gives every tile the whole reduction, so its time goes by rounds of tiles; slices of unequal length do not share well: the
+// work-groups of an XCD are neighbours, and the XCDs with the long ones finish last (4 replicas, b = 16384: 249 us shared,
+// 185 apart).  Which way is best turns with every net, some of them in us per step (apart, shared fine, shared coarse, shared
+// with slices, this rule's choice last): 784-512-512-10, 4 replicas, b = 8192 265, 288, 300, 286 -> 265; 8 replicas, b = 4096
+// 275, 244, 249, 300 -> 244; 16 replicas, b = 8192 842, 886, 891, 1003 -> 842; 784-768-768-768-100, 4 replicas, b = 8192 626,
+// 663, 567, 657 -> 567; 1024-256-256-256-100, 2 replicas, b = 8192 204, 246, 269, 180 (coarse 166) -> 166.
+constexpr int WHOLE_MAX_B = 960;
+WgradPlan plan_wgrad(const Plan &pl, int b, int fused) {
+  const double ring = 0.9, coarse[2] = {1.13, 1.42}, fine[3] = {0.95, 1.2, 1.47}, launch = 4.5;
+  const int KT = (b + 63) / 64;
+  WgradPlan w = {{0}, true, 1};
+  double tiles_c = 0.0, tiles_f = 0.0, apart = 0.0, finish = 0.0;
+  double nb[2][MAXL], kt[MAXL], total[2] = {0.0, 0.0};
+  int n = 0;
+  bool split = false;
+  for (int l = 1; l <= pl.L; ++l) {
+    const int sh = gemm_bf16_wgrad_shape(pl.dims[l], pl.dims[l - 1], b, pl.M, fused);
+    const int te = sh == 2 ? 256 : 128;
+    const long long tiles = wgrad_tiles(pl, l, te, sh == 0 ? 64 : te);
+    const double outputs = (double)pl.M * pl.dims[l] * pl.dims[l - 1];
+    // never split: short batches, launches that give every CU a work-group
+    w.ksplit[l] = 1;
+    if (sh != 3 && !(sh == 1 && b <= WHOLE_MAX_B) && tiles < 256 && !(pl.dims[l - 1] & 3))
+      w.ksplit[l] = choose_ksplit(sh, tiles, KT, outputs, pl.kpart_floats_l[l]);
+    if (sh != 1) continue;
+    const int S = w.ksplit[l];
+    kt[n] = (KT + S - 1) / S;
+    nb[0][n] = (double)tiles * S; nb[1][n] = (double)wgrad_tiles(pl, l, 64, 128) * S;
+    total[0] += nb[0][n]; total[1] += nb[1][n];
+    tiles_c += nb[0][n] / S; tiles_f += nb[1][n] / S;
+    apart += kt[n] * (nb[0][n] <= 256 ? ring : round_cost(nb[0][n], 512, coarse)) + launch;
+    if (S > 1) { split = true; finish += S * outputs * 8.0 / 9e6; }
+    ++n;
+  }
+  if (b <= WHOLE_MAX_B || n == 0) return w;
+  if (split) finish += 10.0;
+  const double epi = 5.0 * tiles_c / 512;
+  const double whole_f = KT * round_cost(tiles_f, 768, fine) + launch, whole_c = KT * round_cost(tiles_c, 512, coarse) + launch + epi;
+  double cost = apart + finish;
+  w.shared = false; w.fine = 0;
+  double sliced[2] = {1e30, 1e30};
+  for (int f = 0; f < 2 && split; ++f) {           // the slowest XCD's eighth of the work-groups: 64 or 96 places
+    const double chunk = std::ceil(total[f] / 8), per = f ? fine[2] : coarse[1], places = f ? 96 : 64;
+    double worst = 0.0;
+    for (double lo = 0.0; lo < total[f]; lo += chunk) {
+      double at = 0.0, work = 0.0, cnt = 0.0, longest = 0.0;
+      for (int l = 0; l < n; at += nb[f][l++]) {
+        const double part = std::min(lo + chunk, at + nb[f][l]) - std::max(lo, at);
+        if (part > 0) { work += part * kt[l]; cnt += part; longest = std::max(longest, kt[l]); }
+      }
+      const double alone = longest * (cnt <= 32 ? (f ? fine[0] : coarse[0]) : f && cnt <= 64 ? fine[1] : per);
+      worst = std::max(worst, std::max(alone, cnt > places || !f ? (cnt <= 32 ? 0.0 : std::ceil(cnt / places) * work / cnt * per) : 0.0));
+    }
+    sliced[f] = worst + finish + launch + (f ? 0.0 : epi);
+  }
+  const double best = std::min(std::min(whole_f, whole_c), std::min(sliced[0], sliced[1]));
+  if (cost <= best) return w;
+  w.shared = true;
+  w.fine = best == whole_f || best == sliced[1];
+  if (best == whole_f || best == whole_c)
+    for (int l = 1; l <= pl.L; ++l)
+      if (gemm_bf16_wgrad_shape(pl.dims[l], pl.dims[l - 1], b, pl.M, fused) == 1) w.ksplit[l] = 1;
+  return w;
+}
+
 }  // namespace
 
 // Event-timed launch classes (abs_profile_*): one entry per kernel symbol of interest.
@@ -713,36 +802,10 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
   // 22 us), if no layer's reduction is split
   bool f32_step = !pl.bf16 && ph.wgrad && ph.update && ph.s2 && !ph.acc_grad;
   for (int l = 1; l <= L && f32_step; ++l) f32_step = f32_plan(l).ksplit <= 1;
-  // Number of slices of layer l's weight-gradient reduction (bf16 mode): few output tiles and a long reduction
-  // (small layers, or any layer while b is the long side) are cut into slices so that the launch fills the chip;
-  // the slices are added in order afterwards.
+  // bf16 mode: few output tiles and a long reduction (small layers, or any layer while b is the long side) are cut into
+  // slices so that the launch fills the chip; the slices are added in order afterwards (plan_wgrad).
   const bool want_fused = c->fused_update && pl.bf16 && ph.wgrad && ph.update && ph.s2 && !ph.acc_grad;
-  auto wgrad_tiles = [&](int l, int sh) -> long long {
-    const int te = sh == 2 ? 256 : 128, tn_e = sh == 0 ? 64 : te;
-    return (long long)((pl.dims[l] + te - 1) / te) * ((pl.dims[l - 1] + tn_e - 1) / tn_e) * M;
-  };
-  auto wgrad_shape = [&](int l) { return gemm_bf16_wgrad_shape(pl.dims[l], pl.dims[l - 1], b, M, want_fused); };
-  long long tiles_shared = 0, n_shared = 0;     // 128 x 128 tiles of the layers that share a launch
-  if (pl.bf16)
-    for (int l = 1; l <= L; ++l) if (wgrad_shape(l) == 1) { tiles_shared += wgrad_tiles(l, 1); ++n_shared; }
-  // 64 x 128 tiles level the load of the CUs where a shared launch has a place or two per CU, and stream a short reduction's
-  // epilogue better; long reductions over many tiles want the operand reuse of 128 x 128.  128 x 128 -> 64 x 128, us per step:
-  // 784-512-512-10, 8 replicas (384 tiles) b = 501 106.8 -> 105.7, b = 4096 260 -> 255; 784-256-10, 4 replicas, b = 1024 94.9 ->
-  // 90.0; 784-768-768-768-100, 16 replicas (1920 tiles) b = 512 428 -> 420, b = 1024 612 -> 611, but b = 2048 948 -> 972.  A layer alone on a long
-  // reduction keeps the deep ring of its own launch (3072-1024-1024-100, 8 replicas, b = 8192: 2151 us, 2173 with 64 x 128).
-  const int wgrad_fine = b <= 1024 || (n_shared > 1 && tiles_shared <= 512);
-  auto bf16_ksplit = [&](int l) -> int {
-    if (!pl.bf16 || (pl.dims[l - 1] & 3)) return 1;
-    const int sh = wgrad_shape(l);
-    if (sh == 3) return 1;                      // short batches: never split
-    const long long tiles = wgrad_tiles(l, sh);
-    // a launch that gives every CU a work-group stays whole, whatever form the update takes (measured on the
-    // 100 x 2048 layer of config 3 at b = 8192: 256 tiles un-split take as long as the split launch and its finish;
-    // 784-512-512-10, 8 replicas, b = 4096, 384 tiles in one launch: 283 -> 260 us per
-    // step against three split launches and their finish)
-    if ((sh == 1 ? tiles_shared : tiles) >= 256) return 1;
-    return choose_ksplit(sh, tiles, (b + 63) / 64, (double)M * pl.dims[l] * pl.dims[l - 1], pl.kpart_floats_l[l]);
-  };
+  const WgradPlan wplan = pl.bf16 && ph.wgrad ? plan_wgrad(pl, b, want_fused) : WgradPlan{};
   // The optimizer step moves into the weight-gradient epilogue when the caller asked for it and this call both
   // finishes the gradient and updates, no reduction is split and the per-wavefront sums of squares fit their scratch.
   bool fused = want_fused;
@@ -751,8 +814,8 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
     for (int l = 1; l <= L; ++l) {
       if (pl.dims[l - 1] & 3) fused = false;
       // a layer whose reduction is split takes its step in the launch that adds the slices
-      slots += bf16_ksplit(l) > 1 ? splitk_finish_slots((long long)pl.dims[l] * pl.dims[l - 1])
-                                  : gemm_bf16_upd_slots(pl.dims[l], pl.dims[l - 1], b, M, 1, wgrad_fine);
+      slots += wplan.ksplit[l] > 1 ? splitk_finish_slots((long long)pl.dims[l] * pl.dims[l - 1])
+                                   : gemm_bf16_upd_slots(pl.dims[l], pl.dims[l - 1], b, M, 1, wplan.fine);
     }
     if (hb) slots += col_finish_slots(L, max_width);
     if (slots > pl.sq_slots) fused = false;
@@ -785,8 +848,8 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
         }
       }
       if (hb && !pl.bf16 && p.ksplit <= 1) { p.rowsum = grad + pl.offB[l]; p.sRowsumg = pl.Ppad; }
-      if (bf16_ksplit(l) > 1) {
-        const int KT = (b + 63) / 64, S = bf16_ksplit(l);
+      if (wplan.ksplit[l] > 1) {
+        const int KT = (b + 63) / 64, S = wplan.ksplit[l];
         p.ksplit = S;
         p.kchunk = ((KT + S - 1) / S) * 64;
         p.kpart = c->at<float>(pl.o_kpart_l[l]);
@@ -801,11 +864,11 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
         p.upd_beta2 = c->cfg.beta2; p.upd_eps = c->cfg.eps; p.upd_wd = c->cfg.weight_decay;
         p.upd_c1 = ph.c1; p.upd_c2 = ph.c2; p.upd_scal = ph.scal;
         p.upd_sq = c->at<float>(pl.o_sqwave); p.upd_sSqg = pl.sq_slots; p.upd_slot0 = fused_slots;
-        fused_slots += pl.bf16 ? gemm_bf16_upd_slots(p.Md, p.Nd, b, M, 1, wgrad_fine) : gemm_f32_upd_slots(p.Md, p.Nd, p.f32_tile);
+        fused_slots += pl.bf16 ? gemm_bf16_upd_slots(p.Md, p.Nd, b, M, 1, wplan.fine) : gemm_f32_upd_slots(p.Md, p.Nd, p.f32_tile);
       }
       const int wsh = pl.bf16 ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, M, p.upd_x != nullptr) : 0;
-      p.fine = wsh == 1 ? wgrad_fine : 0;
-      if (wsh == 1 || wsh == 3) many[wsh == 3][p.upd_x != nullptr].push_back(p);
+      p.fine = wsh == 1 ? wplan.fine : 0;
+      if ((wsh == 1 && wplan.shared) || wsh == 3) many[wsh == 3][p.upd_x != nullptr].push_back(p);
       else HIPCHK(c, gemm(c, p, EPI_WGRAD, l));
       if (p.ksplit > 1) {                    // its slices are added up after the loop, with those of the other layers
         const int e = kf.n++;

@@ -320,3 +320,55 @@ def _check_fp32_step(rep, w, orc, idx, sampled):
             mm = rep.get_opt_state(m, 1).astype(np.float64)
             assert np.abs(mm - orc.st[m].m).max() <= 4e-5 * np.abs(orc.st[m].m).max(), m
             orc.st[m].m = mm
+
+
+# Launches of the bf16 weight gradients on 128 x 128 tiles, with and without the step in the epilogue: all layers in one launch on
+# 128 x 128 or 64 x 128 tiles, with slices or whole, or a launch per layer; `own` of them have a launch to themselves.  The form of
+# the update changes neither the launches' sums nor the parameters.
+@pytest.mark.parametrize("dims,M,b,opt,own", [
+    ((784, 512, 512, 10), 2, 4096, W.OPT_SHB, 3),             # long reductions in slices of unequal length: a launch each
+    ((784, 768, 768, 768, 100), 4, 1101, W.OPT_ADAMW, 0),     # 480 coarse tiles: one round, whole reductions
+    ((784, 512, 512, 10), 8, 1101, W.OPT_SGD, 0),             # 384 coarse tiles: 736 of 64 x 128
+    ((1024, 256, 256, 256, 100), 2, 2305, W.OPT_SHB, 0),      # slices in one launch (64 x 128 tiles)
+    ((512, 200, 10), 3, 2305, W.OPT_SGD, 0),                  # the same on 128 x 128 tiles, widths that are no multiple
+])
+def test_weight_gradient_launches_of_long_batches(dims, M, b, opt, own):
+    A = _A()
+    w = W.Workload("wgrad", dims, W.ACT_RELU, True, W.PREC_BF16, N=4096, M=M, H=1, rounds=1, b0=b, b_cap=b, opt=opt, lr=0.02, momentum=0.9,
+                   weight_decay=0.05, test=W.TEST_NORM, data="teacher_mlp", seed=19)
+    X, y = W.make_dataset(w)
+    x0 = W.make_x0(w)
+    orc = O.Replicas(O.Net(w.dims, w.act, True), x0, X, y, M, opt=opt, momentum=w.momentum, beta1=w.beta1, beta2=w.beta2, eps=w.eps,
+                     weight_decay=w.weight_decay, mixed=True)
+    idx = W.step_indices(w, 0, 0, b)
+    orc.local_step(idx, w.lr, only=[M - 1])
+    g = orc.grads[M - 1]
+    params = []
+    for fused in (True, False):
+        rep = A.Replicas.from_workload(w, X, y, x0)
+        try:
+            rep.set_fused_update(fused)
+            rep.profile_enable(True)
+            rep.local_step(idx, w.lr)
+            names = [n for n in rep.profile_read() if n.startswith("gemm_wgrad_")]
+            rep.profile_enable(False)
+            assert sum(not n.endswith("_L0") for n in names) == own, names
+            res = rep.norm_test(0.5)
+            assert abs(res[M - 1].gbar_sq - orc.stats[M - 1]["S2"]) <= 2e-3 * orc.stats[M - 1]["S2"]
+            p = rep.get_params(M - 1)
+            got = rep.get_grad(M - 1).astype(np.float64)
+            assert np.linalg.norm(got - g) <= 2e-3 * np.linalg.norm(g)
+            at = 0                                            # layer by layer: a small one would drown in the norm of all
+            for fin, fout in zip(dims[:-1], dims[1:]):
+                for size in (fin * fout, fout):
+                    part = slice(at, at + size)
+                    assert np.linalg.norm(got[part] - g[part]) <= 4e-3 * np.linalg.norm(g[part]), (fin, fout, size)
+                    at += size
+            sel = np.abs(g) >= 1e-2 * np.abs(g).max() if opt == W.OPT_ADAMW else slice(None)
+            assert np.abs(p - orc.x[M - 1])[sel].max() <= 1e-3 * np.abs(orc.x[M - 1]).max()
+            params.append((p, rep.get_params(0), got))
+            assert rep.guard_intact()
+        finally:
+            rep.close()
+    for a, c in zip(*params):
+        assert np.array_equal(a, c)
