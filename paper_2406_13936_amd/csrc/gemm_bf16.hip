@@ -1057,11 +1057,24 @@ int tiled_shape(int Md, int Nd, int groups) {
   return 1;
 }
 
-// Launches of at most this many 32 x 32 tiles go to gemm_small.hip (half as many for outputs of at most 64 columns, whose
-// 128 x 64 tiles read A once as well).  Whole steps, tiled -> small: 784-512-512-10, 8 replicas, b = 32 (128 tiles) 102 ->
-// 91 us, b = 128 (512) 117 -> 105, b = 256 (1024) 130 -> 126, b = 501 (2048) 147 -> 163 with the line at 2048;
-// 784-768-768-768-100, 16 replicas, b = 16 (384) 221 -> 203; config 3 at b = 64 only its logits (128 tiles) 21 -> 14 us.
+// Launches of at most this many 32 x 32 tiles go to gemm_small.hip: a latency chain instead of a nearly empty chip.  Past two
+// work-groups per CU their re-reads of both operands cost more than the tiled family's empty places: forward and logits of 512
+// tiles; of 384 where more than 32 classes leave the head to a launch of its own; backward-data, whose work-groups hold two
+// tiles, of 1024, unless those are one row of 32768 columns, whose weights the ring streams faster; 1024 also where the
+// alternative is 16 tiles of 256 x 256.  One launch, tiled -> small, us:
+//   forward 512 x 512: 16 replicas, b = 32 (256 tiles) 12.7 -> 9.6; 8 replicas, b = 128 (512) 12.7 -> 11.5, b = 256 (1024)
+//     13.6 -> 16.3; 2048 x 2048, 16 replicas, b = 32 (1024) 34 -> 53
+//   backward 512 x 512, 8 replicas: b = 256 (1024) 13.1 -> 11.3, b = 501 (2048) 13.1 -> 17.3; 2048 x 2048, 16 replicas, b = 32
+//     27.6 -> 31.1; 1024 x 1024, 32 replicas, b = 32 17.8 -> 19.3
+//   logits and head 512 -> 10, 8 replicas, b = 32 9.8 -> 5.0; 512 -> 100, 8 replicas, b = 512 (512) 17.3 -> 18.0, b = 1024
+//     (1024) 19.1 -> 23.2
+//   3072-1024-1024-100, 1 replica, b = 1024, the step: 336 -> 298
 constexpr long long SMALL_TILES = 1024;
+long long small_limit(int epi, int Md, int Nd, int groups) {
+  if (tiled_shape(Md, Nd, groups) == 2) return SMALL_TILES;
+  if (epi == EPI_BWD) return (long long)Nd * groups < 32768 ? SMALL_TILES : SMALL_TILES / 2;
+  return epi == EPI_LOGITS && Nd > 32 ? 384 : 512;
+}
 long long small_tiles(int Md, int Nd, int groups) { return (long long)((Md + 31) / 32) * ((Nd + 31) / 32) * groups; }
 
 template <int BM, int BN, int BK, int WM, int WN, int EPI, int ACT>
@@ -1107,7 +1120,7 @@ bool operands_ok(const GemmP &p, int epi) {
 }  // namespace
 
 int gemm_bf16_tile_shape(int epi, int Md, int Nd, int groups) {
-  if ((epi == EPI_FWD_ACT || epi == EPI_LOGITS || epi == EPI_BWD) && small_tiles(Md, Nd, groups) <= (Nd <= 64 ? SMALL_TILES / 2 : SMALL_TILES))
+  if ((epi == EPI_FWD_ACT || epi == EPI_LOGITS || epi == EPI_BWD) && small_tiles(Md, Nd, groups) <= small_limit(epi, Md, Nd, groups))
     return 5;
   return tiled_shape(Md, Nd, groups);
 }

@@ -372,3 +372,43 @@ def test_weight_gradient_launches_of_long_batches(dims, M, b, opt, own):
             rep.close()
     for a, c in zip(*params):
         assert np.array_equal(a, c)
+
+
+# Around the largest launches that take the 32-row tiles (32 x 32 tiles over all replicas: forward and logits 512, logits of more
+# than 32 classes 384, backward-data 1024): the last size on them, the first beyond, against the oracle.
+@pytest.mark.parametrize("dims,M,b,fwd,logits,bwd", [
+    ((64, 512, 256, 10), 8, 128, "32x32", "32x32", "32x64"),      # 512 / 256, 32 tiles
+    ((64, 512, 256, 10), 8, 129, "64x128", "32x32", "32x64"),     # 640
+    ((64, 512, 512, 100), 8, 256, "64x128", "32x32", "32x64"),    # 1024; logits 256
+    ((64, 264, 512, 100), 12, 256, "64x128", "32x32", "32x64"),   # 864 / 1536; logits 384
+    ((64, 512, 512, 100), 8, 289, "64x128", "32x32", "64x128"),   # 1280; logits 320
+    ((64, 512, 512, 100), 8, 417, "64x128", "64x128", "64x128"),  # 1792; logits 448
+    ((64, 1024, 64, 10), 32, 32, "64x128", "32x32", "64x128"),   # 1024, one row of tiles; 32
+])
+def test_edge_of_the_small_launches(dims, M, b, fwd, logits, bwd):
+    A = _A()
+    w = W.Workload("small", dims, W.ACT_RELU, True, W.PREC_BF16, N=1024, M=M, H=1, rounds=1, b0=b, b_cap=b, opt=W.OPT_SGD, lr=0.05,
+                   test=W.TEST_NORM, data="teacher_mlp", seed=23)
+    X, y = W.make_dataset(w)
+    x0 = W.make_x0(w)
+    rep = A.Replicas.from_workload(w, X, y, x0)
+    orc = O.Replicas(O.Net(w.dims, w.act, True), x0, X, y, M, opt=w.opt, mixed=True)
+    try:
+        rep.profile_enable(True)
+        idx = W.step_indices(w, 0, 0, b)
+        rep.local_step(idx, w.lr)
+        names = set(rep.profile_read())
+        rep.profile_enable(False)
+        # (layer 1 for the forward, the middle one for backward-data)
+        assert {"gemm_fwd_%s_L1" % fwd, "gemm_logits_%s_L3" % logits, "gemm_bwd_%s_L2" % bwd} <= names, names
+        res = rep.norm_test(0.5)
+        orc.local_step(idx, w.lr, only=[0, M - 1])
+        for m in (0, M - 1):
+            s = orc.stats[m]
+            for got, want in ((res[m].sum_sq, s["S1"]), (res[m].gbar_sq, s["S2"]), (res[m].loss_sum, s["loss_sum"])):
+                assert abs(got - want) <= 2e-3 * abs(want), (m, got, want)
+            grad = rep.get_grad(m).astype(np.float64)
+            assert np.linalg.norm(grad - orc.grads[m]) <= 2e-3 * np.linalg.norm(orc.grads[m]), m
+        assert rep.guard_intact()
+    finally:
+        rep.close()
