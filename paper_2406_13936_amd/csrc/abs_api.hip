@@ -225,7 +225,7 @@ double round_cost(double blocks, int places, const double *t) {
 // (784-512-512-10, us per step, against 128 x 128 tiles / launches of their own: 8 replicas, b = 512 103 / 108 / 126; 4 replicas,
 // b = 768 97 / 99 / 130).
 // Beyond, the launch of least modelled time, constants from 34 nets and replica counts at b = 300 to 16384 (per k-tile of 64;
-// a split's finish 10 us and its traffic, a launch 4.5, 5 for every 512 coarse tiles' epilogues).  Either shared form un-split
+// a split's finish 8 us and its traffic, a launch 7, 5 for every 512 coarse tiles' epilogues).  Either shared form un-split
 // gives every tile the whole reduction, so its time goes by rounds of tiles; slices of unequal length do not share well: the
 // work-groups of an XCD are neighbours, and the XCDs with the long ones finish last (4 replicas, b = 16384: 249 us shared,
 // 185 apart).  Which way is best turns with every net, some of them in us per step (apart, shared fine, shared coarse, shared
@@ -234,7 +234,7 @@ double round_cost(double blocks, int places, const double *t) {
 // 663, 567, 657 -> 567; 1024-256-256-256-100, 2 replicas, b = 8192 204, 246, 269, 180 (coarse 166) -> 166.
 constexpr int WHOLE_MAX_B = 960;
 WgradPlan plan_wgrad(const Plan &pl, int b, int fused) {
-  const double ring = 0.9, coarse[2] = {1.13, 1.42}, fine[3] = {0.95, 1.2, 1.47}, launch = 4.5;
+  const double ring = 0.9, coarse[2] = {1.13, 1.42}, fine[3] = {0.95, 1.2, 1.47}, launch = 7.0;
   const int KT = (b + 63) / 64;
   WgradPlan w = {{0}, true, 1};
   double tiles_c = 0.0, tiles_f = 0.0, apart = 0.0, finish = 0.0;
@@ -261,7 +261,7 @@ WgradPlan plan_wgrad(const Plan &pl, int b, int fused) {
     ++n;
   }
   if (b <= WHOLE_MAX_B || n == 0) return w;
-  if (split) finish += 10.0;
+  if (split) finish += 8.0;
   const double epi = 5.0 * tiles_c / 512;
   const double whole_f = KT * round_cost(tiles_f, 768, fine) + launch, whole_c = KT * round_cost(tiles_c, 512, coarse) + launch + epi;
   double cost = apart + finish;
