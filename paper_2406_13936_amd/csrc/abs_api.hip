@@ -256,7 +256,7 @@ WgradPlan plan_wgrad(const Plan &pl, int b, int fused) {
     nb[0][n] = (double)tiles * S; nb[1][n] = (double)wgrad_tiles(pl, l, 64, 128) * S;
     total[0] += nb[0][n]; total[1] += nb[1][n];
     tiles_c += nb[0][n] / S; tiles_f += nb[1][n] / S;
-    apart += kt[n] * (nb[0][n] <= 256 ? ring : round_cost(nb[0][n], 512, coarse)) + launch;
+    apart += kt[n] * (b > 1024 && nb[0][n] <= 256 ? ring : round_cost(nb[0][n], 512, coarse)) + launch;
     if (S > 1) { split = true; finish += S * outputs * 8.0 / 9e6; }
     ++n;
   }
