@@ -297,7 +297,7 @@ WgradPlan plan_wgrad(const Plan &pl, int b, int fused) {
 enum {
   T_GATHER = 0, T_SOFTMAX, T_ROWNORM, T_COLSUM, T_STATS, T_UPDATE, T_AVERAGE, T_ROWDOT, T_GRAM,
   T_GEMM0,                       // + epi * 6 + tile shape (bf16) ; fp32 family uses shape 1
-  T_GEMM_KINDS = 5 * 6, T_LAYERS = 17,   // GEMM classes are resolved per layer
+  T_GEMM_KINDS = 5 * 6, T_LAYERS = 17,   // GEMM classes are resolved per layer (0: a launch that several layers share)
   T_COUNT = T_GEMM0 + T_GEMM_KINDS * T_LAYERS
 };
 static const char *const kTagNames[T_GEMM0 + T_GEMM_KINDS] = {
@@ -305,8 +305,8 @@ static const char *const kTagNames[T_GEMM0 + T_GEMM_KINDS] = {
   "gemm_fwd_128x64", "gemm_fwd_128x128", "gemm_fwd_256x256", "gemm_fwd_64x256", "gemm_fwd_64x128", "gemm_fwd_32x32",
   "gemm_logits_128x64", "gemm_logits_128x128", "gemm_logits_256x256", "gemm_logits_64x256", "gemm_logits_64x128", "gemm_logits_32x32",
   "gemm_bwd_128x64", "gemm_bwd_128x128", "gemm_bwd_256x256", "gemm_bwd_64x256", "gemm_bwd_64x128", "gemm_bwd_32x64",
-  "gemm_wgrad_128x64", "gemm_wgrad_128x128", "gemm_wgrad_256x256", "gemm_wgrad_64x256", "gemm_wgrad_64x128", "gemm_wgrad_32x32",
-  "gemm_ipdot_128x64", "gemm_ipdot_128x128", "gemm_ipdot_256x256", "gemm_ipdot_64x256", "gemm_ipdot_64x128", "gemm_ipdot_32x32"};
+  "gemm_wgrad_128x64", "gemm_wgrad_128x128", "gemm_wgrad_256x256", "gemm_wgrad_64x256", "gemm_wgrad_64x128", "",     // (no 32-row form)
+  "gemm_ipdot_128x64", "gemm_ipdot_128x128", "gemm_ipdot_256x256", "gemm_ipdot_64x256", "gemm_ipdot_64x128", ""};
 
 struct ProfRec { int tag; hipEvent_t e0, e1; double flops, bytes; };
 
@@ -412,10 +412,11 @@ double gemm_bytes(const abs_ctx *c, const GemmP &p, int epi) {
   const double e = c->pl.esz, mn = (double)p.Md * p.Nd;
   double bytes = ((double)p.Md + p.Nd) * p.Kd * e;
   if (epi == EPI_FWD_ACT) bytes += mn * e * (p.C2 ? 2 : 1);
+  else if (epi == EPI_LOGITS && p.head.y) bytes += (double)p.Md * (p.head.ldd * e + 16);   // signal; index, label, norm, loss
   else if (epi == EPI_LOGITS) bytes += mn * 4;
   else if (epi == EPI_BWD) bytes += mn * e * (p.act != ABS_ACT_NONE ? 2 : 1);
   else if (epi == EPI_IPDOT) bytes += mn * e;
-  else if (p.upd_x) bytes += mn * (8 + (p.upd_v ? 8 : 0) + (p.upd_m ? 8 : 0) + (p.upd_shadow ? 2 : 0) + (p.C2 ? 2 : 0));
+  else if (p.upd_x) bytes += mn * (8 + (c->pl.bf16 ? 0 : 4) + (p.upd_v ? 8 : 0) + (p.upd_m ? 8 : 0) + (p.upd_shadow ? 2 : 0) + (p.C2 ? 2 : 0));
   else bytes += mn * (4 + (p.C2 ? 2 : 0) + (p.accumulate ? 4 : 0));
   return bytes * p.groups;
 }
@@ -423,8 +424,8 @@ double gemm_flops(const std::vector<GemmP> &v) { double s = 0.0; for (const Gemm
 double gemm_bytes(const abs_ctx *c, const std::vector<GemmP> &v, int epi) { double s = 0.0; for (const GemmP &p : v) s += gemm_bytes(c, p, epi); return s; }
 
 hipError_t gemm(abs_ctx *c, const GemmP &p, int epi, int layer) {
-  int shape = !c->pl.bf16 ? 1 : (epi == EPI_WGRAD ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr)
-                                                   : gemm_bf16_tile_shape(epi, p.Md, p.Nd, p.groups));
+  int shape = !c->pl.bf16 ? 1 : p.fine ? 4 : (epi == EPI_WGRAD ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr)
+                                                                : gemm_bf16_tile_shape(epi, p.Md, p.Nd, p.groups));
   ProfScope ps(c, T_GEMM0 + (epi * 6 + shape) * T_LAYERS + layer, gemm_flops(p), gemm_bytes(c, p, epi));
   return c->pl.bf16 ? launch_gemm_bf16(p, epi, c->stream) : launch_gemm_f32(p, epi, c->stream);
 }
@@ -829,6 +830,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
   // local batch gradient, eq. (batch_grad): Gbar_l = delta^T a / b, betabar_l = mean_i delta_i
   if (ph.wgrad) {
     std::vector<GemmP> many[2][2];         // layers that share a launch: [tile shape 1, 3][with the step in the epilogue]
+    int many_layer[2][2] = {{0, 0}, {0, 0}};   // its last layer
     for (int l = 1; l <= L; ++l) {
       GemmP p;
       std::memset(&p, 0, sizeof(p));
@@ -868,7 +870,10 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       }
       const int wsh = pl.bf16 ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, M, p.upd_x != nullptr) : 0;
       p.fine = wsh == 1 ? wplan.fine : 0;
-      if ((wsh == 1 && wplan.shared) || wsh == 3) many[wsh == 3][p.upd_x != nullptr].push_back(p);
+      if ((wsh == 1 && wplan.shared) || wsh == 3) {
+        many[wsh == 3][p.upd_x != nullptr].push_back(p);
+        many_layer[wsh == 3][p.upd_x != nullptr] = l;
+      }
       else HIPCHK(c, gemm(c, p, EPI_WGRAD, l));
       if (p.ksplit > 1) {                    // its slices are added up after the loop, with those of the other layers
         const int e = kf.n++;
@@ -898,10 +903,11 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       }
     }
     for (int sh = 0; sh < 2; ++sh)
-      for (const std::vector<GemmP> &v : many[sh]) {
-        if (sh == 0 && v.size() == 1 && !v[0].fine) { HIPCHK(c, gemm(c, v[0], EPI_WGRAD, 0)); continue; }   // (may take a deeper ring)
+      for (int u = 0; u < 2; ++u) {
+        const std::vector<GemmP> &v = many[sh][u];
         if (v.empty()) continue;
-        ProfScope ps_(c, T_GEMM0 + (EPI_WGRAD * 6 + (sh ? 3 : 1)) * T_LAYERS, gemm_flops(v), gemm_bytes(c, v, EPI_WGRAD));
+        if (v.size() == 1) { HIPCHK(c, gemm(c, v[0], EPI_WGRAD, many_layer[sh][u])); continue; }   // (may take a deeper ring)
+        ProfScope ps_(c, T_GEMM0 + (EPI_WGRAD * 6 + (sh ? 3 : v[0].fine ? 4 : 1)) * T_LAYERS, gemm_flops(v), gemm_bytes(c, v, EPI_WGRAD));
         HIPCHK(c, launch_wgrad_many(v.data(), (int)v.size(), sh ? 3 : 1, s));
       }
     if (kf.n > 0) {                        // all split reductions of the step in one launch

@@ -412,3 +412,33 @@ def test_edge_of_the_small_launches(dims, M, b, fwd, logits, bwd):
         assert rep.guard_intact()
     finally:
         rep.close()
+
+
+# What the per-kernel profile says of a launch: the layer where only one is in it, the tile that ran, the bytes of what it stores.
+def test_profile_names_the_launch_and_counts_its_bytes():
+    A = _A()
+
+    def profile(dims, prec, M, b):
+        w = W.Workload("prof", dims, W.ACT_RELU, True, prec, N=256, M=M, H=1, rounds=1, b0=b, b_cap=b, opt=W.OPT_SGD, lr=0.05,
+                       test=W.TEST_NORM, data="teacher_mlp", seed=29)
+        X, y = W.make_dataset(w)
+        rep = A.Replicas.from_workload(w, X, y, W.make_x0(w))
+        try:
+            rep.profile_enable(True)
+            rep.local_step(W.step_indices(w, 0, 0, b), w.lr)
+            return rep.profile_read()
+        finally:
+            rep.close()
+
+    p = profile((64, 136, 40), W.PREC_BF16, 2, 300)
+    assert {n for n in p if "wgrad" in n} == {"gemm_wgrad_128x64_L1", "gemm_wgrad_64x128_L2"}
+    p = profile((256, 136, 40), W.PREC_BF16, 2, 300)
+    assert {n for n in p if "wgrad" in n} == {"gemm_wgrad_64x128_L0"}
+    p = profile((256, 136, 40), W.PREC_BF16, 2, 100)
+    assert {n for n in p if "wgrad" in n} == {"gemm_wgrad_64x256_L0"}
+    p = profile((64, 10), W.PREC_BF16, 3, 50)
+    # operands; rows of 16 stored signals, index, label, norm and loss
+    assert p["gemm_logits_32x32_L1"]["bytes"] == 3 * ((50 + 10) * 64 * 2 + 50 * (16 * 2 + 16))
+    p = profile((64, 10), W.PREC_F32, 3, 50)
+    assert p["gemm_logits_128x128_L1"]["bytes"] == 3 * ((50 + 10) * 64 * 4 + 50 * (16 * 4 + 16))
+    assert p["gemm_wgrad_128x128_L1"]["bytes"] == 3 * ((10 + 64) * 50 * 4 + 640 * (8 + 4))      # gradient stored beside the step
