@@ -889,14 +889,10 @@ hipError_t launch_softmax_ce(int is_bf16, const float *Z, long long sZg, int ldz
                              int N, const int32_t *idx, int ldi, int groups, int b, void *D, long long sDg, int ldd,
                              float *dn, float *loss, long long sNg, const int *rows, hipStream_t s) {
   const dim3 blk(256);
-  if (ldd <= 16) {
+  if (is_bf16 && ldd <= 16) {                    // (fp32: the logits' launch carries the head of so few classes)
     const dim3 grid((b + 15) / 16, groups);
-    if (is_bf16)
-      hipLaunchKernelGGL((softmax_ce_kernel<bf16_t, 16>), grid, blk, 0, s, Z, sZg, ldz, K, y, N, idx, ldi, b,
-                         static_cast<bf16_t *>(D), sDg, ldd, dn, loss, sNg, rows);
-    else
-      hipLaunchKernelGGL((softmax_ce_kernel<float, 16>), grid, blk, 0, s, Z, sZg, ldz, K, y, N, idx, ldi, b,
-                         static_cast<float *>(D), sDg, ldd, dn, loss, sNg, rows);
+    hipLaunchKernelGGL((softmax_ce_kernel<bf16_t, 16>), grid, blk, 0, s, Z, sZg, ldz, K, y, N, idx, ldi, b,
+                       static_cast<bf16_t *>(D), sDg, ldd, dn, loss, sNg, rows);
     return hipGetLastError();
   }
   if (ldd <= 128 && (ldd & 3) == 0 && (ldz & 3) == 0 && ldz >= ldd && (sZg & 3) == 0 && (sDg & 3) == 0) {
