@@ -276,10 +276,14 @@ abs_status abs_n_params(const abs_config *cfg, int64_t *n /*host*/);
  * Statistics and averaging alone, on caller-supplied layer inputs and backprop signals
  * (no model run): for each of M replicas and L stacked linear layers without bias,
  *   a_dev[l]     : device, bf16 [M x b x in_l],  delta_dev[l] : device, bf16 [M x b x out_l]
- * computes Gbar_l = delta^T a / b (fp32, into workspace), n_i, S1, S2, q_i, S3, S4 with the
- * same kernels as abs_local_step.   out : host, M entries (b, sum_sq, gbar_sq, sum_q, sum_q2).
+ * computes Gbar_l = delta^T a / b, n_i, S1, S2, q_i, S3, S4 with the same kernels as
+ * abs_local_step.   out : host, M entries (b, sum_sq, gbar_sq, sum_q, sum_q2).
  *   n_out_dev, q_out_dev : device, float [M x b] (either may be NULL).
- *   gbar_out_dev : device, float, sum_l out_l*in_l per replica, replica-major (may be NULL).
+ *   gbar_out_dev : device, float, sum_l out_l*in_l per replica, replica-major (may be NULL: the
+ *     fp32 Gbar is then never stored; the workspace keeps the bf16 copy that the inner products
+ *     read).  The launches that form Gbar write it; a buffer that is not 16-byte aligned or
+ *     overlaps an input is filled at the end instead, through a piece of the workspace that is
+ *     reserved for this (4 of the about 6 bytes per entry of Gbar that the workspace holds).
  */
 abs_status abs_layer_stats(int L, const int *in_dims, const int *out_dims, int M, int b,
                            const void *const *a_dev, const void *const *delta_dev,
