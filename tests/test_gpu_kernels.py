@@ -442,3 +442,44 @@ def test_profile_names_the_launch_and_counts_its_bytes():
     p = profile((64, 10), W.PREC_F32, 3, 50)
     assert p["gemm_logits_128x128_L1"]["bytes"] == 3 * ((50 + 10) * 64 * 4 + 50 * (16 * 4 + 16))
     assert p["gemm_wgrad_128x128_L1"]["bytes"] == 3 * ((10 + 64) * 50 * 4 + 640 * (8 + 4))      # gradient stored beside the step
+
+
+# Nets of more layers than a shared weight-gradient launch holds (eight): on the short-batch tiles (b = 200), whole reductions on
+# 64 x 128 tiles (b = 300, 960 and, around the batch from which slices are weighed, 961) and slices (b = 1100), two steps, with and
+# without the step in the epilogue.  Ten layers of bf16 roundings lie between input and gradient: a unit on a tie moves a
+# sample's signal by 2^-8 of itself, a few ties per layer and sample; the norms of whole layers stay within 1e-2.
+@pytest.mark.parametrize("b", [200, 300, 960, 961, 1100])
+@pytest.mark.parametrize("fused", [True, False])
+def test_weight_gradients_of_more_layers_than_one_launch_holds(b, fused):
+    A = _A()
+    dims, M = (128,) * 10 + (10,), 3
+    w = W.Workload("deep", dims, W.ACT_GELU, True, W.PREC_BF16, N=2048, M=M, H=1, rounds=1, b0=b, b_cap=b, opt=W.OPT_SHB, lr=0.05, momentum=0.9,
+                   test=W.TEST_NORM, data="teacher_mlp", seed=31)
+    X, y = W.make_dataset(w)
+    x0 = W.make_x0(w)
+    rep = A.Replicas.from_workload(w, X, y, x0)
+    orc = O.Replicas(O.Net(w.dims, w.act, True), x0, X, y, M, opt=w.opt, momentum=w.momentum, mixed=True)
+    try:
+        rep.set_fused_update(fused)
+        for h in range(2):
+            idx = W.step_indices(w, 0, h, b)
+            rep.local_step(idx, w.lr)
+            res = rep.norm_test(0.5)
+            orc.local_step(idx, w.lr, only=[0, M - 1])
+            for m in (0, M - 1):
+                g, s = orc.grads[m], orc.stats[m]
+                for got, want in ((res[m].sum_sq, s["S1"]), (res[m].gbar_sq, s["S2"]), (res[m].loss_sum, s["loss_sum"])):
+                    assert abs(got - want) <= 5e-3 * abs(want), (h, m, got, want)
+                got, at = rep.get_grad(m).astype(np.float64), 0
+                for fin, fout in zip(dims[:-1], dims[1:]):
+                    for size in (fin * fout, fout):
+                        part = slice(at, at + size)
+                        assert np.linalg.norm(got[part] - g[part]) <= 1e-2 * np.linalg.norm(g[part]), (h, m, at)
+                        at += size
+                p, v = rep.get_params(m).astype(np.float64), rep.get_opt_state(m, 0).astype(np.float64)
+                assert np.abs(p - orc.x[m]).max() <= 1e-3 * np.abs(orc.x[m]).max(), (h, m)
+                assert np.linalg.norm(v - orc.st[m].v) <= 1e-2 * np.linalg.norm(orc.st[m].v), (h, m)
+                orc.x[m], orc.st[m].v = p, v
+        assert rep.guard_intact()
+    finally:
+        rep.close()
