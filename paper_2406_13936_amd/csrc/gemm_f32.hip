@@ -11,7 +11,7 @@
 // 7.8 + 4.9 (split and finish) + 3.3 + 1.9 (column sums).
 // Weight gradients on 64 x 64 tiles, whose operands both come row-contiguous, keep them so in LDS ([k][64 + 4], four rows of a
 // k per read): as [row][BK + 4] their stores met in 16 of the 64 banks and the loop took 180 registers, two waves to a SIMD
-// (86 and five now): 256 x 1024 outputs of 8 replicas, b = 8192: 683 -> 530 us.
+// (106 and four now): 256 x 1024 outputs of 8 replicas, b = 8192: 683 -> 512 us.
 #include <algorithm>
 #include "abs_internal.h"
 #include "device_utils.h"
@@ -100,6 +100,20 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmP pin) {
       rb[e] = BT ? B[(long long)k * p.ldb + n] : B[(long long)n * p.ldb + k];
     }
   };
+  // Weight gradients sum over the batch, which may be long: in one chain per output the sum loses a digit against one cut into
+  // slices (784 -> 10, b = 1024: relative error 5.4e-7, in slices 1.7e-7, as here 1.3e-7; the same time).  So at most 128
+  // products follow one another (in the smaller tiles 32 in each of four chains), and these sums are added up.
+  float part[R][R];
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+#pragma unroll
+    for (int j = 0; j < R; ++j) part[i][j] = 0.0f;
+  auto join = [&]() {
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+      for (int j = 0; j < R; ++j) { acc[i][j] += part[i][j]; part[i][j] = 0.0f; }
+  };
   if (kbeg < p.Kd) fetch(kbeg);
   for (int k0 = kbeg; k0 < p.Kd; k0 += BK) {
     float fs = 0.0f;
@@ -125,13 +139,46 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmP pin) {
 #pragma unroll
         for (int i = 0; i < R; ++i)
 #pragma unroll
-          for (int j = 0; j < R; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+          for (int j = 0; j < R; ++j) part[i][j] = fmaf(a[i], b[j], part[i][j]);
+      }
+      if ((k0 & 96) == 96) join();               // (uniform: kbeg is a multiple of 128)
+    } else if constexpr (EPI == EPI_WGRAD) {
+      const int k4 = (min(BK, p.Kd - k0) + 3) / 4;
+      for (int q0 = 0; q0 < k4; q0 += 32) {
+        float4 ks[R], c4[R][R];
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+          ks[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+          for (int j = 0; j < R; ++j) c4[i][j] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        const int q1 = min(q0 + 32, k4);
+#pragma unroll 8
+        for (int q = q0; q < q1; ++q) {
+          float4 a[R], b[R];
+#pragma unroll
+          for (int i = 0; i < R; ++i) a[i] = *reinterpret_cast<const float4 *>(As + (ty + 16 * i) * LD + q * 4);
+#pragma unroll
+          for (int j = 0; j < R; ++j) b[j] = *reinterpret_cast<const float4 *>(Bs + (tx + 16 * j) * LD + q * 4);
+#pragma unroll
+          for (int i = 0; i < R; ++i) {
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+              c4[i][j].x = fmaf(a[i].x, b[j].x, c4[i][j].x); c4[i][j].y = fmaf(a[i].y, b[j].y, c4[i][j].y);
+              c4[i][j].z = fmaf(a[i].z, b[j].z, c4[i][j].z); c4[i][j].w = fmaf(a[i].w, b[j].w, c4[i][j].w);
+            }
+            ks[i].x += a[i].x; ks[i].y += a[i].y; ks[i].z += a[i].z; ks[i].w += a[i].w;
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+          rs[i] += (ks[i].x + ks[i].y) + (ks[i].z + ks[i].w);
+#pragma unroll
+          for (int j = 0; j < R; ++j) acc[i][j] += (c4[i][j].x + c4[i][j].y) + (c4[i][j].z + c4[i][j].w);
+        }
       }
     } else {
       const int k4 = (min(BK, p.Kd - k0) + 3) / 4;
-      float4 ks[R];
-#pragma unroll
-      for (int i = 0; i < R; ++i) ks[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 8
       for (int q = 0; q < k4; ++q) {
         float4 a[R], b[R];
@@ -144,18 +191,11 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmP pin) {
 #pragma unroll
           for (int j = 0; j < R; ++j)
             acc[i][j] = fmaf(a[i].w, b[j].w, fmaf(a[i].z, b[j].z, fmaf(a[i].y, b[j].y, fmaf(a[i].x, b[j].x, acc[i][j]))));
-        if (EPI == EPI_WGRAD) {
-#pragma unroll
-          for (int i = 0; i < R; ++i) { ks[i].x += a[i].x; ks[i].y += a[i].y; ks[i].z += a[i].z; ks[i].w += a[i].w; }
-        }
-      }
-      if (EPI == EPI_WGRAD) {
-#pragma unroll
-        for (int i = 0; i < R; ++i) rs[i] += (ks[i].x + ks[i].y) + (ks[i].z + ks[i].w);
       }
     }
     __syncthreads();
   }
+  if (KM) join();
   if (KM && row_sums) {                           // (uniform; the last k-step ended with a barrier)
     As[tid] = rs[0];
     __syncthreads();

@@ -483,3 +483,27 @@ def test_weight_gradients_of_more_layers_than_one_launch_holds(b, fused):
         assert rep.guard_intact()
     finally:
         rep.close()
+
+
+# fp32 weight gradients over long batches: products follow one another for at most 128 samples before their sum is put down, so the
+# rounding error does not grow with the batch.  2^-24 is one rounding: the gradient (signals of 1024-long sums included) lies within
+# 4.5 of them of its 64-bit value in norm; one chain over the batch drifts by sqrt(b) / 3 of them (9 at b = 1024, 18 at 4096).
+@pytest.mark.parametrize("dims,b,roundings", [((784, 10), 1024, 4.5), ((784, 10), 4096, 4.5), ((520, 136, 100), 2048, 7), ((100, 64, 7), 256, 4.5),
+                                              ((1024, 256, 100), 1024, 9)])
+def test_fp32_weight_gradients_do_not_lose_precision_over_the_batch(dims, b, roundings):
+    A = _A()
+    act = W.ACT_GELU if len(dims) > 2 else W.ACT_NONE
+    w = W.Workload("prec", dims, act, True, W.PREC_F32, N=4096, M=4, H=1, rounds=1, b0=b, b_cap=b, opt=W.OPT_SGD, lr=0.05, test=W.TEST_NORM,
+                   data="teacher_mlp" if len(dims) > 2 else "mixture", seed=101)
+    X, y = W.make_dataset(w)
+    x0 = W.make_x0(w)
+    rep = A.Replicas.from_workload(w, X, y, x0)
+    orc = O.Replicas(O.Net(w.dims, w.act, True), x0, X, y, w.M, opt=w.opt)
+    try:
+        idx = W.step_indices(w, 0, 0, b)
+        rep.local_step(idx, w.lr)
+        orc.local_step(idx, w.lr, only=[0, 3])
+        err = [np.linalg.norm(rep.get_grad(m).astype(np.float64) - orc.grads[m]) / np.linalg.norm(orc.grads[m]) for m in (0, 3)]
+        assert max(err) <= roundings * EPS32, err
+    finally:
+        rep.close()
