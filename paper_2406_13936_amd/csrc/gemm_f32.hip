@@ -32,9 +32,8 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmP pin) {
   constexpr bool AT = EPI == EPI_WGRAD, BT = EPI == EPI_WGRAD || EPI == EPI_BWD;   // operand layouts (GemmP::a_trans, b_trans)
   constexpr bool KM = EPI == EPI_WGRAD && TS == 64;   // operands in LDS as [k][TS + 4]: a thread's rows and columns are R neighbours
   constexpr int STAGE = KM ? BK * (TS + 4) : TS * LD;
-  __shared__ __attribute__((aligned(16))) float As[STAGE];
-  __shared__ __attribute__((aligned(16))) float Bs[STAGE];
-  auto own = [](int t, int i) -> int { return KM ? t * R + i : t + 16 * i; };   // row (column) i of thread row (column) t
+  __shared__ __attribute__((aligned(16))) float lds[2 * STAGE];
+  float *const As = lds, *const Bs = lds + STAGE;
   auto slot = [](int rr, int kk) -> int { return KM ? kk * (TS + 4) + rr : rr * LD + kk; };
   // blockIdx.z = group, or (group, k-slice) of a weight gradient whose reduction is split
   const int ksplit = (EPI == EPI_WGRAD && pin.ksplit > 1) ? pin.ksplit : 1;
@@ -195,15 +194,29 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmP pin) {
     }
     __syncthreads();
   }
-  if (KM) join();
-  if (KM && row_sums) {                           // (uniform; the last k-step ended with a barrier)
-    As[tid] = rs[0];
+  if constexpr (KM) {                             // (the last k-step ended with a barrier)
+    join();
+    if (row_sums) {                               // uniform
+      As[tid] = rs[0];
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        const int r = ty + 16 * i;
+        rs[i] = (As[r] + As[TS + r]) + (As[2 * TS + r] + As[3 * TS + r]);
+      }
+      __syncthreads();
+    }
+    // outputs from R x R neighbours to rows ty + 16 i and columns tx + 16 j, whose accesses are runs of 64 bytes (a step of
+    // AdamW touches seven words per output)
+    static_assert(2 * STAGE >= TS * (TS + 4), "the tile passes through LDS");
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+      *reinterpret_cast<float4 *>(lds + (ty * R + i) * (TS + 4) + tx * R) = make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < R; ++i) {
-      const int r = own(ty, i);
-      rs[i] = (As[r] + As[TS + r]) + (As[2 * TS + r] + As[3 * TS + r]);
-    }
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+      for (int j = 0; j < R; ++j) acc[i][j] = lds[(ty + 16 * i) * (TS + 4) + tx + 16 * j];
   }
   // the optimizer step where the gradient is finished: parameter, state and squared entry of the gradient at offset o of group g
   constexpr bool STEP = EPI == EPI_WGRAD && ACT != NO_STEP;
@@ -222,7 +235,7 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmP pin) {
   if (row_sums && tx == 0) {
 #pragma unroll
     for (int i = 0; i < R; ++i) {
-      const int m = m0 + own(ty, i);
+      const int m = m0 + ty + 16 * i;
       float *o = p.rowsum + (long long)g * p.sRowsumg + m;
       if (m < p.Md) {
         const float gr = p.accumulate ? fmaf(rs[i], p.alpha, *o) : rs[i] * p.alpha;
@@ -262,11 +275,11 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmP pin) {
   }
 #pragma unroll
   for (int i = 0; i < R; ++i) {
-    const int m = m0 + own(ty, i);
+    const int m = m0 + ty + 16 * i;
     if (m >= p.Md) continue;
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-      const int n = n0 + own(tx, j);
+      const int n = n0 + tx + 16 * j;
       const bool nin = n < p.Nd;
       const float v = acc[i][j];
       const float bv = (bias && nin) ? bias[n] : 0.0f;
