@@ -993,7 +993,7 @@ hipError_t launch_rowdot_f32(const float *D, long long sDg, int ldd, const float
   return hipGetLastError();
 }
 
-static constexpr int STATS_ONE_B = 512;
+static constexpr int STATS_ONE_B = 256;
 static constexpr long long STATS_ONE_SQ = 8192;
 
 hipError_t launch_stats(const StatsP &p, hipStream_t s) {
@@ -1012,7 +1012,12 @@ hipError_t launch_stats(const StatsP &p, hipStream_t s) {
                        p.partials);
     n2 = STATS_PBLK;
   }
-  // One block per group while a thread has at most two samples and eight partial sums to walk.
+  // One block per group while its four thread groups take every sample in one pass and a thread has at most eight partial
+  // sums of the gradient to walk.  A second pass doubles the chain of dependent loads, which costs more than the launch it
+  // saves.  us for one block | two launches (norms, then norms and inner products):
+  //   784-512-512-10, M = 1          b = 256: 10.9 | 11.5, 11.2 | 11.8    b = 257: 13.2 | 11.8, 14.5 | 12.5
+  //   3072-2048-2048-2048-100, M = 4 b = 256: 11.7 | 11.9, 12.3 | 12.6    b = 257: 14.9 | 11.8, 19.3 | 14.0
+  //   256-10, M = 4                  b = 256:  9.7 | 10.8, 10.9 | 11.8    b = 384: 11.2 | 10.7, 12.7 | 11.7
   if ((!samples || p.b <= STATS_ONE_B) && (!parts || p.n_sq_wave <= STATS_ONE_SQ)) {
     hipLaunchKernelGGL(stats_one_kernel, dim3(p.groups), dim3(1024), 0, s, p, n2, sel, acc);
     return hipGetLastError();
