@@ -39,6 +39,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
@@ -48,7 +49,7 @@ namespace {
 // keep them from displacing the operand tiles that other work-groups of the launch re-read from L2.
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef f32x4 f32x4_t;
 __device__ __forceinline__ uint4 ld_once(const bf16_t *p) {
   const u32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(p));
   return make_uint4(v.x, v.y, v.z, v.w);
@@ -75,14 +76,19 @@ constexpr int IPDOT_NORMS = 1;
 
 constexpr uint32_t OOB = 0x80000000u;   // byte offset beyond any operand (operands are < 2 GiB)
 
+// XOR on the 16-byte chunk index of k-row k in a row-contiguous tile.  A 32-lane half of a transpose read meets four values of
+// k x 4 chunks (KR = 16: 32 rows) or eight values of k, 0 .. 3 and 8 .. 11 of the step, x 2 chunks (KR = 32: 16 rows); either
+// way the 16 chunks spread over all 64 banks.  The same for k and k + 4, the fragment's second read, and for every k-step.
+template <int KR> __device__ __forceinline__ int tr_swizzle(int k) { return KR == 16 ? 4 * (k & 3) : 2 * (k & 3) + (k & 8); }
+
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
   // s_waitcnt immediate on gfx9: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[5:4] at [15:14]
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
 // ---- one operand's stage: addressing of the direct loads and of the fragment reads ---------
-// ROWS = tile extent along m (or n); TRANS = memory is [k][row].
-template <int ROWS, int BK, bool TRANS, int NW>
+// ROWS = tile extent along m (or n); TRANS = memory is [k][row]; KR: k per MFMA (which k-rows a transpose read meets).
+template <int ROWS, int BK, bool TRANS, int NW, int KR = 16>
 struct Operand {
   static constexpr int ELEMS = ROWS * BK;                 // bf16 elements per stage
   static constexpr int NI = ELEMS / 8 / 64 / NW;          // load instructions per wave per stage
@@ -108,7 +114,7 @@ struct Operand {
         kofs[i] = kc * 8;
         voff[i] = (mrow < rows) ? (uint32_t)(mrow * ld + kc * 8) * 2u : OOB;
       } else {
-        const int kq = c / CH, ch = (c % CH) ^ ((4 * (kq & 3)) & (CH - 1));
+        const int kq = c / CH, ch = (c % CH) ^ (tr_swizzle<KR>(kq) & (CH - 1));
         kofs[i] = kq;
         voff[i] = (row0 + ch * 8 < rows) ? (uint32_t)(kq * ld + row0 + ch * 8) * 2u : OOB;
       }
@@ -155,10 +161,7 @@ struct Frag {
       const int i16 = lane & 15, g16 = lane >> 4;
       const int rr = r0 + (g16 & 1) * 16 + 4 * (i16 & 3);     // first of this lane's 4 rows
       const int kq = (g16 >> 1) * 8 + (i16 >> 2);             // k within the 16-wide step
-      // the chunk swizzle 4*(k&3) does not depend on kk (16 | step) nor on the +4 of the 2nd read.
-      // A 32-lane half of the read covers 4 values of k x 4 chunks (16 bytes each, two lanes per
-      // chunk): XOR-ing k&3 into chunk bits 2..3 spreads these 16 chunks over all 64 banks.
-      const int ch = (rr >> 3) ^ ((4 * (kq & 3)) & (CH - 1));
+      const int ch = (rr >> 3) ^ (tr_swizzle<16>(kq) & (CH - 1));
       tbase[0] = kq * ROWS + ch * 8 + (rr & 7);
       tbase[1] = tbase[0] + 4 * ROWS;
     }
@@ -293,13 +296,23 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
   const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<bf16_t *>(B), 0, (int)((long long)(BT ? p.Kd : p.Nd) * p.ldb * 2), 0x00020000);
 
-  f32x16 acc[MI][NI];
+  // accumulators: 32 x 32 tiles (32x32x16 MFMAs), or 16 x 16 ones in the pipelined loop (16x16x32)
+  constexpr int RT = PP ? 16 : 32;
+  f32x16 acc[PP ? 1 : MI][PP ? 1 : NI];
+  f32x4 acc16[PP ? TM / 16 : 1][PP ? TN / 16 : 1];
+  if constexpr (PP) {
 #pragma unroll
-  for (int i = 0; i < MI; ++i)
+    for (int i = 0; i < TM / 16; ++i)
 #pragma unroll
-    for (int j = 0; j < NI; ++j)
+      for (int j = 0; j < TN / 16; ++j) acc16[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  } else {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+  }
 
   // first row of row slice i (32 rows) of this wave, relative to the tile
   auto slice_row = [&](int i) -> int { return PP ? (i >> 1) * 128 + wm * 64 + (i & 1) * 32 : wm * TM + i * 32; };
@@ -349,8 +362,8 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
   const int KT = (p.Kd + BK - 1) / BK;
   if constexpr (PP) {
     // ---- pipelined main loop of the 256 x 256 tile (see the note above the kernel) -----------------------------
-    typedef Operand<128, 64, AT, NW> UA;                     // A unit h: rows 128 h .. 128 h + 127 of the tile, 64 k
-    typedef Operand<BT ? 256 : 128, BT ? 32 : 64, BT, NW> UB;   // B unit c: k 32 c .. (BT), or columns 64 j + 32 c ..
+    typedef Operand<128, 64, AT, NW, 32> UA;                 // A unit h: rows 128 h .. 128 h + 127 of the tile, 64 k
+    typedef Operand<BT ? 256 : 128, BT ? 32 : 64, BT, NW, 32> UB;   // B unit c: k 32 c .. (BT), or columns 64 j + 32 c ..
     constexpr int UNIT = 8192;                               // elements of a unit (16 KB)
     UA ua[2];
     UB ub[2];
@@ -366,54 +379,55 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
     auto load_b = [&](int kt, int slot, int c) {
       ub[c].load_all(rb, smem + (4 + slot * 2 + c) * UNIT, wave, kt * 64 + (BT ? c * 32 : 0), 0, p.Kd, p.ldb);
     };
-    // LDS byte addresses of this lane's fragments in unit 0; everything else is an immediate offset
+    // LDS byte addresses of this lane's fragments (16 rows x 32 k: lane l holds row l % 16, eight k from 8 (l / 16)) in unit 0;
+    // everything else is an immediate offset
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void *)smem;
-    const int half = lane >> 5, l32 = lane & 31, i16 = lane & 15, g16 = lane >> 4;
-    const int kq = (g16 >> 1) * 8 + (i16 >> 2);              // transpose reads: k within the 16-wide step
-    uint32_t aaddr[AT ? 2 : 4], baddr[BT ? 2 : 4];
+    const int i16 = lane & 15, g16 = lane >> 4;
+    const int kq = g16 * 8 + (i16 >> 2);                     // transpose reads: k within the 32-wide step
+    uint32_t aaddr[AT ? 4 : 2], baddr[BT ? 4 : 2];           // (transpose reads: by row tile; else by k-step)
     if constexpr (AT) {
 #pragma unroll
-      for (int ii = 0; ii < 2; ++ii) {
-        const int rr = wm * 64 + ii * 32 + (g16 & 1) * 16 + 4 * (i16 & 3);
-        aaddr[ii] = lds0 + 2u * (uint32_t)(kq * 128 + ((rr >> 3) ^ (4 * (kq & 3))) * 8 + (rr & 7));
+      for (int ii = 0; ii < 4; ++ii) {
+        const int rr = wm * 64 + ii * 16 + 4 * (i16 & 3);
+        aaddr[ii] = lds0 + 2u * (uint32_t)(kq * 128 + ((rr >> 3) ^ tr_swizzle<32>(kq)) * 8 + (rr & 7));
       }
     } else {
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk)
-        aaddr[kk] = lds0 + (uint32_t)((wm * 64 + l32) * 128 + (((kk * 2 + half) ^ ((l32 >> 1) & 7)) << 4));
+      for (int kk = 0; kk < 2; ++kk)
+        aaddr[kk] = lds0 + (uint32_t)((wm * 64 + i16) * 128 + (((kk * 4 + g16) ^ (i16 >> 1)) << 4));
     }
     if constexpr (BT) {
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int rr = wn * 64 + j * 32 + (g16 & 1) * 16 + 4 * (i16 & 3);
-        baddr[j] = lds0 + 65536u + 2u * (uint32_t)(kq * 256 + ((rr >> 3) ^ (4 * (kq & 3))) * 8 + (rr & 7));
+      for (int j = 0; j < 4; ++j) {
+        const int rr = wn * 64 + j * 16 + 4 * (i16 & 3);
+        baddr[j] = lds0 + 65536u + 2u * (uint32_t)(kq * 256 + ((rr >> 3) ^ tr_swizzle<32>(kq)) * 8 + (rr & 7));
       }
     } else {
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk)
-        baddr[kk] = lds0 + 65536u + (uint32_t)((wn * 32 + l32) * 128 + (((kk * 2 + half) ^ ((l32 >> 1) & 7)) << 4));
+      for (int kk = 0; kk < 2; ++kk)
+        baddr[kk] = lds0 + 65536u + (uint32_t)((wn * 32 + i16) * 128 + (((kk * 4 + g16) ^ (i16 >> 1)) << 4));
     }
-    bf16x8 fa[2][4], fb[2][4];                               // fa[row tile][k-step]; fb[unit][k-step (BT: 2 col tile + k-step)]
+    bf16x8 fa[4][2], fb[2][4];                               // fa[row tile][k-step]; fb[unit][BT: column tile, else 2 column tile + k-step]
     auto read_a = [&](auto SLOT, auto H) {
       constexpr int U = (decltype(SLOT)::value * 2 + decltype(H)::value) * UNIT * 2;
       static_for<8>([&](auto I) {
-        constexpr int kk = decltype(I)::value >> 1, ii = decltype(I)::value & 1;
-        if constexpr (AT) fa[ii][kk] = lds_read_cols<U + kk * 4096, 1024>(aaddr[ii]);
-        else fa[ii][kk] = lds_read_rows<U + ii * 4096>(aaddr[kk]);
+        constexpr int kk = decltype(I)::value >> 2, ii = decltype(I)::value & 3;
+        if constexpr (AT) fa[ii][kk] = lds_read_cols<U + kk * 8192, 1024>(aaddr[ii]);
+        else fa[ii][kk] = lds_read_rows<U + ii * 2048>(aaddr[kk]);
       });
     };
     auto read_b = [&](auto SLOT, auto C) {
       constexpr int c = decltype(C)::value, U = (decltype(SLOT)::value * 2 + c) * UNIT * 2;
       static_for<4>([&](auto I) {
         constexpr int q = decltype(I)::value;
-        if constexpr (BT) fb[c][q] = lds_read_cols<U + (q & 1) * 8192, 2048>(baddr[q >> 1]);
-        else fb[c][q] = lds_read_rows<U>(baddr[q]);
+        if constexpr (BT) fb[c][q] = lds_read_cols<U, 2048>(baddr[q]);
+        else fb[c][q] = lds_read_rows<U + (q >> 1) * 2048>(baddr[q & 1]);
       });
     };
     auto close_reads = [&]() {                               // this wave's fragment reads are done
       __builtin_amdgcn_s_waitcnt(0xC07F);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) asm volatile("" : "+v"(fa[0][q]), "+v"(fa[1][q]), "+v"(fb[0][q]), "+v"(fb[1][q]));
+      for (int q = 0; q < 4; ++q) asm volatile("" : "+v"(fa[q][0]), "+v"(fa[q][1]), "+v"(fb[0][q]), "+v"(fb[1][q]));
     };
     auto phase = [&](auto SLOT, auto F, int kt) {
       constexpr int f = decltype(F)::value, h = f >> 1, c = f & 1;
@@ -427,14 +441,14 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
       __builtin_amdgcn_s_setprio(1);
-      static_for<8>([&](auto I) {
+      static_for<16>([&](auto I) {                           // (operands swapped as below: a lane owns one row of C)
         constexpr int q = decltype(I)::value;
         if constexpr (BT) {
-          constexpr int kk = q >> 2, ii = (q >> 1) & 1, j = q & 1;
-          acc[2 * h + ii][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[c][2 * j + kk], fa[ii][2 * c + kk], acc[2 * h + ii][j], 0, 0, 0);
+          constexpr int ii = q >> 2, j = q & 3;
+          acc16[4 * h + ii][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[c][j], fa[ii][c], acc16[4 * h + ii][j], 0, 0, 0);
         } else {
-          constexpr int kk = q >> 1, ii = q & 1;
-          acc[2 * h + ii][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[c][kk], fa[ii][kk], acc[2 * h + ii][c], 0, 0, 0);
+          constexpr int kk = q >> 3, ii = (q >> 1) & 3, j = q & 1;
+          acc16[4 * h + ii][2 * c + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[c][2 * j + kk], fa[ii][kk], acc16[4 * h + ii][2 * c + j], 0, 0, 0);
         }
       });
       __builtin_amdgcn_s_setprio(0);
@@ -548,13 +562,24 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
     }
   }
 
-  // ---- epilogue.  With the operands swapped in the MFMA, accumulator element r = 4q + e of tile
-  // (i, j) belongs to   row  m = wm*TM + 32 i + lane % 32,
-  //                     col  n = wn*TN + 32 j + 8 q + 4 (lane / 32) + e      (tile-relative),
-  // i.e. a lane holds four consecutive columns per q.  bf16 outputs and the elementwise operand E
+  // ---- epilogue.  With the operands swapped in the MFMA, a lane holds groups of four consecutive columns of one row.  Of slice
+  // i (32 rows x TN columns) it holds, e = 0 .. 3 (tile-relative):
+  //   32 x 32 tiles: row lane % 32,        group c: col 32 (c / 4) + 8 (c % 4) + 4 (lane / 32) + e = acc[i][c / 4][4 (c % 4) + e]
+  //   16 x 16 tiles: row 16 h + lane % 16, group c: col 16 c + 4 (lane / 16) + e                   = acc16[2 i + h][c][e]
+  // bf16 outputs and the elementwise operand E
   // go through a per-wave LDS staging slice of 32 rows x TN columns, so that every global access
   // of the epilogue is a 16-byte vector, 8 lanes to a 128-byte row segment.
-  const int lcol = lane & 31, lhalf = lane >> 5;
+  constexpr int NH = 32 / RT, NC = TN / (4 * (64 / RT));    // rows and column groups of a lane per slice
+  const int lrow = lane & (RT - 1), lq = lane / RT;
+  auto gcol = [&](int c) -> int { return RT == 32 ? (c >> 2) * 32 + (c & 3) * 8 + lq * 4 : c * 16 + lq * 4; };
+  auto val = [&](int i, int h, int c, int e) -> float {
+    if constexpr (PP) return acc16[2 * i + h][c][e];
+    else return acc[i][c >> 2][4 * (c & 3) + e];
+  };
+  auto row_total = [&](float v) -> float {                  // over the lanes that share a row
+    if (RT == 16) v += __shfl_xor(v, 16, 64);
+    return v + __shfl_xor(v, 32, 64);
+  };
   const float *bias = p.bias ? p.bias + (long long)g * p.sBiasg : nullptr;
   constexpr int SLD = TN + 8;                               // staging row stride (elements)
   bf16_t *stg = smem + wave * (32 * SLD);
@@ -564,21 +589,19 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
   const int nw0 = n0 + wn * TN;                             // first column of this wave
   const bool nfull = n0 + BN <= p.Nd;                       // no ragged columns in this tile (uniform)
   // this lane's 4-column groups of the bias vector, loaded once for all row slices
-  float bv[NI][4][4];
+  float bv[NC][4];
   if (EPI == EPI_FWD_ACT || EPI == EPI_IPDOT || EPI == EPI_LOGITS) {
 #pragma unroll
-    for (int j = 0; j < NI; ++j)
+    for (int c = 0; c < NC; ++c) {
+      const int n = nw0 + gcol(c);
+      if (bias && nfull) {
+        const float4 b4 = *reinterpret_cast<const float4 *>(bias + n);
+        bv[c][0] = b4.x; bv[c][1] = b4.y; bv[c][2] = b4.z; bv[c][3] = b4.w;
+      } else {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int n = nw0 + j * 32 + q * 8 + lhalf * 4;
-        if (bias && nfull) {
-          const float4 b4 = *reinterpret_cast<const float4 *>(bias + n);
-          bv[j][q][0] = b4.x; bv[j][q][1] = b4.y; bv[j][q][2] = b4.z; bv[j][q][3] = b4.w;
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) bv[j][q][e] = (bias && n + e < p.Nd) ? bias[n + e] : 0.0f;
-        }
+        for (int e = 0; e < 4; ++e) bv[c][e] = (bias && n + e < p.Nd) ? bias[n + e] : 0.0f;
       }
+    }
   }
 
   // rows [mrow0, mrow0+32) x this wave's TN columns of a bf16 matrix: global -> registers (so the
@@ -613,7 +636,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
         st_once(dst + (long long)(mrow0 + row) * ld + nw0 + cc * 8, v);
     }
   };
-  auto piece = [&](int j, int q) -> bf16_t * { return stg + lcol * SLD + j * 32 + q * 8 + lhalf * 4; };
+  auto piece = [&](int h, int c) -> bf16_t * { return stg + (h * RT + lrow) * SLD + gcol(c); };
 
   if (EPI == EPI_FWD_ACT || EPI == EPI_BWD || EPI == EPI_IPDOT) __syncthreads();   // stages are dead
   static_assert(32 * (TN / 4) % 64 == 0, "fp32 staging slice");
@@ -646,25 +669,24 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
       const int mrow0 = m0 + slice_row(i);
       if (i + 1 < MI) load_slice(Eg, p.lde, m0 + slice_row(i + 1), p.Nd, ereg[(i + 1) & 1]);
       put_slice(ereg[i & 1]);
-      float rs = 0.0f, es = 0.0f;
 #pragma unroll
-      for (int j = 0; j < NI; ++j)
+      for (int h = 0; h < NH; ++h) {
+        float rs = 0.0f, es = 0.0f;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const uint2 ev = *reinterpret_cast<const uint2 *>(piece(j, q));
+        for (int c = 0; c < NC; ++c) {
+          const uint2 ev = *reinterpret_cast<const uint2 *>(piece(h, c));
           if (ACT == IPDOT_NORMS) es += sq4(ev);
           const float e4[4] = {__uint_as_float(ev.x << 16), __uint_as_float(ev.x & 0xffff0000u),
                                __uint_as_float(ev.y << 16), __uint_as_float(ev.y & 0xffff0000u)};
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            rs = fmaf(e4[e], acc[i][j][4 * q + e] + bv[j][q][e], rs);   // E is zero outside the matrix
-          }
+          for (int e = 0; e < 4; ++e) rs = fmaf(e4[e], val(i, h, c, e) + bv[c][e], rs);   // E is zero outside the matrix
         }
-      rs += __shfl_xor(rs, 32, 64);                               // the two column halves of the row
-      if (lhalf == 0) red[wn * BM + slice_row(i) + lcol] = rs;
-      if (ACT == IPDOT_NORMS) {
-        es += __shfl_xor(es, 32, 64);
-        if (lhalf == 0) red[(WN + wn) * BM + slice_row(i) + lcol] = es;
+        rs = row_total(rs);
+        if (lq == 0) red[wn * BM + slice_row(i) + h * RT + lrow] = rs;
+        if (ACT == IPDOT_NORMS) {
+          es = row_total(es);
+          if (lq == 0) red[(WN + wn) * BM + slice_row(i) + h * RT + lrow] = es;
+        }
       }
     }
     finish_rows();
@@ -679,35 +701,36 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
       const int mrow0 = m0 + slice_row(i);
-      uint2 dpk[NI][4];
-      float rs = 0.0f;
+      uint2 dpk[NH][NC];
 #pragma unroll
-      for (int j = 0; j < NI; ++j)
+      for (int h = 0; h < NH; ++h) {
+        float rs = 0.0f;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
+        for (int c = 0; c < NC; ++c) {
           float a4[4], d4[4];
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             // columns beyond Nd: accumulator and bias are both zero there (operand rows past the
             // matrix read as zeros), so phi(0) = 0 is what the pad columns of C receive
-            act_fwd<ACT>(acc[i][j][4 * q + e] + bv[j][q][e], a4[e], d4[e]);
+            act_fwd<ACT>(val(i, h, c, e) + bv[c][e], a4[e], d4[e]);
           }
           uint2 apk;
           apk.x = pack2bf(a4[0], a4[1]); apk.y = pack2bf(a4[2], a4[3]);
-          dpk[j][q].x = pack2bf(d4[0], d4[1]); dpk[j][q].y = pack2bf(d4[2], d4[3]);
-          *reinterpret_cast<uint2 *>(piece(j, q)) = apk;
+          dpk[h][c].x = pack2bf(d4[0], d4[1]); dpk[h][c].y = pack2bf(d4[2], d4[3]);
+          *reinterpret_cast<uint2 *>(piece(h, c)) = apk;
           rs += sq4(apk);
         }
-      if (p.part) {
-        rs += __shfl_xor(rs, 32, 64);
-        if (lhalf == 0) red[wn * BM + slice_row(i) + lcol] = rs;
+        if (p.part) {
+          rs = row_total(rs);
+          if (lq == 0) red[wn * BM + slice_row(i) + h * RT + lrow] = rs;
+        }
       }
       stage_out(C, p.ldc, mrow0, ncols);
       if (ACT == ACT_GELU && C2) {
 #pragma unroll
-        for (int j = 0; j < NI; ++j)
+        for (int h = 0; h < NH; ++h)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) *reinterpret_cast<uint2 *>(piece(j, q)) = dpk[j][q];
+          for (int c = 0; c < NC; ++c) *reinterpret_cast<uint2 *>(piece(h, c)) = dpk[h][c];
         stage_out(C2, p.ldc2, mrow0, ncols);
       }
     }
@@ -729,32 +752,33 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
         if (i + 1 < MI) load_slice(Eg, p.lde, m0 + slice_row(i + 1), p.Nd, ereg[(i + 1) & 1]);
         put_slice(ereg[i & 1]);
       }
-      float rs = 0.0f;
 #pragma unroll
-      for (int j = 0; j < NI; ++j)
+      for (int h = 0; h < NH; ++h) {
+        float rs = 0.0f;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
+        for (int c = 0; c < NC; ++c) {
           float e4[4] = {1.0f, 1.0f, 1.0f, 1.0f};
           if (ACT != ACT_NONE) {
-            const uint2 ev = *reinterpret_cast<const uint2 *>(piece(j, q));
+            const uint2 ev = *reinterpret_cast<const uint2 *>(piece(h, c));
             e4[0] = __uint_as_float(ev.x << 16); e4[1] = __uint_as_float(ev.x & 0xffff0000u);
             e4[2] = __uint_as_float(ev.y << 16); e4[3] = __uint_as_float(ev.y & 0xffff0000u);
           }
           float o4[4];
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const float v = acc[i][j][4 * q + e];
+            const float v = val(i, h, c, e);
             o4[e] = (ACT == ACT_RELU) ? (e4[e] > 0.0f ? v : 0.0f) : (ACT == ACT_GELU ? v * e4[e] : v);
-            if (!nfull && nw0 + j * 32 + q * 8 + lhalf * 4 + e >= p.Nd) o4[e] = 0.0f;
+            if (!nfull && nw0 + gcol(c) + e >= p.Nd) o4[e] = 0.0f;
           }
           uint2 opk;
           opk.x = pack2bf(o4[0], o4[1]); opk.y = pack2bf(o4[2], o4[3]);
-          *reinterpret_cast<uint2 *>(piece(j, q)) = opk;      // each lane overwrites the piece it read
+          *reinterpret_cast<uint2 *>(piece(h, c)) = opk;      // each lane overwrites the piece it read
           rs += sq4(opk);
         }
-      if (p.part) {
-        rs += __shfl_xor(rs, 32, 64);
-        if (lhalf == 0) red[wn * BM + slice_row(i) + lcol] = rs;
+        if (p.part) {
+          rs = row_total(rs);
+          if (lq == 0) red[wn * BM + slice_row(i) + h * RT + lrow] = rs;
+        }
       }
       stage_out(C, p.ldc, mrow0, ncols);
       if (p.cpart) {
@@ -822,13 +846,11 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
       if (bi % BPS == 0) {                                   // a new slice: accumulators -> staging
         const int i = bi / BPS;
 #pragma unroll
-        for (int j = 0; j < NI; ++j)
+        for (int h = 0; h < NH; ++h)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const float4 o = make_float4(acc[i][j][4 * q] * p.alpha, acc[i][j][4 * q + 1] * p.alpha,
-                                         acc[i][j][4 * q + 2] * p.alpha, acc[i][j][4 * q + 3] * p.alpha);
-            *reinterpret_cast<float4 *>(stf + lcol * FLD + j * 32 + q * 8 + lhalf * 4) = o;
-          }
+          for (int c = 0; c < NC; ++c)
+            *reinterpret_cast<float4 *>(stf + (h * RT + lrow) * FLD + gcol(c)) =
+                make_float4(val(i, h, c, 0) * p.alpha, val(i, h, c, 1) * p.alpha, val(i, h, c, 2) * p.alpha, val(i, h, c, 3) * p.alpha);
       }
       if (bi + 1 < NBATCH) prefetch(bi + 1);
 #pragma unroll
@@ -868,18 +890,16 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
   for (int i = 0; i < MI; ++i) {
     const int mrow0 = m0 + slice_row(i);
 #pragma unroll
-    for (int j = 0; j < NI; ++j)
+    for (int h = 0; h < NH; ++h)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+      for (int c = 0; c < NC; ++c) {
         float4 o;
         if (IS_WGRAD) {
-          o = make_float4(acc[i][j][4 * q] * p.alpha, acc[i][j][4 * q + 1] * p.alpha, acc[i][j][4 * q + 2] * p.alpha,
-                          acc[i][j][4 * q + 3] * p.alpha);
+          o = make_float4(val(i, h, c, 0) * p.alpha, val(i, h, c, 1) * p.alpha, val(i, h, c, 2) * p.alpha, val(i, h, c, 3) * p.alpha);
         } else {
-          o = make_float4(acc[i][j][4 * q] + bv[j][q][0], acc[i][j][4 * q + 1] + bv[j][q][1],
-                          acc[i][j][4 * q + 2] + bv[j][q][2], acc[i][j][4 * q + 3] + bv[j][q][3]);
+          o = make_float4(val(i, h, c, 0) + bv[c][0], val(i, h, c, 1) + bv[c][1], val(i, h, c, 2) + bv[c][2], val(i, h, c, 3) + bv[c][3]);
         }
-        *reinterpret_cast<float4 *>(stf + lcol * FLD + j * 32 + q * 8 + lhalf * 4) = o;
+        *reinterpret_cast<float4 *>(stf + (h * RT + lrow) * FLD + gcol(c)) = o;
       }
 #pragma unroll
     for (int it = 0; it < FIT; ++it) {
