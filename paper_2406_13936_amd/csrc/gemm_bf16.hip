@@ -220,6 +220,11 @@ __device__ __forceinline__ void wait_frags(bf16x8 (&a)[MI], bf16x8 (&b)[NI]) {
   for (int j = 0; j < NI; ++j) asm volatile("" : "+v"(b[j]));
 }
 
+// 32 tiles of 256 x 256 run side by side on an XCD; they fetch one operand panel per row and one per column of their arrangement
+// into its L2.  Rows of more than BAND tiles are cut into bands of at most BAND columns, so that the 32 tiles stand 4 x 8 or
+// nearly so (12 panels) and not 2 x 16 (18).
+constexpr int BAND = 8;
+
 // ---- the kernel --------------------------------------------------------------------------
 //
 // Main loop of the 256 x 256 tile.  64 KB of operands per k-tile of 64 and 256 x 256 outputs is what a CU has to take in
@@ -266,7 +271,14 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
   const int ksplit = (EPI == EPI_WGRAD && pin.ksplit > 1) ? pin.ksplit : 1;   // (no split with the step fused)
   const int gv = vg / ksplit, ksl = vg - gv * ksplit;
   const int g = pin.gperm ? pin.gperm[gv] : gv;   // position in the launch order -> group
-  const int tm = t / tilesN, tn = t - tm * tilesN;
+  int tm, tn;
+  if (BM == 256 && tilesN > BAND) {               // bands of columns (see BAND), row by row inside a band
+    const int nb = (tilesN + BAND - 1) / BAND, bw = (tilesN + nb - 1) / nb, b = t / (bw * tilesM);
+    const int w = min(bw, tilesN - b * bw), r = t - b * bw * tilesM;
+    tm = r / w; tn = b * bw + r - tm * w;
+  } else {
+    tm = t / tilesN; tn = t - tm * tilesN;
+  }
   const int m0 = tm * BM, n0 = tn * BN;
   GemmP p = pin;
   if (p.rows) {                                   // ragged groups: this group's own extent
@@ -883,7 +895,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
       }
     }
     sq = wave_sum(sq);
-    if (lane == 0) p.upd_sq[(long long)g * p.upd_sSqg + p.upd_slot0 + (long long)t * NW + wave] = sq;
+    if (lane == 0) p.upd_sq[(long long)g * p.upd_sSqg + p.upd_slot0 + (long long)(tm * tilesN + tn) * NW + wave] = sq;
     return;
   }
 #pragma unroll
@@ -934,7 +946,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
   }
   if (EPI == EPI_WGRAD && p.sq64) {                         // uniform
     sq64 = wave_sum(sq64);
-    if (lane == 0) p.sq64[(long long)g * p.sSq64g + (long long)t * NW + wave] = sq64;
+    if (lane == 0) p.sq64[(long long)g * p.sSq64g + (long long)(tm * tilesN + tn) * NW + wave] = sq64;
   }
 }
 
