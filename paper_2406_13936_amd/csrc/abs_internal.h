@@ -114,7 +114,7 @@ bool gemm_head_fits(int is_bf16, int Md, int Nd, int groups);
 // Tile shape of an EPI_WGRAD launch whose reduction runs over Kd samples: as above, or 3 = 64x256 with a k-step of
 // 32 and several work-groups per CU while the batch is short and the launch is bound by its epilogue's memory traffic;
 // fused != 0: the launch carries the optimizer step in its epilogue (GemmP::upd_x), which keeps medium batches on
-// 128x128 tiles.
+// 128x128 tiles, or 5 = 128x256 tiles of eight wavefronts.
 int gemm_bf16_wgrad_shape(int Md, int Nd, int Kd, int groups, int fused);
 // Number of upd_sq slots (fused: with the optimizer step in the epilogue) or sq64 slots an EPI_WGRAD launch writes per group.
 int gemm_bf16_upd_slots(int Md, int Nd, int Kd, int groups, int fused, int fine);

@@ -1029,6 +1029,9 @@ hipError_t launch_shape(const GemmP &p, hipStream_t s) {
     case 4:
       if constexpr (!IS_WGRAD) return launch_cfg<64, 128, 64, 2, 2, 6, false, AT, BT, EPI, ACT>(p, s);
       else return hipErrorInvalidValue;
+    case 5:
+      if constexpr (EPI == EPI_WGRAD_UPD) return launch_cfg<128, 256, 32, 2, 4, 3, false, AT, BT, EPI, ACT>(p, s);
+      else return hipErrorInvalidValue;
     default: {
       // Two stages (64 KB) let two work-groups share a CU; a deeper ring keeps one work-group fed through a long
       // reduction.  Two when the reduction is short or the launch has more blocks than CUs (measured: 2048-wide
@@ -1176,11 +1179,15 @@ int gemm_bf16_wgrad_shape(int Md, int Nd, int Kd, int groups, int fused) {
   // work-groups per CU stream it better than one 256 x 256 work-group (config 3: b = 384 1.92 -> 1.87 ms per step,
   // b = 512 2.02 -> 2.00; from b = 768 on the large tile wins)
   if (fused && sh == 2 && Kd <= 512) return 1;
+  // up to 1536 two 128 x 256 work-groups of eight wavefronts share a CU where there are tiles for two: sixteen waves keep more of
+  // the epilogue's memory requests in flight than eight (3072-2048-2048-2048-100, 16 replicas, heavy ball, the three wide layers:
+  // b = 600 1107 -> 1020 us, b = 1001 1196 -> 1145, b = 2048 1514 -> 1536; four wavefronts of 64 x 128 1290 / 1530 / 2170)
+  if (fused && sh == 2 && Kd <= 1536 && (long long)((Md + 255) / 256) * ((Nd + 255) / 256) * groups >= 256) return 5;
   return sh;
 }
 
 int gemm_bf16_upd_slots(int Md, int Nd, int Kd, int groups, int fused, int fine) {
-  const int bm[4] = {128, fine ? 64 : 128, 256, 64}, bn[4] = {64, 128, 256, 256}, nw[4] = {4, 4, 8, 4};
+  const int bm[6] = {128, fine ? 64 : 128, 256, 64, 0, 128}, bn[6] = {64, 128, 256, 256, 1, 256}, nw[6] = {4, 4, 8, 4, 0, 8};
   const int sh = gemm_bf16_wgrad_shape(Md, Nd, Kd, groups, fused);
   return ((Md + bm[sh] - 1) / bm[sh]) * ((Nd + bn[sh] - 1) / bn[sh]) * nw[sh];
 }

@@ -507,3 +507,35 @@ def test_fp32_weight_gradients_do_not_lose_precision_over_the_batch(dims, b, rou
         assert max(err) <= roundings * EPS32, err
     finally:
         rep.close()
+
+
+# Layers of 256 x 256 tiles: up to 512 samples, and up to 1536 where the tiles are many, the step in the epilogue takes smaller
+# tiles than the separate update, and MFMAs of another shape; both add the products of an entry in the same order, so the
+# parameters and the gradient formed on demand equal those of the separate update.
+@pytest.mark.parametrize("b,M,opt,tile", [(257, 2, W.OPT_SHB, "64x128"), (512, 2, W.OPT_SGD, "64x128"), (513, 2, W.OPT_SHB, "256x256"),
+                                          (513, 16, W.OPT_ADAMW, "128x256"), (1536, 16, W.OPT_ADAGRAD, "128x256"),
+                                          (1537, 16, W.OPT_SHB, "256x256")])
+def test_wide_layers_take_the_same_step_in_either_form_of_the_update(b, M, opt, tile):
+    A = _A()
+    w = W.Workload("wide", (1024, 1032, 1024, 10), W.ACT_RELU, True, W.PREC_BF16, N=1024, M=M, H=1, rounds=1, b0=b, b_cap=b, opt=opt,
+                   lr=0.02, momentum=0.9, weight_decay=0.05, test=W.TEST_NORM, data="teacher_mlp", seed=5)
+    X, y = W.make_dataset(w)
+    x0 = W.make_x0(w)
+    out = []
+    for fused in (True, False):
+        rep = A.Replicas.from_workload(w, X, y, x0)
+        try:
+            rep.set_fused_update(fused)
+            rep.profile_enable(True)
+            rep.local_step(W.step_indices(w, 0, 0, b), w.lr)
+            names = [n for n in rep.profile_read() if n.startswith("gemm_wgrad_")]
+            rep.profile_enable(False)
+            assert not fused or any(n.startswith("gemm_wgrad_" + tile) for n in names), names
+            res = rep.norm_test(0.5)
+            out.append((rep.get_params(M - 1), rep.get_grad(M - 1)))
+            assert abs(res[M - 1].gbar_sq - np.sum(out[-1][1].astype(np.float64) ** 2)) <= 1e-5 * res[M - 1].gbar_sq
+            assert rep.guard_intact()
+        finally:
+            rep.close()
+    assert np.array_equal(out[0][0], out[1][0])
+    assert np.array_equal(out[0][1], out[1][1])
