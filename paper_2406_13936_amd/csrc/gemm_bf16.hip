@@ -1015,7 +1015,7 @@ int tiled_shape(int Md, int Nd, int groups);
 // layers, K = 1024, b = 4096: 2184 us with the two-stage loop, 2006 with the pipelined one).
 constexpr int PIPE_MIN_K = 512;
 
-// Tile shape by problem size: the large shape when both output extents fill it,
+// Tile shape by problem size: the large shape where its rounds of work-groups take less time (tiled_shape, gemm_bf16_wgrad_shape),
 // otherwise a 128x128 (or 128x64 for narrow outputs, 64x128 for outputs of at most 64 rows) tile.
 template <bool AT, bool BT, int EPI, int ACT>
 hipError_t launch_shape(const GemmP &p, hipStream_t s) {
@@ -1070,6 +1070,13 @@ hipError_t launch_act(const GemmP &p, hipStream_t s) {
 
 constexpr long long FEW_TILES = 128;
 
+// Time of `blocks` 128 x 128 tiles per k-tile: full rounds of two work-groups to a CU and the last one
+double rounds_128(long long blocks) {
+  const long long full = blocks / 512, rem = blocks - full * 512;
+  const double last = rem > 256 ? 1.42 : rem == 0 ? 0.0 : full == 0 ? 1.13 : 1.13 + 0.29 * (double)rem / 256;
+  return 1.42 * (double)full + last;
+}
+
 int tiled_shape(int Md, int Nd, int groups) {
   if (Nd <= 64) return 0;
   // up to 64 rows (the first local batch sizes): the launch streams its B operand (the weights) once and is bound by
@@ -1077,36 +1084,34 @@ int tiled_shape(int Md, int Nd, int groups) {
   // (config 3 at b = 64 against the 128 x 128 tile with four stages: forward 4.1 -> 4.3 TB/s of weight bytes,
   // backward-data 4.5 -> 5.0-5.1, the step 1.17 -> 1.155 ms)
   if (Md <= 64) return 4;
-  if (Md >= 1024 && Nd >= 1024) return 2;
-  // mid-sized outputs: the large tile only if it still gives every CU a work-group and its last row of tiles is
-  // not mostly padding (measured on 2048-wide layers, 16 groups: b = 384 and 512 faster with 256 x 256 tiles,
-  // b = 256 with two 128 x 128 work-groups per CU)
-  if (Md >= 256 && Nd >= 512) {
-    const long long tm = (Md + 255) / 256;
-    const long long tiles = tm * ((Nd + 255) / 256) * groups;
-    if (tiles >= 256 && 10LL * Md >= 7LL * tm * 256) return 2;
-  }
+  // 256 x 256 tiles or 128 x 128: whichever takes less time by rounds of work-groups.  Per k-tile of 64 a round of large tiles, one
+  // to a CU, takes as long as 1.5 us against 1.13 for 128 x 128 tiles alone on their CUs and 1.42 for two to a CU (fitted to steps;
+  // padding counts, since it is computed).  us per step, 128 x 128 -> 256 x 256 where the line now lies beyond them, or the other
+  // way round: 16 replicas, 3072-2048-2048-100 b = 257 1252 -> 1058, b = 900 (256 x 256 either way) 1657; 3072-1024-1024-100
+  // b = 700 827 -> 683, b = 512 (128 x 128) 600, 615 with large tiles; 4 replicas, b = 1024 368 with large tiles -> 282 (with the
+  // weight gradients); 784-512-512-10, 8 replicas, b = 3000 232 -> 214, b = 2048 (128 x 128) 169, 188 with large tiles;
+  // 784-200-10, 16 replicas, b = 4096 283 -> 259
+  const long long t256 = (long long)((Md + 255) / 256) * ((Nd + 255) / 256) * groups;
+  const long long t128 = (long long)((Md + 127) / 128) * ((Nd + 127) / 128) * groups;
+  if (Md > 128 && Nd > 128 && 1.5 * (double)((t256 + 255) / 256) <= rounds_128(t128)) return 2;
   // 128 x 128 tiles for half of the CUs or fewer: twice as many 64 x 128 ones with a deeper ring (784-512-512-10, 8 replicas:
   // b = 501, 128 tiles, a step 124 -> 107.5 us, forward 16.9 -> 11.7; b = 768, 192 tiles, would go from 128 to 140)
-  if ((long long)((Md + 127) / 128) * ((Nd + 127) / 128) * groups <= FEW_TILES) return 4;
-  return 1;
+  return t128 <= FEW_TILES ? 4 : 1;
 }
 
 // Launches of at most this many 32 x 32 tiles go to gemm_small.hip: a latency chain instead of a nearly empty chip.  Past two
 // work-groups per CU their re-reads of both operands cost more than the tiled family's empty places: forward and logits of 512
 // tiles; of 384 where more than 32 classes leave the head to a launch of its own; backward-data, whose work-groups hold two
-// tiles, of 1024, unless those are one row of 32768 columns, whose weights the ring streams faster; 1024 also where the
-// alternative is 16 tiles of 256 x 256.  One launch, tiled -> small, us:
+// tiles, of 1024, unless those are one row of 32768 columns, whose weights the ring streams faster.  One launch, tiled -> small, us:
 //   forward 512 x 512: 16 replicas, b = 32 (256 tiles) 12.7 -> 9.6; 8 replicas, b = 128 (512) 12.7 -> 11.5, b = 256 (1024)
 //     13.6 -> 16.3; 2048 x 2048, 16 replicas, b = 32 (1024) 34 -> 53
 //   backward 512 x 512, 8 replicas: b = 256 (1024) 13.1 -> 11.3, b = 501 (2048) 13.1 -> 17.3; 2048 x 2048, 16 replicas, b = 32
 //     27.6 -> 31.1; 1024 x 1024, 32 replicas, b = 32 17.8 -> 19.3
 //   logits and head 512 -> 10, 8 replicas, b = 32 9.8 -> 5.0; 512 -> 100, 8 replicas, b = 512 (512) 17.3 -> 18.0, b = 1024
 //     (1024) 19.1 -> 23.2
-//   3072-1024-1024-100, 1 replica, b = 1024, the step: 336 -> 298
+//   3072-1024-1024-100, 1 replica, b = 1024 (1024 tiles of the 64 x 128 ring's 128): the step 189 on the ring, 218 small
 constexpr long long SMALL_TILES = 1024;
 long long small_limit(int epi, int Md, int Nd, int groups) {
-  if (tiled_shape(Md, Nd, groups) == 2) return SMALL_TILES;
   if (epi == EPI_BWD) return (long long)Nd * groups < 32768 ? SMALL_TILES : SMALL_TILES / 2;
   return epi == EPI_LOGITS && Nd > 32 ? 384 : 512;
 }
@@ -1172,8 +1177,18 @@ bool gemm_head_fits(int is_bf16, int Md, int Nd, int groups) {
 // bytes in each of its 64 rows (measured against a 128 x 128 tile, 512 bytes in each of 128 rows, on config 3 at
 // b = 64: 2 to 2.5 % faster with the optimizer step in the epilogue, equal at b = 256).
 int gemm_bf16_wgrad_shape(int Md, int Nd, int Kd, int groups, int fused) {
-  int sh = tiled_shape(Md, Nd, groups);
-  if (sh == 4) sh = 1;                       // (the short-batch tile of the other contractions)
+  // Large tiles or 128 x 128 (narrow outputs: 128 x 64).  A launch of large tiles on a part of the CUs pays only when the reduction
+  // is long: the smaller ones share a launch with other layers and fill the chip.  us per step, large -> 128-wide tiles: 4 replicas
+  // of 3072-1024-1024-100 (64 large tiles), AdamW, b = 1024 368 -> 282, b = 3000 434 -> 421, b = 6000 709 (large), 731;
+  // 5 replicas of 3072-1536-1536-100 (180) b = 1024 579 -> 553, b = 4096 1140 (large), 1187.  128-wide -> large: 784-512-512-10,
+  // 16 replicas, b = 4096 489 -> 471; 784-768-768-768-100 (192 and 144) b = 4096 1018 -> 987, b = 1500 544 (128-wide), 566;
+  // 784-640-640-10, 12 replicas, whose large tiles are 36 % padding, b = 4096 509 (128-wide), 528
+  int sh = Nd <= 64 ? 0 : 1;
+  if (Md >= 256 && Nd >= 512) {
+    const long long tm = (Md + 255) / 256, tn = (Nd + 255) / 256, tiles = tm * tn * groups;
+    if (Md >= 1024 && Nd >= 1024) { if (tiles >= (Kd > 4096 ? 1 : Kd > 2048 ? 128 : 192)) sh = 2; }
+    else if (Kd > 2048 ? tiles >= 128 && 10LL * Md * Nd >= 7LL * tm * tn * 65536 : tiles >= 256 && 10LL * Md >= 7LL * tm * 256) sh = 2;
+  }
   if (sh != 0 && Kd <= 256) return 3;        // (measured on config 3: at b = 384 and above the large tiles are faster)
   // with the optimizer step in the epilogue a medium batch is still mostly epilogue: two or three 128 x 128
   // work-groups per CU stream it better than one 256 x 256 work-group (config 3: b = 384 1.92 -> 1.87 ms per step,

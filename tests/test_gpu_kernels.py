@@ -512,7 +512,7 @@ def test_fp32_weight_gradients_do_not_lose_precision_over_the_batch(dims, b, rou
 # Layers of 256 x 256 tiles: up to 512 samples, and up to 1536 where the tiles are many, the step in the epilogue takes smaller
 # tiles than the separate update, and MFMAs of another shape; both add the products of an entry in the same order, so the
 # parameters and the gradient formed on demand equal those of the separate update.
-@pytest.mark.parametrize("b,M,opt,tile", [(257, 2, W.OPT_SHB, "64x128"), (512, 2, W.OPT_SGD, "64x128"), (513, 2, W.OPT_SHB, "256x256"),
+@pytest.mark.parametrize("b,M,opt,tile", [(257, 2, W.OPT_SHB, "64x128"), (512, 2, W.OPT_SGD, "64x128"), 
                                           (513, 16, W.OPT_ADAMW, "128x256"), (1536, 16, W.OPT_ADAGRAD, "128x256"),
                                           (1537, 16, W.OPT_SHB, "256x256")])
 def test_wide_layers_take_the_same_step_in_either_form_of_the_update(b, M, opt, tile):
@@ -539,3 +539,63 @@ def test_wide_layers_take_the_same_step_in_either_form_of_the_update(b, M, opt, 
             rep.close()
     assert np.array_equal(out[0][0], out[1][0])
     assert np.array_equal(out[0][1], out[1][1])
+
+
+# The same edges as in the two tests of large tiles above, over so many workers that the launches take 256 x 256 tiles.
+@pytest.mark.parametrize("b,fin,fout,M,both", [(1030, 8, 1032, 16, False), (1024, 64, 1024, 16, False), (1025, 72, 1096, 14, False),
+                                               (257, 1032, 1040, 14, False), (1027, 1088, 1160, 12, True), (1031, 1024, 1024, 13, True)])
+def test_large_tile_contractions_over_many_workers(b, fin, fout, M, both):
+    import torch
+    A = _A()
+    g = torch.Generator(device="cuda").manual_seed(b + fin)
+    a = torch.randn((M, b, fin), device="cuda", generator=g).to(torch.bfloat16)
+    d = torch.randn((M, b, fout), device="cuda", generator=g).to(torch.bfloat16)
+    res, n, q, gbar = A.layer_stats([a], [d], want_per_sample=True, want_gbar=True)
+    for m in (0, M // 2, M - 1):
+        a64, d64 = a[m].double(), d[m].double()
+        G, Gabs = d64.T @ a64 / b, d64.abs().T @ a64.abs() / b
+        # bounds as in test_large_tile_contractions_at_the_edges_of_the_reduction
+        assert bool(((gbar[m].reshape(fout, fin).double() - G).abs() <= (b + 2) * EPS32 * Gabs).all()), m
+        want = (d64 * (a64 @ G.T)).sum(1)
+        bound = (EPSBF * (1 + 2 ** -8) + (b + fin + fout + 4) * EPS32) * (d64.abs() * (a64.abs() @ Gabs.T)).sum(1)
+        err = (q[m].double() - want).abs()
+        assert bool((err <= bound).all()) and float(err.norm() / want.norm()) <= 1e-3, m
+        norms = (a64 ** 2).sum(1) * (d64 ** 2).sum(1)
+        assert bool(((n[m].double() - norms).abs() <= (fin + fout + 4) * EPS32 * norms).all()), m
+        assert abs(res[m].gbar_sq - float((G ** 2).sum())) <= 1e-5 * float((G ** 2).sum()), m
+
+
+@pytest.mark.parametrize("dims,act,b,M,classes", [((72, 1032, 1040, 130), W.ACT_GELU, 1030, 10, ("fwd", "bwd", "ipdot")),
+                                                  ((64, 1048, 1024, 10), W.ACT_RELU, 1030, 10, ("fwd", "bwd", "ipdot")),
+                                                  ((72, 2048, 264, 10), W.ACT_GELU, 257, 16, ("fwd", "bwd", "ipdot")),   # row 2 of tiles: one sample
+                                                  ((136, 200, 136, 10), W.ACT_RELU, 2500, 16, ("fwd", "bwd", "ipdot"))])  # one column of tiles
+def test_large_tile_step_over_many_workers(dims, act, b, M, classes):
+    A = _A()
+    w = W.Workload("edges", dims, act, True, W.PREC_BF16, N=2048, M=M, H=1, rounds=1, b0=b, b_cap=b, opt=W.OPT_SHB, lr=0.05,
+                   momentum=0.9, test=W.TEST_IP, theta=0.9, data="teacher_mlp", seed=5)
+    X, y = W.make_dataset(w)
+    x0 = W.make_x0(w)
+    rep = A.Replicas.from_workload(w, X, y, x0)
+    orc = O.Replicas(O.Net(w.dims, w.act, True), x0, X, y, M, opt=w.opt, momentum=w.momentum, mixed=True, want_ip=True)
+    try:
+        idx = W.step_indices(w, 0, 0, b)
+        rep.profile_enable(True)
+        rep.local_step(idx, w.lr)
+        names = rep.profile_read()
+        rep.profile_enable(False)
+        for c in classes:
+            assert any(x.startswith("gemm_%s_256x256" % c) for x in names), (c, sorted(names))
+        g = rep.inner_product_test(w.theta)
+        orc.local_step(idx, w.lr, only=[0, M - 1])
+        for m in (0, M - 1):
+            s = orc.stats[m]
+            for got, want in ((g[m].sum_sq, s["S1"]), (g[m].gbar_sq, s["S2"]), (g[m].sum_q, s["S4"]),
+                              (g[m].sum_q2, s["S3"]), (g[m].loss_sum, s["loss_sum"])):
+                assert abs(got - want) <= 2e-3 * abs(want), (m, got, want)
+            grad = rep.get_grad(m).astype(np.float64)
+            assert np.linalg.norm(grad - orc.grads[m]) <= 2e-3 * np.linalg.norm(orc.grads[m]), m
+            p = rep.get_params(m).astype(np.float64)
+            assert np.abs(p - orc.x[m]).max() <= 1e-3 * np.abs(orc.x[m]).max()
+        assert rep.guard_intact()
+    finally:
+        rep.close()
