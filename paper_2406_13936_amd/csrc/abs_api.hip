@@ -22,6 +22,10 @@ namespace {
 thread_local std::string g_err;
 
 constexpr int MAXL = 16;
+// Signals of the last layer are added up column by column in one go (in double) while a lane walks at most 64 rows (16 lanes to a
+// column of a narrow layer, else 4); longer batches take a first stage of their own (784-512-100, 8 replicas, b = 1000: 250 rows
+// to a lane made the weight-gradient launch that carries them 34 us instead of 25).
+bool col_sum_direct(int cols, int b) { return b <= (cols <= 16 ? 1024 : 256); }
 constexpr int GRAM_IP_DEFAULT_B = 256;   // largest local batch that takes the Gram form of the inner products by default
 
 inline long long rup(long long v, long long a) { return (v + a - 1) / a * a; }
@@ -818,7 +822,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       slots += wplan.ksplit[l] > 1 ? splitk_finish_slots((long long)pl.dims[l] * pl.dims[l - 1])
                                    : gemm_bf16_upd_slots(pl.dims[l], pl.dims[l - 1], b, M, 1, wplan.fine);
     }
-    if (hb) slots += col_finish_slots(L, max_width);
+    if (hb) slots += col_finish_slots(L, max_width, 64);
     if (slots > pl.sq_slots) fused = false;
   }
   int fused_slots = 0;
@@ -827,6 +831,22 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
   // accumulated step needs the products between samples of different micro-batches).
   const bool use_gram = pl.bf16 && pl.want_ip && ph.ip && ph.passes && ph.wgrad && !ph.acc_grad && !ph.acc_q &&
                         ph.b_total == 0 && b <= c->gram_ip_max_b && b <= GRAM_MAX_B;
+  // what the statistics read and leave (the inner products' partials come with their launches)
+  const bool do_ip = pl.want_ip && ph.ip;
+  StatsP sp;
+  std::memset(&sp, 0, sizeof(sp));
+  sp.L = L; sp.has_bias = hb ? 1 : 0; sp.groups = M; sp.b = b; sp.want_ip = pl.want_ip ? 1 : 0; sp.rows = rows;
+  sp.do_n = ph.nstats ? 1 : 0; sp.do_q = do_ip ? 1 : 0; sp.acc_n = ph.acc_n ? 1 : 0; sp.acc_q = ph.acc_q ? 1 : 0;
+  for (int l = 0; l < L; ++l) {
+    sp.an[l] = c->at<float>(pl.o_an[l]); sp.dn[l] = c->at<float>(pl.o_dn[l + 1]);
+    sp.an_parts[l] = an_parts[l]; sp.an_sg[l] = (long long)pl.rpart_floats[l];
+    sp.dn_parts[l] = dn_parts[l + 1]; sp.dn_sg[l] = (long long)pl.rpart_floats[l + 1];
+  }
+  sp.sNg = cap; sp.sPart = part_ld;
+  sp.loss = c->at<float>(pl.o_loss);
+  if (ph.ps_off >= 0) { sp.n_out = c->at<float>(pl.o_nout) + ph.ps_off; sp.q_out = c->at<float>(pl.o_qout) + ph.ps_off; }
+  sp.Ppad = pl.Ppad;
+  sp.partials = c->at<double>(pl.o_partials); sp.stats = c->at<double>(pl.o_stats);
   // local batch gradient, eq. (batch_grad): Gbar_l = delta^T a / b, betabar_l = mean_i delta_i
   if (ph.wgrad) {
     std::vector<GemmP> many[2][2];         // layers that share a launch: [tile shape 1, 3][with the step in the epilogue]
@@ -890,7 +910,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
         const int e = cf.n++;
         cf.cols[e] = pl.dims[L]; cf.nsplit[e] = (b + COLSUM_ROWS - 1) / COLSUM_ROWS;
         cf.tile_m[e] = 0; cf.parts_per_tile[e] = 0; cf.out_off[e] = pl.offB[L];
-        if (b <= COLSUM_ROWS) {           // one partial per column would be the sum itself
+        if (col_sum_direct(cf.cols[e], b)) {
           cf.src[e] = static_cast<const bf16_t *>(p.A); cf.sXg[e] = p.sAg; cf.ldx[e] = pl.ld[l];
         } else {
           float *scr = c->at<float>(pl.o_colpart_l[L]);
@@ -902,10 +922,47 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
         }
       }
     }
+    if (cf.n > 0) {                        // all bias gradients of the step together, with the biases' step if the weights take theirs
+      // few partials to a column: 256 columns to a block, a quarter of the blocks (3072-2048-2048-2048-100, 16 replicas, b = 64, in
+      // front of the weight gradients: the step 1019 -> 1009 us)
+      cf.cb = 256;
+      for (int e = 0; e < cf.n; ++e) if (!cf.src[e] && cf.nsplit[e] > 16) cf.cb = 64;
+      cf.alpha = inv_b; cf.out = grad; cf.sOg = pl.Ppad; cf.rows = rows; cf.accumulate = ph.acc_grad ? 1 : 0; cf.b = b;
+      if (fused) {
+        cf.upd_x = xm;
+        cf.upd_v = c->cfg.opt != ABS_OPT_SGD ? c->at<float>(pl.o_v) : nullptr;
+        cf.upd_m = c->cfg.opt == ABS_OPT_ADAMW ? c->at<float>(pl.o_m) : nullptr;
+        cf.upd_shadow = c->at<bf16_t>(pl.o_xs);
+        cf.upd_opt = c->cfg.opt; cf.upd_lr = lr; cf.upd_momentum = c->cfg.momentum; cf.upd_beta1 = c->cfg.beta1;
+        cf.upd_beta2 = c->cfg.beta2; cf.upd_eps = c->cfg.eps; cf.upd_wd = c->cfg.weight_decay;
+        cf.upd_c1 = ph.c1; cf.upd_c2 = ph.c2; cf.upd_scal = ph.scal;
+        cf.sq = c->at<float>(pl.o_sqwave); cf.sSqg = pl.sq_slots; cf.slot0 = fused_slots;
+        fused_slots += col_finish_slots(cf.n, max_width, cf.cb);
+      }
+    }
+    // The end of the step that waits for nothing but the signals rides in front of a launch that several layers share, where
+    // there is one: the bias gradients and, unless inner products come later, the per-sample part of the statistics.  us per
+    // step, launches of their own -> in front: 784-512-512-10, 8 replicas, b = 32 74 -> 65, b = 501 102 -> 93, b = 1000 130 -> 121;
+    // 784-512-100, b = 200 78 -> 66; 3072-2048-2048-2048-100, 16 replicas, b = 200 1152 -> 1127, with inner products 1288 -> 1271.
+    StepTail tail;
+    std::memset(&tail, 0, sizeof(tail));
+    tail.groups = M;
+    tail.cf = cf;
+    if (cf.n > 0) tail.cf_x = col_finish_slots(1, max_width, cf.cb);
+    if (ph.nstats && !do_ip) { tail.st = sp; tail.st.do_n = 1; tail.st.nb_done = stats_sample_blocks(b); }
+    bool tail_taken = cf.n == 0 && tail.st.nb_done == 0;
+    const bool any_tail = !tail_taken;
     for (int sh = 0; sh < 2; ++sh)
       for (int u = 0; u < 2; ++u) {
         const std::vector<GemmP> &v = many[sh][u];
         if (v.empty()) continue;
+        if (!tail_taken && (v.size() > 1 || sh) && (cf.n == 0 || (u == 1) == fused)) {
+          ProfScope ps_(c, T_GEMM0 + (EPI_WGRAD * 6 + (sh ? 3 : v[0].fine ? 4 : 1)) * T_LAYERS + (v.size() == 1 ? many_layer[sh][u] : 0),
+                        gemm_flops(v), gemm_bytes(c, v, EPI_WGRAD) + cf_bytes);
+          HIPCHK(c, launch_wgrad_many(v.data(), (int)v.size(), sh ? 3 : 1, s, &tail));
+          tail_taken = true;
+          continue;
+        }
         if (v.size() == 1) { HIPCHK(c, gemm(c, v[0], EPI_WGRAD, many_layer[sh][u])); continue; }   // (may take a deeper ring)
         ProfScope ps_(c, T_GEMM0 + (EPI_WGRAD * 6 + (sh ? 3 : v[0].fine ? 4 : 1)) * T_LAYERS, gemm_flops(v), gemm_bytes(c, v, EPI_WGRAD));
         HIPCHK(c, launch_wgrad_many(v.data(), (int)v.size(), sh ? 3 : 1, s));
@@ -927,27 +984,13 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       }
       HIPCHK(c, launch_splitk_finish(kf, M, s));
     }
-    if (cf.n > 0) {                        // all bias gradients of the step in one launch, with the biases' step if the weights take theirs
+    if (any_tail && tail_taken) sp.nb_done = tail.st.nb_done;
+    else if (cf.n > 0) {
       ProfScope ps_(c, T_COLSUM, 0.0, cf_bytes);
-      cf.alpha = inv_b; cf.out = grad; cf.sOg = pl.Ppad; cf.rows = rows; cf.accumulate = ph.acc_grad ? 1 : 0; cf.b = b;
-      if (fused) {
-        cf.upd_x = xm;
-        cf.upd_v = c->cfg.opt != ABS_OPT_SGD ? c->at<float>(pl.o_v) : nullptr;
-        cf.upd_m = c->cfg.opt == ABS_OPT_ADAMW ? c->at<float>(pl.o_m) : nullptr;
-        cf.upd_shadow = c->at<bf16_t>(pl.o_xs);
-        cf.upd_opt = c->cfg.opt; cf.upd_lr = lr; cf.upd_momentum = c->cfg.momentum; cf.upd_beta1 = c->cfg.beta1;
-        cf.upd_beta2 = c->cfg.beta2; cf.upd_eps = c->cfg.eps; cf.upd_wd = c->cfg.weight_decay;
-        cf.upd_c1 = ph.c1; cf.upd_c2 = ph.c2; cf.upd_scal = ph.scal;
-        cf.sq = c->at<float>(pl.o_sqwave); cf.sSqg = pl.sq_slots; cf.slot0 = fused_slots;
-        fused_slots += col_finish_slots(cf.n, max_width);
-      }
       HIPCHK(c, launch_col_sum_finish_many(cf, M, s));
     }
   }
   // inner products <g_i, gbar>
-  StatsP sp;
-  std::memset(&sp, 0, sizeof(sp));
-  const bool do_ip = pl.want_ip && ph.ip;
   if (do_ip && use_gram) {
     GramP gp;
     std::memset(&gp, 0, sizeof(gp));
@@ -997,18 +1040,6 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
     }
   }
   // statistics
-  sp.L = L; sp.has_bias = hb ? 1 : 0; sp.groups = M; sp.b = b; sp.want_ip = pl.want_ip ? 1 : 0; sp.rows = rows;
-  sp.do_n = ph.nstats ? 1 : 0; sp.do_q = do_ip ? 1 : 0; sp.acc_n = ph.acc_n ? 1 : 0; sp.acc_q = ph.acc_q ? 1 : 0;
-  for (int l = 0; l < L; ++l) {
-    sp.an[l] = c->at<float>(pl.o_an[l]); sp.dn[l] = c->at<float>(pl.o_dn[l + 1]);
-    sp.an_parts[l] = an_parts[l]; sp.an_sg[l] = (long long)pl.rpart_floats[l];
-    sp.dn_parts[l] = dn_parts[l + 1]; sp.dn_sg[l] = (long long)pl.rpart_floats[l + 1];
-  }
-  sp.sNg = cap; sp.sPart = part_ld;
-  sp.loss = c->at<float>(pl.o_loss);
-  if (ph.ps_off >= 0) { sp.n_out = c->at<float>(pl.o_nout) + ph.ps_off; sp.q_out = c->at<float>(pl.o_qout) + ph.ps_off; }
-  sp.Ppad = pl.Ppad;
-  sp.partials = c->at<double>(pl.o_partials); sp.stats = c->at<double>(pl.o_stats);
   sp.stats_host = c->host_stats_dev;
   if (sp.stats_host) { c->ticket += 1.0; sp.ticket = c->ticket; c->ticket_live = true; }
   // When this call both finishes the gradient and updates, the update kernel gathers ||gbar||^2 on

@@ -93,7 +93,8 @@ struct GemmP {
 hipError_t launch_gemm_bf16(const GemmP &p, int epi, hipStream_t s);
 // EPI_WGRAD of n layers whose tile shape (gemm_bf16_wgrad_shape) is `shape`, 1 or 3, in one launch per eight layers: all of
 // them with the optimizer step in the epilogue or none
-hipError_t launch_wgrad_many(const GemmP *p, int n, int shape, hipStream_t s);
+struct StepTail;
+hipError_t launch_wgrad_many(const GemmP *p, int n, int shape, hipStream_t s, const StepTail *tail = nullptr);
 int gemm_bf16_ipdot_parts(int Nd);
 // Exact number of row partials (tiles along n) and of column-partial rows (tiles along m times
 // wave rows) that launch_gemm_bf16 writes for epilogue epi (forward, logits, backward-data, inner products) of an
@@ -181,14 +182,14 @@ hipError_t launch_col_sum_partials(int is_bf16, const void *X, long long sXg, in
 // out[g][out_off_l + j] = alpha * sum_r part_l[g][r][j], r < nsplit_l (partials from a GEMM epilogue or from
 // launch_col_sum_partials).  With rows: alpha = 1 / rows[g] and, where tile_m_l > 0, only the first
 // ceil(rows[g] / tile_m_l) * parts_per_tile_l partials of group g exist.
-// A layer with src_l set has no partials: its b <= COLSUM_ROWS signals src_l[g][i][j] (bf16, group stride sXg_l, row stride
+// A layer with src_l set has no partials: its b signals src_l[g][i][j] (bf16, group stride sXg_l, row stride
 // ldx_l) are added up directly.
 // With upd_x the biases take their optimizer step in the same launch (accumulate == 0): parameters, state and shadow lie at
 // out_off_l + j of every group's vector (group stride sOg), and block (x, layer l) of group g leaves its squared gradient
-// entries' sum in sq[g * sSqg + slot0 + l * gridDim.x + x] (col_finish_slots of them).
+// entries' sum in sq[g * sSqg + slot0 + l * gridDim.x + x] (col_finish_slots of them).  A block owns cb columns, 64 or 256.
 struct ColFinishMany {
   enum { MAXN = 16 };
-  int n;                         // layers
+  int n, cb;                     // layers; columns to a block
   const bf16_t *src[MAXN];
   long long sXg[MAXN];
   int ldx[MAXN], b;
@@ -207,7 +208,7 @@ struct ColFinishMany {
   int accumulate;
 };
 hipError_t launch_col_sum_finish_many(const ColFinishMany &p, int groups, hipStream_t s);
-inline int col_finish_slots(int layers, int max_cols) { return layers * ((max_cols + 63) / 64); }
+inline int col_finish_slots(int layers, int max_cols, int cb) { return layers * ((max_cols + cb - 1) / cb); }
 // q[g][i] += sum_j D[g][i][j] * U[g][i][j]  (fp32 path of the inner products)
 hipError_t launch_rowdot_f32(const float *D, long long sDg, int ldd, const float *U,
                              long long sUg, int ldu, int cols, int groups, int b, float *q,
@@ -242,8 +243,14 @@ struct StatsP {
   // which sums this launch produces: S1 and the loss (do_n), S3 and S4 (do_q; needs want_ip),
   // S2 (grad != null); acc_n / acc_q add to the stored sums instead of replacing them
   int do_n, do_q, acc_n, acc_q;
+  int nb_done;              // do_n without do_q: the sample blocks (stats_sample_blocks) have run already (StepTail)
 };
 enum { STATS_PBLK = 256 };
+inline int stats_sample_blocks(int b) { return (b + 63) / 64 < STATS_PBLK ? (b + 63) / 64 : (int)STATS_PBLK; }
+// What of a step's end needs nothing but the signals and rides in front of a weight-gradient launch (launch_wgrad_many), one
+// block of 256 threads each: the bias gradients (cf.n > 0; with the weights' step if the launch carries it) and the per-sample
+// part of the statistics (st.nb_done > 0 blocks per group, which leave their sums in st.partials).
+struct StepTail { int groups, blocks, cf_x; ColFinishMany cf; StatsP st; };
 hipError_t launch_stats(const StatsP &p, hipStream_t s);
 
 struct UpdateP {

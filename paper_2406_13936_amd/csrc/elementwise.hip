@@ -5,6 +5,7 @@
 #include <algorithm>
 #include "abs_internal.h"
 #include "device_utils.h"
+#include "step_tail.h"
 
 namespace absk {
 namespace {
@@ -297,61 +298,8 @@ __global__ void __launch_bounds__(256) col_sum_stage2(const float *__restrict__ 
 // as its work: 784-512-512-10, b = 32: 3.0 + 3.2 us apart, and 3.4 us for the first stage of the last layer's sums).
 template <int OPT>
 __global__ void __launch_bounds__(256) col_finish_many_kernel(const ColFinishMany p) {
-  __shared__ float red[256];
-  const int l = blockIdx.z, g = blockIdx.y;
-  const int cols = p.cols[l];
-  const bf16_t *src = p.src[l];
-  // 64 columns x 4 row-lanes per block; 16 x 16 for a narrow layer summed directly (a shorter serial walk per lane)
-  const int CL = src && cols <= 16 ? 16 : 64, RL = 256 / CL;
-  const int cl = threadIdx.x & (CL - 1), rl = threadIdx.x / CL;
-  const int c = blockIdx.x * CL + cl;
-  float gg = 0.0f;
-  if (blockIdx.x * CL < cols) {                    // uniform over the block
-    float alpha = p.alpha;
-    int ns = src ? p.b : p.nsplit[l];
-    if (p.rows) {
-      alpha = 1.0f / (float)p.rows[g];
-      if (src) ns = p.rows[g];
-      else if (p.tile_m[l] > 0) ns = (p.rows[g] + p.tile_m[l] - 1) / p.tile_m[l] * p.parts_per_tile[l];
-    }
-    float s = 0.0f;
-    if (c < cols) {
-      if (src) {
-        const bf16_t *q = src + (long long)g * p.sXg[l] + c;
-#pragma unroll 8
-        for (int r = rl; r < ns; r += RL) s += bf2f(q[(long long)r * p.ldx[l]]);
-      } else {
-        const float *q = p.part[l] + (long long)g * p.nsplit[l] * cols + c;
-#pragma unroll 4
-        for (int r = rl; r < ns; r += RL) s += q[(long long)r * cols];
-      }
-    }
-    red[threadIdx.x] = s;
-    __syncthreads();
-    if (rl == 0 && c < cols) {
-      float t = red[cl];
-      for (int k = 1; k < RL; ++k) t += red[k * CL + cl];
-      const long long off = (long long)g * p.sOg + p.out_off[l] + c;
-      float *o = p.out + off;
-      const float gr = p.accumulate ? fmaf(alpha, t, *o) : alpha * t;
-      *o = gr;
-      if constexpr (OPT >= 0) {
-        OptHyper h = {p.upd_lr, p.upd_momentum, p.upd_beta1, p.upd_beta2, p.upd_eps, p.upd_wd, p.upd_c1, p.upd_c2};
-        if (p.upd_scal) { h.lr = p.upd_scal[0]; h.c1 = p.upd_scal[1]; h.c2 = p.upd_scal[2]; }
-        float x = p.upd_x[off], v = OPT != OPT_SGD ? p.upd_v[off] : 0.0f, m = OPT == OPT_ADAMW ? p.upd_m[off] : 0.0f;
-        opt_step_elem<OPT>(x, gr, v, m, h);
-        p.upd_x[off] = x;
-        if (OPT != OPT_SGD) p.upd_v[off] = v;
-        if (OPT == OPT_ADAMW) p.upd_m[off] = m;
-        if (p.upd_shadow) p.upd_shadow[off] = f2bf(x);
-        gg = gr * gr;
-      }
-    }
-  }
-  if constexpr (OPT >= 0) {                        // columns sit in the first wavefront; blocks beyond the layer leave zeros
-    const double r = wave_sum((double)gg);
-    if (threadIdx.x == 0) p.sq[(long long)g * p.sSqg + p.slot0 + l * gridDim.x + blockIdx.x] = (float)r;
-  }
+  __shared__ __attribute__((aligned(8))) float red[256];
+  col_finish_block<OPT>(p, blockIdx.x, gridDim.x, blockIdx.z, blockIdx.y, red);
 }
 
 __global__ void rowdot_f32_kernel(const float *__restrict__ D, long long sDg, int ldd,
@@ -374,82 +322,6 @@ __global__ void rowdot_f32_kernel(const float *__restrict__ D, long long sDg, in
 }
 
 // ---- statistics ---------------------------------------------------------------------------
-// Per-sample squared gradient norms  n_i = sum_l ||delta_i^l||^2 (||a_i^{l-1}||^2 + [bias])  and inner products
-// q_i = sum_l sum_parts ..., their sums (n, q, q^2, the loss) and ||gbar||^2, in double.
-//
-// What bounds these launches is the chain of dependent loads per sample (a norm is the sum of up to 64 tile partials),
-// so four thread groups of a block share a sample: group j takes the layers j, j + 4, ..., with both norms' partials eight
-// at a time in flight (b = 64 of config 3, one thread per sample: 12.6 us, of which 11 were these chains).
-// Summation order: partials in index order, a group's layers in order, the four groups in order.
-__device__ __forceinline__ void sum_partials2(const float *__restrict__ a, int na, const float *__restrict__ d, int nd,
-                                              long long stride, float &sa, float &sd) {
-  sa = sd = 0.0f;
-  for (int k = 0; k < na || k < nd; k += 8) {
-    float va[8], vd[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) va[u] = k + u < na ? a[(long long)(k + u) * stride] : 0.0f;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) vd[u] = k + u < nd ? d[(long long)(k + u) * stride] : 0.0f;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) { sa += va[u]; sd += vd[u]; }
-  }
-}
-
-struct StatsSums { double s[5]; };      // n, ||gbar||^2, q^2, q, loss
-
-// Blocks 0 .. nb-1 of a group share its samples: block j owns samples (NT / 4) j + t, then strides of nb NT / 4.
-template <int NT>
-__device__ __forceinline__ void stats_samples(const StatsP &p, int g, int blk, int nb, StatsSums &o) {
-  constexpr int SL = NT / 4;
-  __shared__ float comb[2][4][SL];
-  const int gl = threadIdx.x / SL, sl = threadIdx.x % SL;
-  const float hb = p.has_bias ? 1.0f : 0.0f;
-  const int bg = p.rows ? p.rows[g] : p.b;
-  for (int base = blk * SL; base < bg; base += nb * SL) {        // uniform over the block
-    const int i = base + sl;
-    const bool live = i < bg;
-    float n = 0.0f, q = 0.0f;
-    if (live) {
-      for (int l = gl; l < p.L; l += 4) {
-        if (p.do_n) {
-          float a, d;
-          sum_partials2(p.an[l] + (long long)g * p.an_sg[l] + i, p.an_parts[l], p.dn[l] + (long long)g * p.dn_sg[l] + i,
-                        p.dn_parts[l], p.sPart, a, d);
-          n = fmaf(d, a + hb, n);
-        }
-        if (p.do_q) {
-          const float *qp = p.qpart[l] + (long long)g * p.sQg[l] + i;
-          for (int k = 0; k < p.nparts[l]; k += 8) {
-            float v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = k + u < p.nparts[l] ? qp[(long long)(k + u) * p.sQpart[l]] : 0.0f;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) q += v[u];
-          }
-        }
-      }
-    }
-    comb[0][gl][sl] = n;
-    comb[1][gl][sl] = q;
-    __syncthreads();
-    if (gl == 0 && live) {
-      const long long at = (long long)g * p.sNg + i;
-      if (p.do_n) {
-        n = ((n + comb[0][1][sl]) + comb[0][2][sl]) + comb[0][3][sl];
-        if (p.n_out) p.n_out[at] = n;
-        o.s[0] += (double)n;
-        if (p.loss) o.s[4] += (double)p.loss[at];
-      }
-      if (p.do_q) {
-        q = ((q + comb[1][1][sl]) + comb[1][2][sl]) + comb[1][3][sl];
-        if (p.q_out) p.q_out[at] = q;
-        o.s[3] += (double)q;
-        o.s[2] += (double)q * (double)q;
-      }
-    }
-    __syncthreads();
-  }
-}
 // ||gbar||^2 from the partial sums that the launches which applied or stored the gradient left (blk of nb blocks)
 template <int NT>
 __device__ __forceinline__ void stats_gradsq_parts(const StatsP &p, int g, int blk, int nb, StatsSums &o) {
@@ -462,22 +334,6 @@ __device__ __forceinline__ void stats_gradsq_parts(const StatsP &p, int g, int b
   const float *q = p.sq_wave + at;
 #pragma unroll 4
   for (long long i = (long long)blk * NT + threadIdx.x; i < p.n_sq_wave; i += step) o.s[1] += (double)q[i];
-}
-// Sum over a block, fixed order; sum k ends in thread k < 5.
-template <int NT>
-__device__ __forceinline__ double stats_block_sums(const StatsSums &o) {
-  constexpr int NW = NT / 64;
-  __shared__ double fin[5][NW];
-#pragma unroll
-  for (int k = 0; k < 5; ++k) {
-    const double v = wave_sum(o.s[k]);
-    if ((threadIdx.x & 63) == 0) fin[k][threadIdx.x >> 6] = v;
-  }
-  __syncthreads();
-  double r = 0.0;
-  if (threadIdx.x < 5)
-    for (int w = 0; w < NW; ++w) r += fin[threadIdx.x][w];
-  return r;
 }
 // thread k < 5 holds sum k of group g.  sel / acc: bit k set = sum k is produced by this launch / is added to the stored value.
 __device__ __forceinline__ void stats_deliver(const StatsP &p, int g, int sel, int acc, double r) {
@@ -497,27 +353,45 @@ __device__ __forceinline__ void stats_deliver(const StatsP &p, int g, int sel, i
 // their work (784-512-512-10, b = 32: 8.6 + 3.9 us apart; b = 64 of config 3: 12.6 + 5.6).
 // n2: ||gbar||^2 partials left by stats_gradsq_kernel (0: none).
 __global__ void __launch_bounds__(1024) stats_one_kernel(const StatsP p, const int n2, const int sel, const int acc) {
+  __shared__ float comb[2 * 1024];
+  __shared__ double fin[5 * 16];
   const int g = blockIdx.x;
   StatsSums o = {{0.0, 0.0, 0.0, 0.0, 0.0}};
   if (p.sq_wave || p.sq_wave64) stats_gradsq_parts<1024>(p, g, 0, 1, o);
   else if ((int)threadIdx.x < n2) o.s[1] = p.partials[((long long)g * 5 + 1) * STATS_PBLK + threadIdx.x];
-  if (p.do_n || p.do_q) stats_samples<1024>(p, g, 0, 1, o);
-  stats_deliver(p, g, sel, acc, stats_block_sums<1024>(o));
+  if (p.do_n || p.do_q) stats_samples<1024>(p, g, 0, 1, o, comb);
+  stats_deliver(p, g, sel, acc, stats_block_sums<1024>(o, fin));
+}
+// The sums of a step whose samples a weight-gradient launch has taken along (StatsP::nb_done blocks of them): one block per group.
+template <int NT>
+__global__ void __launch_bounds__(NT) stats_close_kernel(const StatsP p, const int sel, const int acc) {
+  __shared__ double fin[5 * (NT / 64)];
+  const int g = blockIdx.x;
+  StatsSums o = {{0.0, 0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+  for (int k = 0; k < 5; ++k)
+    if (k != 1 && ((sel >> k) & 1) && (int)threadIdx.x < p.nb_done)
+      o.s[k] = p.partials[((long long)g * 5 + k) * STATS_PBLK + threadIdx.x];
+  stats_gradsq_parts<NT>(p, g, 0, 1, o);
+  stats_deliver(p, g, sel, acc, stats_block_sums<NT>(o, fin));
 }
 // grid (nb_samples + nb_parts) x groups: the first nb_samples blocks of a group take the per-sample sums, the other
 // nb_parts the ||gbar||^2 partials; stats_final_kernel adds the blocks' sums in index order.
 __global__ void __launch_bounds__(256) stats_samples_kernel(const StatsP p, const int nb_samples, const int nb_parts) {
+  __shared__ float comb[2 * 256];
+  __shared__ double fin[5 * 4];
   const int g = blockIdx.y, blk = blockIdx.x;
   StatsSums o = {{0.0, 0.0, 0.0, 0.0, 0.0}};
   const bool samples = blk < nb_samples;
-  if (samples) stats_samples<256>(p, g, blk, nb_samples, o);
+  if (samples) stats_samples<256>(p, g, blk, nb_samples, o, comb);
   else stats_gradsq_parts<256>(p, g, blk - nb_samples, nb_parts, o);
-  const double r = stats_block_sums<256>(o);
+  const double r = stats_block_sums<256>(o, fin);
   const int t = threadIdx.x;
   if (t < 5 && samples == (t != 1)) p.partials[((long long)g * 5 + t) * STATS_PBLK + (samples ? blk : blk - nb_samples)] = r;
 }
 __global__ void __launch_bounds__(256) stats_final_kernel(const StatsP p, const int nb_samples, const int n2, const int sel,
                                                           const int acc) {
+  __shared__ double fin[5 * 4];
   const int g = blockIdx.x;
   StatsSums o;
   static_assert(STATS_PBLK == 256, "one partial per thread");
@@ -526,7 +400,7 @@ __global__ void __launch_bounds__(256) stats_final_kernel(const StatsP p, const 
     const bool live = ((sel >> k) & 1) && (int)threadIdx.x < (k == 1 ? n2 : nb_samples);
     o.s[k] = live ? p.partials[((long long)g * 5 + k) * STATS_PBLK + threadIdx.x] : 0.0;
   }
-  stats_deliver(p, g, sel, acc, stats_block_sums<256>(o));
+  stats_deliver(p, g, sel, acc, stats_block_sums<256>(o, fin));
 }
 
 // Stage 1b (grid: PBLK x groups): ||gbar||^2 over the padded gradient vector.
@@ -974,7 +848,8 @@ hipError_t launch_col_sum_finish_many(const ColFinishMany &p, int groups, hipStr
     if (!p.src[l] && !p.part[l]) return hipErrorInvalidValue;
     mx = p.cols[l] > mx ? p.cols[l] : mx;
   }
-  const dim3 grid((mx + 63) / 64, groups, p.n), blk(256);
+  if (p.cb != 64 && p.cb != 256) return hipErrorInvalidValue;
+  const dim3 grid((mx + p.cb - 1) / p.cb, groups, p.n), blk(256);
   if (!p.upd_x) { hipLaunchKernelGGL(col_finish_many_kernel<-1>, grid, blk, 0, s, p); return hipGetLastError(); }
   if (p.accumulate || !p.sq || (p.upd_opt != OPT_SGD && !p.upd_v) || (p.upd_opt == OPT_ADAMW && !p.upd_m))
     return hipErrorInvalidValue;
@@ -1018,16 +893,22 @@ hipError_t launch_stats(const StatsP &p, hipStream_t s) {
   //   784-512-512-10, M = 1          b = 256: 10.9 | 11.5, 11.2 | 11.8    b = 257: 13.2 | 11.8, 14.5 | 12.5
   //   3072-2048-2048-2048-100, M = 4 b = 256: 11.7 | 11.9, 12.3 | 12.6    b = 257: 14.9 | 11.8, 19.3 | 14.0
   //   256-10, M = 4                  b = 256:  9.7 | 10.8, 10.9 | 11.8    b = 384: 11.2 | 10.7, 12.7 | 11.7
-  if ((!samples || p.b <= STATS_ONE_B) && (!parts || p.n_sq_wave <= STATS_ONE_SQ)) {
+  if (p.nb_done > 0 && (p.do_q || !p.do_n)) return hipErrorInvalidValue;
+  if (p.nb_done > 0 && parts && p.n_sq_wave <= STATS_ONE_SQ) {
+    if (p.n_sq_wave <= 1024) hipLaunchKernelGGL(stats_close_kernel<256>, dim3(p.groups), dim3(256), 0, s, p, sel, acc);
+    else hipLaunchKernelGGL(stats_close_kernel<1024>, dim3(p.groups), dim3(1024), 0, s, p, sel, acc);
+    return hipGetLastError();
+  }
+  if (p.nb_done == 0 && (!samples || p.b <= STATS_ONE_B) && (!parts || p.n_sq_wave <= STATS_ONE_SQ)) {
     hipLaunchKernelGGL(stats_one_kernel, dim3(p.groups), dim3(1024), 0, s, p, n2, sel, acc);
     return hipGetLastError();
   }
-  const int nb_samples = samples ? std::min((p.b + 63) / 64, (int)STATS_PBLK) : 0;
+  const int nb_samples = p.nb_done > 0 || !samples ? 0 : stats_sample_blocks(p.b);
   if (parts) n2 = (int)std::min<long long>(STATS_PBLK, (p.n_sq_wave + 255) / 256);
   const int nb_parts = parts ? n2 : 0;
   if (nb_samples + nb_parts > 0)
     hipLaunchKernelGGL(stats_samples_kernel, dim3(nb_samples + nb_parts, p.groups), dim3(256), 0, s, p, nb_samples, nb_parts);
-  hipLaunchKernelGGL(stats_final_kernel, dim3(p.groups), dim3(256), 0, s, p, nb_samples, n2, sel, acc);
+  hipLaunchKernelGGL(stats_final_kernel, dim3(p.groups), dim3(256), 0, s, p, nb_samples + p.nb_done, n2, sel, acc);
   return hipGetLastError();
 }
 

@@ -28,10 +28,12 @@
 // dealt round-robin to the 8 XCDs) works on a contiguous range of tiles and its L2 sees one
 // replica's operands at a time.
 #include <algorithm>
+#include <cstring>
 #include <mutex>
 #include <utility>
 #include "abs_internal.h"
 #include "device_utils.h"
+#include "step_tail.h"
 
 namespace absk {
 
@@ -964,22 +966,76 @@ gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int 
 // tiles of narrow nets and medium batches): what separate launches add is their starts, their nearly empty last waves and, where a
 // layer alone has fewer tiles than the chip has places, idle CUs.  The tiles of the layers lie one behind the other;
 // a work-group picks its layer by the tile number.
+// In front of them go the blocks of a step's end that need nothing but the signals (StepTail): launches of their own cost their
+// starts and a gap each.
 struct WgradMany {
   enum { MAXN = 8 };
+  struct Layer {
+    const void *A, *B;
+    long long sAg, sBg;
+    int lda, ldb, Md, Nd;
+    void *C, *C2;
+    int ldc, ldc2;
+    float *upd_x, *upd_v, *upd_m;
+    bf16_t *upd_shadow;
+    int upd_slot0, ksplit, kchunk;
+    float *kpart;
+    double *sq64;
+  };
   int n, nblk, chunk;
   int end[MAXN], tilesM[MAXN], tilesN[MAXN];
-  GemmP p[MAXN];
+  int Kd, groups, accumulate;                     // of every layer
+  long long sCg, sC2g;
+  float alpha;
+  const int *rows, *gperm;
+  float upd_lr, upd_momentum, upd_beta1, upd_beta2, upd_eps, upd_wd, upd_c1, upd_c2;
+  const float *upd_scal;
+  float *upd_sq; long long upd_sSqg, sSq64g;
+  Layer p[MAXN];
 };
-static_assert(sizeof(WgradMany) <= 4096, "kernel arguments");
+static_assert(sizeof(WgradMany) + sizeof(StepTail) <= 4096, "kernel arguments");
+
+template <int OPT>
+__device__ __forceinline__ void step_tail_block(const StepTail &t, int id) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+  const int ncf = t.cf_x * t.cf.n * t.groups;
+  if (id < ncf) {
+    const int bx = id % t.cf_x, l = id / t.cf_x % t.cf.n, g = id / (t.cf_x * t.cf.n);
+    col_finish_block<OPT>(t.cf, bx, t.cf_x, l, g, reinterpret_cast<float *>(smem_raw));
+    return;
+  }
+  id -= ncf;
+  const int nb = t.st.nb_done;
+  if (id >= nb * t.groups) return;
+  const int g = id / nb, blk = id - g * nb;
+  StatsSums o = {{0.0, 0.0, 0.0, 0.0, 0.0}};
+  stats_samples<256>(t.st, g, blk, nb, o, reinterpret_cast<float *>(smem_raw));
+  const double r = stats_block_sums<256>(o, reinterpret_cast<double *>(smem_raw + 4096));
+  if (threadIdx.x < 5 && threadIdx.x != 1) t.st.partials[((long long)g * 5 + threadIdx.x) * STATS_PBLK + blk] = r;
+}
+
 template <int BM, int BN, int BK, int WM, int WN, int EPI, int ACT>
-__global__ void __launch_bounds__(256) wgrad_many_kernel(const WgradMany q) {
-  const int bid = blockIdx.x;
+__global__ void __launch_bounds__(256) wgrad_many_kernel(const WgradMany q, const StepTail t) {
+  if ((int)blockIdx.x < t.blocks) { step_tail_block<EPI == EPI_WGRAD_UPD ? ACT : -1>(t, blockIdx.x); return; }
+  const int bid = blockIdx.x - t.blocks;          // (t.blocks is a multiple of 8: the XCDs stay where they were)
   int lb = (bid & 7) * q.chunk + (bid >> 3);
   if (lb >= q.nblk) return;
   int l = 0;
   while (lb >= q.end[l]) ++l;                     // uniform; end[n - 1] == nblk
   if (l > 0) lb -= q.end[l - 1];
-  gemm_bf16_tile<BM, BN, BK, WM, WN, 2, false, true, true, EPI, ACT>(q.p[l], q.tilesM[l], q.tilesN[l], lb);
+  const WgradMany::Layer &y = q.p[l];
+  GemmP p = {};
+  p.A = y.A; p.B = y.B; p.sAg = y.sAg; p.sBg = y.sBg; p.lda = y.lda; p.ldb = y.ldb; p.a_trans = p.b_trans = 1;
+  p.Md = y.Md; p.Nd = y.Nd; p.Kd = q.Kd; p.groups = q.groups;
+  p.C = y.C; p.sCg = q.sCg; p.ldc = y.ldc; p.C2 = y.C2; p.sC2g = q.sC2g; p.ldc2 = y.ldc2;
+  p.alpha = q.alpha; p.accumulate = q.accumulate; p.rows = q.rows; p.rows_is_k = 1; p.gperm = q.gperm;
+  p.ksplit = y.ksplit; p.kchunk = y.kchunk; p.kpart = y.kpart;
+  p.upd_x = y.upd_x; p.upd_v = y.upd_v; p.upd_m = y.upd_m; p.upd_shadow = y.upd_shadow;
+  p.upd_lr = q.upd_lr; p.upd_momentum = q.upd_momentum; p.upd_beta1 = q.upd_beta1; p.upd_beta2 = q.upd_beta2;
+  p.upd_eps = q.upd_eps; p.upd_wd = q.upd_wd; p.upd_c1 = q.upd_c1; p.upd_c2 = q.upd_c2; p.upd_scal = q.upd_scal;
+  p.upd_sq = q.upd_sq; p.upd_sSqg = q.upd_sSqg; p.upd_slot0 = y.upd_slot0;
+  p.sq64 = y.sq64; p.sSq64g = q.sSq64g;
+  gemm_bf16_tile<BM, BN, BK, WM, WN, 2, false, true, true, EPI, ACT>(p, q.tilesM[l], q.tilesN[l], lb);
 }
 
 template <int BM, int BN, int BK, int WM, int WN, int NS, bool PP, bool AT, bool BT, int EPI, int ACT>
@@ -1118,17 +1174,17 @@ long long small_limit(int epi, int Md, int Nd, int groups) {
 long long small_tiles(int Md, int Nd, int groups) { return (long long)((Md + 31) / 32) * ((Nd + 31) / 32) * groups; }
 
 template <int BM, int BN, int BK, int WM, int WN, int EPI, int ACT>
-hipError_t launch_many_cfg(const WgradMany &q, hipStream_t s) {
+hipError_t launch_many_cfg(const WgradMany &q, const StepTail &t, hipStream_t s) {
   // dynamic LDS: two stages, or the epilogue's fp32 staging slices
   constexpr size_t lds = std::max<size_t>((size_t)2 * (BM + BN) * BK * sizeof(bf16_t), (size_t)4 * 32 * (BN / WN + 4) * sizeof(float));
-  static_assert(lds <= 64 * 1024 && WM * WN == 4, "no attribute needed");
-  hipLaunchKernelGGL((wgrad_many_kernel<BM, BN, BK, WM, WN, EPI, ACT>), dim3(q.chunk * 8), dim3(256), lds, s, q);
+  static_assert(lds <= 64 * 1024 && lds >= 8192 && WM * WN == 4, "no attribute needed; room for a StepTail block");
+  hipLaunchKernelGGL((wgrad_many_kernel<BM, BN, BK, WM, WN, EPI, ACT>), dim3(t.blocks + q.chunk * 8), dim3(256), lds, s, q, t);
   return hipGetLastError();
 }
 template <int EPI, int ACT>
-hipError_t launch_many(const WgradMany &q, int shape, hipStream_t s) {
-  if (shape == 1 && q.p[0].fine) return launch_many_cfg<64, 128, 64, 2, 2, EPI, ACT>(q, s);
-  return shape == 3 ? launch_many_cfg<64, 256, 32, 1, 4, EPI, ACT>(q, s) : launch_many_cfg<128, 128, 64, 2, 2, EPI, ACT>(q, s);
+hipError_t launch_many(const WgradMany &q, const StepTail &t, int shape, int fine, hipStream_t s) {
+  if (shape == 1 && fine) return launch_many_cfg<64, 128, 64, 2, 2, EPI, ACT>(q, t, s);
+  return shape == 3 ? launch_many_cfg<64, 256, 32, 1, 4, EPI, ACT>(q, t, s) : launch_many_cfg<128, 128, 64, 2, 2, EPI, ACT>(q, t, s);
 }
 
 // operand checks that every launch relies on: 16-byte aligned rows, operands below 2 GiB per replica
@@ -1240,39 +1296,66 @@ int gemm_bf16_ipdot_parts(int Nd) {
   return (Nd + 127) / 128;
 }
 
-hipError_t launch_wgrad_many(const GemmP *p, int n, int shape, hipStream_t s) {
+hipError_t launch_wgrad_many(const GemmP *p, int n, int shape, hipStream_t s, const StepTail *tail) {
   if (shape != 1 && shape != 3) return hipErrorInvalidValue;
-  if (n < 1) return hipSuccess;
-  const int bm = shape == 3 || p[0].fine ? 64 : 128, bn = shape == 3 ? 256 : 128;
+  if (n < 1) return tail ? hipErrorInvalidValue : hipSuccess;
+  const GemmP &c0 = p[0];
+  const int bm = shape == 3 || c0.fine ? 64 : 128, bn = shape == 3 ? 256 : 128;
+  const bool upd = c0.upd_x != nullptr;
+  StepTail t;
+  std::memset(&t, 0, sizeof(t));
+  if (tail) {
+    t = *tail;
+    // the bias gradients take their step exactly if the weights do
+    if (t.groups != c0.groups || (t.cf.n > 0 && ((t.cf.upd_x != nullptr) != upd || (upd && (t.cf.upd_opt != c0.upd_opt || !t.cf.sq)) ||
+                                                 (upd && t.cf.accumulate) || t.cf.n > ColFinishMany::MAXN || t.cf_x < 1 || (t.cf.cb != 64 && t.cf.cb != 256))) ||
+        (t.st.nb_done > 0 && (!t.st.do_n || t.st.do_q || !t.st.partials || t.st.nb_done > STATS_PBLK)))
+      return hipErrorInvalidValue;
+    t.blocks = (t.groups * (t.cf_x * t.cf.n + t.st.nb_done) + 7) / 8 * 8;
+  }
   for (int at = 0; at < n;) {
     WgradMany q;
-    q.n = 0;
+    std::memset(&q, 0, sizeof(q));
     long long blocks = 0;
-    const bool upd = p[at].upd_x != nullptr;
     for (; at < n && q.n < WgradMany::MAXN; ++at) {
       const GemmP &c = p[at];
       // one kernel variant for all: every layer carries the same optimizer step, or none
       if (!operands_ok(c, EPI_WGRAD) || !c.a_trans || !c.b_trans || (c.upd_x != nullptr) != upd ||
-          (upd && c.upd_opt != p[0].upd_opt) || (shape == 3 && c.ksplit > 1) || c.fine != p[0].fine ||
+          (upd && c.upd_opt != c0.upd_opt) || (shape == 3 && c.ksplit > 1) || c.fine != c0.fine ||
           gemm_bf16_wgrad_shape(c.Md, c.Nd, c.Kd, c.groups, upd) != shape)
+        return hipErrorInvalidValue;
+      // and the fields that the launch holds once
+      if (c.Kd != c0.Kd || c.groups != c0.groups || c.accumulate != c0.accumulate || c.sCg != c0.sCg || (c.C2 && c.sC2g != c0.sC2g) ||
+          (c.C2 != nullptr) != (c0.C2 != nullptr) || c.alpha != c0.alpha || c.rows != c0.rows || (c.rows && !c.rows_is_k) ||
+          c.gperm != c0.gperm || c.upd_scal != c0.upd_scal || c.upd_sq != c0.upd_sq || c.upd_sSqg != c0.upd_sSqg || c.sSq64g != c0.sSq64g)
         return hipErrorInvalidValue;
       q.tilesM[q.n] = (c.Md + bm - 1) / bm; q.tilesN[q.n] = (c.Nd + bn - 1) / bn;
       blocks += (long long)q.tilesM[q.n] * q.tilesN[q.n] * c.groups * (c.ksplit > 1 ? c.ksplit : 1);
       if (blocks > 0x3fffffff) return hipErrorInvalidValue;
       q.end[q.n] = (int)blocks;
-      q.p[q.n++] = c;
+      WgradMany::Layer &y = q.p[q.n++];
+      y.A = c.A; y.B = c.B; y.sAg = c.sAg; y.sBg = c.sBg; y.lda = c.lda; y.ldb = c.ldb; y.Md = c.Md; y.Nd = c.Nd;
+      y.C = c.C; y.C2 = c.C2; y.ldc = c.ldc; y.ldc2 = c.ldc2;
+      y.upd_x = c.upd_x; y.upd_v = c.upd_v; y.upd_m = c.upd_m; y.upd_shadow = c.upd_shadow; y.upd_slot0 = c.upd_slot0;
+      y.ksplit = c.ksplit; y.kchunk = c.kchunk; y.kpart = c.kpart; y.sq64 = c.sq64;
     }
-    if (blocks <= 0) continue;
+    q.Kd = c0.Kd; q.groups = c0.groups; q.accumulate = c0.accumulate; q.sCg = c0.sCg; q.sC2g = c0.sC2g; q.alpha = c0.alpha;
+    q.rows = c0.rows; q.gperm = c0.gperm;
+    q.upd_lr = c0.upd_lr; q.upd_momentum = c0.upd_momentum; q.upd_beta1 = c0.upd_beta1; q.upd_beta2 = c0.upd_beta2;
+    q.upd_eps = c0.upd_eps; q.upd_wd = c0.upd_wd; q.upd_c1 = c0.upd_c1; q.upd_c2 = c0.upd_c2; q.upd_scal = c0.upd_scal;
+    q.upd_sq = c0.upd_sq; q.upd_sSqg = c0.upd_sSqg; q.sSq64g = c0.sSq64g;
+    if (blocks <= 0 && t.blocks == 0) continue;
     q.nblk = (int)blocks;
     q.chunk = (q.nblk + 7) / 8;
     hipError_t e;
-    if (!upd) e = launch_many<EPI_WGRAD, ACT_NONE>(q, shape, s);
-    else if (p[0].upd_opt == OPT_SGD) e = launch_many<EPI_WGRAD_UPD, OPT_SGD>(q, shape, s);
-    else if (p[0].upd_opt == OPT_SHB) e = launch_many<EPI_WGRAD_UPD, OPT_SHB>(q, shape, s);
-    else if (p[0].upd_opt == OPT_ADAMW) e = launch_many<EPI_WGRAD_UPD, OPT_ADAMW>(q, shape, s);
-    else if (p[0].upd_opt == OPT_ADAGRAD) e = launch_many<EPI_WGRAD_UPD, OPT_ADAGRAD>(q, shape, s);
+    if (!upd) e = launch_many<EPI_WGRAD, ACT_NONE>(q, t, shape, c0.fine, s);
+    else if (c0.upd_opt == OPT_SGD) e = launch_many<EPI_WGRAD_UPD, OPT_SGD>(q, t, shape, c0.fine, s);
+    else if (c0.upd_opt == OPT_SHB) e = launch_many<EPI_WGRAD_UPD, OPT_SHB>(q, t, shape, c0.fine, s);
+    else if (c0.upd_opt == OPT_ADAMW) e = launch_many<EPI_WGRAD_UPD, OPT_ADAMW>(q, t, shape, c0.fine, s);
+    else if (c0.upd_opt == OPT_ADAGRAD) e = launch_many<EPI_WGRAD_UPD, OPT_ADAGRAD>(q, t, shape, c0.fine, s);
     else return hipErrorInvalidValue;
     if (e != hipSuccess) return e;
+    std::memset(&t, 0, sizeof(t));                 // (the first launch took it along)
   }
   return hipSuccess;
 }

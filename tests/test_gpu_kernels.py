@@ -599,3 +599,50 @@ def test_large_tile_step_over_many_workers(dims, act, b, M, classes):
         assert rep.guard_intact()
     finally:
         rep.close()
+
+
+# Bias gradients and per-sample statistics in front of a weight-gradient launch: 64 and 256 columns to a block (more than 16
+# partials a column, or not), the last layer summed directly up to 1024 samples (16 classes) or 256 (more), sample blocks of 64,
+# workers with batches of their own; every form of the update and the separate statistics agree.
+@pytest.mark.parametrize("dims,sizes", [((784, 264, 16), [1024] * 2), ((784, 264, 16), [1025] * 2), ((136, 520, 264, 17), [256, 65, 2]),
+                                        ((136, 520, 264, 17), [257, 129, 64]), ((64, 72, 40, 100), [33] * 3), ((64, 136, 10), [2300] * 4)])
+def test_the_end_of_a_step_in_front_of_the_weight_gradients(dims, sizes):
+    A = _A()
+    M, cap = len(sizes), max(sizes)
+    out = []
+    for fused, mask in ((True, 1), (False, 1), (True, 3)):
+        w = W.Workload("tail", dims, W.ACT_GELU, True, W.PREC_BF16, N=2048, M=M, H=1, rounds=1, b0=cap, b_cap=cap, opt=W.OPT_SHB, lr=0.05,
+                       momentum=0.9, test=W.TEST_IP if mask == 3 else W.TEST_NORM, theta=0.9, data="teacher_mlp", seed=7)
+        X, y = W.make_dataset(w)
+        x0 = W.make_x0(w)
+        rep = A.Replicas.from_workload(w, X, y, x0)
+        orc = O.Replicas(O.Net(w.dims, w.act, True), x0, X, y, M, opt=w.opt, momentum=w.momentum, mixed=True)
+        try:
+            rep.set_fused_update(fused)
+            idx = W.step_indices(w, 0, 0, cap)
+            rows = [idx[m][:s] for m, s in enumerate(sizes)]
+            if len(set(sizes)) == 1:
+                rep.local_step(idx, w.lr)
+            else:
+                rep.local_step_ragged(rows, w.lr)
+            orc.local_step(rows, w.lr)
+            res = rep.norm_test(0.5)
+            for m in range(M):
+                st = orc.stats[m]
+                for got, want in ((res[m].sum_sq, st["S1"]), (res[m].gbar_sq, st["S2"]), (res[m].loss_sum, st["loss_sum"])):
+                    assert abs(got - want) <= 2e-3 * abs(want), (m, got, want)
+                at = 0                             # layer by layer: the bias gradients apart
+                grad = rep.get_grad(m).astype(np.float64)
+                for fin, fout in zip(dims[:-1], dims[1:]):
+                    bias = slice(at + fin * fout, at + fin * fout + fout)
+                    assert np.linalg.norm(grad[bias] - orc.grads[m][bias]) <= 4e-3 * np.linalg.norm(orc.grads[m][bias]), (m, fout)
+                    at = bias.stop
+            n = [rep.get_per_sample(m, sizes[m])[0] for m in range(M)]
+            out.append(([rep.get_params(m) for m in range(M)], n, [(r.sum_sq, r.loss_sum) for r in res]))
+            assert rep.guard_intact()
+        finally:
+            rep.close()
+    for other in out[1:]:
+        for m in range(M):
+            assert np.array_equal(out[0][0][m], other[0][m]) and np.array_equal(out[0][1][m], other[1][m]), m
+            np.testing.assert_allclose(out[0][2][m], other[2][m], rtol=1e-12)      # (the samples' sums in double, other blocks)
