@@ -674,8 +674,8 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
   const int L = pl.L, M = pl.M, isb = pl.bf16 ? 1 : 0;
   const int *rows = nullptr, *gperm = nullptr;
   if (b_host) {
-    // row counts, and an order of the groups in which each of the 8 XCDs (which take contiguous ranges of
-    // that order) gets about the same number of rows: sort by size, deal in snake order
+    // row counts, and an order of the groups in which each of the 8 XCDs (which take contiguous ranges of that order in
+    // the weight gradients) gets about the same number of rows: sort by size, deal in snake order
     std::vector<int> both(2 * (size_t)M);
     std::copy(b_host, b_host + M, both.begin());
     std::vector<int> order(M);
@@ -732,7 +732,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       std::memset(&p, 0, sizeof(p));
       p.A = act_ptr(pl.o_A[l - 1]); p.sAg = cap * pl.ld[l - 1]; p.lda = pl.ld[l - 1];
       p.B = wptr(l); p.sBg = pl.Ppad; p.ldb = pl.dims[l - 1];
-      p.Md = b; p.Nd = pl.dims[l]; p.Kd = pl.dims[l - 1]; p.groups = M; p.rows = rows; p.gperm = gperm;
+      p.Md = b; p.Nd = pl.dims[l]; p.Kd = pl.dims[l - 1]; p.groups = M; p.rows = rows; p.rows_host = b_host;
       if (hb) { p.bias = xm + pl.offB[l]; p.sBiasg = pl.Ppad; }
       p.act = c->cfg.act;
       if (l < L) {
@@ -771,7 +771,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       std::memset(&p, 0, sizeof(p));
       p.A = act_ptr(pl.o_Dl[l]); p.sAg = cap * pl.ld[l]; p.lda = pl.ld[l];
       p.B = wptr(l); p.sBg = pl.Ppad; p.ldb = pl.dims[l - 1]; p.b_trans = 1;
-      p.Md = b; p.Nd = pl.dims[l - 1]; p.Kd = pl.dims[l]; p.groups = M; p.rows = rows; p.gperm = gperm;
+      p.Md = b; p.Nd = pl.dims[l - 1]; p.Kd = pl.dims[l]; p.groups = M; p.rows = rows; p.rows_host = b_host;
       p.C = act_ptr(pl.o_Dl[l - 1]); p.sCg = cap * pl.ld[l - 1]; p.ldc = pl.ld[l - 1]; p.pad_to_ld = 1;
       p.act = c->cfg.act;
       p.E = pl.gelu ? act_ptr(pl.o_Dact[l - 1]) : act_ptr(pl.o_A[l - 1]);
@@ -1014,7 +1014,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       GemmP p;
       std::memset(&p, 0, sizeof(p));
       p.A = act_ptr(pl.o_A[l - 1]); p.sAg = cap * pl.ld[l - 1]; p.lda = pl.ld[l - 1];
-      p.Md = b; p.Nd = pl.dims[l]; p.Kd = pl.dims[l - 1]; p.groups = M; p.rows = rows; p.gperm = gperm;
+      p.Md = b; p.Nd = pl.dims[l]; p.Kd = pl.dims[l - 1]; p.groups = M; p.rows = rows; p.rows_host = b_host;
       p.ldb = pl.dims[l - 1]; p.sBg = pl.Ppad;
       if (hb) { p.bias = grad + pl.offB[l]; p.sBiasg = pl.Ppad; }
       if (pl.bf16) {

@@ -55,9 +55,10 @@ struct GemmP {
   // grid.  Memory beyond a group's own rows is neither read nor written.
   const int *rows;
   int rows_is_k;
-  // Optional (device, bf16 family): the order in which the launch walks the groups.  Work-group ids are dealt
+  const int *rows_host;        // the same counts on the host (rows_is_k == 0, bf16 family): the grid has only the tiles they make
+  // Optional (device, EPI_WGRAD of the bf16 family): the order in which the launch walks the groups.  Work-group ids are dealt
   // to the XCDs in contiguous ranges of groups, so with ragged groups the host orders them such that every
-  // XCD gets about the same number of rows.
+  // XCD gets about the same number of rows to reduce over.
   const int *gperm;
   int accumulate;              // EPI_WGRAD: C = alpha * acc + C  (micro-batch accumulation)
   // Split reduction (EPI_WGRAD of the bf16 family, optional): ksplit > 1 cuts k into ksplit slices of

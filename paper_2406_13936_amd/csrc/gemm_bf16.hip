@@ -227,6 +227,34 @@ __device__ __forceinline__ void wait_frags(bf16x8 (&a)[MI], bf16x8 (&b)[NI]) {
 // nearly so (12 panels) and not 2 x 16 (18).
 constexpr int BAND = 8;
 
+// Ragged groups with extents of their own along m: tile lb of those that exist, group by group, is tile t of group g.  Numbering
+// the tiles of the largest extent for every group instead, an XCD's share of whole groups is what its groups happen to have: 16
+// workers of 1024 to 8192 rows, the largest paired with the smallest, gave one XCD a third more than the mean.  3072-2048-2048-2048-100:
+// forward 587 -> 526 us, inner products 505 -> 464, backward-data 501 -> 464, logits 94 -> 63, the step 6750 -> 6299.
+// One lane per group, a scan, 64 groups at a time; uniform over the wavefront.
+template <int BM>
+__device__ __forceinline__ bool ragged_tile(const int *__restrict__ rows, int groups, int tilesN, int lb, int &g, int &t) {
+  const int lane = threadIdx.x & 63;
+  t = lb;
+  for (int g0 = 0; g0 < groups; g0 += 64) {
+    int sum = g0 + lane < groups ? (rows[g0 + lane] + BM - 1) / BM * tilesN : 0;
+    const int own = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int up = __shfl_up(sum, d);
+      if (lane >= d) sum += up;
+    }
+    const int before = __popcll(__ballot(sum <= t));           // groups that end in front of the tile
+    if (before < 64) {
+      g = g0 + before;
+      t -= __builtin_amdgcn_readlane(sum - own, before);
+      return true;
+    }
+    t -= __builtin_amdgcn_readlane(sum, 63);
+  }
+  return false;
+}
+
 // ---- the kernel --------------------------------------------------------------------------
 //
 // Main loop of the 256 x 256 tile.  64 KB of operands per k-tile of 64 and 256 x 256 outputs is what a CU has to take in
@@ -267,16 +295,23 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   bf16_t *smem = reinterpret_cast<bf16_t *>(smem_raw);
 
-  const int per_g = tilesM * tilesN;
-  const int vg = lb / per_g;                      // group, or (group, k-slice) pair of a split reduction
-  const int t = lb - vg * per_g;
+  int g, t, ksl = 0, rowsM = tilesM;              // group, tile of the group, k-slice, the group's rows of tiles
   const int ksplit = (EPI == EPI_WGRAD && pin.ksplit > 1) ? pin.ksplit : 1;   // (no split with the step fused)
-  const int gv = vg / ksplit, ksl = vg - gv * ksplit;
-  const int g = pin.gperm ? pin.gperm[gv] : gv;   // position in the launch order -> group
+  if (!IS_WGRAD && pin.rows) {                    // only the tiles that ragged groups have are numbered (ragged_blocks)
+    if (!ragged_tile<BM>(pin.rows, pin.groups, tilesN, lb, g, t)) return;
+    rowsM = (pin.rows[g] + BM - 1) / BM;
+  } else {
+    const int per_g = tilesM * tilesN;
+    const int vg = lb / per_g;                    // group, or (group, k-slice) pair of a split reduction
+    t = lb - vg * per_g;
+    const int gv = vg / ksplit;
+    ksl = vg - gv * ksplit;
+    g = pin.gperm ? pin.gperm[gv] : gv;           // position in the launch order -> group
+  }
   int tm, tn;
   if (BM == 256 && tilesN > BAND) {               // bands of columns (see BAND), row by row inside a band
-    const int nb = (tilesN + BAND - 1) / BAND, bw = (tilesN + nb - 1) / nb, b = t / (bw * tilesM);
-    const int w = min(bw, tilesN - b * bw), r = t - b * bw * tilesM;
+    const int nb = (tilesN + BAND - 1) / BAND, bw = (tilesN + nb - 1) / nb, b = t / (bw * rowsM);
+    const int w = min(bw, tilesN - b * bw), r = t - b * bw * rowsM;
     tm = r / w; tn = b * bw + r - tm * w;
   } else {
     tm = t / tilesN; tn = t - tm * tilesN;
@@ -1038,6 +1073,13 @@ __global__ void __launch_bounds__(256) wgrad_many_kernel(const WgradMany q, cons
   gemm_bf16_tile<BM, BN, BK, WM, WN, 2, false, true, true, EPI, ACT>(p, q.tilesM[l], q.tilesN[l], lb);
 }
 
+// Tiles that ragged groups have (ragged_tile)
+long long ragged_blocks(const GemmP &p, int bm, int tilesN) {
+  long long n = 0;
+  for (int g = 0; g < p.groups; ++g) n += (long long)((p.rows_host[g] + bm - 1) / bm) * tilesN;
+  return n;
+}
+
 template <int BM, int BN, int BK, int WM, int WN, int NS, bool PP, bool AT, bool BT, int EPI, int ACT>
 hipError_t launch_cfg(const GemmP &p, hipStream_t s) {
   constexpr int NT = WM * WN * 64;
@@ -1056,9 +1098,10 @@ hipError_t launch_cfg(const GemmP &p, hipStream_t s) {
   });
   if (attr_err != hipSuccess) return attr_err;
   const int tilesM = (p.Md + BM - 1) / BM, tilesN = (p.Nd + BN - 1) / BN;
-  const long long nblk = (long long)tilesM * tilesN * p.groups * ((EPI == EPI_WGRAD && p.ksplit > 1) ? p.ksplit : 1);
+  long long nblk = (long long)tilesM * tilesN * p.groups * ((EPI == EPI_WGRAD && p.ksplit > 1) ? p.ksplit : 1);
   if (nblk <= 0) return hipSuccess;
   if (nblk > 0x3fffffff) return hipErrorInvalidValue;
+  if (EPI != EPI_WGRAD && EPI != EPI_WGRAD_UPD && p.rows) nblk = ragged_blocks(p, BM, tilesN);
   const int chunk = (int)((nblk + 7) / 8);
   hipLaunchKernelGGL(kern, dim3(chunk * 8), dim3(NT), lds, s, p, tilesM, tilesN, (int)nblk, chunk);
   return hipGetLastError();
@@ -1203,6 +1246,10 @@ bool operands_ok(const GemmP &p, int epi) {
   if (p.ksplit > 1 && (epi != EPI_WGRAD || !p.kpart || p.kchunk <= 0 || (p.kchunk & 63) ||
                        (long long)p.kchunk * p.ksplit < p.Kd || (p.Nd & 3)))
     return false;
+  if (p.rows && epi != EPI_WGRAD) {               // the grid has exactly the tiles that these counts make
+    if (!p.rows_host || p.rows_is_k) return false;
+    for (int g = 0; g < p.groups; ++g) if (p.rows_host[g] < 1 || p.rows_host[g] > p.Md) return false;
+  }
   if (p.sq64 && (epi != EPI_WGRAD || p.ksplit > 1 || p.upd_x)) return false;
   if (epi == EPI_WGRAD && !p.C && (!p.C2 || p.accumulate || p.ksplit > 1 || p.upd_x)) return false;
   if (p.part2 && epi != EPI_IPDOT) return false;

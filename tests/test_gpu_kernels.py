@@ -646,3 +646,36 @@ def test_the_end_of_a_step_in_front_of_the_weight_gradients(dims, sizes):
         for m in range(M):
             assert np.array_equal(out[0][0][m], other[0][m]) and np.array_equal(out[0][1][m], other[1][m]), m
             np.testing.assert_allclose(out[0][2][m], other[2][m], rtol=1e-12)      # (the samples' sums in double, other blocks)
+
+
+# Launches over workers with batches of their own number only the tiles that the workers have: extents at the edges of 64, 128 and
+# 256 rows, outputs in bands (wider than eight 256-wide tiles), narrow logits, more workers than a wavefront has lanes.  Sample i's
+# activations and signals do not depend on who else is in the batch: norms bit for bit those of a step on the whole batches.
+@pytest.mark.parametrize("dims,sizes", [
+    ((72, 512, 264, 100), [501, 2, 64, 65]),                                         # 64 x 128
+    ((136, 520, 40), [1030, 128, 129, 1025, 2, 127, 384, 1030]),                     # 128 x 128, 128 x 64
+    ((40, 2312, 264, 12), [600, 2, 256, 257, 512, 513, 255, 300]),                   # 256 x 256, in bands
+    ((72, 264, 264, 100), [257, 2, 129] * 22 + [64, 300, 128, 300]),                 # 70 workers
+    ((72, 1032, 1032, 100), [1024, 2, 256] * 21 + [2, 2, 513]),                      # 66 workers, the last ones short
+])
+def test_ragged_launches_number_the_tiles_that_there_are(dims, sizes):
+    A = _A()
+    M, cap = len(sizes), max(sizes)
+    w = W.Workload("ragged", dims, W.ACT_GELU, True, W.PREC_BF16, N=2048, M=M, H=1, rounds=1, b0=cap, b_cap=cap, opt=W.OPT_SGD, lr=0.0,
+                   test=W.TEST_IP, theta=0.9, data="teacher_mlp", seed=13)
+    X, y = W.make_dataset(w)
+    rep = A.Replicas.from_workload(w, X, y, W.make_x0(w))
+    try:
+        idx = W.step_indices(w, 0, 0, cap)
+        rep.local_step(idx, 0.0)
+        whole = [rep.get_per_sample(m, cap)[0] for m in range(M)]
+        rep.local_step_ragged([idx[m][:s] for m, s in enumerate(sizes)], 0.0)
+        res = rep.inner_product_test(0.9)
+        for m, s in enumerate(sizes):
+            n, q = rep.get_per_sample(m, s, want_q=True)
+            assert np.array_equal(n, whole[m][:s]), m
+            # sum of q_i = b <gbar, gbar rounded to bf16>: off b ||gbar||^2 by at most 2^-9 of it (and fp32 sums)
+            assert abs(q.astype(np.float64).sum() - s * res[m].gbar_sq) <= 2.0 ** -8 * s * res[m].gbar_sq, m
+        assert rep.guard_intact()
+    finally:
+        rep.close()
