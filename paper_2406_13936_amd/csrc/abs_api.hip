@@ -721,9 +721,13 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
   if (ph.passes) {
     // batch gather (Alg. 1: "sample the local batch")
     const void *Xsrc = pl.bf16 ? static_cast<const void *>(c->at<bf16_t>(pl.o_Xbf)) : static_cast<const void *>(c->X);
-    { ProfScope ps_(c, T_GATHER, 0.0, 2.0 * M * b * pl.dims[0] * pl.esz);
-    HIPCHK(c, launch_gather_rows(isb, Xsrc, pl.dims[0], (int)c->N, idx_dev, ldi, M, b, act_ptr(pl.o_A[0]), cap * pl.ld[0],
-                                 pl.ld[0], c->at<float>(pl.o_an[0]), cap, rows, s)); }
+    GatherP ga = {Xsrc, pl.dims[0], (int)c->N, idx_dev, ldi, b, M, act_ptr(pl.o_A[0]), cap * pl.ld[0], pl.ld[0],
+                  c->at<float>(pl.o_an[0]), cap, rows};
+    const int ride = gather_rides(isb, L, b, pl.dims.data(), M, c->N, rows != nullptr);
+    if (!ride) {
+      ProfScope ps_(c, T_GATHER, 0.0, 2.0 * M * b * pl.dims[0] * pl.esz);
+      HIPCHK(c, launch_gather_rows(isb, ga, s));
+    }
 
     // forward
     const bool head_fused = gemm_head_fits(isb, b, pl.dims[L], M);
@@ -735,6 +739,8 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       p.Md = b; p.Nd = pl.dims[l]; p.Kd = pl.dims[l - 1]; p.groups = M; p.rows = rows; p.rows_host = b_host;
       if (hb) { p.bias = xm + pl.offB[l]; p.sBiasg = pl.Ppad; }
       p.act = c->cfg.act;
+      if (ride && l == 1) { p.A = Xsrc; p.sAg = 0; p.lda = pl.dims[0]; p.aidx = idx_dev; p.aN = (int)c->N; p.aldi = ldi; }
+      if (ride == (l == 1 ? 1 : l == L ? 2 : 3)) p.gather = &ga;
       if (l < L) {
         p.C = act_ptr(pl.o_A[l]); p.sCg = cap * pl.ld[l]; p.ldc = pl.ld[l]; p.pad_to_ld = 1;
         if (pl.gelu) { p.C2 = act_ptr(pl.o_Dact[l]); p.sC2g = cap * pl.ld[l]; p.ldc2 = pl.ld[l]; }

@@ -30,6 +30,22 @@ struct HeadP {
   float *dn, *loss; long long sNg;
 };
 
+struct GatherP {
+  const void *X; int d, N;               // dataset: N rows of d elements
+  const int32_t *idx; int ldi, b, groups;
+  void *A0; long long sA0g; int ldo;
+  float *an0; long long sNg;
+  const int *rows;                       // ragged groups (optional): rows[g] <= b of them
+};
+inline long long gather_blocks(const GatherP &p) { return (long long)((p.b + 3) / 4) * p.groups; }
+constexpr long long GATHER_RIDES = 1024;       // blocks that may ride with another launch
+inline bool gather_ok(const GatherP &p) {
+  return p.X && p.idx && p.A0 && p.an0 && p.N > 0 && p.d > 0 && p.ldo >= p.d && p.ldi >= p.b && gather_blocks(p) <= GATHER_RIDES;
+}
+// Which launch of the step takes the gather along (GemmP::gather), the first layer's contraction (1) or the logits (2), or none (0);
+// the first layer then reads its rows from the dataset (GemmP::aidx).
+int gather_rides(int is_bf16, int L, int b, const int *dims, int groups, long long N, bool ragged);
+
 struct GemmP {
   const void *A, *B;           // operands (bf16 bits or float, by kernel family)
   long long sAg, sBg;          // group (replica) strides in elements
@@ -41,6 +57,9 @@ struct GemmP {
   const float *bias; long long sBiasg;   // per-column vector (may be null)
   const void *E; long long sEg; int lde; // elementwise operand of the epilogue
   HeadP head;                  // EPI_LOGITS (optional)
+  const GatherP *gather;       // EPI_FWD_ACT, EPI_LOGITS (optional, host): the gather's blocks ride behind the tiles (bf16: gemm_small.hip)
+  const int32_t *aidx;         // EPI_FWD_ACT, EPI_LOGITS (optional): row i of group g is row aidx[g * aldi + i], clamped, of the
+  int aN, aldi;                //   aN rows at A (sAg 0; bf16: lda a multiple of 8, gemm_small.hip or 64 x 128 tiles)
   float *part; long long sPartg; long long sPartTile; // row partials: part[g][tile_n][m]
                                //   EPI_IPDOT: the row dots; EPI_FWD_ACT / EPI_BWD (bf16 family, optional):
                                //   sum over the tile's columns of the squared stored outputs
@@ -158,9 +177,7 @@ hipError_t launch_convert_f32_to_bf16(const float *src, bf16_t *dst, long long n
 // A0[g][i][:] = X[idx[g][i]][:]  and  an0[g][i] = ||row||^2
 // Every launcher below takes `rows` (device, may be null): per-group row counts that replace b
 // (then b is the largest count and sizes the grid).  `ldi` is the row stride of idx.
-hipError_t launch_gather_rows(int is_bf16, const void *X, int d, int N, const int32_t *idx, int ldi, int groups,
-                              int b, void *A0, long long sA0g, int ldo, float *an0, long long sNg,
-                              const int *rows, hipStream_t s);
+hipError_t launch_gather_rows(int is_bf16, const GatherP &p, hipStream_t s);
 // softmax cross-entropy head: delta = p - e_y (stored in T, pad columns zeroed),
 // dn[g][i] = ||stored delta_i||^2, loss[g][i] = f_i
 hipError_t launch_softmax_ce(int is_bf16, const float *Z, long long sZg, int ldz, int K,

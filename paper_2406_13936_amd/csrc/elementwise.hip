@@ -5,6 +5,7 @@
 #include <algorithm>
 #include "abs_internal.h"
 #include "device_utils.h"
+#include "gather.h"
 #include "step_tail.h"
 
 namespace absk {
@@ -37,31 +38,9 @@ __device__ __forceinline__ void st_stream(uint2 *p, uint2 v) {
   __builtin_nontemporal_store(w, reinterpret_cast<u32x2_t *>(p));
 }
 
-template <class T> struct Vec;                      // 16-byte vector of T
-template <> struct Vec<float> {
-  enum { N = 4 };
-  static __device__ __forceinline__ void load(const float *p, float (&o)[4]) {
-    const float4 v = *reinterpret_cast<const float4 *>(p);
-    o[0] = v.x; o[1] = v.y; o[2] = v.z; o[3] = v.w;
-  }
-};
-template <> struct Vec<bf16_t> {
-  enum { N = 8 };
-  static __device__ __forceinline__ void unpack(uint4 v, float (&o)[8]) {
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      o[2 * i] = __uint_as_float(w[i] << 16);
-      o[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-    }
-  }
-  static __device__ __forceinline__ void load(const bf16_t *p, float (&o)[8]) {
-    unpack(*reinterpret_cast<const uint4 *>(p), o);
-  }
-  static __device__ __forceinline__ void load_stream(const bf16_t *p, float (&o)[8]) {
-    unpack(ld_stream(reinterpret_cast<const uint4 *>(p)), o);
-  }
-};
+__device__ __forceinline__ void load_stream8(const bf16_t *p, float (&o)[8]) {
+  Vec<bf16_t>::unpack(ld_stream(reinterpret_cast<const uint4 *>(p)), o);
+}
 
 __global__ void convert_kernel(const float *__restrict__ src, bf16_t *__restrict__ dst, long long n) {
   long long i = (blockIdx.x * (long long)blockDim.x + threadIdx.x) * 4;
@@ -77,43 +56,8 @@ __global__ void convert_kernel(const float *__restrict__ src, bf16_t *__restrict
     for (long long j = n & ~3LL; j < n; ++j) dst[j] = f2bf(src[j]);
 }
 
-// One wavefront per gathered row.  Source rows have d elements (row stride d); the
-// destination row stride is ldo >= d (multiple of 8), pad columns are written as zeros.
-// Indices outside [0, N) are clamped into the range (the kernels never read out of bounds).
 template <class T>
-__global__ void gather_kernel(const T *__restrict__ X, int d, int N, const int32_t *__restrict__ idx, int ldi, int b,
-                              T *__restrict__ A0, long long sAg, int ldo, float *__restrict__ an0,
-                              long long sNg, const int *__restrict__ rows) {
-  const int g = blockIdx.y;
-  const int i = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (i >= (rows ? rows[g] : b)) return;
-  const int lane = threadIdx.x & 63;
-  const int32_t id = min(max(idx[(long long)g * ldi + i], 0), N - 1);
-  const long long src = (long long)id * d;
-  T *dst = A0 + (long long)g * sAg + (long long)i * ldo;
-  float s = 0.0f;
-  constexpr int V = Vec<T>::N;
-  if ((d % V) == 0) {
-    for (int c = lane * V; c < d; c += 64 * V) {
-      const uint4 raw = *reinterpret_cast<const uint4 *>(X + src + c);
-      float f[V];
-      Vec<T>::load(X + src + c, f);
-#pragma unroll
-      for (int k = 0; k < V; ++k) s = fmaf(f[k], f[k], s);
-      *reinterpret_cast<uint4 *>(dst + c) = raw;
-    }
-  } else {
-    for (int c = lane; c < d; c += 64) {
-      const T raw = X[src + c];
-      const float f = Elem<T>::ld(&raw);
-      s = fmaf(f, f, s);
-      dst[c] = raw;
-    }
-  }
-  for (int c = d + lane; c < ldo; c += 64) Elem<T>::st(dst + c, 0.0f);
-  s = wave_sum(s);
-  if (lane == 0) an0[(long long)g * sNg + i] = s;
-}
+__global__ void __launch_bounds__(256) gather_kernel(const GatherP p) { gather_rows_block<T>(p, blockIdx.y, blockIdx.x); }
 
 // LPR lanes per row of logits: a whole wavefront, or 16 lanes (four rows per wavefront) for at most 16
 // classes.  The butterflies stay inside a row's lanes (xor distances below LPR).
@@ -494,10 +438,10 @@ __global__ void __launch_bounds__(256) average_bf16_kernel(bf16_t *__restrict__ 
   const float Mf = (float)groups;
   for (long long i = blockIdx.x * 256LL + threadIdx.x; i < n8; i += stride) {
     float s[8];
-    Vec<bf16_t>::load_stream(x + i * 8, s);
+    load_stream8(x + i * 8, s);
     for (int g = 1; g < groups; ++g) {
       float v[8];
-      Vec<bf16_t>::load_stream(x + (long long)g * n + i * 8, v);
+      load_stream8(x + (long long)g * n + i * 8, v);
 #pragma unroll
       for (int k = 0; k < 8; ++k) s[k] += v[k];
     }
@@ -567,7 +511,7 @@ __global__ void __launch_bounds__(256) average_bf16_reduce_kernel(const bf16_t *
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const long long i = base + u * 256;
-    if (i < n8) Vec<bf16_t>::load_stream(x + i * 8, s[u]);
+    if (i < n8) load_stream8(x + i * 8, s[u]);
   }
   for (int g = 1; g < groups; ++g) {
 #pragma unroll
@@ -575,7 +519,7 @@ __global__ void __launch_bounds__(256) average_bf16_reduce_kernel(const bf16_t *
       const long long i = base + u * 256;
       if (i < n8) {
         float v[8];
-        Vec<bf16_t>::load_stream(x + (long long)g * n + i * 8, v);
+        load_stream8(x + (long long)g * n + i * 8, v);
 #pragma unroll
         for (int k = 0; k < 8; ++k) s[u][k] += v[k];
       }
@@ -746,16 +690,10 @@ hipError_t launch_convert_f32_to_bf16(const float *src, bf16_t *dst, long long n
   return hipGetLastError();
 }
 
-hipError_t launch_gather_rows(int is_bf16, const void *X, int d, int N, const int32_t *idx, int ldi, int groups, int b,
-                              void *A0, long long sA0g, int ldo, float *an0, long long sNg, const int *rows,
-                              hipStream_t s) {
-  const dim3 grid((b + 3) / 4, groups), blk(256);
-  if (is_bf16)
-    hipLaunchKernelGGL(gather_kernel<bf16_t>, grid, blk, 0, s, static_cast<const bf16_t *>(X), d, N, idx, ldi, b,
-                       static_cast<bf16_t *>(A0), sA0g, ldo, an0, sNg, rows);
-  else
-    hipLaunchKernelGGL(gather_kernel<float>, grid, blk, 0, s, static_cast<const float *>(X), d, N, idx, ldi, b,
-                       static_cast<float *>(A0), sA0g, ldo, an0, sNg, rows);
+hipError_t launch_gather_rows(int is_bf16, const GatherP &p, hipStream_t s) {
+  const dim3 grid((p.b + 3) / 4, p.groups), blk(256);
+  if (is_bf16) hipLaunchKernelGGL(gather_kernel<bf16_t>, grid, blk, 0, s, p);
+  else hipLaunchKernelGGL(gather_kernel<float>, grid, blk, 0, s, p);
   return hipGetLastError();
 }
 

@@ -33,6 +33,7 @@
 #include <utility>
 #include "abs_internal.h"
 #include "device_utils.h"
+#include "gather.h"
 #include "step_tail.h"
 
 namespace absk {
@@ -120,6 +121,15 @@ struct Operand {
         kofs[i] = kq;
         voff[i] = (row0 + ch * 8 < rows) ? (uint32_t)(kq * ld + row0 + ch * 8) * 2u : OOB;
       }
+    }
+  }
+  // rows from elsewhere: matrix row r at row_of(r) of the operand (k-contiguous)
+  template <class F>
+  __device__ __forceinline__ void init_rows(int wave, int lane, int row0, int rows, int ld, F row_of) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int mrow = row0 + ((wave * NI + i) * 64 + lane) / CPR;
+      if (mrow < rows) voff[i] = ((uint32_t)row_of(mrow) * (uint32_t)ld + (uint32_t)kofs[i]) * 2u;
     }
   }
   // byte offset added for k-tile kt (scalar)
@@ -277,7 +287,10 @@ __device__ __forceinline__ bool ragged_tile(const int *__restrict__ rows, int gr
 // Measured, 16 replicas, against the two-stage loop: inner products 8192 x 2048 x 2048 1017 -> 850 us (1.30 PFLOP/s),
 // forward 1160 -> 1043, backward-data 1110 -> 922, weight gradient with the step in its epilogue 1178 -> 993.
 // (the work of one work-group: tile lb of the tilesM x tilesN x groups of a launch)
-template <int BM, int BN, int BK, int WM, int WN, int NS, bool PP, bool AT, bool BT, int EPI, int ACT>
+// MODE, a kernel of its own each, since what the short launches do not need costs them up to 0.7 of 11 us in front of their first
+// load: ROWS_OWN: ragged groups (not the weight gradients); ROWS_DATASET: the rows of A are rows of the dataset (GemmP::aidx).
+enum { ROWS_PLAIN = 0, ROWS_OWN = 1, ROWS_DATASET = 2 };
+template <int BM, int BN, int BK, int WM, int WN, int NS, bool PP, bool AT, bool BT, int EPI, int ACT, int MODE = ROWS_PLAIN>
 __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tilesM, const int tilesN, const int lb) {
   constexpr int NW = WM * WN, NT = NW * 64;
   constexpr int TM = BM / WM, TN = BN / WN;
@@ -286,6 +299,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
   constexpr int STAGE = (BM + BN) * BK;                 // bf16 elements per stage
   constexpr int NPART = BK / 16;                        // MFMA groups per k-tile
   static_assert(TM % 32 == 0 && TN % 32 == 0 && BK % 16 == 0 && NS >= 2, "tile shape");
+  static_assert(MODE == ROWS_PLAIN || !IS_WGRAD, "weight gradients read p.rows");
   typedef Operand<BM, BK, AT, NW> OpA;
   typedef Operand<BN, BK, BT, NW> OpB;
   constexpr int NL = OpA::NI + OpB::NI;                 // load instructions per wave per stage
@@ -297,7 +311,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
 
   int g, t, ksl = 0, rowsM = tilesM;              // group, tile of the group, k-slice, the group's rows of tiles
   const int ksplit = (EPI == EPI_WGRAD && pin.ksplit > 1) ? pin.ksplit : 1;   // (no split with the step fused)
-  if (!IS_WGRAD && pin.rows) {                    // only the tiles that ragged groups have are numbered (ragged_blocks)
+  if constexpr (MODE == ROWS_OWN) {               // only the tiles that ragged groups have are numbered (ragged_blocks)
     if (!ragged_tile<BM>(pin.rows, pin.groups, tilesN, lb, g, t)) return;
     rowsM = (pin.rows[g] + BM - 1) / BM;
   } else {
@@ -306,7 +320,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
     t = lb - vg * per_g;
     const int gv = vg / ksplit;
     ksl = vg - gv * ksplit;
-    g = pin.gperm ? pin.gperm[gv] : gv;           // position in the launch order -> group
+    g = IS_WGRAD && pin.gperm ? pin.gperm[gv] : gv;   // position in the launch order -> group
   }
   int tm, tn;
   if (BM == 256 && tilesN > BAND) {               // bands of columns (see BAND), row by row inside a band
@@ -318,9 +332,9 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
   }
   const int m0 = tm * BM, n0 = tn * BN;
   GemmP p = pin;
-  if (p.rows) {                                   // ragged groups: this group's own extent
+  if (MODE == ROWS_OWN || (IS_WGRAD && p.rows)) { // ragged groups: this group's own extent
     const int r = p.rows[g];
-    if (p.rows_is_k) { p.Kd = r; p.alpha = 1.0f / (float)r; } else p.Md = r;
+    if (IS_WGRAD) { p.Kd = r; p.alpha = 1.0f / (float)r; } else p.Md = r;
     if (m0 >= p.Md) return;                       // uniform over the block, before any barrier
   }
   long long kofsA = 0, kofsB = 0;                 // element offsets of this block's k-slice
@@ -341,7 +355,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
   const bf16_t *B = static_cast<const bf16_t *>(p.B) + (long long)g * p.sBg + kofsB;
   // range = the operand's extent in memory: rows*ld (k-contiguous) or K*ld (row-contiguous)
   const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<bf16_t *>(A), 0, (int)((long long)(AT ? p.Kd : p.Md) * p.lda * 2), 0x00020000);
+      const_cast<bf16_t *>(A), 0, (int)((long long)(AT ? p.Kd : MODE == ROWS_DATASET ? p.aN : p.Md) * p.lda * 2), 0x00020000);
   const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<bf16_t *>(B), 0, (int)((long long)(BT ? p.Kd : p.Nd) * p.ldb * 2), 0x00020000);
 
@@ -524,6 +538,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
     OpB ob;
     oa.init(wave, lane, m0, p.Md, p.lda);
     ob.init(wave, lane, n0, p.Nd, p.ldb);
+    if constexpr (MODE == ROWS_DATASET) oa.init_rows(wave, lane, m0, p.Md, p.lda, [&](int row) { return dataset_row(p, g, row); });
 
     // issue the loads of stage-slot `buf` for k-tile kt whose index l satisfies l % NPART == part
     auto issue = [&](int kt, int buf, int part) {
@@ -987,14 +1002,14 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
   }
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int NS, bool PP, bool AT, bool BT, int EPI, int ACT>
+template <int BM, int BN, int BK, int WM, int WN, int NS, bool PP, bool AT, bool BT, int EPI, int ACT, int MODE>
 __global__ void __launch_bounds__(WM * WN * 64)
 gemm_bf16_kernel(const GemmP pin, const int tilesM, const int tilesN, const int nblk, const int chunk) {
   // XCD-aware remap of the flat work-group id
   const int bid = blockIdx.x;
   const int lb = (bid & 7) * chunk + (bid >> 3);
   if (lb >= nblk) return;
-  gemm_bf16_tile<BM, BN, BK, WM, WN, NS, PP, AT, BT, EPI, ACT>(pin, tilesM, tilesN, lb);
+  gemm_bf16_tile<BM, BN, BK, WM, WN, NS, PP, AT, BT, EPI, ACT, MODE>(pin, tilesM, tilesN, lb);
 }
 
 // Weight gradients of several layers in one launch (64 x 256 x 32 tiles of short batches, two-stage 128 x 128 or 64 x 128
@@ -1080,8 +1095,8 @@ long long ragged_blocks(const GemmP &p, int bm, int tilesN) {
   return n;
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int NS, bool PP, bool AT, bool BT, int EPI, int ACT>
-hipError_t launch_cfg(const GemmP &p, hipStream_t s) {
+template <int BM, int BN, int BK, int WM, int WN, int NS, bool PP, bool AT, bool BT, int EPI, int ACT, int MODE>
+hipError_t launch_mode(const GemmP &p, hipStream_t s) {
   constexpr int NT = WM * WN * 64;
   constexpr size_t tile_bytes = (size_t)NS * (BM + BN) * BK * sizeof(bf16_t);
   constexpr size_t epi_bf16 = (size_t)WM * WN * 32 * (BN / WN + 8) * sizeof(bf16_t) + (size_t)(EPI == EPI_IPDOT ? 2 : 1) * WN * BM * sizeof(float);
@@ -1089,7 +1104,7 @@ hipError_t launch_cfg(const GemmP &p, hipStream_t s) {
   constexpr size_t epi_bytes = epi_bf16 > epi_f32 ? epi_bf16 : epi_f32;
   constexpr size_t lds = tile_bytes > epi_bytes ? tile_bytes : epi_bytes;
   static_assert(lds <= 160 * 1024, "LDS budget");
-  auto kern = gemm_bf16_kernel<BM, BN, BK, WM, WN, NS, PP, AT, BT, EPI, ACT>;
+  auto kern = gemm_bf16_kernel<BM, BN, BK, WM, WN, NS, PP, AT, BT, EPI, ACT, MODE>;
   // once per kernel variant, also when several host threads (each with a context of its own) launch it first together
   static std::once_flag attr_once;
   static hipError_t attr_err = hipSuccess;
@@ -1101,10 +1116,20 @@ hipError_t launch_cfg(const GemmP &p, hipStream_t s) {
   long long nblk = (long long)tilesM * tilesN * p.groups * ((EPI == EPI_WGRAD && p.ksplit > 1) ? p.ksplit : 1);
   if (nblk <= 0) return hipSuccess;
   if (nblk > 0x3fffffff) return hipErrorInvalidValue;
-  if (EPI != EPI_WGRAD && EPI != EPI_WGRAD_UPD && p.rows) nblk = ragged_blocks(p, BM, tilesN);
+  if (MODE == ROWS_OWN) nblk = ragged_blocks(p, BM, tilesN);
   const int chunk = (int)((nblk + 7) / 8);
   hipLaunchKernelGGL(kern, dim3(chunk * 8), dim3(NT), lds, s, p, tilesM, tilesN, (int)nblk, chunk);
   return hipGetLastError();
+}
+
+template <int BM, int BN, int BK, int WM, int WN, int NS, bool PP, bool AT, bool BT, int EPI, int ACT>
+hipError_t launch_cfg(const GemmP &p, hipStream_t s) {
+  if constexpr (EPI != EPI_WGRAD && EPI != EPI_WGRAD_UPD) {
+    if (p.rows) return p.aidx ? hipErrorInvalidValue : launch_mode<BM, BN, BK, WM, WN, NS, PP, AT, BT, EPI, ACT, ROWS_OWN>(p, s);
+    if constexpr (EPI == EPI_FWD_ACT && BM == 64)
+      if (p.aidx) return launch_mode<BM, BN, BK, WM, WN, NS, PP, AT, BT, EPI, ACT, ROWS_DATASET>(p, s);
+  }
+  return p.aidx ? hipErrorInvalidValue : launch_mode<BM, BN, BK, WM, WN, NS, PP, AT, BT, EPI, ACT, ROWS_PLAIN>(p, s);
 }
 
 int tiled_shape(int Md, int Nd, int groups);
@@ -1253,6 +1278,13 @@ bool operands_ok(const GemmP &p, int epi) {
   if (p.sq64 && (epi != EPI_WGRAD || p.ksplit > 1 || p.upd_x)) return false;
   if (epi == EPI_WGRAD && !p.C && (!p.C2 || p.accumulate || p.ksplit > 1 || p.upd_x)) return false;
   if (p.part2 && epi != EPI_IPDOT) return false;
+  if (p.rows && epi == EPI_WGRAD && !p.rows_is_k) return false;
+  if (p.gather || p.aidx) {
+    const int sh = epi == EPI_FWD_ACT || epi == EPI_LOGITS ? gemm_bf16_tile_shape(epi, p.Md, p.Nd, p.groups) : -1;
+    if (p.gather && sh != 5) return false;
+    if (p.aidx && ((sh != 5 && !(sh == 4 && epi == EPI_FWD_ACT)) || p.aN < 1 || p.aldi < p.Md || p.sAg || (long long)p.aN * p.lda * 2 >= (1LL << 31)))
+      return false;
+  }
   if (p.upd_x && (epi != EPI_WGRAD || p.ksplit > 1 || p.accumulate || !p.upd_sq || (p.ldc & 3) || (p.Nd & 3) ||
                   (p.sCg & 3) || (reinterpret_cast<uintptr_t>(p.upd_x) & 15) || (p.C2 && ((p.ldc2 & 3) || p.ldc2 != p.ldc)) ||
                   (p.upd_opt != OPT_SGD && !p.upd_v) || (p.upd_opt == OPT_ADAMW && !p.upd_m)))
@@ -1271,6 +1303,20 @@ int gemm_bf16_tile_shape(int epi, int Md, int Nd, int groups) {
 // (bf16: the 32-row tiles hold 32 columns; fp32: the smallest tile holds 16)
 bool gemm_head_fits(int is_bf16, int Md, int Nd, int groups) {
   return is_bf16 ? Nd <= 32 && gemm_bf16_tile_shape(EPI_LOGITS, Md, Nd, groups) == 5 : Nd <= 16;
+}
+
+// The gather rides with a launch that is a chain of latencies, as long as its blocks find a place beside the tiles (four to a CU):
+// its own launch cost 3 to 8 us and a gap.  us per step: 256-10 in fp32, 4 replicas, b = 16 31.9 -> 28.6, b = 512 39.8 -> 36.6;
+// 784-512-512-10, 8 replicas, b = 32 66 -> 63, b = 501 87 -> 82; 784-144-4, 9 replicas, b = 61 64.4 -> 61.4.  A first layer on
+// 64 x 128 tiles, one work-group to a CU, leaves it to small logits (nothing before the weight gradients needs it).
+// bf16: 16-byte chunks of a dataset row, which has no padding, and 32-bit byte offsets into the dataset.
+int gather_rides(int is_bf16, int L, int b, const int *dims, int groups, long long N, bool ragged) {
+  if ((long long)((b + 3) / 4) * groups > GATHER_RIDES) return 0;
+  if (!is_bf16) return 1;
+  if ((dims[0] & 7) || N * dims[0] * 2 >= (1LL << 31)) return 0;
+  const int first = gemm_bf16_tile_shape(L == 1 ? EPI_LOGITS : EPI_FWD_ACT, b, dims[1], groups);
+  if (first == 5) return 1;
+  return first == 4 && !ragged && L > 1 && gemm_bf16_tile_shape(EPI_LOGITS, b, dims[L], groups) == 5 ? 2 : 0;
 }
 
 // Weight gradients reduce over the local batch (Kd = b).  While the batch is short the launch is all epilogue

@@ -15,6 +15,7 @@
 #include <algorithm>
 #include "abs_internal.h"
 #include "device_utils.h"
+#include "gather.h"
 
 namespace absk {
 namespace {
@@ -24,8 +25,9 @@ constexpr int KSTEP[5] = {0, 256, 128, 0, 32};     // k-step of the tile of 16 t
 // (EPI_WGRAD with GemmP::upd_x: ACT carries the optimizer, NO_STEP without)
 constexpr int NO_STEP = 15;
 
-template <int EPI, int ACT, int TS, int BK>
-__global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmP pin) {
+// GA: the batch gather rides in slices of the grid behind the tiles, which read their rows of A from the dataset.
+template <int EPI, int ACT, int TS, int BK, bool GA>
+__global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmP pin, const GatherP ga) {
   constexpr int PT = TS * BK / 256;              // elements per thread, operand and k-step
   constexpr int R = TS / 16;                     // outputs per thread and dimension
   constexpr int LD = BK + 4;
@@ -35,6 +37,10 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmP pin) {
   __shared__ __attribute__((aligned(16))) float lds[2 * STAGE];
   float *const As = lds, *const Bs = lds + STAGE;
   auto slot = [](int rr, int kk) -> int { return KM ? kk * (TS + 4) + rr : rr * LD + kk; };
+  if (GA && (int)blockIdx.z >= pin.groups) {
+    gather_riding_block<float>(ga, ((int)(blockIdx.z - pin.groups) * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x);
+    return;
+  }
   // blockIdx.z = group, or (group, k-slice) of a weight gradient whose reduction is split
   const int ksplit = (EPI == EPI_WGRAD && pin.ksplit > 1) ? pin.ksplit : 1;
   const int g = blockIdx.z / ksplit, ksl = blockIdx.z - g * ksplit;
@@ -81,6 +87,15 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmP pin) {
     const int id = tid + e * 256;
     if (!trans) { kk = id % BK; rr = id / BK; } else { rr = id % TS; kk = id / TS; }
   };
+  int src[GA ? PT : 1];                           // rows of the dataset
+  if constexpr (GA) {
+#pragma unroll
+    for (int e = 0; e < PT; ++e) {
+      int rr, kk;
+      where(e, false, rr, kk);
+      src[e] = dataset_row(p, g, min(m0 + rr, p.Md - 1));
+    }
+  }
   // addresses are clamped into the operand here; what lies outside it is replaced by zeros on the way to LDS, so that
   // nothing waits for these loads before the multiplications they overlap with
   auto fetch = [&](int k0) {
@@ -89,7 +104,8 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmP pin) {
       int rr, kk;
       where(e, AT, rr, kk);
       const int m = min(m0 + rr, p.Md - 1), k = min(k0 + kk, p.Kd - 1);
-      ra[e] = AT ? A[(long long)k * p.lda + m] : A[(long long)m * p.lda + k];
+      if constexpr (GA) ra[e] = A[(long long)src[e] * p.lda + k];
+      else ra[e] = AT ? A[(long long)k * p.lda + m] : A[(long long)m * p.lda + k];
     }
 #pragma unroll
     for (int e = 0; e < PT; ++e) {
@@ -330,6 +346,14 @@ int tile_size(int Md, int Nd, long long groups) {
   return blocks(64) >= 128 ? 64 : blocks(32) >= 128 ? 32 : 16;
 }
 
+template <int EPI, int ACT, bool GA>
+hipError_t launch2(const GemmP &p, const GatherP &ga, int ts, dim3 grid, hipStream_t s) {
+  if (ts == 16) hipLaunchKernelGGL((gemm_f32_kernel<EPI, ACT, 16, KSTEP[1], GA>), grid, dim3(256), 0, s, p, ga);
+  else if (ts == 32) hipLaunchKernelGGL((gemm_f32_kernel<EPI, ACT, 32, KSTEP[2], GA>), grid, dim3(256), 0, s, p, ga);
+  else hipLaunchKernelGGL((gemm_f32_kernel<EPI, ACT, 64, KSTEP[4], GA>), grid, dim3(256), 0, s, p, ga);
+  return hipGetLastError();
+}
+
 template <int EPI, int ACT>
 hipError_t launch1(const GemmP &p, hipStream_t s) {
   const int ks = (EPI == EPI_WGRAD && p.ksplit > 1) ? p.ksplit : 1;
@@ -341,12 +365,17 @@ hipError_t launch1(const GemmP &p, hipStream_t s) {
   if (ks > 1 && (!p.kpart || p.kchunk <= 0 || (p.kchunk & 31) || (long long)p.kchunk * ks < p.Kd)) return hipErrorInvalidValue;
   const int ts = EPI == EPI_WGRAD && p.f32_tile ? p.f32_tile : tile_size(p.Md, p.Nd, (long long)p.groups * ks);
   if (ts != 16 && ts != 32 && ts != 64) return hipErrorInvalidValue;
-  const dim3 grid((p.Nd + ts - 1) / ts, (p.Md + ts - 1) / ts, p.groups * ks);
+  dim3 grid((p.Nd + ts - 1) / ts, (p.Md + ts - 1) / ts, p.groups * ks);
   if (grid.y > 65535 || grid.z > 65535) return hipErrorInvalidValue;
-  if (ts == 16) hipLaunchKernelGGL((gemm_f32_kernel<EPI, ACT, 16, KSTEP[1]>), grid, dim3(256), 0, s, p);
-  else if (ts == 32) hipLaunchKernelGGL((gemm_f32_kernel<EPI, ACT, 32, KSTEP[2]>), grid, dim3(256), 0, s, p);
-  else hipLaunchKernelGGL((gemm_f32_kernel<EPI, ACT, 64, KSTEP[4]>), grid, dim3(256), 0, s, p);
-  return hipGetLastError();
+  if constexpr (EPI == EPI_FWD_ACT || EPI == EPI_LOGITS) {
+    if (p.gather) {                             // (one variant: the gather rides with the launch that reads the dataset)
+      if (!p.aidx || p.aN < 1 || p.aldi < p.Md || p.sAg || !gather_ok(*p.gather)) return hipErrorInvalidValue;
+      grid.z += (unsigned)((gather_blocks(*p.gather) + grid.x * grid.y - 1) / (grid.x * grid.y));
+      return launch2<EPI, ACT, true>(p, *p.gather, ts, grid, s);
+    }
+  }
+  if (p.gather || p.aidx) return hipErrorInvalidValue;
+  return launch2<EPI, ACT, false>(p, GatherP{}, ts, grid, s);
 }
 template <int EPI>
 hipError_t launch_act(const GemmP &p, hipStream_t s) {

@@ -17,6 +17,7 @@
 // Out-of-range rows and k come back as zeros from the buffer descriptor's range check.
 #include "abs_internal.h"
 #include "device_utils.h"
+#include "gather.h"
 
 namespace absk {
 namespace {
@@ -27,8 +28,9 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr uint32_t OOB = 0x80000000u;   // byte offset beyond any operand (operands are < 2 GiB)
 
-template <bool BT, int EPI, int ACT>
-__global__ void __launch_bounds__(256) gemm_small_kernel(const GemmP p, const int tilesM, const int tilesN) {
+// GA: 1: the batch gather rides behind the tiles; 2: and they read their rows of A from the dataset.
+template <bool BT, int EPI, int ACT, int GA>
+__global__ void __launch_bounds__(256) gemm_small_kernel(const GemmP p, const int tilesM, const int tilesN, const GatherP ga) {
   constexpr int NJ = BT ? 2 : 1;                          // accumulator tiles of 32 x 32 per wave
   constexpr int BN = 32 * NJ, CPT = 4 * NJ;               // columns per work-group, columns per thread at the end
   constexpr int KC = BT ? 32 : 64, KS = KC / 16;          // k per chunk, MFMA steps per chunk
@@ -37,6 +39,10 @@ __global__ void __launch_bounds__(256) gemm_small_kernel(const GemmP p, const in
   __shared__ __attribute__((aligned(16))) float red[4 * 32 * RLD];
 
   int id = blockIdx.x;
+  if (GA != 0) {
+    const int tiles = tilesM * tilesN * p.groups;
+    if (id >= tiles) { gather_riding_block<bf16_t>(ga, id - tiles); return; }
+  }
   const int tn = id % tilesN; id /= tilesN;
   const int tm = id % tilesM, g = id / tilesM;
   const int m0 = tm * 32, n0 = tn * BN;
@@ -47,7 +53,7 @@ __global__ void __launch_bounds__(256) gemm_small_kernel(const GemmP p, const in
   const int l32 = lane & 31, half = lane >> 5;
   const bf16_t *A = static_cast<const bf16_t *>(p.A) + (long long)g * p.sAg;
   const bf16_t *B = static_cast<const bf16_t *>(p.B) + (long long)g * p.sBg;
-  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(A), 0, (int)((long long)Md * p.lda * 2), 0x00020000);
+  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(A), 0, (int)((long long)(GA == 2 ? p.aN : Md) * p.lda * 2), 0x00020000);
   const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t *>(B), 0, (int)((long long)(BT ? p.Kd : p.Nd) * p.ldb * 2), 0x00020000);
 
   // outputs of this thread once the waves' partial tiles are added: row mr, columns nc .. nc + CPT - 1
@@ -81,7 +87,11 @@ __global__ void __launch_bounds__(256) gemm_small_kernel(const GemmP p, const in
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[j][r] = 0.0f;
 
-  const uint32_t arow = m0 + l32 < Md ? (uint32_t)((m0 + l32) * p.lda + half * 8) * 2u : OOB;
+  uint32_t arow = OOB;
+  if (m0 + l32 < Md) {
+    const int r = GA == 2 ? dataset_row(p, g, m0 + l32) : m0 + l32;
+    arow = ((uint32_t)r * (uint32_t)p.lda + (uint32_t)half * 8) * 2u;
+  }
   const uint32_t brow = BT ? (n0 + 2 * l32 < p.Nd ? (uint32_t)(half * 8 * p.ldb + n0 + 2 * l32) * 2u : OOB)
                            : (n0 + l32 < p.Nd ? (uint32_t)((n0 + l32) * p.ldb + half * 8) * 2u : OOB);
   for (int kb = wave * KC; kb < p.Kd; kb += D * 4 * KC) {
@@ -242,10 +252,22 @@ __global__ void __launch_bounds__(256) gemm_small_kernel(const GemmP p, const in
 template <bool BT, int EPI, int ACT>
 hipError_t launch1(const GemmP &p, hipStream_t s) {
   const int tilesM = (p.Md + 31) / 32, tilesN = (p.Nd + (BT ? 63 : 31)) / (BT ? 64 : 32);
-  const long long nblk = (long long)tilesM * tilesN * p.groups;
+  long long nblk = (long long)tilesM * tilesN * p.groups;
   if (nblk <= 0) return hipSuccess;
   if (nblk > 0x3fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((gemm_small_kernel<BT, EPI, ACT>), dim3((unsigned)nblk), dim3(256), 0, s, p, tilesM, tilesN);
+  if constexpr (EPI != EPI_BWD) {
+    if (p.gather) {
+      const GatherP &ga = *p.gather;
+      nblk += gather_blocks(ga);
+      if (p.aidx) hipLaunchKernelGGL((gemm_small_kernel<BT, EPI, ACT, 2>), dim3((unsigned)nblk), dim3(256), 0, s, p, tilesM, tilesN, ga);
+      else if constexpr (EPI == EPI_LOGITS)
+        hipLaunchKernelGGL((gemm_small_kernel<BT, EPI, ACT, 1>), dim3((unsigned)nblk), dim3(256), 0, s, p, tilesM, tilesN, ga);
+      else return hipErrorInvalidValue;
+      return hipGetLastError();
+    }
+  }
+  if (p.aidx) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((gemm_small_kernel<BT, EPI, ACT, 0>), dim3((unsigned)nblk), dim3(256), 0, s, p, tilesM, tilesN, GatherP{});
   return hipGetLastError();
 }
 template <bool BT, int EPI>
@@ -269,6 +291,7 @@ hipError_t launch_gemm_small(const GemmP &p, int epi, hipStream_t s) {
                    !p.head.dn || !p.head.loss || p.head.ldd < p.Nd || p.head.ldd > 32 || (p.head.ldd & 7) || (p.head.sDg & 7) ||
                    (reinterpret_cast<uintptr_t>(p.head.D) & 15)))
     return hipErrorInvalidValue;
+  if (p.gather && (epi == EPI_BWD || !gather_ok(*p.gather))) return hipErrorInvalidValue;
   if (epi == EPI_FWD_ACT && p.C2 && ((p.ldc2 & 7) || (p.sC2g & 7) || (reinterpret_cast<uintptr_t>(p.C2) & 15)))
     return hipErrorInvalidValue;
   if (epi == EPI_BWD && p.act != ACT_NONE && (!p.E || (p.lde & 7) || (p.sEg & 7) || (reinterpret_cast<uintptr_t>(p.E) & 15)))

@@ -679,3 +679,42 @@ def test_ragged_launches_number_the_tiles_that_there_are(dims, sizes):
         assert rep.guard_intact()
     finally:
         rep.close()
+
+
+# The batch gather behind the tiles of the first layer or of the logits, as its own launch beyond 1024 blocks of four
+# rows: gathered rows (the gradient reads them), their norms, and a first layer that reads
+# the dataset, against the oracle.
+@pytest.mark.parametrize("prec,dims,sizes", [
+    (W.PREC_F32, (30, 7), [1024] * 4), (W.PREC_F32, (30, 7), [1025] * 4), (W.PREC_F32, (257, 33, 18), [2]), (W.PREC_F32, (100, 66, 10), [33, 2, 17]),
+    (W.PREC_F32, (65, 70), [130] * 13), (W.PREC_BF16, (64, 10), [1024] * 4), (W.PREC_BF16, (64, 10), [1025] * 4), (W.PREC_BF16, (72, 10), [2]),
+    (W.PREC_BF16, (136, 264, 40), [33, 2, 17]), (W.PREC_BF16, (136, 512, 10), [501] * 8),
+    (W.PREC_BF16, (136, 512, 10), [501, 2, 64, 65, 500, 501, 333, 8]),
+])
+def test_the_gather_behind_the_tiles_of_a_contraction(prec, dims, sizes):
+    A = _A()
+    M, cap = len(sizes), max(sizes)
+    w = W.Workload("gather", dims, W.ACT_RELU if len(dims) > 2 else W.ACT_NONE, True, prec, N=2048, M=M, H=1, rounds=1, b0=cap, b_cap=cap,
+                   opt=W.OPT_SGD, lr=0.0, test=W.TEST_NORM, data="teacher_mlp", seed=19)
+    X, y = W.make_dataset(w)
+    x0 = W.make_x0(w)
+    rep = A.Replicas.from_workload(w, X, y, x0)
+    orc = O.Replicas(O.Net(w.dims, w.act, True), x0, X, y, M, opt=w.opt, mixed=prec == W.PREC_BF16)
+    tol = 4e-3 if prec == W.PREC_BF16 else 1e-5      # (signals on a rounding tie of bf16; fp32 sums of at most 1025 terms)
+    try:
+        idx = W.step_indices(w, 0, 0, cap)
+        idx[:, :2] = [0, w.N - 1]                    # the ends of the dataset
+        rows = [idx[m][:s] for m, s in enumerate(sizes)]
+        if len(set(sizes)) == 1:
+            rep.local_step(idx, 0.0)
+        else:
+            rep.local_step_ragged(rows, 0.0)
+        orc.local_step(rows, 0.0)
+        res = rep.norm_test(0.5)
+        for m in range(M):
+            st, grad = orc.stats[m], rep.get_grad(m).astype(np.float64)
+            for got, want in ((res[m].sum_sq, st["S1"]), (res[m].gbar_sq, st["S2"]), (res[m].loss_sum, st["loss_sum"])):
+                assert abs(got - want) <= tol * abs(want), (m, got, want)
+            assert np.linalg.norm(grad - orc.grads[m]) <= tol * np.linalg.norm(orc.grads[m]), m
+        assert rep.guard_intact()
+    finally:
+        rep.close()
