@@ -718,3 +718,34 @@ def test_the_gather_behind_the_tiles_of_a_contraction(prec, dims, sizes):
         assert rep.guard_intact()
     finally:
         rep.close()
+
+
+# The gradient that is formed on demand after a step in the weight gradients' epilogue is the one that the step applied, which the
+# separate update stores: bias sums of a last layer with few column partials (b / 128) beside hidden layers with more than sixteen
+# (784-512-512-100: 12 and 48), and the other way round; summed directly; workers with batches of their own.
+@pytest.mark.parametrize("dims,sizes", [((784, 512, 512, 100), [1500] * 2), ((784, 512, 512, 10), [1100] * 8), ((784, 264, 16), [1025] * 2),
+                                        ((72, 264, 136, 100), [2300] * 2), ((72, 264, 136, 100), [500] * 2), ((72, 264, 136, 17), [1500, 900, 2])])
+def test_the_gradient_on_demand_is_the_one_that_the_step_applied(dims, sizes):
+    A = _A()
+    M, cap = len(sizes), max(sizes)
+    w = W.Workload("demand", dims, W.ACT_RELU, True, W.PREC_BF16, N=4096, M=M, H=1, rounds=1, b0=cap, b_cap=cap, opt=W.OPT_SGD, lr=0.05,
+                   test=W.TEST_NORM, data="teacher_mlp", seed=23)
+    X, y = W.make_dataset(w)
+    x0 = 5.0 * W.make_x0(w)                          # (probabilities from 1e-9 to 1: the sums of the signals are not exact in fp32)
+    idx = W.step_indices(w, 0, 0, cap)
+    out = []
+    for fused in (True, False):
+        rep = A.Replicas.from_workload(w, X, y, x0)
+        try:
+            rep.set_fused_update(fused)
+            if len(set(sizes)) == 1:
+                rep.local_step(idx, w.lr)
+            else:
+                rep.local_step_ragged([idx[m][:s] for m, s in enumerate(sizes)], w.lr)
+            out.append([(rep.get_grad(m), rep.get_params(m)) for m in range(M)])
+            assert rep.guard_intact()
+        finally:
+            rep.close()
+    for m in range(M):
+        assert np.array_equal(out[0][m][0], out[1][m][0]), (m, np.flatnonzero(out[0][m][0] != out[1][m][0])[:8])
+        assert np.array_equal(out[0][m][1], out[1][m][1]), m
