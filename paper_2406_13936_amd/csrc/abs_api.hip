@@ -429,7 +429,7 @@ double gemm_bytes(const abs_ctx *c, const std::vector<GemmP> &v, int epi) { doub
 
 hipError_t gemm(abs_ctx *c, const GemmP &p, int epi, int layer) {
   int shape = !c->pl.bf16 ? 1 : p.fine ? 4 : (epi == EPI_WGRAD ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr)
-                                                                : gemm_bf16_tile_shape(epi, p.Md, p.Nd, p.groups));
+                                                                : gemm_bf16_tile_shape(epi, p.Md, p.Nd, p.groups, p.rows_host));
   ProfScope ps(c, T_GEMM0 + (epi * 6 + shape) * T_LAYERS + layer, gemm_flops(p), gemm_bytes(c, p, epi));
   return c->pl.bf16 ? launch_gemm_bf16(p, epi, c->stream) : launch_gemm_f32(p, epi, c->stream);
 }
@@ -723,7 +723,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
     const void *Xsrc = pl.bf16 ? static_cast<const void *>(c->at<bf16_t>(pl.o_Xbf)) : static_cast<const void *>(c->X);
     GatherP ga = {Xsrc, pl.dims[0], (int)c->N, idx_dev, ldi, b, M, act_ptr(pl.o_A[0]), cap * pl.ld[0], pl.ld[0],
                   c->at<float>(pl.o_an[0]), cap, rows};
-    const int ride = gather_rides(isb, L, b, pl.dims.data(), M, c->N, rows != nullptr);
+    const int ride = gather_rides(isb, L, b, pl.dims.data(), M, c->N, b_host);
     if (!ride) {
       ProfScope ps_(c, T_GATHER, 0.0, 2.0 * M * b * pl.dims[0] * pl.esz);
       HIPCHK(c, launch_gather_rows(isb, ga, s));
@@ -746,7 +746,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
         if (pl.gelu) { p.C2 = act_ptr(pl.o_Dact[l]); p.sC2g = cap * pl.ld[l]; p.ldc2 = pl.ld[l]; }
         if (pl.bf16) {
           // ||a_i^l||^2 as per-tile partials out of the GEMM epilogue (summed by the statistics kernel)
-          an_parts[l] = gemm_bf16_row_parts(EPI_FWD_ACT, b, pl.dims[l], M);
+          an_parts[l] = gemm_bf16_row_parts(EPI_FWD_ACT, b, pl.dims[l], M, b_host);
           if ((size_t)(an_parts[l] * part_ld) > pl.rpart_floats[l]) return cfail(c, ABS_ENOMEM, "row-partial scratch too small for this tile shape");
           if (want_parts) { p.part = c->at<float>(pl.o_an[l]); p.sPartg = (long long)pl.rpart_floats[l]; p.sPartTile = part_ld; }
           HIPCHK(c, gemm(c, p, EPI_FWD_ACT, l));
@@ -784,17 +784,17 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       p.sEg = cap * pl.ld[l - 1]; p.lde = pl.ld[l - 1];
       if (pl.bf16) {
         // ||delta_i^{l-1}||^2 and (with biases) the column sums of delta^{l-1} as epilogue partials
-        dn_parts[l - 1] = gemm_bf16_row_parts(EPI_BWD, b, pl.dims[l - 1], M);
+        dn_parts[l - 1] = gemm_bf16_row_parts(EPI_BWD, b, pl.dims[l - 1], M, b_host);
         if ((size_t)(dn_parts[l - 1] * part_ld) > pl.rpart_floats[l - 1]) return cfail(c, ABS_ENOMEM, "row-partial scratch too small for this tile shape");
         if (want_parts) { p.part = c->at<float>(pl.o_dn[l - 1]); p.sPartg = (long long)pl.rpart_floats[l - 1]; p.sPartTile = part_ld; }
         if (hb && ph.wgrad) {
           p.cpart = c->at<float>(pl.o_colpart_l[l - 1]);
-          p.sCpartg = (long long)gemm_bf16_col_parts(EPI_BWD, b, pl.dims[l - 1], M) * pl.dims[l - 1];
+          p.sCpartg = (long long)gemm_bf16_col_parts(EPI_BWD, b, pl.dims[l - 1], M, b_host) * pl.dims[l - 1];
           if ((size_t)p.sCpartg > pl.colpart_l_per[l - 1]) return cfail(c, ABS_ENOMEM, "column-partial scratch too small for this tile shape");
           // the partials are added up for all layers at once after the weight gradients
           const int e = cf.n++;
-          cf.part[e] = p.cpart; cf.cols[e] = pl.dims[l - 1]; cf.nsplit[e] = gemm_bf16_col_parts(EPI_BWD, b, pl.dims[l - 1], M);
-          gemm_bf16_col_part_shape(EPI_BWD, b, pl.dims[l - 1], M, &cf.tile_m[e], &cf.parts_per_tile[e]);
+          cf.part[e] = p.cpart; cf.cols[e] = pl.dims[l - 1]; cf.nsplit[e] = gemm_bf16_col_parts(EPI_BWD, b, pl.dims[l - 1], M, b_host);
+          gemm_bf16_col_part_shape(EPI_BWD, b, pl.dims[l - 1], M, b_host, &cf.tile_m[e], &cf.parts_per_tile[e]);
           cf.out_off[e] = pl.offB[l - 1];
           cf_bytes += 4.0 * M * cf.nsplit[e] * cf.cols[e];
         }
@@ -1029,7 +1029,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
         p.part = c->at<float>(pl.o_qpart[l - 1]);
         p.sPartg = cap * pl.qparts[l - 1]; p.sPartTile = cap;
         HIPCHK(c, gemm(c, p, EPI_IPDOT, l));
-        sp.qpart[l - 1] = p.part; sp.nparts[l - 1] = gemm_bf16_row_parts(EPI_IPDOT, b, pl.dims[l], M);
+        sp.qpart[l - 1] = p.part; sp.nparts[l - 1] = gemm_bf16_row_parts(EPI_IPDOT, b, pl.dims[l], M, b_host);
         if (sp.nparts[l - 1] > pl.qparts[l - 1]) return cfail(c, ABS_ENOMEM, "inner-product scratch too small for this tile shape");
         sp.sQg[l - 1] = p.sPartg; sp.sQpart[l - 1] = cap;
       } else {
@@ -1600,7 +1600,7 @@ abs_status abs_layer_stats(int L, const int *in_dims, const int *out_dims, int M
     p.part = reinterpret_cast<float *>(ws + off[8 + l]); p.sPartg = (long long)b * np; p.sPartTile = b;
     p.part2 = dn;
     HIPCHK(nc, launch_gemm_bf16(p, EPI_IPDOT, s));
-    sp.qpart[l] = p.part; sp.nparts[l] = gemm_bf16_row_parts(EPI_IPDOT, b, out_dims[l], M); sp.sQg[l] = p.sPartg; sp.sQpart[l] = b;
+    sp.qpart[l] = p.part; sp.nparts[l] = gemm_bf16_row_parts(EPI_IPDOT, b, out_dims[l], M, nullptr); sp.sQg[l] = p.sPartg; sp.sQpart[l] = b;
     sp.an[l] = an + (size_t)l * M * b; sp.an_parts[l] = 1; sp.an_sg[l] = b;
     sp.dn[l] = dn; sp.dn_parts[l] = sp.nparts[l]; sp.dn_sg[l] = p.sPartg;
     dn += (size_t)M * b * np;

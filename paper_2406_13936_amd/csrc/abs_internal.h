@@ -44,7 +44,7 @@ inline bool gather_ok(const GatherP &p) {
 }
 // Which launch of the step takes the gather along (GemmP::gather), the first layer's contraction (1) or the logits (2), or none (0);
 // the first layer then reads its rows from the dataset (GemmP::aidx).
-int gather_rides(int is_bf16, int L, int b, const int *dims, int groups, long long N, bool ragged);
+int gather_rides(int is_bf16, int L, int b, const int *dims, int groups, long long N, const int *rows_host);
 
 struct GemmP {
   const void *A, *B;           // operands (bf16 bits or float, by kernel family)
@@ -74,7 +74,7 @@ struct GemmP {
   // grid.  Memory beyond a group's own rows is neither read nor written.
   const int *rows;
   int rows_is_k;
-  const int *rows_host;        // the same counts on the host (rows_is_k == 0, bf16 family): the grid has only the tiles they make
+  const int *rows_host;        // the same counts on the host (rows_is_k == 0, bf16 family): tile shape and grid go by the tiles they make
   // Optional (device, EPI_WGRAD of the bf16 family): the order in which the launch walks the groups.  Work-group ids are dealt
   // to the XCDs in contiguous ranges of groups, so with ragged groups the host orders them such that every
   // XCD gets about the same number of rows to reduce over.
@@ -119,16 +119,17 @@ int gemm_bf16_ipdot_parts(int Nd);
 // Exact number of row partials (tiles along n) and of column-partial rows (tiles along m times
 // wave rows) that launch_gemm_bf16 writes for epilogue epi (forward, logits, backward-data, inner products) of an
 // Md x Nd output; the rows of a column partial's tile and the partials per tile.
-int gemm_bf16_row_parts(int epi, int Md, int Nd, int groups);
-int gemm_bf16_col_parts(int epi, int Md, int Nd, int groups);
-void gemm_bf16_col_part_shape(int epi, int Md, int Nd, int groups, int *tile_m, int *parts_per_tile);
+int gemm_bf16_row_parts(int epi, int Md, int Nd, int groups, const int *rows_host);
+int gemm_bf16_col_parts(int epi, int Md, int Nd, int groups, const int *rows_host);
+void gemm_bf16_col_part_shape(int epi, int Md, int Nd, int groups, const int *rows_host, int *tile_m, int *parts_per_tile);
 // Floats per group that hold the row partials of forward / backward-data launches over any b <= cap rows when
 // partials lie b (rounded up to 64) apart.
 size_t gemm_bf16_row_part_floats(int Nd, int groups, int cap);
 // Tile shape the bf16 family uses for an Md x Nd output over `groups` replicas: 0 = 128x64, 1 = 128x128, 2 = 256x256,
 // 4 = 64x128 with a six-stage ring (outputs of at most 64 rows; 3 is a weight-gradient shape, see below),
 // 5 = 32-row tiles of gemm_small.hip (forward, logits and backward-data launches that would leave most CUs idle).
-int gemm_bf16_tile_shape(int epi, int Md, int Nd, int groups);
+// rows_host (here and below): the rows of ragged groups, at most Md each, or null.
+int gemm_bf16_tile_shape(int epi, int Md, int Nd, int groups, const int *rows_host);
 hipError_t launch_gemm_small(const GemmP &p, int epi, hipStream_t s);
 // Whether an EPI_LOGITS launch can carry the softmax head: a row's classes lie in one tile, eight or sixteen lanes to the row.
 bool gemm_head_fits(int is_bf16, int Md, int Nd, int groups);

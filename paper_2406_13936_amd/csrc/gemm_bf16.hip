@@ -1132,7 +1132,7 @@ hipError_t launch_cfg(const GemmP &p, hipStream_t s) {
   return p.aidx ? hipErrorInvalidValue : launch_mode<BM, BN, BK, WM, WN, NS, PP, AT, BT, EPI, ACT, ROWS_PLAIN>(p, s);
 }
 
-int tiled_shape(int Md, int Nd, int groups);
+int tiled_shape(int Md, int Nd, int groups, const int *rows_host);
 // Reductions up to this length keep the two-stage loop in 256 x 256 tiles: the pipelined loop fetches two k-tiles beyond the
 // last one and starts later, which a handful of k-tiles does not pay back (784-512-512-10, 8 replicas, b = 4096, one tile
 // per CU: 285.7 us per step with the pipelined loop everywhere, 281.9 with this line at 512, 283.0 at 1024; 1024-wide
@@ -1144,7 +1144,8 @@ constexpr int PIPE_MIN_K = 512;
 template <bool AT, bool BT, int EPI, int ACT>
 hipError_t launch_shape(const GemmP &p, hipStream_t s) {
   constexpr bool IS_WGRAD = EPI == EPI_WGRAD || EPI == EPI_WGRAD_UPD;
-  switch (IS_WGRAD ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr) : tiled_shape(p.Md, p.Nd, p.groups)) {
+  switch (IS_WGRAD ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr)
+                   : tiled_shape(p.Md, p.Nd, p.groups, p.rows_host)) {
     case 0: return launch_cfg<128, 64, 64, 4, 1, 3, false, AT, BT, EPI, ACT>(p, s);
     case 3: return hipErrorInvalidValue;         // (launch_wgrad_many)
     case 2:
@@ -1201,7 +1202,14 @@ double rounds_128(long long blocks) {
   return 1.42 * (double)full + last;
 }
 
-int tiled_shape(int Md, int Nd, int groups) {
+// Tiles of e x e that ragged groups make of an output Nd wide
+long long tile_count(int Nd, int groups, const int *rows_host, int e) {
+  long long tm = 0;
+  for (int g = 0; g < groups; ++g) tm += (rows_host[g] + e - 1) / e;
+  return tm * ((Nd + e - 1) / e);
+}
+
+int tiled_shape(int Md, int Nd, int groups, const int *rows_host) {
   if (Nd <= 64) return 0;
   // up to 64 rows (the first local batch sizes): the launch streams its B operand (the weights) once and is bound by
   // that stream; a 64-row tile leaves LDS for a ring of six stages, five k-tiles of B in flight per work-group
@@ -1217,7 +1225,18 @@ int tiled_shape(int Md, int Nd, int groups) {
   // 784-200-10, 16 replicas, b = 4096 283 -> 259
   const long long t256 = (long long)((Md + 255) / 256) * ((Nd + 255) / 256) * groups;
   const long long t128 = (long long)((Md + 127) / 128) * ((Nd + 127) / 128) * groups;
-  if (Md > 128 && Nd > 128 && 1.5 * (double)((t256 + 255) / 256) <= rounds_128(t128)) return 2;
+  if (Md > 128 && Nd > 128 && 1.5 * (double)((t256 + 255) / 256) <= rounds_128(t128)) {
+    if (!rows_host) return 2;
+    // Workers with batches of their own make fewer tiles, and the large ones soon leave most CUs idle: the largest worker's shape
+    // goes where 128 x 128 tiles cost a tenth less (less than that the model does not tell); second places that a single round
+    // does not fill count as far as it does.  us per step, always 256 x 256 -> this line (tiles of 256, of 128): 16 replicas,
+    // 784-384-384-10 one of 2048 samples beside fifteen of 257 (76, 183) 159 -> 135; 784-768-768-768-100, 1024 beside 130
+    // (57, 228) 269 -> 233; 784-432-432-432-10, 2 to 1221 samples (82, 300) 336 -> 284; 10 replicas, 784-496-496-496-10, 2717 beside 169
+    // (40, 160) 334 -> 251.  Long reductions at more than 256 tiles of 128 gain nothing: 3072-1168-1168-1168-100 (115, 310) 910, 932
+    const long long r256 = tile_count(Nd, groups, rows_host, 256), r128 = tile_count(Nd, groups, rows_host, 128);
+    const double c128 = r128 > 256 && r128 < 512 ? 1.13 + 0.29 * (double)(r128 - 256) / 256 : rounds_128(r128);
+    return 1.5 * (double)((r256 + 255) / 256) <= 1.1 * c128 ? 2 : 1;
+  }
   // 128 x 128 tiles for half of the CUs or fewer: twice as many 64 x 128 ones with a deeper ring (784-512-512-10, 8 replicas:
   // b = 501, 128 tiles, a step 124 -> 107.5 us, forward 16.9 -> 11.7; b = 768, 192 tiles, would go from 128 to 140)
   return t128 <= FEW_TILES ? 4 : 1;
@@ -1280,7 +1299,7 @@ bool operands_ok(const GemmP &p, int epi) {
   if (p.part2 && epi != EPI_IPDOT) return false;
   if (p.rows && epi == EPI_WGRAD && !p.rows_is_k) return false;
   if (p.gather || p.aidx) {
-    const int sh = epi == EPI_FWD_ACT || epi == EPI_LOGITS ? gemm_bf16_tile_shape(epi, p.Md, p.Nd, p.groups) : -1;
+    const int sh = epi == EPI_FWD_ACT || epi == EPI_LOGITS ? gemm_bf16_tile_shape(epi, p.Md, p.Nd, p.groups, p.rows_host) : -1;
     if (p.gather && sh != 5) return false;
     if (p.aidx && ((sh != 5 && !(sh == 4 && epi == EPI_FWD_ACT)) || p.aN < 1 || p.aldi < p.Md || p.sAg || (long long)p.aN * p.lda * 2 >= (1LL << 31)))
       return false;
@@ -1294,15 +1313,15 @@ bool operands_ok(const GemmP &p, int epi) {
 
 }  // namespace
 
-int gemm_bf16_tile_shape(int epi, int Md, int Nd, int groups) {
+int gemm_bf16_tile_shape(int epi, int Md, int Nd, int groups, const int *rows_host) {
   if ((epi == EPI_FWD_ACT || epi == EPI_LOGITS || epi == EPI_BWD) && small_tiles(Md, Nd, groups) <= small_limit(epi, Md, Nd, groups))
     return 5;
-  return tiled_shape(Md, Nd, groups);
+  return tiled_shape(Md, Nd, groups, rows_host);
 }
 
 // (bf16: the 32-row tiles hold 32 columns; fp32: the smallest tile holds 16)
 bool gemm_head_fits(int is_bf16, int Md, int Nd, int groups) {
-  return is_bf16 ? Nd <= 32 && gemm_bf16_tile_shape(EPI_LOGITS, Md, Nd, groups) == 5 : Nd <= 16;
+  return is_bf16 ? Nd <= 32 && gemm_bf16_tile_shape(EPI_LOGITS, Md, Nd, groups, nullptr) == 5 : Nd <= 16;
 }
 
 // The gather rides with a launch that is a chain of latencies, as long as its blocks find a place beside the tiles (four to a CU):
@@ -1310,13 +1329,13 @@ bool gemm_head_fits(int is_bf16, int Md, int Nd, int groups) {
 // 784-512-512-10, 8 replicas, b = 32 66 -> 63, b = 501 87 -> 82; 784-144-4, 9 replicas, b = 61 64.4 -> 61.4.  A first layer on
 // 64 x 128 tiles, one work-group to a CU, leaves it to small logits (nothing before the weight gradients needs it).
 // bf16: 16-byte chunks of a dataset row, which has no padding, and 32-bit byte offsets into the dataset.
-int gather_rides(int is_bf16, int L, int b, const int *dims, int groups, long long N, bool ragged) {
+int gather_rides(int is_bf16, int L, int b, const int *dims, int groups, long long N, const int *rows_host) {
   if ((long long)((b + 3) / 4) * groups > GATHER_RIDES) return 0;
   if (!is_bf16) return 1;
   if ((dims[0] & 7) || N * dims[0] * 2 >= (1LL << 31)) return 0;
-  const int first = gemm_bf16_tile_shape(L == 1 ? EPI_LOGITS : EPI_FWD_ACT, b, dims[1], groups);
+  const int first = gemm_bf16_tile_shape(L == 1 ? EPI_LOGITS : EPI_FWD_ACT, b, dims[1], groups, rows_host);
   if (first == 5) return 1;
-  return first == 4 && !ragged && L > 1 && gemm_bf16_tile_shape(EPI_LOGITS, b, dims[L], groups) == 5 ? 2 : 0;
+  return first == 4 && !rows_host && L > 1 && gemm_bf16_tile_shape(EPI_LOGITS, b, dims[L], groups, nullptr) == 5 ? 2 : 0;
 }
 
 // Weight gradients reduce over the local batch (Kd = b).  While the batch is short the launch is all epilogue
@@ -1356,22 +1375,22 @@ int gemm_bf16_upd_slots(int Md, int Nd, int Kd, int groups, int fused, int fine)
   return ((Md + bm[sh] - 1) / bm[sh]) * ((Nd + bn[sh] - 1) / bn[sh]) * nw[sh];
 }
 
-int gemm_bf16_row_parts(int epi, int Md, int Nd, int groups) {
+int gemm_bf16_row_parts(int epi, int Md, int Nd, int groups, const int *rows_host) {
   const int bn[6] = {64, 128, 256, 0, 128, epi == EPI_BWD ? 64 : 32};
-  const int sh = gemm_bf16_tile_shape(epi, Md, Nd, groups);
+  const int sh = gemm_bf16_tile_shape(epi, Md, Nd, groups, rows_host);
   return (Nd + bn[sh] - 1) / bn[sh];
 }
 
-void gemm_bf16_col_part_shape(int epi, int Md, int Nd, int groups, int *tile_m, int *parts_per_tile) {
+void gemm_bf16_col_part_shape(int epi, int Md, int Nd, int groups, const int *rows_host, int *tile_m, int *parts_per_tile) {
   const int bm[6] = {128, 128, 256, 0, 64, 32}, wm[6] = {4, 2, 2, 0, 2, 1};
-  const int sh = gemm_bf16_tile_shape(epi, Md, Nd, groups);
+  const int sh = gemm_bf16_tile_shape(epi, Md, Nd, groups, rows_host);
   *tile_m = bm[sh];
   *parts_per_tile = wm[sh];
 }
 
-int gemm_bf16_col_parts(int epi, int Md, int Nd, int groups) {
+int gemm_bf16_col_parts(int epi, int Md, int Nd, int groups, const int *rows_host) {
   int bm, wm;
-  gemm_bf16_col_part_shape(epi, Md, Nd, groups, &bm, &wm);
+  gemm_bf16_col_part_shape(epi, Md, Nd, groups, rows_host, &bm, &wm);
   return (Md + bm - 1) / bm * wm;
 }
 
@@ -1458,7 +1477,7 @@ hipError_t launch_gemm_bf16(const GemmP &p, int epi, hipStream_t s) {
   if (epi == EPI_WGRAD && gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr) == 3)
     return launch_wgrad_many(&p, 1, 3, s);
   if (epi == EPI_WGRAD && p.fine) return launch_wgrad_many(&p, 1, 1, s);
-  if (epi != EPI_WGRAD && gemm_bf16_tile_shape(epi, p.Md, p.Nd, p.groups) == 5) return launch_gemm_small(p, epi, s);
+  if (epi != EPI_WGRAD && gemm_bf16_tile_shape(epi, p.Md, p.Nd, p.groups, p.rows_host) == 5) return launch_gemm_small(p, epi, s);
   if (!p.a_trans && !p.b_trans) {
     if (epi == EPI_FWD_ACT) return launch_act<false, false, EPI_FWD_ACT>(p, s);
     if (epi == EPI_LOGITS) return launch_act<false, false, EPI_LOGITS>(p, s);

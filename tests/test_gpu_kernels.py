@@ -749,3 +749,49 @@ def test_the_gradient_on_demand_is_the_one_that_the_step_applied(dims, sizes):
     for m in range(M):
         assert np.array_equal(out[0][m][0], out[1][m][0]), (m, np.flatnonzero(out[0][m][0] != out[1][m][0])[:8])
         assert np.array_equal(out[0][m][1], out[1][m][1]), m
+
+
+# Workers with batches of their own take the tiles that suit what these make, not the largest worker's: one long batch beside short ones
+# leaves the 256 x 256 shape of forward, backward-data and inner products.
+@pytest.mark.parametrize("dims,sizes,test,gone,there", [
+    ((784, 384, 384, 10), [2048] + [257] * 15, W.TEST_IP, ("fwd_256x256", "bwd_256x256", "ipdot_256x256"), ("fwd_128x128", "bwd_128x128", "ipdot_128x128")),
+    ((64, 768, 776, 100), [1024] + [130] * 15, W.TEST_NORM, ("fwd_256x256", "bwd_256x256"), ("fwd_128x128", "bwd_128x128"))])
+def test_ragged_launches_take_the_tiles_that_suit_their_workers(dims, sizes, test, gone, there):
+    A = _A()
+    M, cap = len(sizes), max(sizes)
+    w = W.Workload("shapes", dims, W.ACT_RELU, True, W.PREC_BF16, N=4096, M=M, H=1, rounds=1, b0=cap, b_cap=cap, opt=W.OPT_SHB, lr=0.05,
+                   momentum=0.9, test=test, theta=0.9, data="teacher_mlp", seed=31)
+    X, y = W.make_dataset(w)
+    x0 = W.make_x0(w)
+    idx = W.step_indices(w, 0, 0, cap)
+    rows = [idx[m][:s] for m, s in enumerate(sizes)]
+    orc = O.Replicas(O.Net(w.dims, w.act, True), x0, X, y, M, opt=w.opt, momentum=w.momentum, mixed=True, want_ip=test == W.TEST_IP)
+    orc.local_step(rows, w.lr, only=[0, M - 1])
+    grads = []
+    for fused in (True, False):
+        rep = A.Replicas.from_workload(w, X, y, x0)
+        try:
+            rep.set_fused_update(fused)
+            rep.profile_enable(True)
+            rep.local_step_ragged(rows, w.lr)
+            names = [n for n in rep.profile_read() if n.startswith("gemm_")]
+            rep.profile_enable(False)
+            assert not [n for n in names for c in gone if n.startswith("gemm_" + c)], names
+            assert all(any(n.startswith("gemm_" + c) for n in names) for c in there), names
+            res = rep.norm_test(0.5)
+            for m in (0, M - 1):
+                s = orc.stats[m]
+                for got, want in ((res[m].sum_sq, s["S1"]), (res[m].gbar_sq, s["S2"]), (res[m].loss_sum, s["loss_sum"])):
+                    assert abs(got - want) <= 2e-3 * abs(want), (m, got, want)
+                if test == W.TEST_IP:
+                    assert abs(res[m].sum_q - s["S4"]) <= 2e-3 * abs(s["S4"]), m
+                grad = rep.get_grad(m).astype(np.float64)
+                assert np.linalg.norm(grad - orc.grads[m]) <= 2e-3 * np.linalg.norm(orc.grads[m]), m
+                p = rep.get_params(m).astype(np.float64)
+                assert np.abs(p - orc.x[m]).max() <= 1e-3 * np.abs(orc.x[m]).max()
+            grads.append([rep.get_grad(m) for m in range(M)])
+            assert rep.guard_intact()
+        finally:
+            rep.close()
+    for m in range(M):
+        assert np.array_equal(grads[0][m], grads[1][m]), m
