@@ -237,7 +237,7 @@ double round_cost(double blocks, int places, const double *t) {
 // 275, 244, 249, 300 -> 244; 16 replicas, b = 8192 842, 886, 891, 1003 -> 842; 784-768-768-768-100, 4 replicas, b = 8192 626,
 // 663, 567, 657 -> 567; 1024-256-256-256-100, 2 replicas, b = 8192 204, 246, 269, 180 (coarse 166) -> 166.
 constexpr int WHOLE_MAX_B = 960;
-WgradPlan plan_wgrad(const Plan &pl, int b, int fused) {
+WgradPlan plan_wgrad(const Plan &pl, int b, int fused, const int *b_host) {
   const double ring = 0.9, coarse[2] = {1.13, 1.42}, fine[3] = {0.95, 1.2, 1.47}, launch = 7.0;
   const int KT = (b + 63) / 64;
   WgradPlan w = {{0}, true, 1};
@@ -246,7 +246,7 @@ WgradPlan plan_wgrad(const Plan &pl, int b, int fused) {
   int n = 0;
   bool split = false;
   for (int l = 1; l <= pl.L; ++l) {
-    const int sh = gemm_bf16_wgrad_shape(pl.dims[l], pl.dims[l - 1], b, pl.M, fused);
+    const int sh = gemm_bf16_wgrad_shape(pl.dims[l], pl.dims[l - 1], b, pl.M, fused, b_host);
     const int te = sh == 2 ? 256 : 128;
     const long long tiles = wgrad_tiles(pl, l, te, sh == 0 ? 64 : te);
     const double outputs = (double)pl.M * pl.dims[l] * pl.dims[l - 1];
@@ -291,7 +291,7 @@ WgradPlan plan_wgrad(const Plan &pl, int b, int fused) {
   w.fine = best == whole_f || best == sliced[1];
   if (best == whole_f || best == whole_c)
     for (int l = 1; l <= pl.L; ++l)
-      if (gemm_bf16_wgrad_shape(pl.dims[l], pl.dims[l - 1], b, pl.M, fused) == 1) w.ksplit[l] = 1;
+      if (gemm_bf16_wgrad_shape(pl.dims[l], pl.dims[l - 1], b, pl.M, fused, b_host) == 1) w.ksplit[l] = 1;
   return w;
 }
 
@@ -428,7 +428,7 @@ double gemm_flops(const std::vector<GemmP> &v) { double s = 0.0; for (const Gemm
 double gemm_bytes(const abs_ctx *c, const std::vector<GemmP> &v, int epi) { double s = 0.0; for (const GemmP &p : v) s += gemm_bytes(c, p, epi); return s; }
 
 hipError_t gemm(abs_ctx *c, const GemmP &p, int epi, int layer) {
-  int shape = !c->pl.bf16 ? 1 : p.fine ? 4 : (epi == EPI_WGRAD ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr)
+  int shape = !c->pl.bf16 ? 1 : p.fine ? 4 : (epi == EPI_WGRAD ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr, p.rows_host)
                                                                 : gemm_bf16_tile_shape(epi, p.Md, p.Nd, p.groups, p.rows_host));
   ProfScope ps(c, T_GEMM0 + (epi * 6 + shape) * T_LAYERS + layer, gemm_flops(p), gemm_bytes(c, p, epi));
   return c->pl.bf16 ? launch_gemm_bf16(p, epi, c->stream) : launch_gemm_f32(p, epi, c->stream);
@@ -816,7 +816,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
   // bf16 mode: few output tiles and a long reduction (small layers, or any layer while b is the long side) are cut into
   // slices so that the launch fills the chip; the slices are added in order afterwards (plan_wgrad).
   const bool want_fused = c->fused_update && pl.bf16 && ph.wgrad && ph.update && ph.s2 && !ph.acc_grad;
-  const WgradPlan wplan = pl.bf16 && ph.wgrad ? plan_wgrad(pl, b, want_fused) : WgradPlan{};
+  const WgradPlan wplan = pl.bf16 && ph.wgrad ? plan_wgrad(pl, b, want_fused, b_host) : WgradPlan{};
   // The optimizer step moves into the weight-gradient epilogue when the caller asked for it and this call both
   // finishes the gradient and updates, no reduction is split and the per-wavefront sums of squares fit their scratch.
   bool fused = want_fused;
@@ -826,7 +826,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       if (pl.dims[l - 1] & 3) fused = false;
       // a layer whose reduction is split takes its step in the launch that adds the slices
       slots += wplan.ksplit[l] > 1 ? splitk_finish_slots((long long)pl.dims[l] * pl.dims[l - 1])
-                                   : gemm_bf16_upd_slots(pl.dims[l], pl.dims[l - 1], b, M, 1, wplan.fine);
+                                   : gemm_bf16_upd_slots(pl.dims[l], pl.dims[l - 1], b, M, 1, wplan.fine, b_host);
     }
     if (hb) slots += col_finish_slots(L, max_width, 64);
     if (slots > pl.sq_slots) fused = false;
@@ -862,7 +862,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       std::memset(&p, 0, sizeof(p));
       p.A = act_ptr(pl.o_Dl[l]); p.sAg = cap * pl.ld[l]; p.lda = pl.ld[l]; p.a_trans = 1;
       p.B = act_ptr(pl.o_A[l - 1]); p.sBg = cap * pl.ld[l - 1]; p.ldb = pl.ld[l - 1]; p.b_trans = 1;
-      p.Md = pl.dims[l]; p.Nd = pl.dims[l - 1]; p.Kd = b; p.groups = M; p.rows = rows; p.gperm = gperm; p.rows_is_k = 1;
+      p.Md = pl.dims[l]; p.Nd = pl.dims[l - 1]; p.Kd = b; p.groups = M; p.rows = rows; p.rows_host = b_host; p.gperm = gperm; p.rows_is_k = 1;
       p.C = grad + pl.offW[l]; p.sCg = pl.Ppad; p.ldc = pl.dims[l - 1];
       p.alpha = inv_b; p.accumulate = ph.acc_grad ? 1 : 0;
       if (pl.bf16 && pl.want_ip && !use_gram) { p.C2 = c->at<bf16_t>(pl.o_gradbf) + pl.offW[l]; p.sC2g = pl.Ppad; p.ldc2 = pl.dims[l - 1]; }
@@ -892,9 +892,9 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
         p.upd_beta2 = c->cfg.beta2; p.upd_eps = c->cfg.eps; p.upd_wd = c->cfg.weight_decay;
         p.upd_c1 = ph.c1; p.upd_c2 = ph.c2; p.upd_scal = ph.scal;
         p.upd_sq = c->at<float>(pl.o_sqwave); p.upd_sSqg = pl.sq_slots; p.upd_slot0 = fused_slots;
-        fused_slots += pl.bf16 ? gemm_bf16_upd_slots(p.Md, p.Nd, b, M, 1, wplan.fine) : gemm_f32_upd_slots(p.Md, p.Nd, p.f32_tile);
+        fused_slots += pl.bf16 ? gemm_bf16_upd_slots(p.Md, p.Nd, b, M, 1, wplan.fine, b_host) : gemm_f32_upd_slots(p.Md, p.Nd, p.f32_tile);
       }
-      const int wsh = pl.bf16 ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, M, p.upd_x != nullptr) : 0;
+      const int wsh = pl.bf16 ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, M, p.upd_x != nullptr, b_host) : 0;
       p.fine = wsh == 1 ? wplan.fine : 0;
       if ((wsh == 1 && wplan.shared) || wsh == 3) {
         many[wsh == 3][p.upd_x != nullptr].push_back(p);
@@ -1516,7 +1516,7 @@ static abs_status ls_plan(int L, const int *in_dims, const int *out_dims, int M,
   off.push_back(take((size_t)M * 8 * 8));                    // 7: stats
   for (int l = 0; l < L; ++l) off.push_back(take((size_t)M * b * 4 * gemm_bf16_ipdot_parts(out_dims[l])));  // 8+l
   size_t slots = 0;
-  for (int l = 0; l < L; ++l) slots += gemm_bf16_upd_slots(out_dims[l], in_dims[l], b, M, 0, 0);
+  for (int l = 0; l < L; ++l) slots += gemm_bf16_upd_slots(out_dims[l], in_dims[l], b, M, 0, 0, nullptr);
   off.push_back(take((size_t)M * slots * 8));                // 8+L: ||gbar||^2 by wavefront
   total = o;
   return ABS_OK;
@@ -1558,7 +1558,7 @@ abs_status abs_layer_stats(int L, const int *in_dims, const int *out_dims, int M
   long long Wsum = 0, n_slots = 0;
   for (int l = 0; l < L; ++l) {
     Wsum += (long long)in_dims[l] * out_dims[l];
-    n_slots += gemm_bf16_upd_slots(out_dims[l], in_dims[l], b, M, 0, 0);
+    n_slots += gemm_bf16_upd_slots(out_dims[l], in_dims[l], b, M, 0, 0, nullptr);
   }
   bool direct = gbar_out_dev && !(reinterpret_cast<uintptr_t>(gbar_out_dev) & 15);
   for (int l = 0; l < L && direct; ++l) {       // (a buffer that overlaps an input is filled last, through the workspace)
@@ -1585,7 +1585,7 @@ abs_status abs_layer_stats(int L, const int *in_dims, const int *out_dims, int M
     p.alpha = inv_b;
     p.sq64 = sq + slot0; p.sSq64g = n_slots;
     HIPCHK(nc, launch_gemm_bf16(p, EPI_WGRAD, s));
-    slot0 += gemm_bf16_upd_slots(out_dims[l], in_dims[l], b, M, 0, 0);
+    slot0 += gemm_bf16_upd_slots(out_dims[l], in_dims[l], b, M, 0, 0, nullptr);
     woff_out += (long long)in_dims[l] * out_dims[l];
   }
   for (int l = 0; l < L; ++l) {

@@ -74,7 +74,7 @@ struct GemmP {
   // grid.  Memory beyond a group's own rows is neither read nor written.
   const int *rows;
   int rows_is_k;
-  const int *rows_host;        // the same counts on the host (rows_is_k == 0, bf16 family): tile shape and grid go by the tiles they make
+  const int *rows_host;        // the same counts on the host (bf16 family): the tile shape goes by them and, rows_is_k == 0, the grid
   // Optional (device, EPI_WGRAD of the bf16 family): the order in which the launch walks the groups.  Work-group ids are dealt
   // to the XCDs in contiguous ranges of groups, so with ragged groups the host orders them such that every
   // XCD gets about the same number of rows to reduce over.
@@ -128,7 +128,7 @@ size_t gemm_bf16_row_part_floats(int Nd, int groups, int cap);
 // Tile shape the bf16 family uses for an Md x Nd output over `groups` replicas: 0 = 128x64, 1 = 128x128, 2 = 256x256,
 // 4 = 64x128 with a six-stage ring (outputs of at most 64 rows; 3 is a weight-gradient shape, see below),
 // 5 = 32-row tiles of gemm_small.hip (forward, logits and backward-data launches that would leave most CUs idle).
-// rows_host (here and below): the rows of ragged groups, at most Md each, or null.
+// rows_host (here and below): the rows of ragged groups, at most Md (weight gradients: Kd) each, or null.
 int gemm_bf16_tile_shape(int epi, int Md, int Nd, int groups, const int *rows_host);
 hipError_t launch_gemm_small(const GemmP &p, int epi, hipStream_t s);
 // Whether an EPI_LOGITS launch can carry the softmax head: a row's classes lie in one tile, eight or sixteen lanes to the row.
@@ -137,9 +137,9 @@ bool gemm_head_fits(int is_bf16, int Md, int Nd, int groups);
 // 32 and several work-groups per CU while the batch is short and the launch is bound by its epilogue's memory traffic;
 // fused != 0: the launch carries the optimizer step in its epilogue (GemmP::upd_x), which keeps medium batches on
 // 128x128 tiles, or 5 = 128x256 tiles of eight wavefronts.
-int gemm_bf16_wgrad_shape(int Md, int Nd, int Kd, int groups, int fused);
+int gemm_bf16_wgrad_shape(int Md, int Nd, int Kd, int groups, int fused, const int *rows_host);
 // Number of upd_sq slots (fused: with the optimizer step in the epilogue) or sq64 slots an EPI_WGRAD launch writes per group.
-int gemm_bf16_upd_slots(int Md, int Nd, int Kd, int groups, int fused, int fine);
+int gemm_bf16_upd_slots(int Md, int Nd, int Kd, int groups, int fused, int fine, const int *rows_host);
 // fp32 SIMT family (gemm_f32.hip); EPI_IPDOT is not offered (U is materialised instead).
 hipError_t launch_gemm_f32(const GemmP &p, int epi, hipStream_t s);
 // Its EPI_WGRAD takes the optimizer step as well (GemmP::upd_x; the gradient is stored in C all the same, rowsum's entries take

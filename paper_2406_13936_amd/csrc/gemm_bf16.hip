@@ -1144,7 +1144,7 @@ constexpr int PIPE_MIN_K = 512;
 template <bool AT, bool BT, int EPI, int ACT>
 hipError_t launch_shape(const GemmP &p, hipStream_t s) {
   constexpr bool IS_WGRAD = EPI == EPI_WGRAD || EPI == EPI_WGRAD_UPD;
-  switch (IS_WGRAD ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr)
+  switch (IS_WGRAD ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr, p.rows_host)
                    : tiled_shape(p.Md, p.Nd, p.groups, p.rows_host)) {
     case 0: return launch_cfg<128, 64, 64, 4, 1, 3, false, AT, BT, EPI, ACT>(p, s);
     case 3: return hipErrorInvalidValue;         // (launch_wgrad_many)
@@ -1290,14 +1290,12 @@ bool operands_ok(const GemmP &p, int epi) {
   if (p.ksplit > 1 && (epi != EPI_WGRAD || !p.kpart || p.kchunk <= 0 || (p.kchunk & 63) ||
                        (long long)p.kchunk * p.ksplit < p.Kd || (p.Nd & 3)))
     return false;
-  if (p.rows && epi != EPI_WGRAD) {               // the grid has exactly the tiles that these counts make
-    if (!p.rows_host || p.rows_is_k) return false;
-    for (int g = 0; g < p.groups; ++g) if (p.rows_host[g] < 1 || p.rows_host[g] > p.Md) return false;
-  }
+  if ((p.rows != nullptr) != (p.rows_host != nullptr) || (p.rows && p.rows_is_k != (epi == EPI_WGRAD))) return false;
+  if (p.rows)                                     // the grid has exactly the tiles that these counts make
+    for (int g = 0; g < p.groups; ++g) if (p.rows_host[g] < 1 || p.rows_host[g] > (p.rows_is_k ? p.Kd : p.Md)) return false;
   if (p.sq64 && (epi != EPI_WGRAD || p.ksplit > 1 || p.upd_x)) return false;
   if (epi == EPI_WGRAD && !p.C && (!p.C2 || p.accumulate || p.ksplit > 1 || p.upd_x)) return false;
   if (p.part2 && epi != EPI_IPDOT) return false;
-  if (p.rows && epi == EPI_WGRAD && !p.rows_is_k) return false;
   if (p.gather || p.aidx) {
     const int sh = epi == EPI_FWD_ACT || epi == EPI_LOGITS ? gemm_bf16_tile_shape(epi, p.Md, p.Nd, p.groups, p.rows_host) : -1;
     if (p.gather && sh != 5) return false;
@@ -1344,7 +1342,7 @@ int gather_rides(int is_bf16, int L, int b, const int *dims, int groups, long lo
 // 256 x 256 work-group does; its four wavefronts sit side by side, so a work-group touches 1 KB of consecutive
 // bytes in each of its 64 rows (measured against a 128 x 128 tile, 512 bytes in each of 128 rows, on config 3 at
 // b = 64: 2 to 2.5 % faster with the optimizer step in the epilogue, equal at b = 256).
-int gemm_bf16_wgrad_shape(int Md, int Nd, int Kd, int groups, int fused) {
+int gemm_bf16_wgrad_shape(int Md, int Nd, int Kd, int groups, int fused, const int *rows_host) {
   // Large tiles or 128 x 128 (narrow outputs: 128 x 64).  A launch of large tiles on a part of the CUs pays only when the reduction
   // is long: the smaller ones share a launch with other layers and fill the chip.  us per step, large -> 128-wide tiles: 4 replicas
   // of 3072-1024-1024-100 (64 large tiles), AdamW, b = 1024 368 -> 282, b = 3000 434 -> 421, b = 6000 709 (large), 731;
@@ -1354,8 +1352,14 @@ int gemm_bf16_wgrad_shape(int Md, int Nd, int Kd, int groups, int fused) {
   int sh = Nd <= 64 ? 0 : 1;
   if (Md >= 256 && Nd >= 512) {
     const long long tm = (Md + 255) / 256, tn = (Nd + 255) / 256, tiles = tm * tn * groups;
+    long long K = Kd;                        // ragged groups: on average (the largest: 16 replicas, us per step, -> this:
+    if (rows_host) {                         //   784-768-768-768-100, two of 4096 samples beside fourteen of 256, 547 -> 407;
+      K = 0;                                 //   784-656-656-100, 1258 and 2517, 603 -> 570)
+      for (int g = 0; g < groups; ++g) K += rows_host[g];
+      K = (K + groups - 1) / groups;
+    }
     if (Md >= 1024 && Nd >= 1024) { if (tiles >= (Kd > 4096 ? 1 : Kd > 2048 ? 128 : 192)) sh = 2; }
-    else if (Kd > 2048 ? tiles >= 128 && 10LL * Md * Nd >= 7LL * tm * tn * 65536 : tiles >= 256 && 10LL * Md >= 7LL * tm * 256) sh = 2;
+    else if (K > 2048 ? tiles >= 128 && 10LL * Md * Nd >= 7LL * tm * tn * 65536 : tiles >= 256 && 10LL * Md >= 7LL * tm * 256) sh = 2;
   }
   if (sh != 0 && Kd <= 256) return 3;        // (measured on config 3: at b = 384 and above the large tiles are faster)
   // with the optimizer step in the epilogue a medium batch is still mostly epilogue: two or three 128 x 128
@@ -1369,9 +1373,9 @@ int gemm_bf16_wgrad_shape(int Md, int Nd, int Kd, int groups, int fused) {
   return sh;
 }
 
-int gemm_bf16_upd_slots(int Md, int Nd, int Kd, int groups, int fused, int fine) {
+int gemm_bf16_upd_slots(int Md, int Nd, int Kd, int groups, int fused, int fine, const int *rows_host) {
   const int bm[6] = {128, fine ? 64 : 128, 256, 64, 0, 128}, bn[6] = {64, 128, 256, 256, 1, 256}, nw[6] = {4, 4, 8, 4, 0, 8};
-  const int sh = gemm_bf16_wgrad_shape(Md, Nd, Kd, groups, fused);
+  const int sh = gemm_bf16_wgrad_shape(Md, Nd, Kd, groups, fused, rows_host);
   return ((Md + bm[sh] - 1) / bm[sh]) * ((Nd + bn[sh] - 1) / bn[sh]) * nw[sh];
 }
 
@@ -1434,7 +1438,7 @@ hipError_t launch_wgrad_many(const GemmP *p, int n, int shape, hipStream_t s, co
       // one kernel variant for all: every layer carries the same optimizer step, or none
       if (!operands_ok(c, EPI_WGRAD) || !c.a_trans || !c.b_trans || (c.upd_x != nullptr) != upd ||
           (upd && c.upd_opt != c0.upd_opt) || (shape == 3 && c.ksplit > 1) || c.fine != c0.fine ||
-          gemm_bf16_wgrad_shape(c.Md, c.Nd, c.Kd, c.groups, upd) != shape)
+          gemm_bf16_wgrad_shape(c.Md, c.Nd, c.Kd, c.groups, upd, c.rows_host) != shape)
         return hipErrorInvalidValue;
       // and the fields that the launch holds once
       if (c.Kd != c0.Kd || c.groups != c0.groups || c.accumulate != c0.accumulate || c.sCg != c0.sCg || (c.C2 && c.sC2g != c0.sC2g) ||
@@ -1474,7 +1478,7 @@ hipError_t launch_wgrad_many(const GemmP *p, int n, int shape, hipStream_t s, co
 
 hipError_t launch_gemm_bf16(const GemmP &p, int epi, hipStream_t s) {
   if (!operands_ok(p, epi)) return hipErrorInvalidValue;
-  if (epi == EPI_WGRAD && gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr) == 3)
+  if (epi == EPI_WGRAD && gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr, p.rows_host) == 3)
     return launch_wgrad_many(&p, 1, 3, s);
   if (epi == EPI_WGRAD && p.fine) return launch_wgrad_many(&p, 1, 1, s);
   if (epi != EPI_WGRAD && gemm_bf16_tile_shape(epi, p.Md, p.Nd, p.groups, p.rows_host) == 5) return launch_gemm_small(p, epi, s);
