@@ -38,10 +38,13 @@ __device__ __forceinline__ void col_finish_block(const ColFinishMany &p, int bx,
         const float *q = p.part[l] + (long long)g * p.nsplit[l] * cols + c;
         if (RL == 1) {
           float chain[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 4
-          for (int r = 0; r < ns; r += 4)
+          for (int r = 0; r < ns; r += 8) {
+            float v[8];                            // (eight loads in flight; a row beyond the last is read again and left out)
 #pragma unroll
-            for (int k = 0; k < 4; ++k) if (r + k < ns) chain[k] += q[(long long)(r + k) * cols];
+            for (int k = 0; k < 8; ++k) v[k] = q[(long long)min(r + k, ns - 1) * cols];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) chain[k & 3] += r + k < ns ? v[k] : 0.0f;
+          }
           s = ((chain[0] + chain[1]) + chain[2]) + chain[3];
         } else {
 #pragma unroll 4
