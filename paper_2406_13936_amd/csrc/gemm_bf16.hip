@@ -241,23 +241,30 @@ constexpr int BAND = 8;
 // the tiles of the largest extent for every group instead, an XCD's share of whole groups is what its groups happen to have: 16
 // workers of 1024 to 8192 rows, the largest paired with the smallest, gave one XCD a third more than the mean.  3072-2048-2048-2048-100:
 // forward 587 -> 526 us, inner products 505 -> 464, backward-data 501 -> 464, logits 94 -> 63, the step 6750 -> 6299.
-// One lane per group, a scan, 64 groups at a time; uniform over the wavefront.
+// One lane per group, a scan, 64 groups at a time; uniform over the wavefront.  The lookup stands in front of the first operand load:
+// one load and a scan on DPP.  us per step with shuffles through LDS and the count loaded again -> this (grids of the largest
+// extent, without a lookup): 784-336-336-336-100, 9 replicas of up to 1123 samples, 212.7 -> 207.5 (211.2); 784-128-128-100,
+// 8 replicas of up to 1498, 106.8 -> 105.1 (105.5).
+__device__ __forceinline__ int wave_scan(int v) {              // inclusive
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);      // row_shr:1, 2, 4, 8: inside 16 lanes
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);      // row_bcast:15 into lanes 16 .. 31 and 48 .. 63
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);      // row_bcast:31 into lanes 32 .. 63
+  return v;
+}
 template <int BM>
-__device__ __forceinline__ bool ragged_tile(const int *__restrict__ rows, int groups, int tilesN, int lb, int &g, int &t) {
+__device__ __forceinline__ bool ragged_tile(const int *__restrict__ rows, int groups, int tilesN, int lb, int &g, int &t, int &rows_g) {
   const int lane = threadIdx.x & 63;
   t = lb;
   for (int g0 = 0; g0 < groups; g0 += 64) {
-    int sum = g0 + lane < groups ? (rows[g0 + lane] + BM - 1) / BM * tilesN : 0;
-    const int own = sum;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int up = __shfl_up(sum, d);
-      if (lane >= d) sum += up;
-    }
+    const int r = g0 + lane < groups ? rows[g0 + lane] : 0, own = (r + BM - 1) / BM * tilesN, sum = wave_scan(own);
     const int before = __popcll(__ballot(sum <= t));           // groups that end in front of the tile
     if (before < 64) {
       g = g0 + before;
       t -= __builtin_amdgcn_readlane(sum - own, before);
+      rows_g = __builtin_amdgcn_readlane(r, before);
       return true;
     }
     t -= __builtin_amdgcn_readlane(sum, 63);
@@ -309,11 +316,11 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   bf16_t *smem = reinterpret_cast<bf16_t *>(smem_raw);
 
-  int g, t, ksl = 0, rowsM = tilesM;              // group, tile of the group, k-slice, the group's rows of tiles
+  int g, t, ksl = 0, rowsM = tilesM, own = 0;     // group, tile of the group, k-slice, the group's rows of tiles and its own extent
   const int ksplit = (EPI == EPI_WGRAD && pin.ksplit > 1) ? pin.ksplit : 1;   // (no split with the step fused)
   if constexpr (MODE == ROWS_OWN) {               // only the tiles that ragged groups have are numbered (ragged_blocks)
-    if (!ragged_tile<BM>(pin.rows, pin.groups, tilesN, lb, g, t)) return;
-    rowsM = (pin.rows[g] + BM - 1) / BM;
+    if (!ragged_tile<BM>(pin.rows, pin.groups, tilesN, lb, g, t, own)) return;
+    rowsM = (own + BM - 1) / BM;
   } else {
     const int per_g = tilesM * tilesN;
     const int vg = lb / per_g;                    // group, or (group, k-slice) pair of a split reduction
@@ -333,8 +340,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
   const int m0 = tm * BM, n0 = tn * BN;
   GemmP p = pin;
   if (MODE == ROWS_OWN || (IS_WGRAD && p.rows)) { // ragged groups: this group's own extent
-    const int r = p.rows[g];
-    if (IS_WGRAD) { p.Kd = r; p.alpha = 1.0f / (float)r; } else p.Md = r;
+    if (IS_WGRAD) { p.Kd = p.rows[g]; p.alpha = 1.0f / (float)p.Kd; } else p.Md = own;
     if (m0 >= p.Md) return;                       // uniform over the block, before any barrier
   }
   long long kofsA = 0, kofsB = 0;                 // element offsets of this block's k-slice
