@@ -797,3 +797,36 @@ def test_ragged_launches_take_the_tiles_that_suit_their_workers(dims, sizes, tes
             rep.close()
     for m in range(M):
         assert np.array_equal(grads[0][m], grads[1][m]), m
+
+
+# Sample indices outside the dataset are clamped into it, wherever a row is read from it: in fp32 and in bf16, by the first layer's 32 x 32 and
+# 64 x 128 tiles, by the gather behind the tiles or in a launch of its own, by the loss head beside or behind the logits.
+@pytest.mark.parametrize("prec,dims,M,b,own", [(W.PREC_F32, (30, 7), 2, 33, False), (W.PREC_F32, (257, 33, 18), 3, 66, False),
+                                               (W.PREC_F32, (64, 10), 4, 1025, True), (W.PREC_BF16, (72, 10), 2, 33, False),
+                                               (W.PREC_BF16, (136, 264, 40), 3, 33, False), (W.PREC_BF16, (136, 512, 10), 8, 501, False),
+                                               (W.PREC_BF16, (136, 264, 100), 8, 600, True)])
+def test_indices_outside_the_dataset_are_clamped(prec, dims, M, b, own):
+    A = _A()
+    w = W.Workload("clamp", dims, W.ACT_RELU if len(dims) > 2 else W.ACT_NONE, True, prec, N=1000, M=M, H=1, rounds=1, b0=b, b_cap=b,
+                   opt=W.OPT_SGD, lr=0.05, test=W.TEST_NORM, data="teacher_mlp", seed=29)
+    X, y = W.make_dataset(w)
+    x0 = W.make_x0(w)
+    outside = np.array(W.step_indices(w, 0, 0, b), dtype=np.int32)
+    outside[:, 1::7], outside[:, 2::7] = -1, w.N
+    outside[:, 3::7], outside[:, 4::7] = np.iinfo(np.int32).min, np.iinfo(np.int32).max
+    out = []
+    for idx in (outside, np.clip(outside, 0, w.N - 1)):
+        rep = A.Replicas.from_workload(w, X, y, x0)
+        try:
+            rep.profile_enable(True)
+            rep.local_step(idx, w.lr)
+            assert ("gather_rows" in rep.profile_read()) == own
+            rep.profile_enable(False)
+            res = rep.norm_test(0.5)
+            out.append([(rep.get_per_sample(m, b)[0], rep.get_grad(m), rep.get_params(m), [res[m].loss_sum]) for m in range(M)])
+            assert rep.guard_intact()
+        finally:
+            rep.close()
+    for m in range(M):
+        for got, want in zip(out[0][m], out[1][m]):
+            assert np.array_equal(got, want), m
