@@ -319,7 +319,10 @@ abs_status abs_average_bf16_static(void *params_dev, int M, int64_t n, void *hip
  * totals (accumulated since abs_profile_enable) and returns one entry per kernel class that ran:
  * calls, total milliseconds, and the algorithmic work of those calls (flops for the matrix-core
  * GEMMs: 2 m n k per replica, with the largest b^m for every replica after a ragged step; bytes
- * for the bandwidth-bound kernels).   out : host.
+ * for the bandwidth-bound kernels).  Bias gradients and per-sample statistics in front of the weight
+ * gradients count in that launch, time and bytes.  A batch gather beside a contraction of the forward
+ * pass has no entry: its time is part of that launch's, its bytes (two rows per sample) of no entry.
+ *   out : host.
  */
 typedef struct {
   char name[32];

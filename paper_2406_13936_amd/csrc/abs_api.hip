@@ -412,7 +412,8 @@ struct ProfScope {
 
 double gemm_flops(const GemmP &p) { return 2.0 * p.Md * p.Nd * p.Kd * p.groups; }
 double gemm_bytes(const abs_ctx *c, const GemmP &p, int epi) {
-  // algorithmic bytes of the launch: both operands once, the outputs once, the epilogue's elementwise operand once
+  // algorithmic bytes of the contraction: both operands once, the outputs once, the epilogue's elementwise operand once (a gather
+  // that rides beside the tiles is none of its own)
   const double e = c->pl.esz, mn = (double)p.Md * p.Nd;
   double bytes = ((double)p.Md + p.Nd) * p.Kd * e;
   if (epi == EPI_FWD_ACT) bytes += mn * e * (p.C2 ? 2 : 1);
@@ -423,6 +424,17 @@ double gemm_bytes(const abs_ctx *c, const GemmP &p, int epi) {
   else if (p.upd_x) bytes += mn * (8 + (c->pl.bf16 ? 0 : 4) + (p.upd_v ? 8 : 0) + (p.upd_m ? 8 : 0) + (p.upd_shadow ? 2 : 0) + (p.C2 ? 2 : 0));
   else bytes += mn * (4 + (p.C2 ? 2 : 0) + (p.accumulate ? 4 : 0));
   return bytes * p.groups;
+}
+// of the per-sample statistics: row-norm and inner-product partials, losses, n_i and q_i
+double sample_bytes(const StatsP &p) {
+  double v = 0.0;                                                          // floats per sample
+  for (int l = 0; l < p.L; ++l) {
+    if (p.do_n) v += p.an_parts[l] + p.dn_parts[l];
+    if (p.do_q) v += p.nparts[l];
+  }
+  if (p.do_n) v += (p.loss ? 1 : 0) + (p.n_out ? 1 : 0);
+  if (p.do_q) v += p.q_out ? 1 : 0;
+  return 4.0 * v * p.b * p.groups;
 }
 double gemm_flops(const std::vector<GemmP> &v) { double s = 0.0; for (const GemmP &p : v) s += gemm_flops(p); return s; }
 double gemm_bytes(const abs_ctx *c, const std::vector<GemmP> &v, int epi) { double s = 0.0; for (const GemmP &p : v) s += gemm_bytes(c, p, epi); return s; }
@@ -964,7 +976,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
         if (v.empty()) continue;
         if (!tail_taken && (v.size() > 1 || sh) && (cf.n == 0 || (u == 1) == fused)) {
           ProfScope ps_(c, T_GEMM0 + (EPI_WGRAD * 6 + (sh ? 3 : v[0].fine ? 4 : 1)) * T_LAYERS + (v.size() == 1 ? many_layer[sh][u] : 0),
-                        gemm_flops(v), gemm_bytes(c, v, EPI_WGRAD) + cf_bytes);
+                        gemm_flops(v), gemm_bytes(c, v, EPI_WGRAD) + cf_bytes + (tail.st.nb_done > 0 ? sample_bytes(tail.st) : 0.0));
           HIPCHK(c, launch_wgrad_many(v.data(), (int)v.size(), sh ? 3 : 1, s, &tail));
           tail_taken = true;
           continue;
@@ -1046,6 +1058,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
     }
   }
   // statistics
+  const double sp_bytes = sp.nb_done > 0 ? 0.0 : sample_bytes(sp);
   sp.stats_host = c->host_stats_dev;
   if (sp.stats_host) { c->ticket += 1.0; sp.ticket = c->ticket; c->ticket_live = true; }
   // When this call both finishes the gradient and updates, the update kernel gathers ||gbar||^2 on
@@ -1057,7 +1070,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
     // every parameter has taken its step; ||gbar||^2 is the sum of the slots that the launches which did it left
     sp.sq_wave = c->at<float>(pl.o_sqwave); sp.n_sq_wave = fused_slots;
     sp.sq_stride = pl.sq_slots;
-    ProfScope ps_(c, T_STATS, 0.0, 4.0 * M * fused_slots);
+    ProfScope ps_(c, T_STATS, 0.0, sp_bytes + 4.0 * M * fused_slots);
     HIPCHK(c, launch_stats(sp, s));
     note_step(c, ph.b_total > 0 ? ph.b_total : b, b_host);
     c->last_fused = fused;
@@ -1065,7 +1078,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
   }
   c->last_fused = false;
   if (!s2_in_update) {
-    ProfScope ps_(c, T_STATS, 0.0, ph.s2 ? 4.0 * M * pl.Ppad : 0.0);
+    ProfScope ps_(c, T_STATS, 0.0, sp_bytes + (ph.s2 ? 4.0 * M * pl.Ppad : 0.0));
     HIPCHK(c, launch_stats(sp, s));
   }
   if (!ph.update) return ABS_OK;
@@ -1085,7 +1098,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
   HIPCHK(c, launch_update(up, s)); }
   if (s2_in_update) {
     sp.sq_wave = up.sq_wave; sp.n_sq_wave = pl.Ppad / 256;
-    ProfScope ps_(c, T_STATS, 0.0, 4.0 * M * (pl.Ppad / 256));
+    ProfScope ps_(c, T_STATS, 0.0, sp_bytes + 4.0 * M * (pl.Ppad / 256));
     HIPCHK(c, launch_stats(sp, s));
   }
   note_step(c, ph.b_total > 0 ? ph.b_total : b, b_host);

@@ -830,3 +830,25 @@ def test_indices_outside_the_dataset_are_clamped(prec, dims, M, b, own):
     for m in range(M):
         for got, want in zip(out[0][m], out[1][m]):
             assert np.array_equal(got, want), m
+
+
+# The per-sample statistics count where they run: norm partials, losses and norms, four bytes each, with the weight gradients that they ride
+# in front of or, with inner products, with the statistics.  72 -> 104 -> 40: partials ||a||^2 1 and 4 (forward, 32 columns each), ||delta||^2
+# 2 (backward-data, 64 columns) and 1.
+def test_profile_counts_the_per_sample_statistics_where_they_run():
+    A = _A()
+    M, b, got = 3, 33, []
+    for test in (W.TEST_NORM, W.TEST_IP):
+        w = W.Workload("bytes", (72, 104, 40), W.ACT_RELU, True, W.PREC_BF16, N=1024, M=M, H=1, rounds=1, b0=b, b_cap=b,
+                       opt=W.OPT_SGD, lr=0.05, test=test, theta=0.9, data="teacher_mlp", seed=3)
+        X, y = W.make_dataset(w)
+        rep = A.Replicas.from_workload(w, X, y, W.make_x0(w))
+        try:
+            rep.profile_enable(True)
+            rep.local_step(W.step_indices(w, 0, 0, b), w.lr)
+            got.append({n: e["bytes"] for n, e in rep.profile_read().items()})
+        finally:
+            rep.close()
+    sample = 4 * M * b * (1 + 4 + 2 + 1 + 2)
+    assert got[0]["gemm_wgrad_64x256_L0"] - got[1]["gemm_wgrad_64x256_L0"] == sample
+    assert got[1]["stats"] - got[0]["stats"] == sample + 4 * M * b * 2        # (and q from the Gram matrices: read and stored)
