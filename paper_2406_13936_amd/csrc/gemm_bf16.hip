@@ -255,21 +255,20 @@ __device__ __forceinline__ int wave_scan(int v) {              // inclusive
   return v;
 }
 template <int BM>
-__device__ __forceinline__ bool ragged_tile(const int *__restrict__ rows, int groups, int tilesN, int lb, int &g, int &t, int &rows_g) {
+__device__ __forceinline__ void ragged_tile(const int *__restrict__ rows, int groups, int tilesN, int lb, int &g, int &t, int &rows_g) {
   const int lane = threadIdx.x & 63;
   t = lb;
-  for (int g0 = 0; g0 < groups; g0 += 64) {
+  for (int g0 = 0;; g0 += 64) {
     const int r = g0 + lane < groups ? rows[g0 + lane] : 0, own = (r + BM - 1) / BM * tilesN, sum = wave_scan(own);
     const int before = __popcll(__ballot(sum <= t));           // groups that end in front of the tile
-    if (before < 64) {
+    if (before < 64 || g0 + 64 >= groups) {                    // (the grid has the groups' tiles: in the last 64 one holds it)
       g = g0 + before;
       t -= __builtin_amdgcn_readlane(sum - own, before);
       rows_g = __builtin_amdgcn_readlane(r, before);
-      return true;
+      return;
     }
     t -= __builtin_amdgcn_readlane(sum, 63);
   }
-  return false;
 }
 
 // ---- the kernel --------------------------------------------------------------------------
@@ -319,7 +318,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
   int g, t, ksl = 0, rowsM = tilesM, own = 0;     // group, tile of the group, k-slice, the group's rows of tiles and its own extent
   const int ksplit = (EPI == EPI_WGRAD && pin.ksplit > 1) ? pin.ksplit : 1;   // (no split with the step fused)
   if constexpr (MODE == ROWS_OWN) {               // only the tiles that ragged groups have are numbered (ragged_blocks)
-    if (!ragged_tile<BM>(pin.rows, pin.groups, tilesN, lb, g, t, own)) return;
+    ragged_tile<BM>(pin.rows, pin.groups, tilesN, lb, g, t, own);
     rowsM = (own + BM - 1) / BM;
   } else {
     const int per_g = tilesM * tilesN;
@@ -341,7 +340,6 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmP &pin, const int tiles
   GemmP p = pin;
   if (MODE == ROWS_OWN || (IS_WGRAD && p.rows)) { // ragged groups: this group's own extent
     if (IS_WGRAD) { p.Kd = p.rows[g]; p.alpha = 1.0f / (float)p.Kd; } else p.Md = own;
-    if (m0 >= p.Md) return;                       // uniform over the block, before any barrier
   }
   long long kofsA = 0, kofsB = 0;                 // element offsets of this block's k-slice
   if (EPI == EPI_WGRAD && ksplit > 1) {
@@ -1332,11 +1330,11 @@ bool gemm_head_fits(int is_bf16, int Md, int Nd, int groups) {
 // its own launch cost 3 to 8 us and a gap.  us per step: 256-10 in fp32, 4 replicas, b = 16 31.9 -> 28.6, b = 512 39.8 -> 36.6;
 // 784-512-512-10, 8 replicas, b = 32 66 -> 63, b = 501 87 -> 82; 784-144-4, 9 replicas, b = 61 64.4 -> 61.4.  A first layer on
 // 64 x 128 tiles, one work-group to a CU, leaves it to small logits (nothing before the weight gradients needs it).
-// bf16: 16-byte chunks of a dataset row, which has no padding, and 32-bit byte offsets into the dataset.
+// bf16: 32-bit byte offsets into the dataset (its rows are whole 16-byte chunks: widths are multiples of 8).
 int gather_rides(int is_bf16, int L, int b, const int *dims, int groups, long long N, const int *rows_host) {
   if ((long long)((b + 3) / 4) * groups > GATHER_RIDES) return 0;
   if (!is_bf16) return 1;
-  if ((dims[0] & 7) || N * dims[0] * 2 >= (1LL << 31)) return 0;
+  if (N * dims[0] * 2 >= (1LL << 31)) return 0;
   const int first = gemm_bf16_tile_shape(L == 1 ? EPI_LOGITS : EPI_FWD_ACT, b, dims[1], groups, rows_host);
   if (first == 5) return 1;
   return first == 4 && !rows_host && L > 1 && gemm_bf16_tile_shape(EPI_LOGITS, b, dims[L], groups, nullptr) == 5 ? 2 : 0;
