@@ -70,8 +70,8 @@ struct GemmP {
   int act;
   int pad_to_ld;               // also write zeros to columns [Nd, ldc) of C (and C2)
   // Ragged groups (optional): rows[g] (device) replaces Md (rows_is_k == 0) or Kd (rows_is_k == 1,
-  // where alpha becomes 1 / rows[g]) for group g; Md / Kd then hold the largest count and size the
-  // grid.  Memory beyond a group's own rows is neither read nor written.
+  // where alpha becomes 1 / rows[g]) for group g; Md / Kd then hold the largest count, which sizes
+  // the grid of the fp32 and of the 32-row kernels.  Memory beyond a group's own rows is neither read nor written.
   const int *rows;
   int rows_is_k;
   const int *rows_host;        // the same counts on the host (bf16 family): the tile shape goes by them and, rows_is_k == 0, the grid

@@ -32,8 +32,7 @@ template <> struct Vec<bf16_t> {
 // One wavefront per gathered row, four to a block of 256 threads.  Source rows have d elements (row stride d); the
 // destination row stride is ldo >= d (multiple of 8), pad columns are written as zeros.
 // Indices outside [0, N) are clamped into the range (the kernels never read out of bounds).
-// The row goes through restricted pointers, so that its loads are under way together and not each behind the store before it
-// (9 x 748 rows of 784: 4 us).
+// (Source and destination never overlap: the dataset and the workspace.)
 template <class T>
 __device__ __forceinline__ float gather_row(const T *__restrict__ src, T *__restrict__ dst, int d, int ldo, int lane) {
   float s = 0.0f;

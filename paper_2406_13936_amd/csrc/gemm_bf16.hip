@@ -24,7 +24,7 @@
 //   * the 256 x 256 tile has a main loop of its own (see the note above the kernel).
 //
 // Tiling: BM x BN x BK block tile, WM x WN wavefronts of 64 lanes, each a grid of 32x32x16
-// bf16 MFMAs with fp32 accumulators.  Work-group ids are remapped so that each XCD (ids are
+// (256 x 256 tile: 16x16x32) bf16 MFMAs with fp32 accumulators.  Work-group ids are remapped so that each XCD (ids are
 // dealt round-robin to the 8 XCDs) works on a contiguous range of tiles and its L2 sees one
 // replica's operands at a time.
 #include <algorithm>
@@ -81,7 +81,7 @@ constexpr uint32_t OOB = 0x80000000u;   // byte offset beyond any operand (opera
 
 // XOR on the 16-byte chunk index of k-row k in a row-contiguous tile.  A 32-lane half of a transpose read meets four values of
 // k x 4 chunks (KR = 16: 32 rows) or eight values of k, 0 .. 3 and 8 .. 11 of the step, x 2 chunks (KR = 32: 16 rows); either
-// way the 16 chunks spread over all 64 banks.  The same for k and k + 4, the fragment's second read, and for every k-step.
+// way the 16 chunks spread over all 64 banks (conflicts: 1 % of a weight gradient's LDS cycles, with either).  The same for k and k + 4, the fragment's second read, and for every k-step.
 template <int KR> __device__ __forceinline__ int tr_swizzle(int k) { return KR == 16 ? 4 * (k & 3) : 2 * (k & 3) + (k & 8); }
 
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
@@ -277,7 +277,7 @@ __device__ __forceinline__ void ragged_tile(const int *__restrict__ rows, int gr
 // every 2048 matrix-core cycles; a fifth of it misses the XCD's L2 and comes back after 1000 to 1600 cycles, so a load that
 // is issued during the k-tile before it is needed arrives late (two 64 KB stages with one wait per k-tile: the waves
 // stood at that wait for a third of their time).  Here LDS holds the same 128 KB as eight units of 16 KB (A rows in two
-// halves h, B in two halves c, two k-tiles), each with its own life: a k-tile is four phases (h, c) of eight MFMAs per wave,
+// halves h, B in two halves c, two k-tiles), each with its own life: a k-tile is four phases (h, c) of sixteen MFMAs per wave,
 // a phase reads one unit's fragments and refills, for the k-tile after the next, the unit that the phase before read, so every
 // load has seven phases (3500 cycles) to arrive and six units stay in flight at each wait.
 // The four waves with wm = 1 (one per SIMD) run one barrier behind those with wm = 0: while one wave of a SIMD issues its
@@ -290,8 +290,10 @@ __device__ __forceinline__ void ragged_tile(const int *__restrict__ rows, int gr
 // wait in phase f covers the unit of phase f + 1, and a barrier of all waves lies between.
 // B halves: k-contiguous operands split by columns (unit c holds columns 64 j + 32 c .. + 31 of every wave column j, so that
 // a wave still owns 64 consecutive columns), row-contiguous ones by k (unit c = 32 of the 64 k: 512 bytes of a memory row).
-// Measured, 16 replicas, against the two-stage loop: inner products 8192 x 2048 x 2048 1017 -> 850 us (1.30 PFLOP/s),
-// forward 1160 -> 1043, backward-data 1110 -> 922, weight gradient with the step in its epilogue 1178 -> 993.
+// Measured, 16 replicas, 8192 x 2048 x 2048, two-stage loop -> this one with 32x32x16 MFMAs -> with 16x16x32: inner products 1017 ->
+// 850 -> 843 us (1.30 PFLOP/s), forward 1160 -> 1043 -> 1035, backward-data 1110 -> 922 -> 932, weight gradient with the step in
+// its epilogue 1178 -> 993 -> 1019, launch by launch on different boxes; side by side the step at 16 replicas went from 13.22 to
+// 12.65 ms with the last change: at the power limit the clock rises with what an MFMA saves.
 // (the work of one work-group: tile lb of the tilesM x tilesN x groups of a launch)
 // MODE, a kernel of its own each, since what the short launches do not need costs them up to 0.7 of 11 us in front of their first
 // load: ROWS_OWN: ragged groups (not the weight gradients); ROWS_DATASET: the rows of A are rows of the dataset (GemmP::aidx).
@@ -1368,7 +1370,7 @@ int gemm_bf16_wgrad_shape(int Md, int Nd, int Kd, int groups, int fused, const i
   if (sh != 0 && Kd <= 256) return 3;        // (measured on config 3: at b = 384 and above the large tiles are faster)
   // with the optimizer step in the epilogue a medium batch is still mostly epilogue: two or three 128 x 128
   // work-groups per CU stream it better than one 256 x 256 work-group (config 3: b = 384 1.92 -> 1.87 ms per step,
-  // b = 512 2.02 -> 2.00; from b = 768 on the large tile wins)
+  // b = 512 2.02 -> 2.00)
   if (fused && sh == 2 && Kd <= 512) return 1;
   // up to 1536 two 128 x 256 work-groups of eight wavefronts share a CU where there are tiles for two: sixteen waves keep more of
   // the epilogue's memory requests in flight than eight (3072-2048-2048-2048-100, 16 replicas, heavy ball, the three wide layers:
