@@ -941,10 +941,12 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       }
     }
     if (cf.n > 0) {                        // all bias gradients of the step together, with the biases' step if the weights take theirs
-      // few partials to a column: 256 columns to a block, a quarter of the blocks (3072-2048-2048-2048-100, 16 replicas, b = 64, in
-      // front of the weight gradients: the step 1019 -> 1009 us)
+      // few partials to a column: 256 columns to a block, one lane each, a quarter of the blocks (3072-2048-2048-2048-100, 16 replicas,
+      // b = 64, in front of the weight gradients: the step 1019 -> 1009 us).  At most four: one lane then adds them in the order of
+      // four lanes and their sum, so a layer's bits do not depend on what else is in the launch (the gradient on demand has the last
+      // layer alone)
       cf.cb = 256;
-      for (int e = 0; e < cf.n; ++e) if (!cf.src[e] && cf.nsplit[e] > 16) cf.cb = 64;
+      for (int e = 0; e < cf.n; ++e) if (!cf.src[e] && cf.nsplit[e] > 4) cf.cb = 64;
       cf.alpha = inv_b; cf.out = grad; cf.sOg = pl.Ppad; cf.rows = rows; cf.accumulate = ph.acc_grad ? 1 : 0; cf.b = b;
       if (fused) {
         cf.upd_x = xm;

@@ -12,8 +12,7 @@ __device__ __forceinline__ void col_finish_block(const ColFinishMany &p, int bx,
   const int cols = p.cols[l];
   const bf16_t *src = p.src[l];
   // columns x row-lanes at a time: 64 x 4; 256 x 1 over few partials; 16 x 16 for a narrow layer summed directly (a shorter
-  // serial walk per lane).  Partials are added up in four chains, r, r + 4, ..., and then chain by chain, on four lanes or on one:
-  // cb follows from all layers of a launch, and a layer alone (the gradient on demand) has to give the same bits.
+  // serial walk per lane)
   const int CL = src ? (cols <= 16 ? 16 : 64) : p.cb, RL = 256 / CL;
   const int cl = threadIdx.x & (CL - 1), rl = threadIdx.x / CL;
   double gg = 0.0;
@@ -36,20 +35,8 @@ __device__ __forceinline__ void col_finish_block(const ColFinishMany &p, int bx,
         s = (float)s64;
       } else {
         const float *q = p.part[l] + (long long)g * p.nsplit[l] * cols + c;
-        if (RL == 1) {
-          float chain[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-          for (int r = 0; r < ns; r += 8) {
-            float v[8];                            // (eight loads in flight; a row beyond the last is read again and left out)
-#pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] = q[(long long)min(r + k, ns - 1) * cols];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) chain[k & 3] += r + k < ns ? v[k] : 0.0f;
-          }
-          s = ((chain[0] + chain[1]) + chain[2]) + chain[3];
-        } else {
 #pragma unroll 4
-          for (int r = rl; r < ns; r += RL) s += q[(long long)r * cols];
-        }
+        for (int r = rl; r < ns; r += RL) s += q[(long long)r * cols];
       }
     }
     red[threadIdx.x] = s;
