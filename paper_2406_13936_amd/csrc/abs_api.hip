@@ -213,7 +213,7 @@ long long wgrad_tiles(const Plan &pl, int l, int bm, int bn) {
 // How the bf16 weight gradients of a step over b samples are launched: the slices of every layer's reduction and, for the
 // layers on 128 x 128 tiles, one launch for all (shared) or one each, and 64 x 128 tiles instead (fine).  The same whatever form
 // the update takes, so that every form adds the same products in the same order.
-struct WgradPlan { int ksplit[MAXL + 1]; bool shared; int fine; };
+struct WgradPlan { int ksplit[MAXL + 1]; bool shared; int fine; const int *rows; };      // rows: the counts that the tile rule goes by (GemmP::rows_host)
 
 // Microseconds per k-tile of 64 for `blocks` work-groups of equal length: `places` fit on the chip, a round that fills the
 // first, second, third 256 of them takes t[0], t[1], t[2] (a last round of at most 256 behind full ones lies between the first
@@ -240,13 +240,19 @@ constexpr int WHOLE_MAX_B = 960;
 WgradPlan plan_wgrad(const Plan &pl, int b, int fused, const int *b_host) {
   const double ring = 0.9, coarse[2] = {1.13, 1.42}, fine[3] = {0.95, 1.2, 1.47}, launch = 7.0;
   const int KT = (b + 63) / 64;
-  WgradPlan w = {{0}, true, 1};
+  WgradPlan w = {{0}, true, 1, b_host};
+  // Ragged workers: tiles by the mean batch pay where all layers leave the large ones and share launches (34 nets with 784 and 3072
+  // inputs, hidden layers of 528 to 1016, mean up to 2048 below a longer largest batch: 784 inputs 0.84 to 1.00 of the time by the
+  // largest batch).  A first layer of 3072 inputs keeps them, and the hidden ones behind it gain little or lose: 27 nets, 0.96 to 1.09
+  // (3072-984-984-984-38, 8 replicas of up to 5995 samples, 1249 us by the largest, 1362 by the mean)
+  for (int l = 1; b_host && l <= pl.L; ++l)
+    if (gemm_bf16_wgrad_shape(pl.dims[l], pl.dims[l - 1], b, pl.M, 0, b_host) == 2) w.rows = nullptr;
   double tiles_c = 0.0, tiles_f = 0.0, apart = 0.0, finish = 0.0;
   double nb[2][MAXL], kt[MAXL], total[2] = {0.0, 0.0};
   int n = 0;
   bool split = false;
   for (int l = 1; l <= pl.L; ++l) {
-    const int sh = gemm_bf16_wgrad_shape(pl.dims[l], pl.dims[l - 1], b, pl.M, fused, b_host);
+    const int sh = gemm_bf16_wgrad_shape(pl.dims[l], pl.dims[l - 1], b, pl.M, fused, w.rows);
     const int te = sh == 2 ? 256 : 128;
     const long long tiles = wgrad_tiles(pl, l, te, sh == 0 ? 64 : te);
     const double outputs = (double)pl.M * pl.dims[l] * pl.dims[l - 1];
@@ -291,7 +297,7 @@ WgradPlan plan_wgrad(const Plan &pl, int b, int fused, const int *b_host) {
   w.fine = best == whole_f || best == sliced[1];
   if (best == whole_f || best == whole_c)
     for (int l = 1; l <= pl.L; ++l)
-      if (gemm_bf16_wgrad_shape(pl.dims[l], pl.dims[l - 1], b, pl.M, fused, b_host) == 1) w.ksplit[l] = 1;
+      if (gemm_bf16_wgrad_shape(pl.dims[l], pl.dims[l - 1], b, pl.M, fused, w.rows) == 1) w.ksplit[l] = 1;
   return w;
 }
 
@@ -838,7 +844,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       if (pl.dims[l - 1] & 3) fused = false;
       // a layer whose reduction is split takes its step in the launch that adds the slices
       slots += wplan.ksplit[l] > 1 ? splitk_finish_slots((long long)pl.dims[l] * pl.dims[l - 1])
-                                   : gemm_bf16_upd_slots(pl.dims[l], pl.dims[l - 1], b, M, 1, wplan.fine, b_host);
+                                   : gemm_bf16_upd_slots(pl.dims[l], pl.dims[l - 1], b, M, 1, wplan.fine, wplan.rows);
     }
     if (hb) slots += col_finish_slots(L, max_width, 64);
     if (slots > pl.sq_slots) fused = false;
@@ -874,7 +880,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       std::memset(&p, 0, sizeof(p));
       p.A = act_ptr(pl.o_Dl[l]); p.sAg = cap * pl.ld[l]; p.lda = pl.ld[l]; p.a_trans = 1;
       p.B = act_ptr(pl.o_A[l - 1]); p.sBg = cap * pl.ld[l - 1]; p.ldb = pl.ld[l - 1]; p.b_trans = 1;
-      p.Md = pl.dims[l]; p.Nd = pl.dims[l - 1]; p.Kd = b; p.groups = M; p.rows = rows; p.rows_host = b_host; p.gperm = gperm; p.rows_is_k = 1;
+      p.Md = pl.dims[l]; p.Nd = pl.dims[l - 1]; p.Kd = b; p.groups = M; p.rows = rows; p.rows_host = wplan.rows; p.gperm = gperm; p.rows_is_k = 1;
       p.C = grad + pl.offW[l]; p.sCg = pl.Ppad; p.ldc = pl.dims[l - 1];
       p.alpha = inv_b; p.accumulate = ph.acc_grad ? 1 : 0;
       if (pl.bf16 && pl.want_ip && !use_gram) { p.C2 = c->at<bf16_t>(pl.o_gradbf) + pl.offW[l]; p.sC2g = pl.Ppad; p.ldc2 = pl.dims[l - 1]; }
@@ -904,9 +910,9 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
         p.upd_beta2 = c->cfg.beta2; p.upd_eps = c->cfg.eps; p.upd_wd = c->cfg.weight_decay;
         p.upd_c1 = ph.c1; p.upd_c2 = ph.c2; p.upd_scal = ph.scal;
         p.upd_sq = c->at<float>(pl.o_sqwave); p.upd_sSqg = pl.sq_slots; p.upd_slot0 = fused_slots;
-        fused_slots += pl.bf16 ? gemm_bf16_upd_slots(p.Md, p.Nd, b, M, 1, wplan.fine, b_host) : gemm_f32_upd_slots(p.Md, p.Nd, p.f32_tile);
+        fused_slots += pl.bf16 ? gemm_bf16_upd_slots(p.Md, p.Nd, b, M, 1, wplan.fine, wplan.rows) : gemm_f32_upd_slots(p.Md, p.Nd, p.f32_tile);
       }
-      const int wsh = pl.bf16 ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, M, p.upd_x != nullptr, b_host) : 0;
+      const int wsh = pl.bf16 ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, M, p.upd_x != nullptr, p.rows_host) : 0;
       p.fine = wsh == 1 ? wplan.fine : 0;
       if ((wsh == 1 && wplan.shared) || wsh == 3) {
         many[wsh == 3][p.upd_x != nullptr].push_back(p);

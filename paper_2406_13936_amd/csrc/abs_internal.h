@@ -74,7 +74,7 @@ struct GemmP {
   // the grid of the fp32 and of the 32-row kernels.  Memory beyond a group's own rows is neither read nor written.
   const int *rows;
   int rows_is_k;
-  const int *rows_host;        // the same counts on the host (bf16 family): the tile shape goes by them and, rows_is_k == 0, the grid
+  const int *rows_host;        // the same counts on the host (bf16 family): the tile shape goes by them (weight gradients: optional) and, rows_is_k == 0, the grid
   // Optional (device, EPI_WGRAD of the bf16 family): the order in which the launch walks the groups.  Work-group ids are dealt
   // to the XCDs in contiguous ranges of groups, so with ragged groups the host orders them such that every
   // XCD gets about the same number of rows to reduce over.

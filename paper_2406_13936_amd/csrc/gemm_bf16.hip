@@ -1296,8 +1296,8 @@ bool operands_ok(const GemmP &p, int epi) {
   if (p.ksplit > 1 && (epi != EPI_WGRAD || !p.kpart || p.kchunk <= 0 || (p.kchunk & 63) ||
                        (long long)p.kchunk * p.ksplit < p.Kd || (p.Nd & 3)))
     return false;
-  if ((p.rows != nullptr) != (p.rows_host != nullptr) || (p.rows && p.rows_is_k != (epi == EPI_WGRAD))) return false;
-  if (p.rows)                                     // the grid has exactly the tiles that these counts make
+  if ((p.rows_host && !p.rows) || (p.rows && p.rows_is_k != (epi == EPI_WGRAD)) || (p.rows && !p.rows_host && epi != EPI_WGRAD)) return false;
+  if (p.rows_host)                                // the grid has exactly the tiles that these counts make
     for (int g = 0; g < p.groups; ++g) if (p.rows_host[g] < 1 || p.rows_host[g] > (p.rows_is_k ? p.Kd : p.Md)) return false;
   if (p.sq64 && (epi != EPI_WGRAD || p.ksplit > 1 || p.upd_x)) return false;
   if (epi == EPI_WGRAD && !p.C && (!p.C2 || p.accumulate || p.ksplit > 1 || p.upd_x)) return false;

@@ -752,12 +752,14 @@ def test_the_gradient_on_demand_is_the_one_that_the_step_applied(dims, sizes):
 
 
 # Workers with batches of their own take the tiles that suit what these make, not the largest worker's: one long batch beside short ones
-# leaves the 256 x 256 shape of forward, backward-data and inner products, weight gradients go by the mean batch.
+# leaves the 256 x 256 shape of forward, backward-data and inner products, weight gradients go by the mean batch if then no layer keeps it
+# (of 3072 inputs the first one does, and the second stays with it).
 @pytest.mark.parametrize("dims,sizes,test,gone,there", [
     ((784, 384, 384, 10), [2048] + [257] * 15, W.TEST_IP, ("fwd_256x256", "bwd_256x256", "ipdot_256x256"), ("fwd_128x128", "bwd_128x128", "ipdot_128x128")),
     ((64, 768, 776, 100), [1024] + [130] * 15, W.TEST_NORM, ("fwd_256x256", "bwd_256x256"), ("fwd_128x128", "bwd_128x128")),
     ((784, 512, 512, 10), [int(3000 * 30.0 ** (-m / 15)) for m in range(16)], W.TEST_NORM, ("wgrad_256x256",), ("fwd_256x256",)),
-    ((784, 512, 512, 10), [3000] * 9 + [2000] * 7, W.TEST_NORM, (), ("fwd_256x256", "wgrad_256x256"))])
+    ((784, 512, 512, 10), [3000] * 9 + [2000] * 7, W.TEST_NORM, (), ("fwd_256x256", "wgrad_256x256")),
+    ((3072, 984, 984, 38), [2100] * 2 + [700] * 6, W.TEST_NORM, (), ("wgrad_256x256_L1", "wgrad_256x256_L2"))])
 def test_ragged_launches_take_the_tiles_that_suit_their_workers(dims, sizes, test, gone, there):
     A = _A()
     M, cap = len(sizes), max(sizes)
