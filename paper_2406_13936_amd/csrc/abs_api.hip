@@ -52,6 +52,8 @@ struct Plan {
   size_t o_qpart[MAXL] = {0}, o_partials = 0, o_stats = 0, o_cw = 0, o_colpart = 0, o_rows = 0, o_sqwave = 0, o_idx = 0, o_scal = 0, o_mean = 0;
   size_t o_kpart_l[MAXL + 1] = {0};    // per layer: partial products of a split weight-gradient reduction
   size_t kpart_floats_l[MAXL + 1] = {0};
+  bool softmax_step = false;           // fp32 without hidden layers: a step may be one launch (softmax_step.hip)
+  size_t o_spart = 0, o_ssums = 0, o_count = 0;
   size_t total = 0;
 };
 
@@ -177,6 +179,13 @@ void make_plan(const abs_config *c, long long N, Plan &pl) {
   pl.o_cw = take((2 * (size_t)cross_worker_blocks(pl.Ppad) + 8) * 8);
   pl.o_idx = take((size_t)pl.M * pl.cap * sizeof(int32_t));      // inputs of replayed (graph) steps
   pl.o_scal = take(256);
+  if (!pl.bf16 && pl.L == 1 && softmax_step_fits(pl.dims[1], pl.dims[0], 2)) {
+    pl.softmax_step = true;
+    const size_t chunks = std::min<size_t>(SOFTMAX_STEP_CHUNKS, softmax_step_chunks(pl.dims[0], std::max(pl.cap, 64)));
+    pl.o_spart = take((size_t)pl.M * std::min<size_t>(chunks * softmax_step_part_floats(pl.dims[1], pl.dims[0]), SOFTMAX_STEP_PARTS) * sizeof(float));
+    pl.o_ssums = take((size_t)pl.M * chunks * 4 * sizeof(double));
+  }
+  pl.o_count = take((size_t)pl.M * 16 * sizeof(int));         // arrivals of work-groups, zero between launches
   pl.o_mean = take((size_t)pl.Ppad * sizeof(float));          // the mean between the two passes of a large average
   pl.total = off;
 }
@@ -318,7 +327,7 @@ static const char *const kTagNames[T_GEMM0 + T_GEMM_KINDS] = {
   "gemm_wgrad_128x64", "gemm_wgrad_128x128", "gemm_wgrad_256x256", "gemm_wgrad_64x256", "gemm_wgrad_64x128", "gemm_wgrad_128x256",
   "gemm_ipdot_128x64", "gemm_ipdot_128x128", "gemm_ipdot_256x256", "gemm_ipdot_64x256", "gemm_ipdot_64x128", ""};
 
-struct ProfRec { int tag; hipEvent_t e0, e1; double flops, bytes; };
+struct ProfRec { int tag; hipEvent_t e0, e1; double flops, bytes, share; };
 
 struct abs_ctx {
   bool prof_on = false;            // launches are being bracketed right now
@@ -398,10 +407,11 @@ void to_external(const Plan &pl, bool has_bias, const float *in, float *ext) {
   }
 }
 
-// Optional event bracket around one launch (profiling on: two hipEventRecord calls).
+// Optional event bracket around one launch (profiling on: two hipEventRecord calls).  share: of a launch that is the work of two
+// classes, the part of its time that counts for this one.
 struct ProfScope {
   abs_ctx *c; ProfRec *r = nullptr;
-  ProfScope(abs_ctx *ctx, int tag, double flops, double bytes) : c(ctx) {
+  ProfScope(abs_ctx *ctx, int tag, double flops, double bytes, double share = 1.0) : c(ctx) {
     if (!c->prof_on) return;
     if (c->prof_used == c->prof_recs.size()) {
       ProfRec n{};
@@ -410,7 +420,7 @@ struct ProfScope {
       c->prof_recs.push_back(n);
     }
     r = &c->prof_recs[c->prof_used++];
-    r->tag = tag; r->flops = flops; r->bytes = bytes;
+    r->tag = tag; r->flops = flops; r->bytes = bytes; r->share = share;
     (void)hipEventRecord(r->e0, c->stream);
   }
   ~ProfScope() { if (r) (void)hipEventRecord(r->e1, c->stream); }
@@ -586,6 +596,7 @@ abs_status abs_init_replicas(const abs_config *cfg, const float *x0_host, const 
   const size_t MP = (size_t)pl.M * pl.Ppad;
   if ((e = launch_fill_zero(c->at<void>(pl.o_xm), MP * 4, c->stream)) != hipSuccess) return bail(hipGetErrorString(e));
   if ((e = launch_fill_zero(c->at<void>(pl.o_grad), MP * 4, c->stream)) != hipSuccess) return bail(hipGetErrorString(e));
+  if ((e = launch_fill_zero(c->at<void>(pl.o_count), (long long)pl.M * 16 * sizeof(int), c->stream)) != hipSuccess) return bail(hipGetErrorString(e));
   if (pl.bf16 && pl.want_ip)
     if ((e = launch_fill_zero(c->at<void>(pl.o_gradbf), MP * 2, c->stream)) != hipSuccess) return bail(hipGetErrorString(e));
   if (cfg->opt != ABS_OPT_SGD)
@@ -636,7 +647,7 @@ abs_status abs_profile_read(abs_ctx *c, int max_entries, abs_profile_entry *out,
     ProfRec &r = c->prof_recs[i];
     float ms = 0.0f;
     HIPCHK(c, hipEventElapsedTime(&ms, r.e0, r.e1));
-    c->prof_ms[r.tag] += ms; c->prof_flops[r.tag] += r.flops; c->prof_bytes[r.tag] += r.bytes;
+    c->prof_ms[r.tag] += ms * r.share; c->prof_flops[r.tag] += r.flops; c->prof_bytes[r.tag] += r.bytes;
     c->prof_calls[r.tag] += 1;
   }
   c->prof_used = 0;
@@ -684,7 +695,45 @@ struct StepPhase {
   float c1 = 1.0f, c2 = 1.0f;   // Adam bias corrections 1 / (1 - beta^t) of this step (set by the caller)
   const float *scal = nullptr;  // device {lr, c1, c2} for replayable launches (then lr / c1 / c2 here are unused)
   long long ps_off = 0;  // offset of this call's samples in the per-sample outputs (-1: not stored)
+  bool whole() const {   // a plain step
+    return passes && wgrad && nstats && s2 && ip && update && !acc_grad && !acc_n && !acc_q && b_total == 0 && ps_off == 0;
+  }
 };
+
+// The step of a net without hidden layers in fp32, in one launch (two with inner products over a long batch)
+static abs_status softmax_step(abs_ctx *c, const int32_t *idx_dev, int ldi, int b, const int *b_host, const int *rows, float lr, const StepPhase &ph) {
+  const Plan &pl = c->pl;
+  const bool hb = c->cfg.has_bias != 0;
+  SoftmaxStepP p;
+  std::memset(&p, 0, sizeof(p));
+  p.X = c->X; p.y = c->y; p.idx = idx_dev; p.N = (int)c->N; p.ldi = ldi; p.d = pl.dims[0]; p.K = pl.dims[1]; p.b = b; p.groups = pl.M;
+  p.has_bias = hb ? 1 : 0; p.rows = rows;
+  p.upd_x = c->at<float>(pl.o_xm); p.grad = c->at<float>(pl.o_grad); p.sPg = pl.Ppad; p.offB = pl.offB[1];
+  p.upd_v = c->cfg.opt != ABS_OPT_SGD ? c->at<float>(pl.o_v) : nullptr;
+  p.upd_m = c->cfg.opt == ABS_OPT_ADAMW ? c->at<float>(pl.o_m) : nullptr;
+  p.alpha = 1.0f / (float)b;
+  p.opt = c->cfg.opt; p.lr = lr; p.momentum = c->cfg.momentum; p.beta1 = c->cfg.beta1; p.beta2 = c->cfg.beta2; p.eps = c->cfg.eps;
+  p.wd = c->cfg.weight_decay; p.c1 = ph.c1; p.c2 = ph.c2; p.scal = ph.scal;
+  p.do_q = pl.want_ip ? 1 : 0;
+  p.n_out = c->at<float>(pl.o_nout); p.q_out = c->at<float>(pl.o_qout); p.sNg = pl.cap;
+  p.D = c->at<float>(pl.o_Dl[1]); p.sDg = (long long)pl.cap * pl.ld[1]; p.ldd = pl.ld[1];
+  p.part = c->at<float>(pl.o_spart); p.csums = c->at<double>(pl.o_ssums); p.count = c->at<int>(pl.o_count);
+  p.stats = c->at<double>(pl.o_stats); p.stats_host = c->host_stats_dev;
+  if (p.stats_host) { c->ticket += 1.0; p.ticket = c->ticket; c->ticket_live = true; }
+  // counted as the two contractions that it is, the time in proportion to their bytes (operands; signals, index, label, norm and
+  // loss of a sample; gradient, parameters and state)
+  const double Kd = (double)p.K * p.d, state = c->cfg.opt == ABS_OPT_SGD ? 8 : c->cfg.opt == ABS_OPT_ADAMW ? 24 : 16;
+  const double fb = pl.M * (((double)b + p.K) * p.d * 4 + b * (pl.ld[1] * 4.0 + 16)), wb = pl.M * (((double)p.K + p.d) * b * 4 + Kd * (state + 4));
+  const double flops = 2.0 * Kd * b * pl.M;
+  {
+    ProfScope pf(c, T_GEMM0 + (EPI_LOGITS * 6 + 1) * T_LAYERS + 1, flops, fb, fb / (fb + wb));
+    ProfScope pw(c, T_GEMM0 + (EPI_WGRAD * 6 + 1) * T_LAYERS + 1, flops, wb, wb / (fb + wb));
+    HIPCHK(c, launch_softmax_step(p, c->stream));
+  }
+  note_step(c, b, b_host);
+  c->last_fused = false;
+  return ABS_OK;
+}
 
 static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, int b, const int *b_host, float lr,
                                   const StepPhase &ph = StepPhase()) {
@@ -711,6 +760,8 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
     rows = rows_dev;
     if (M >= 8) gperm = rows_dev + M;
   }
+  if (pl.softmax_step && ph.whole() && softmax_step_fits(pl.dims[1], pl.dims[0], b))
+    return softmax_step(c, idx_dev, ldi, b, b_host, rows, lr, ph);
   int an_parts[MAXL + 1], dn_parts[MAXL + 2];
   for (int l = 0; l <= MAXL; ++l) an_parts[l] = dn_parts[l] = 1;
   dn_parts[MAXL + 1] = 1;

@@ -151,6 +151,30 @@ struct F32WgradPlan { int tile, ksplit; };
 F32WgradPlan gemm_f32_wgrad_plan(int Md, int Nd, int Kd, int groups, size_t kpart_floats);
 size_t gemm_f32_kpart_floats(int Md, int Nd, int groups);
 
+// ---- softmax_step.hip --------------------------------------------------------
+// One local step of a net without hidden layers in fp32 (weights [K][d] at 0 and biases at offB of every vector of stride sPg): gradient,
+// optimizer step, n_i, and the sums n, ||gbar||^2, loss (with do_q also q^2 and q, and q_i) in stats and its mirror, as StatsP has them.
+struct SoftmaxStepP {
+  const float *X; const int32_t *y, *idx; int N, ldi, d, K, b, groups, has_bias;
+  const int *rows;                       // ragged groups (optional): rows[g] <= b
+  float *upd_x, *upd_v, *upd_m, *grad; long long sPg, offB;
+  float alpha;                           // 1 / b
+  int opt; float lr, momentum, beta1, beta2, eps, wd, c1, c2;
+  const float *scal;                     // optional (device): {lr, c1, c2}
+  int do_q;
+  float *n_out, *q_out; long long sNg;   // [g][i]
+  float *D; long long sDg; int ldd;      // scratch: signals [g][i][ldd], ldd >= K (do_q over several chunks)
+  float *part; double *csums; int *count;   // scratch of several chunks: [g][chunk][part_ld], [g][chunk][4], and 16 ints per group that
+                                            //   are zero before the first launch and after each
+  double *stats, *stats_host, ticket;
+  int chunks, part_ld;                   // set by the launcher
+};
+enum { SOFTMAX_STEP_CHUNKS = 32, SOFTMAX_STEP_PARTS = 1 << 19 };     // chunks, and floats of partial gradients, to a group
+inline int softmax_step_part_floats(int K, int d) { return (K * d + K + 63) / 64 * 64; }
+int softmax_step_chunks(int d, int b);
+bool softmax_step_fits(int K, int d, int b);
+hipError_t launch_softmax_step(SoftmaxStepP p, hipStream_t s);
+
 // ---- gram_ip.hip -----------------------------------------------------------
 // q[g][i] = (1 / b_g) sum_l sum_j (D_l D_l^T)[i][j] ((A_l A_l^T)[i][j] + [has_bias]),  i, j < b_g: the inner products
 // <g_i, gbar> of a short batch from the Gram matrices of the layer inputs A_l = a^{l-1} and backprop signals

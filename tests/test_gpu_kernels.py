@@ -854,3 +854,66 @@ def test_profile_counts_the_per_sample_statistics_where_they_run():
     sample = 4 * M * b * (1 + 4 + 2 + 1 + 2)
     assert got[0]["gemm_wgrad_64x256_L0"] - got[1]["gemm_wgrad_64x256_L0"] == sample
     assert got[1]["stats"] - got[0]["stats"] == sample + 4 * M * b * 2        # (and q from the Gram matrices: read and stored)
+
+
+# The fp32 step of a net without hidden layers in one launch: one work-group to a replica (up to 16, 32 or 64 samples), several whose last
+# one adds up, the lines between them, rows that are no multiple of 4 or of a wavefront, the most classes and features, workers with
+# batches of their own (one chunk beside several); inner products in the same launch or a second one; a second step from non-zero state.
+@pytest.mark.parametrize("dims,sizes,opt", [
+    ((1, 2), [2, 2], W.OPT_SGD), ((3, 16), [16] * 2, W.OPT_SHB), ((16, 10), [17] * 3, W.OPT_ADAMW), ((65, 5), [32] * 2, W.OPT_ADAGRAD),
+    ((257, 16), [33] * 2, W.OPT_SGD), ((512, 10), [64] * 2, W.OPT_ADAMW), ((513, 9), [64] * 2, W.OPT_SHB), ((256, 10), [65] * 4, W.OPT_SGD),
+    ((1024, 16), [100] * 2, W.OPT_ADAGRAD), ((1025, 3), [129] * 2, W.OPT_SGD), ((2048, 16), [256], W.OPT_SHB), ((100, 7), [1024] * 3, W.OPT_ADAMW),
+    ((100, 7), [1025] * 2, W.OPT_SGD), ((256, 10), [200, 2, 64, 65, 33, 16], W.OPT_SHB), ((30, 11), [64, 5, 40], W.OPT_SGD)])
+def test_one_launch_of_a_net_without_hidden_layers(dims, sizes, opt):
+    A = _A()
+    M, b = len(sizes), max(sizes)
+    w = W.Workload("one", dims, W.ACT_NONE, True, W.PREC_F32, N=2048, M=M, H=1, rounds=1, b0=b, b_cap=b, opt=opt, lr=0.05, momentum=0.9,
+                   weight_decay=0.05, test=W.TEST_IP, theta=0.9, data="teacher_mlp", seed=43)
+    X, y = W.make_dataset(w)
+    x0 = W.make_x0(w)
+    rep = A.Replicas.from_workload(w, X, y, x0)
+    try:
+        orc = O.Replicas(O.Net(w.dims, w.act, True), x0, X, y, M, opt=opt, momentum=w.momentum, beta1=w.beta1, beta2=w.beta2, eps=w.eps,
+                         weight_decay=w.weight_decay, want_ip=True)
+        for h in range(2):
+            rows = [W.batch_indices(w.seed, h, 0, m, s, w.N) for m, s in enumerate(sizes)]
+            if len(set(sizes)) > 1:
+                rep.local_step_ragged(rows, w.lr)
+            else:
+                rep.local_step(np.stack(rows), w.lr)
+            _check_fp32_step(rep, w, orc, rows, range(M))
+            res = rep.inner_product_test(0.9)
+            for m in range(M):                       # sums of d, K and b fp32 products; a signal p - 1 keeps p's 2^-24, which a small one shows
+                s, (n, q) = orc.stats[m], rep.get_per_sample(m, sizes[m], want_q=True)
+                np.testing.assert_allclose(n, s["n"], rtol=1e-4, atol=1e-6 * s["n"].max())
+                np.testing.assert_allclose(q, s["q"], rtol=1e-3, atol=1e-5 * np.abs(s["q"]).max())
+                for got, want in ((res[m].sum_sq, s["S1"]), (res[m].loss_sum, s["loss_sum"]), (res[m].sum_q2, s["S3"]), (res[m].sum_q, s["S4"])):
+                    assert abs(got - want) <= 1e-4 * abs(want), (m, got, want)
+        assert rep.guard_intact()
+    finally:
+        rep.close()
+
+
+# Replays of a captured step of that kind, where a replica's work-groups count their arrivals: bit for bit the direct steps.
+def test_replayed_steps_of_a_net_without_hidden_layers():
+    import torch
+    A = _A()
+    w = W.Workload("replay", (100, 10), W.ACT_NONE, True, W.PREC_F32, N=1024, M=3, H=1, rounds=1, b0=40, b_cap=130, opt=W.OPT_SHB, lr=0.05,
+                   momentum=0.9, test=W.TEST_IP, theta=0.9, data="mixture", seed=47)
+    X, y = W.make_dataset(w)
+    x0 = W.make_x0(w)
+    with torch.cuda.stream(torch.cuda.Stream()):
+        ref, rep = (A.Replicas.from_workload(w, X, y, x0) for _ in range(2))
+        try:
+            for s, b in enumerate([130, 40, 130, 130, 40, 40, 130, 40, 130]):
+                idx = W.step_indices(w, s, 0, b)
+                (t1, _), (t2, _) = ref.upload_indices(idx), rep.upload_indices(idx)
+                ref.local_step_dev(t1, b, w.lr)
+                rep.local_step_graphed_dev(t2, b, w.lr)
+                for g1, g2 in zip(ref.inner_product_test(w.theta), rep.inner_product_test(w.theta)):
+                    assert (g1.sum_sq, g1.gbar_sq, g1.sum_q, g1.sum_q2, g1.loss_sum) == (g2.sum_sq, g2.gbar_sq, g2.sum_q, g2.sum_q2, g2.loss_sum), s
+                assert all(np.array_equal(ref.get_params(m), rep.get_params(m)) for m in range(w.M)), s
+            assert rep.graph_count() == 2
+        finally:
+            ref.close()
+            rep.close()
