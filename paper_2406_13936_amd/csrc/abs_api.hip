@@ -54,6 +54,8 @@ struct Plan {
   size_t kpart_floats_l[MAXL + 1] = {0};
   bool softmax_step = false;           // fp32 without hidden layers: a step may be one launch (softmax_step.hip)
   size_t o_spart = 0, o_ssums = 0, o_count = 0;
+  size_t o_chain = 0;                  // arrivals of the tiles of a chained launch, zero between launches
+  int chain_words = 0, chain_max = 0;  // words to a chain, and chains
   size_t total = 0;
 };
 
@@ -186,6 +188,11 @@ void make_plan(const abs_config *c, long long N, Plan &pl) {
     pl.o_ssums = take((size_t)pl.M * chunks * 4 * sizeof(double));
   }
   pl.o_count = take((size_t)pl.M * 16 * sizeof(int));         // arrivals of work-groups, zero between launches
+  if (pl.bf16 && pl.L >= 2 && pl.L <= SmallChain::MAXL) {
+    pl.chain_words = small_chain_words(pl.L, pl.dims.data());
+    pl.chain_max = (int)std::min<long long>((long long)pl.M * ((pl.cap + 31) / 32), 512);     // (512 tiles of 32 x 32 in the first pass at most)
+    pl.o_chain = take((size_t)pl.chain_max * pl.chain_words * sizeof(int));
+  }
   pl.o_mean = take((size_t)pl.Ppad * sizeof(float));          // the mean between the two passes of a large average
   pl.total = off;
 }
@@ -597,6 +604,8 @@ abs_status abs_init_replicas(const abs_config *cfg, const float *x0_host, const 
   if ((e = launch_fill_zero(c->at<void>(pl.o_xm), MP * 4, c->stream)) != hipSuccess) return bail(hipGetErrorString(e));
   if ((e = launch_fill_zero(c->at<void>(pl.o_grad), MP * 4, c->stream)) != hipSuccess) return bail(hipGetErrorString(e));
   if ((e = launch_fill_zero(c->at<void>(pl.o_count), (long long)pl.M * 16 * sizeof(int), c->stream)) != hipSuccess) return bail(hipGetErrorString(e));
+  if (pl.chain_max > 0)
+    if ((e = launch_fill_zero(c->at<void>(pl.o_chain), (long long)pl.chain_max * pl.chain_words * sizeof(int), c->stream)) != hipSuccess) return bail(hipGetErrorString(e));
   if (pl.bf16 && pl.want_ip)
     if ((e = launch_fill_zero(c->at<void>(pl.o_gradbf), MP * 2, c->stream)) != hipSuccess) return bail(hipGetErrorString(e));
   if (cfg->opt != ABS_OPT_SGD)
@@ -793,13 +802,24 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
     GatherP ga = {Xsrc, pl.dims[0], (int)c->N, idx_dev, ldi, b, M, act_ptr(pl.o_A[0]), cap * pl.ld[0], pl.ld[0],
                   c->at<float>(pl.o_an[0]), cap, rows};
     const int ride = gather_rides(isb, L, b, pl.dims.data(), M, c->N, b_host);
+    const bool head_fused = gemm_head_fits(isb, b, pl.dims[L], M);
+    // all passes on 32-row tiles: one launch for them
+    bool chained = (long long)M * ((b + 31) / 32) <= pl.chain_max && ride == 1 && head_fused;
+    for (int l = 1; l < L && chained; ++l)
+      chained = gemm_bf16_tile_shape(EPI_FWD_ACT, b, pl.dims[l], M, b_host) == 5 && gemm_bf16_tile_shape(EPI_BWD, b, pl.dims[l], M, b_host) == 5;
+    SmallChain ch;
+    std::vector<GemmP> passes;
+    auto pass = [&](const GemmP &p, int epi, int l) -> hipError_t {
+      if (!chained) return gemm(c, p, epi, l);
+      passes.push_back(p);
+      return hipSuccess;
+    };
     if (!ride) {
       ProfScope ps_(c, T_GATHER, 0.0, 2.0 * M * b * pl.dims[0] * pl.esz);
       HIPCHK(c, launch_gather_rows(isb, ga, s));
     }
 
     // forward
-    const bool head_fused = gemm_head_fits(isb, b, pl.dims[L], M);
     for (int l = 1; l <= L; ++l) {
       GemmP p;
       std::memset(&p, 0, sizeof(p));
@@ -809,7 +829,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       if (hb) { p.bias = xm + pl.offB[l]; p.sBiasg = pl.Ppad; }
       p.act = c->cfg.act;
       if (ride && l == 1) { p.A = Xsrc; p.sAg = 0; p.lda = pl.dims[0]; p.aidx = idx_dev; p.aN = (int)c->N; p.aldi = ldi; }
-      if (ride == (l == 1 ? 1 : l == L ? 2 : 3)) p.gather = &ga;
+      if (!chained && ride == (l == 1 ? 1 : l == L ? 2 : 3)) p.gather = &ga;
       if (l < L) {
         p.C = act_ptr(pl.o_A[l]); p.sCg = cap * pl.ld[l]; p.ldc = pl.ld[l]; p.pad_to_ld = 1;
         if (pl.gelu) { p.C2 = act_ptr(pl.o_Dact[l]); p.sC2g = cap * pl.ld[l]; p.ldc2 = pl.ld[l]; }
@@ -818,7 +838,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
           an_parts[l] = gemm_bf16_row_parts(EPI_FWD_ACT, b, pl.dims[l], M, b_host);
           if ((size_t)(an_parts[l] * part_ld) > pl.rpart_floats[l]) return cfail(c, ABS_ENOMEM, "row-partial scratch too small for this tile shape");
           if (want_parts) { p.part = c->at<float>(pl.o_an[l]); p.sPartg = (long long)pl.rpart_floats[l]; p.sPartTile = part_ld; }
-          HIPCHK(c, gemm(c, p, EPI_FWD_ACT, l));
+          HIPCHK(c, pass(p, EPI_FWD_ACT, l));
         } else {
           HIPCHK(c, gemm(c, p, EPI_FWD_ACT, l));
           if (!want_parts) continue;
@@ -832,7 +852,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
           p.head.D = act_ptr(pl.o_Dl[L]); p.head.sDg = cap * pl.ld[L];
           p.head.dn = c->at<float>(pl.o_dn[L]); p.head.loss = c->at<float>(pl.o_loss); p.head.sNg = cap;
         }
-        HIPCHK(c, gemm(c, p, EPI_LOGITS, l));
+        HIPCHK(c, pass(p, EPI_LOGITS, l));
       }
     }
     // loss head: per-sample backprop signal of the last layer (few classes: out of the logits' launch)
@@ -867,13 +887,28 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
           cf.out_off[e] = pl.offB[l - 1];
           cf_bytes += 4.0 * M * cf.nsplit[e] * cf.cols[e];
         }
-        HIPCHK(c, gemm(c, p, EPI_BWD, l));
+        HIPCHK(c, pass(p, EPI_BWD, l));
       } else {
         HIPCHK(c, gemm(c, p, EPI_BWD, l));
         if (!want_parts) continue;
         ProfScope ps_(c, T_ROWNORM, 0.0, 1.0 * M * b * pl.ld[l - 1] * pl.esz);
         HIPCHK(c, launch_row_sqnorm(isb, p.C, p.sCg, pl.ld[l - 1], pl.ld[l - 1], M, b, c->at<float>(pl.o_dn[l - 1]), cap, rows, s));
       }
+    }
+    if (chained) {
+      std::memset(&ch, 0, sizeof(ch));
+      ch.L = L; ch.words = pl.chain_words; ch.count = c->at<int>(pl.o_chain); ch.gather = ga;
+      std::copy(passes.begin(), passes.end(), ch.p);
+      // each pass counts as the class that it would be apart, with a share of the time by its bytes
+      auto epi = [&](int i) { return i < L - 1 ? EPI_FWD_ACT : i == L - 1 ? EPI_LOGITS : EPI_BWD; };
+      std::unique_ptr<ProfScope> scopes[2 * SmallChain::MAXL - 1];
+      double bytes = 0.0;
+      for (int i = 0; i < 2 * L - 1; ++i) bytes += gemm_bytes(c, ch.p[i], epi(i));
+      for (int i = 0; i < 2 * L - 1 && c->prof_on; ++i) {
+        const double own = gemm_bytes(c, ch.p[i], epi(i));
+        scopes[i].reset(new ProfScope(c, T_GEMM0 + (epi(i) * 6 + 5) * T_LAYERS + (i < L ? i + 1 : 2 * L - i), gemm_flops(ch.p[i]), own, own / bytes));
+      }
+      HIPCHK(c, launch_small_chain(ch, s));
     }
   }   // passes
   // fp32 mode (small problems): the tile of a weight gradient and the slices that a long batch over few tiles is cut into

@@ -131,6 +131,21 @@ size_t gemm_bf16_row_part_floats(int Nd, int groups, int cap);
 // rows_host (here and below): the rows of ragged groups, at most Md (weight gradients: Kd) each, or null.
 int gemm_bf16_tile_shape(int epi, int Md, int Nd, int groups, const int *rows_host);
 hipError_t launch_gemm_small(const GemmP &p, int epi, hipStream_t s);
+// Passes of a step whose launches are all of them 32-row tiles, in one launch: forward of layers 1 .. L - 1 (the first with GemmP::aidx),
+// logits with the head, backward-data of layers L .. 2, and the gather.  count: `words` ints (small_chain_words) for each replica and 32
+// rows, zero before the first launch and after each.
+struct SmallChain {
+  enum { MAXL = 4 };
+  int L, words;
+  int *count;
+  int end[2 * MAXL - 2], chains;                 // set by the launcher: tiles of a chain up to and with each pass (logits with layer L's backward-data)
+  GatherP gather;
+  GemmP p[2 * MAXL - 1];
+};
+static_assert(sizeof(SmallChain) <= 4096, "kernel arguments");
+int small_chain_words(int L, const int *dims);
+hipError_t launch_small_chain(SmallChain &c, hipStream_t s);
+bool gemm_bf16_operands_ok(const GemmP &p, int epi);       // what every launch of the family relies on
 // Whether an EPI_LOGITS launch can carry the softmax head: a row's classes lie in one tile, eight or sixteen lanes to the row.
 bool gemm_head_fits(int is_bf16, int Md, int Nd, int groups);
 // Tile shape of an EPI_WGRAD launch whose reduction runs over Kd samples: as above, or 3 = 64x256 with a k-step of

@@ -84,6 +84,11 @@ __device__ __forceinline__ void opt_step_elem(float &x, float g, float &v, float
   }
 }
 
+// the value of another lane by a DPP control word, every lane having one
+template <int CTRL> __device__ __forceinline__ float dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);

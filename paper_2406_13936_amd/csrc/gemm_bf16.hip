@@ -1317,6 +1317,8 @@ bool operands_ok(const GemmP &p, int epi) {
 
 }  // namespace
 
+bool gemm_bf16_operands_ok(const GemmP &p, int epi) { return operands_ok(p, epi); }
+
 int gemm_bf16_tile_shape(int epi, int Md, int Nd, int groups, const int *rows_host) {
   if ((epi == EPI_FWD_ACT || epi == EPI_LOGITS || epi == EPI_BWD) && small_tiles(Md, Nd, groups) <= small_limit(epi, Md, Nd, groups))
     return 5;

@@ -50,14 +50,12 @@ __device__ __forceinline__ float wave_sum_last(float v) {
 }
 // and over each sixteen lanes, in all of them
 __device__ __forceinline__ float sum16(float v) {
-  v = dpp_add<0x121, 0xf>(v); v = dpp_add<0x122, 0xf>(v); v = dpp_add<0x124, 0xf>(v);      // row_ror: 1, 2, 4, 8
-  return dpp_add<0x128, 0xf>(v);
+  v += dpp<0x121>(v); v += dpp<0x122>(v); v += dpp<0x124>(v);      // row_ror: 1, 2, 4, 8
+  return v + dpp<0x128>(v);
 }
 __device__ __forceinline__ float max16(float v) {
-  v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x121, 0xf, 0xf, false)));
-  v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x122, 0xf, 0xf, false)));
-  v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x124, 0xf, 0xf, false)));
-  return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, false)));
+  v = fmaxf(v, dpp<0x121>(v)); v = fmaxf(v, dpp<0x122>(v)); v = fmaxf(v, dpp<0x124>(v));
+  return fmaxf(v, dpp<0x128>(v));
 }
 
 // rows s0 .. s0 + ns - 1 of group g to LDS, zeros beyond them and beyond d, and their squared norms.  A wavefront takes rows

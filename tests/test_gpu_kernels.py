@@ -917,3 +917,57 @@ def test_replayed_steps_of_a_net_without_hidden_layers():
         finally:
             ref.close()
             rep.close()
+
+
+# Forward, head and backward-data in one launch (nets of two to four layers on 32-row tiles, at most 32 classes): blocks of rows with one row,
+# empty ones of workers with batches of their own, one and several tiles to a pass, reductions of more than one trip (1096), the most
+# classes, and the first nets beyond (33 classes, five layers); batch sizes that change from step to step, so that every launch finds the
+# arrivals of a differently shaped one put back; the last ones replayed from captured graphs, bit for bit the direct step.
+@pytest.mark.parametrize("dims,act,steps", [
+    ((8, 8, 2), W.ACT_RELU, ([2, 2], [33, 33], [33, 2], [2, 2])), ((72, 40, 32), W.ACT_GELU, ([31] * 3, [65, 32, 2], [65] * 3)),
+    ((264, 72, 104, 17), W.ACT_GELU, ([33] * 2, [96, 1 + 32], [64] * 2)), ((40, 1096, 64, 8, 5), W.ACT_RELU, ([32] * 2, [40, 2], [40] * 2)),
+    ((1096, 136, 520, 10), W.ACT_NONE, ([66], [7], [66])), ((72, 40, 33), W.ACT_GELU, ([33] * 2, [9, 33])),
+    ((40, 24, 24, 24, 24, 6), W.ACT_RELU, ([33] * 2, [9, 33]))])
+def test_passes_in_one_launch(dims, act, steps):
+    import torch
+    A = _A()
+    M, cap = len(steps[0]), max(max(s) for s in steps)
+    w = W.Workload("chain", dims, act, True, W.PREC_BF16, N=512, M=M, H=1, rounds=1, b0=cap, b_cap=cap, opt=W.OPT_SGD, lr=0.02,
+                   test=W.TEST_IP, theta=0.9, data="teacher_mlp", seed=53)
+    X, y = W.make_dataset(w)
+    x0 = W.make_x0(w)
+    with torch.cuda.stream(torch.cuda.Stream()):
+        rep, twin = (A.Replicas.from_workload(w, X, y, x0) for _ in range(2))
+        orc = O.Replicas(O.Net(w.dims, w.act, True), x0, X, y, M, opt=w.opt, mixed=True, want_ip=True, gram_max_b=256)
+        try:
+            for h, sizes in enumerate(steps):
+                rows = [W.batch_indices(w.seed, h, 0, m, s, w.N) for m, s in enumerate(sizes)]
+                if len(set(sizes)) > 1:
+                    rep.local_step_ragged(rows, w.lr)
+                else:
+                    rep.local_step(np.stack(rows), w.lr)
+                orc.local_step(rows, w.lr)
+                res = rep.inner_product_test(w.theta)
+                for m in range(M):
+                    s = orc.stats[m]
+                    for got, want in ((res[m].sum_sq, s["S1"]), (res[m].gbar_sq, s["S2"]), (res[m].loss_sum, s["loss_sum"])):
+                        assert abs(got - want) <= 2e-3 * abs(want), (h, m, got, want)
+                    grad = rep.get_grad(m).astype(np.float64)
+                    assert np.linalg.norm(grad - orc.grads[m]) <= 2e-3 * np.linalg.norm(orc.grads[m]), (h, m)
+                    p = rep.get_params(m).astype(np.float64)
+                    assert np.abs(p - orc.x[m]).max() <= 1e-3 * np.abs(orc.x[m]).max(), (h, m)
+                    orc.x[m] = p
+            for m in range(M):
+                twin.set_params(m, rep.get_params(m))
+            for h in range(4):
+                idx = W.step_indices(w, 10 + h, 0, cap)
+                (t1, _), (t2, _) = rep.upload_indices(idx), twin.upload_indices(idx)
+                rep.local_step_dev(t1, cap, w.lr)
+                twin.local_step_graphed_dev(t2, cap, w.lr)
+                for g1, g2 in zip(rep.inner_product_test(w.theta), twin.inner_product_test(w.theta)):
+                    assert (g1.sum_sq, g1.gbar_sq, g1.sum_q, g1.sum_q2, g1.loss_sum) == (g2.sum_sq, g2.gbar_sq, g2.sum_q, g2.sum_q2, g2.loss_sum), h
+                assert all(np.array_equal(rep.get_params(m), twin.get_params(m)) for m in range(M)), h
+            assert rep.guard_intact() and twin.guard_intact()
+        finally:
+            rep.close()
+            twin.close()
