@@ -417,7 +417,7 @@ void to_external(const Plan &pl, bool has_bias, const float *in, float *ext) {
 // Optional event bracket around one launch (profiling on: two hipEventRecord calls).  share: of a launch that is the work of two
 // classes, the part of its time that counts for this one.
 struct ProfScope {
-  abs_ctx *c; ProfRec *r = nullptr;
+  abs_ctx *c; size_t r = 0; bool on = false;       // (its number: records of scopes inside this one may move the pool)
   ProfScope(abs_ctx *ctx, int tag, double flops, double bytes, double share = 1.0) : c(ctx) {
     if (!c->prof_on) return;
     if (c->prof_used == c->prof_recs.size()) {
@@ -426,11 +426,15 @@ struct ProfScope {
       if (hipEventCreate(&n.e1) != hipSuccess) { (void)hipEventDestroy(n.e0); return; }
       c->prof_recs.push_back(n);
     }
-    r = &c->prof_recs[c->prof_used++];
-    r->tag = tag; r->flops = flops; r->bytes = bytes; r->share = share;
-    (void)hipEventRecord(r->e0, c->stream);
+    r = c->prof_used++;
+    on = true;
+    ProfRec &rec = c->prof_recs[r];
+    rec.tag = tag; rec.flops = flops; rec.bytes = bytes; rec.share = share;
+    (void)hipEventRecord(rec.e0, c->stream);
   }
-  ~ProfScope() { if (r) (void)hipEventRecord(r->e1, c->stream); }
+  ~ProfScope() { if (on) (void)hipEventRecord(c->prof_recs[r].e1, c->stream); }
+  ProfScope(const ProfScope &) = delete;
+  ProfScope &operator=(const ProfScope &) = delete;
 };
 
 double gemm_flops(const GemmP &p) { return 2.0 * p.Md * p.Nd * p.Kd * p.groups; }
