@@ -152,9 +152,9 @@ void make_plan(const abs_config *c, long long N, Plan &pl) {
   }
   if (c->has_bias && pl.bf16) {
     for (int l = 1; l <= pl.L; ++l) {
-      // layers below L: partials from the backward epilogue, at most ceil(b / 128) * 4 rows for any tile shape the
-      // GEMM may pick (128-row tiles of 4 wave rows; the other shapes write fewer); layer L: the standalone sums
-      const size_t rows = l < pl.L ? (size_t)((pl.cap + 127) / 128 * 4) : (size_t)((pl.cap + COLSUM_ROWS - 1) / COLSUM_ROWS);
+      // layers below L: partials from the backward epilogue, at most ceil(b / 128) * 8 rows (blocks of 16 rows
+      // of mlp_rows.hip; 128-row tiles of 4 wave rows write half of it, the other shapes fewer); layer L: the standalone sums
+      const size_t rows = l < pl.L ? (size_t)((pl.cap + 127) / 128 * 8) : (size_t)((pl.cap + COLSUM_ROWS - 1) / COLSUM_ROWS);
       pl.colpart_l_per[l] = rows * pl.dims[l];
       pl.o_colpart_l[l] = take((size_t)pl.M * pl.colpart_l_per[l] * 4);
     }
@@ -805,16 +805,18 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
     const void *Xsrc = pl.bf16 ? static_cast<const void *>(c->at<bf16_t>(pl.o_Xbf)) : static_cast<const void *>(c->X);
     GatherP ga = {Xsrc, pl.dims[0], (int)c->N, idx_dev, ldi, b, M, act_ptr(pl.o_A[0]), cap * pl.ld[0], pl.ld[0],
                   c->at<float>(pl.o_an[0]), cap, rows};
-    const int ride = gather_rides(isb, L, b, pl.dims.data(), M, c->N, b_host);
-    const bool head_fused = gemm_head_fits(isb, b, pl.dims[L], M);
+    int ride = gather_rides(isb, L, b, pl.dims.data(), M, c->N, b_host);
+    bool head_fused = gemm_head_fits(isb, b, pl.dims[L], M);
     // all passes on 32-row tiles: one launch for them
     bool chained = (long long)M * ((b + 31) / 32) <= pl.chain_max && ride == 1 && head_fused;
     for (int l = 1; l < L && chained; ++l)
       chained = gemm_bf16_tile_shape(EPI_FWD_ACT, b, pl.dims[l], M, b_host) == 5 && gemm_bf16_tile_shape(EPI_BWD, b, pl.dims[l], M, b_host) == 5;
-    SmallChain ch;
+    // or blocks of rows, each on its own way through all layers
+    const int block = pl.bf16 && !chained && !b_host ? mlp_rows_block(L, pl.dims.data(), b, M, c->N) : 0;
+    if (block) { ride = 1; head_fused = true; }
     std::vector<GemmP> passes;
     auto pass = [&](const GemmP &p, int epi, int l) -> hipError_t {
-      if (!chained) return gemm(c, p, epi, l);
+      if (!chained && !block) return gemm(c, p, epi, l);
       passes.push_back(p);
       return hipSuccess;
     };
@@ -833,13 +835,13 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       if (hb) { p.bias = xm + pl.offB[l]; p.sBiasg = pl.Ppad; }
       p.act = c->cfg.act;
       if (ride && l == 1) { p.A = Xsrc; p.sAg = 0; p.lda = pl.dims[0]; p.aidx = idx_dev; p.aN = (int)c->N; p.aldi = ldi; }
-      if (!chained && ride == (l == 1 ? 1 : l == L ? 2 : 3)) p.gather = &ga;
+      if (!chained && !block && ride == (l == 1 ? 1 : l == L ? 2 : 3)) p.gather = &ga;
       if (l < L) {
         p.C = act_ptr(pl.o_A[l]); p.sCg = cap * pl.ld[l]; p.ldc = pl.ld[l]; p.pad_to_ld = 1;
         if (pl.gelu) { p.C2 = act_ptr(pl.o_Dact[l]); p.sC2g = cap * pl.ld[l]; p.ldc2 = pl.ld[l]; }
         if (pl.bf16) {
           // ||a_i^l||^2 as per-tile partials out of the GEMM epilogue (summed by the statistics kernel)
-          an_parts[l] = gemm_bf16_row_parts(EPI_FWD_ACT, b, pl.dims[l], M, b_host);
+          an_parts[l] = block ? 1 : gemm_bf16_row_parts(EPI_FWD_ACT, b, pl.dims[l], M, b_host);
           if ((size_t)(an_parts[l] * part_ld) > pl.rpart_floats[l]) return cfail(c, ABS_ENOMEM, "row-partial scratch too small for this tile shape");
           if (want_parts) { p.part = c->at<float>(pl.o_an[l]); p.sPartg = (long long)pl.rpart_floats[l]; p.sPartTile = part_ld; }
           HIPCHK(c, pass(p, EPI_FWD_ACT, l));
@@ -877,17 +879,19 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       p.sEg = cap * pl.ld[l - 1]; p.lde = pl.ld[l - 1];
       if (pl.bf16) {
         // ||delta_i^{l-1}||^2 and (with biases) the column sums of delta^{l-1} as epilogue partials
-        dn_parts[l - 1] = gemm_bf16_row_parts(EPI_BWD, b, pl.dims[l - 1], M, b_host);
+        dn_parts[l - 1] = block ? 1 : gemm_bf16_row_parts(EPI_BWD, b, pl.dims[l - 1], M, b_host);
         if ((size_t)(dn_parts[l - 1] * part_ld) > pl.rpart_floats[l - 1]) return cfail(c, ABS_ENOMEM, "row-partial scratch too small for this tile shape");
         if (want_parts) { p.part = c->at<float>(pl.o_dn[l - 1]); p.sPartg = (long long)pl.rpart_floats[l - 1]; p.sPartTile = part_ld; }
         if (hb && ph.wgrad) {
           p.cpart = c->at<float>(pl.o_colpart_l[l - 1]);
-          p.sCpartg = (long long)gemm_bf16_col_parts(EPI_BWD, b, pl.dims[l - 1], M, b_host) * pl.dims[l - 1];
+          const int parts = block ? (b + block - 1) / block : gemm_bf16_col_parts(EPI_BWD, b, pl.dims[l - 1], M, b_host);
+          p.sCpartg = (long long)parts * pl.dims[l - 1];
           if ((size_t)p.sCpartg > pl.colpart_l_per[l - 1]) return cfail(c, ABS_ENOMEM, "column-partial scratch too small for this tile shape");
           // the partials are added up for all layers at once after the weight gradients
           const int e = cf.n++;
-          cf.part[e] = p.cpart; cf.cols[e] = pl.dims[l - 1]; cf.nsplit[e] = gemm_bf16_col_parts(EPI_BWD, b, pl.dims[l - 1], M, b_host);
-          gemm_bf16_col_part_shape(EPI_BWD, b, pl.dims[l - 1], M, b_host, &cf.tile_m[e], &cf.parts_per_tile[e]);
+          cf.part[e] = p.cpart; cf.cols[e] = pl.dims[l - 1]; cf.nsplit[e] = parts;
+          if (block) { cf.tile_m[e] = block; cf.parts_per_tile[e] = 1; }
+          else gemm_bf16_col_part_shape(EPI_BWD, b, pl.dims[l - 1], M, b_host, &cf.tile_m[e], &cf.parts_per_tile[e]);
           cf.out_off[e] = pl.offB[l - 1];
           cf_bytes += 4.0 * M * cf.nsplit[e] * cf.cols[e];
         }
@@ -899,20 +903,29 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
         HIPCHK(c, launch_row_sqnorm(isb, p.C, p.sCg, pl.ld[l - 1], pl.ld[l - 1], M, b, c->at<float>(pl.o_dn[l - 1]), cap, rows, s));
       }
     }
-    if (chained) {
-      std::memset(&ch, 0, sizeof(ch));
-      ch.L = L; ch.words = pl.chain_words; ch.count = c->at<int>(pl.o_chain); ch.gather = ga;
-      std::copy(passes.begin(), passes.end(), ch.p);
+    if (chained || block) {
       // each pass counts as the class that it would be apart, with a share of the time by its bytes
       auto epi = [&](int i) { return i < L - 1 ? EPI_FWD_ACT : i == L - 1 ? EPI_LOGITS : EPI_BWD; };
       std::unique_ptr<ProfScope> scopes[2 * SmallChain::MAXL - 1];
       double bytes = 0.0;
-      for (int i = 0; i < 2 * L - 1; ++i) bytes += gemm_bytes(c, ch.p[i], epi(i));
+      for (int i = 0; i < 2 * L - 1; ++i) bytes += gemm_bytes(c, passes[i], epi(i));
       for (int i = 0; i < 2 * L - 1 && c->prof_on; ++i) {
-        const double own = gemm_bytes(c, ch.p[i], epi(i));
-        scopes[i].reset(new ProfScope(c, T_GEMM0 + (epi(i) * 6 + 5) * T_LAYERS + (i < L ? i + 1 : 2 * L - i), gemm_flops(ch.p[i]), own, own / bytes));
+        const double own = gemm_bytes(c, passes[i], epi(i));
+        scopes[i].reset(new ProfScope(c, T_GEMM0 + (epi(i) * 6 + 5) * T_LAYERS + (i < L ? i + 1 : 2 * L - i), gemm_flops(passes[i]), own, own / bytes));
       }
-      HIPCHK(c, launch_small_chain(ch, s));
+      if (chained) {
+        SmallChain ch;
+        std::memset(&ch, 0, sizeof(ch));
+        ch.L = L; ch.words = pl.chain_words; ch.count = c->at<int>(pl.o_chain); ch.gather = ga;
+        std::copy(passes.begin(), passes.end(), ch.p);
+        HIPCHK(c, launch_small_chain(ch, s));
+      } else {
+        MlpRows mr;
+        std::memset(&mr, 0, sizeof(mr));
+        mr.L = L; mr.rows = block; mr.gather = ga;
+        std::copy(passes.begin(), passes.end(), mr.p);
+        HIPCHK(c, launch_mlp_rows(mr, s));
+      }
     }
   }   // passes
   // fp32 mode (small problems): the tile of a weight gradient and the slices that a long batch over few tiles is cut into

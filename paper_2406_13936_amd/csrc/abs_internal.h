@@ -145,6 +145,21 @@ struct SmallChain {
 static_assert(sizeof(SmallChain) <= 4096, "kernel arguments");
 int small_chain_words(int L, const int *dims);
 hipError_t launch_small_chain(SmallChain &c, hipStream_t s);
+// ---- mlp_rows.hip ------------------------------------------------------------
+// The same passes with a block of `rows` rows of one replica to a work-group, which walks all layers (p, gather as in SmallChain; one row
+// partial and one column partial to a block).  mlp_rows_block: the rows to a block where that is the faster way, else 0.
+struct MlpRows {
+  enum { MAXL = 4, MAX_CLASSES = 128, MAX_INPUTS = 896 };
+  int L, rows;
+  int per, blocks, share, weight_bytes;          // set by the launcher: blocks to a replica, in all, to an XCD; from the first layer's weights to the last's end
+  GatherP gather;
+  GemmP p[2 * MAXL - 1];
+};
+static_assert(sizeof(MlpRows) <= 4096, "kernel arguments");
+int mlp_rows_block(int L, const int *dims, int b, int groups, long long N);
+hipError_t launch_mlp_rows(MlpRows &c, hipStream_t s);
+
+// ---- gemm_bf16.hip -----------------------------------------------------------
 bool gemm_bf16_operands_ok(const GemmP &p, int epi);       // what every launch of the family relies on
 // Whether an EPI_LOGITS launch can carry the softmax head: a row's classes lie in one tile, eight or sixteen lanes to the row.
 bool gemm_head_fits(int is_bf16, int Md, int Nd, int groups);

@@ -971,3 +971,44 @@ def test_passes_in_one_launch(dims, act, steps):
         finally:
             rep.close()
             twin.close()
+
+
+# All passes of a block of rows in one work-group: blocks of 16, 32 and 64 rows, layers up to 256 and up to 512, last blocks of one row and
+# full ones, the widest inputs and the most classes, widths that fill no whole wavefront, no activation and no biases, indices outside the
+# dataset; and the first nets beyond (904 inputs, 129 classes, a layer of 520).  No ReLU where a layer of 24 takes in 500: a unit within an
+# fp32 rounding of zero (one in 10^6) is on in one order of additions and off in another, a 24th of that sample's signal.
+@pytest.mark.parametrize("dims,act,bias,M,b", [
+    ((896, 256, 40, 2), W.ACT_RELU, True, 16, 129), ((8, 8, 128), W.ACT_GELU, True, 16, 131), ((200, 136, 264 - 8, 16, 17), W.ACT_GELU, True, 16, 257),
+    ((72, 40, 33), W.ACT_NONE, False, 24, 321), ((264, 64, 10), W.ACT_RELU, True, 32, 513), ((784, 264, 10), W.ACT_GELU, True, 24, 145),
+    ((136, 512, 24, 512, 100), W.ACT_GELU, True, 24, 177), ((40, 336, 128), W.ACT_NONE, True, 24, 192), ((328, 48, 504, 5), W.ACT_GELU, False, 24, 321),
+    ((904, 40, 5), W.ACT_RELU, True, 16, 160), ((40, 24, 129), W.ACT_GELU, True, 16, 160), ((40, 520, 24, 6), W.ACT_GELU, True, 24, 177)])
+def test_blocks_of_rows_through_all_layers(dims, act, bias, M, b):
+    A = _A()
+    w = W.Workload("rows", dims, act, bias, W.PREC_BF16, N=512, M=M, H=1, rounds=1, b0=b, b_cap=b, opt=W.OPT_SGD, lr=0.02, test=W.TEST_IP,
+                   theta=0.9, data="teacher_mlp", seed=59)
+    X, y = W.make_dataset(w)
+    x0 = W.make_x0(w)
+    rep = A.Replicas.from_workload(w, X, y, x0)
+    orc = O.Replicas(O.Net(w.dims, w.act, bias), x0, X, y, M, opt=w.opt, mixed=True, want_ip=True, gram_max_b=256)
+    try:
+        for h in range(2):
+            idx = W.step_indices(w, h, 0, b)
+            seen = idx.copy()
+            seen[:, -1], seen[0, 0] = 2 * w.N, -3
+            rep.local_step(seen, w.lr)
+            orc.local_step(np.clip(seen, 0, w.N - 1), w.lr)
+            res = rep.inner_product_test(w.theta)
+            for m in range(M):
+                s = orc.stats[m]
+                for got, want in ((res[m].sum_sq, s["S1"]), (res[m].gbar_sq, s["S2"]), (res[m].loss_sum, s["loss_sum"])):
+                    assert abs(got - want) <= 2e-3 * abs(want), (h, m, got, want)
+                n, _ = rep.get_per_sample(m, b)
+                np.testing.assert_allclose(n, s["n"], rtol=2e-2, atol=2e-3 * s["n"].max())
+                grad = rep.get_grad(m).astype(np.float64)
+                assert np.linalg.norm(grad - orc.grads[m]) <= 2e-3 * np.linalg.norm(orc.grads[m]), (h, m)
+                p = rep.get_params(m).astype(np.float64)
+                assert np.abs(p - orc.x[m]).max() <= 1e-3 * np.abs(orc.x[m]).max(), (h, m)
+                orc.x[m] = p
+        assert rep.guard_intact()
+    finally:
+        rep.close()
