@@ -911,7 +911,8 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       for (int i = 0; i < 2 * L - 1; ++i) bytes += gemm_bytes(c, passes[i], epi(i));
       for (int i = 0; i < 2 * L - 1 && c->prof_on; ++i) {
         const double own = gemm_bytes(c, passes[i], epi(i));
-        scopes[i].reset(new ProfScope(c, T_GEMM0 + (epi(i) * 6 + 5) * T_LAYERS + (i < L ? i + 1 : 2 * L - i), gemm_flops(passes[i]), own, own / bytes));
+        const int shape = gemm_bf16_tile_shape(epi(i), b, passes[i].Nd, M, b_host);
+        scopes[i].reset(new ProfScope(c, T_GEMM0 + (epi(i) * 6 + shape) * T_LAYERS + (i < L ? i + 1 : 2 * L - i), gemm_flops(passes[i]), own, own / bytes));
       }
       if (chained) {
         SmallChain ch;
