@@ -813,6 +813,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       chained = gemm_bf16_tile_shape(EPI_FWD_ACT, b, pl.dims[l], M, b_host) == 5 && gemm_bf16_tile_shape(EPI_BWD, b, pl.dims[l], M, b_host) == 5;
     // or blocks of rows, each on its own way through all layers
     const int block = pl.bf16 && !chained && !b_host ? mlp_rows_block(L, pl.dims.data(), b, M, c->N) : 0;
+    const bool gather_apart = block && !ride;               // (the gather counts as the launch that it would be)
     if (block) { ride = 1; head_fused = true; }
     std::vector<GemmP> passes;
     auto pass = [&](const GemmP &p, int epi, int l) -> hipError_t {
@@ -907,8 +908,11 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       // each pass counts as the class that it would be apart, with a share of the time by its bytes
       auto epi = [&](int i) { return i < L - 1 ? EPI_FWD_ACT : i == L - 1 ? EPI_LOGITS : EPI_BWD; };
       std::unique_ptr<ProfScope> scopes[2 * SmallChain::MAXL - 1];
-      double bytes = 0.0;
+      const double gathered = gather_apart ? 2.0 * M * b * pl.dims[0] * pl.esz : 0.0;
+      double bytes = gathered;
       for (int i = 0; i < 2 * L - 1; ++i) bytes += gemm_bytes(c, passes[i], epi(i));
+      std::unique_ptr<ProfScope> gather_scope;
+      if (gather_apart && c->prof_on) gather_scope.reset(new ProfScope(c, T_GATHER, 0.0, gathered, gathered / bytes));
       for (int i = 0; i < 2 * L - 1 && c->prof_on; ++i) {
         const double own = gemm_bytes(c, passes[i], epi(i));
         const int shape = gemm_bf16_tile_shape(epi(i), b, passes[i].Nd, M, b_host);
