@@ -307,7 +307,36 @@ WgradPlan plan_wgrad(const Plan &pl, int b, int fused, const int *b_host) {
     }
     sliced[f] = worst + finish + launch + (f ? 0.0 : epi);
   }
+  int large = 0;
+  double large_cost = 0.0;
   const double best = std::min(std::min(whole_f, whole_c), std::min(sliced[0], sliced[1]));
+  // Or slices of 256 x 256 tiles, all layers in one launch: a CU takes in about 45 bytes per ns whatever the tile, and these want a third
+  // of the operands' bytes of 64 x 128 ones (1.5 us per k-tile and round; 16: the finish and the step's end in launches of their
+  // own).  Less than 3 % under the other forms
+  // does not count, nor do fewer than 192 slices (2 replicas, b = 4096, 112 of them: they would take 130, launches of their own 141).  us per step, other forms -> slices (2, 3, 4):
+  // 784-512-512-10, 8 replicas, b = 4096 249.5 -> 239, 265, 257; 4 replicas, b = 4096 169 -> 166, 156, 156; 784-256-256-10,
+  // 8 replicas, b = 4096 178 -> 169, 162, 158; 784-512-10, 12 replicas, b = 4000 245 -> 227, 250, 244; not taken: 8 replicas, b = 2048
+  // 144 -> 160, 181, 180; 784-768-768-768-100, 4 replicas, b = 4096 301 -> 335, 317, 340
+  for (int S = 2; S <= 4 && !b_host && (KT + S - 1) / S >= 8; ++S) {
+    double blocks = 0.0, outputs = 0.0;
+    bool fits = true;
+    for (int l = 1; l <= pl.L; ++l) {
+      if (gemm_bf16_wgrad_shape(pl.dims[l], pl.dims[l - 1], b, pl.M, fused, w.rows) != 1) continue;
+      const double o = (double)pl.M * pl.dims[l] * pl.dims[l - 1];
+      fits = fits && S * o <= (double)pl.kpart_floats_l[l] && !(pl.dims[l - 1] & 3);
+      blocks += (double)S * wgrad_tiles(pl, l, 256, 256);
+      outputs += S * o;
+    }
+    const double t = std::ceil(blocks / 256) * ((KT + S - 1) / S) * 1.5 + launch + 16.0 + outputs * 8.0 / 9e6;
+    if (fits && blocks >= 192 && t < 0.97 * std::min(cost, best) && (large == 0 || t < large_cost)) { large = S; large_cost = t; }
+  }
+  if (large) {
+    w.shared = true;
+    w.fine = 2;
+    for (int l = 1; l <= pl.L; ++l)
+      if (gemm_bf16_wgrad_shape(pl.dims[l], pl.dims[l - 1], b, pl.M, fused, w.rows) == 1) w.ksplit[l] = large;
+    return w;
+  }
   if (cost <= best) return w;
   w.shared = true;
   w.fine = best == whole_f || best == sliced[1];
@@ -467,7 +496,7 @@ double gemm_flops(const std::vector<GemmP> &v) { double s = 0.0; for (const Gemm
 double gemm_bytes(const abs_ctx *c, const std::vector<GemmP> &v, int epi) { double s = 0.0; for (const GemmP &p : v) s += gemm_bytes(c, p, epi); return s; }
 
 hipError_t gemm(abs_ctx *c, const GemmP &p, int epi, int layer) {
-  int shape = !c->pl.bf16 ? 1 : p.fine ? 4 : (epi == EPI_WGRAD ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr, p.rows_host)
+  int shape = !c->pl.bf16 ? 1 : p.fine == 2 ? 2 : p.fine ? 4 : (epi == EPI_WGRAD ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr, p.rows_host)
                                                                 : gemm_bf16_tile_shape(epi, p.Md, p.Nd, p.groups, p.rows_host));
   ProfScope ps(c, T_GEMM0 + (epi * 6 + shape) * T_LAYERS + layer, gemm_flops(p), gemm_bytes(c, p, epi));
   return c->pl.bf16 ? launch_gemm_bf16(p, epi, c->stream) : launch_gemm_f32(p, epi, c->stream);
@@ -1090,15 +1119,15 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
       for (int u = 0; u < 2; ++u) {
         const std::vector<GemmP> &v = many[sh][u];
         if (v.empty()) continue;
-        if (!tail_taken && (v.size() > 1 || sh) && (cf.n == 0 || (u == 1) == fused)) {
-          ProfScope ps_(c, T_GEMM0 + (EPI_WGRAD * 6 + (sh ? 3 : v[0].fine ? 4 : 1)) * T_LAYERS + (v.size() == 1 ? many_layer[sh][u] : 0),
+        if (!tail_taken && (v.size() > 1 || sh) && v[0].fine < 2 && (cf.n == 0 || (u == 1) == fused)) {
+          ProfScope ps_(c, T_GEMM0 + (EPI_WGRAD * 6 + (sh ? 3 : v[0].fine == 2 ? 2 : v[0].fine ? 4 : 1)) * T_LAYERS + (v.size() == 1 ? many_layer[sh][u] : 0),
                         gemm_flops(v), gemm_bytes(c, v, EPI_WGRAD) + cf_bytes + (tail.st.nb_done > 0 ? sample_bytes(tail.st) : 0.0));
           HIPCHK(c, launch_wgrad_many(v.data(), (int)v.size(), sh ? 3 : 1, s, &tail));
           tail_taken = true;
           continue;
         }
         if (v.size() == 1) { HIPCHK(c, gemm(c, v[0], EPI_WGRAD, many_layer[sh][u])); continue; }   // (may take a deeper ring)
-        ProfScope ps_(c, T_GEMM0 + (EPI_WGRAD * 6 + (sh ? 3 : v[0].fine ? 4 : 1)) * T_LAYERS, gemm_flops(v), gemm_bytes(c, v, EPI_WGRAD));
+        ProfScope ps_(c, T_GEMM0 + (EPI_WGRAD * 6 + (sh ? 3 : v[0].fine == 2 ? 2 : v[0].fine ? 4 : 1)) * T_LAYERS, gemm_flops(v), gemm_bytes(c, v, EPI_WGRAD));
         HIPCHK(c, launch_wgrad_many(v.data(), (int)v.size(), sh ? 3 : 1, s));
       }
     if (kf.n > 0) {                        // all split reductions of the step in one launch

@@ -85,7 +85,7 @@ struct GemmP {
   // kpart[(g * ksplit + sp) * Md * Nd] (row-major, ld = Nd) and C / C2 are left to launch_splitk_finish.
   int ksplit, kchunk;
   float *kpart;
-  int fine;                    // bf16 family, EPI_WGRAD launches of tile shape 1: 64 x 128 tiles instead of 128 x 128 (two stages)
+  int fine;                    // bf16 family, EPI_WGRAD launches of tile shape 1: 1: 64 x 128 tiles instead of 128 x 128 (two stages); 2: 256 x 256, ksplit > 1
   int f32_tile;                // fp32 family, EPI_WGRAD: extent of the tile, 16, 32 or 64 (0: by the number of outputs)
   // fp32 family, EPI_WGRAD without a split (optional): rowsum[g * sRowsumg + m] = alpha * sum_k A[m][k] (+ the old value
   // if accumulate): the bias gradient beside the weight gradient

@@ -1070,10 +1070,8 @@ __device__ __forceinline__ void step_tail_block(const StepTail &t, int id) {
   if (threadIdx.x < 5 && threadIdx.x != 1) t.st.partials[((long long)g * 5 + threadIdx.x) * STATS_PBLK + blk] = r;
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int EPI, int ACT>
-__global__ void __launch_bounds__(256) wgrad_many_kernel(const WgradMany q, const StepTail t) {
-  if ((int)blockIdx.x < t.blocks) { step_tail_block<EPI == EPI_WGRAD_UPD ? ACT : -1>(t, blockIdx.x); return; }
-  const int bid = blockIdx.x - t.blocks;          // (t.blocks is a multiple of 8: the XCDs stay where they were)
+template <int BM, int BN, int BK, int WM, int WN, bool PP, int EPI, int ACT>
+__device__ __forceinline__ void wgrad_many_tile(const WgradMany &q, const int bid) {
   int lb = (bid & 7) * q.chunk + (bid >> 3);
   if (lb >= q.nblk) return;
   int l = 0;
@@ -1091,7 +1089,18 @@ __global__ void __launch_bounds__(256) wgrad_many_kernel(const WgradMany q, cons
   p.upd_eps = q.upd_eps; p.upd_wd = q.upd_wd; p.upd_c1 = q.upd_c1; p.upd_c2 = q.upd_c2; p.upd_scal = q.upd_scal;
   p.upd_sq = q.upd_sq; p.upd_sSqg = q.upd_sSqg; p.upd_slot0 = y.upd_slot0;
   p.sq64 = y.sq64; p.sSq64g = q.sSq64g;
-  gemm_bf16_tile<BM, BN, BK, WM, WN, 2, false, true, true, EPI, ACT>(p, q.tilesM[l], q.tilesN[l], lb);
+  gemm_bf16_tile<BM, BN, BK, WM, WN, 2, PP, true, true, EPI, ACT>(p, q.tilesM[l], q.tilesN[l], lb);
+}
+template <int BM, int BN, int BK, int WM, int WN, int EPI, int ACT>
+__global__ void __launch_bounds__(256) wgrad_many_kernel(const WgradMany q, const StepTail t) {
+  if ((int)blockIdx.x < t.blocks) { step_tail_block<EPI == EPI_WGRAD_UPD ? ACT : -1>(t, blockIdx.x); return; }
+  // (t.blocks is a multiple of 8: the XCDs stay where they were)
+  wgrad_many_tile<BM, BN, BK, WM, WN, false, EPI, ACT>(q, blockIdx.x - t.blocks);
+}
+// Slices of the layers' reductions on 256 x 256 tiles (GemmP::fine == 2).  What bounds these launches is the way of the operands into a
+// CU, about 45 bytes per ns whatever the tile: 64 x 128 tiles take 24 KB for 1 MFLOP, these 64 KB for 8.4.
+__global__ void __launch_bounds__(512, 2) wgrad_slices_kernel(const WgradMany q) {
+  wgrad_many_tile<256, 256, 64, 2, 4, true, EPI_WGRAD, ACT_NONE>(q, blockIdx.x);
 }
 
 // Tiles that ragged groups have (ragged_tile)
@@ -1280,6 +1289,18 @@ hipError_t launch_many(const WgradMany &q, const StepTail &t, int shape, int fin
   return shape == 3 ? launch_many_cfg<64, 256, 32, 1, 4, EPI, ACT>(q, t, s) : launch_many_cfg<128, 128, 64, 2, 2, EPI, ACT>(q, t, s);
 }
 
+hipError_t launch_wgrad_slices(const WgradMany &q, hipStream_t s) {
+  constexpr size_t lds = std::max<size_t>((size_t)2 * 512 * 64 * sizeof(bf16_t), (size_t)8 * 32 * (64 + 4) * sizeof(float));
+  static std::once_flag attr_once;                 // (as in launch_mode)
+  static hipError_t attr_err = hipSuccess;
+  std::call_once(attr_once, [&] {
+    attr_err = hipFuncSetAttribute(reinterpret_cast<const void *>(wgrad_slices_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  });
+  if (attr_err != hipSuccess) return attr_err;
+  hipLaunchKernelGGL(wgrad_slices_kernel, dim3(q.chunk * 8), dim3(512), lds, s, q);
+  return hipGetLastError();
+}
+
 // operand checks that every launch relies on: 16-byte aligned rows, operands below 2 GiB per replica
 bool operands_ok(const GemmP &p, int epi) {
   if (p.head.y && !(epi == EPI_LOGITS && gemm_head_fits(1, p.Md, p.Nd, p.groups))) return false;
@@ -1424,8 +1445,10 @@ hipError_t launch_wgrad_many(const GemmP *p, int n, int shape, hipStream_t s, co
   if (shape != 1 && shape != 3) return hipErrorInvalidValue;
   if (n < 1) return tail ? hipErrorInvalidValue : hipSuccess;
   const GemmP &c0 = p[0];
-  const int bm = shape == 3 || c0.fine ? 64 : 128, bn = shape == 3 ? 256 : 128;
+  const bool slices = shape == 1 && c0.fine == 2;
+  const int bm = slices ? 256 : shape == 3 || c0.fine ? 64 : 128, bn = slices || shape == 3 ? 256 : 128;
   const bool upd = c0.upd_x != nullptr;
+  if (slices && (tail || upd)) return hipErrorInvalidValue;
   StepTail t;
   std::memset(&t, 0, sizeof(t));
   if (tail) {
@@ -1445,7 +1468,7 @@ hipError_t launch_wgrad_many(const GemmP *p, int n, int shape, hipStream_t s, co
       const GemmP &c = p[at];
       // one kernel variant for all: every layer carries the same optimizer step, or none
       if (!operands_ok(c, EPI_WGRAD) || !c.a_trans || !c.b_trans || (c.upd_x != nullptr) != upd ||
-          (upd && c.upd_opt != c0.upd_opt) || (shape == 3 && c.ksplit > 1) || c.fine != c0.fine ||
+          (upd && c.upd_opt != c0.upd_opt) || (shape == 3 && c.ksplit > 1) || (slices && c.ksplit < 2) || c.fine != c0.fine ||
           gemm_bf16_wgrad_shape(c.Md, c.Nd, c.Kd, c.groups, upd, c.rows_host) != shape)
         return hipErrorInvalidValue;
       // and the fields that the launch holds once
@@ -1472,7 +1495,8 @@ hipError_t launch_wgrad_many(const GemmP *p, int n, int shape, hipStream_t s, co
     q.nblk = (int)blocks;
     q.chunk = (q.nblk + 7) / 8;
     hipError_t e;
-    if (!upd) e = launch_many<EPI_WGRAD, ACT_NONE>(q, t, shape, c0.fine, s);
+    if (slices) e = launch_wgrad_slices(q, s);
+    else if (!upd) e = launch_many<EPI_WGRAD, ACT_NONE>(q, t, shape, c0.fine, s);
     else if (c0.upd_opt == OPT_SGD) e = launch_many<EPI_WGRAD_UPD, OPT_SGD>(q, t, shape, c0.fine, s);
     else if (c0.upd_opt == OPT_SHB) e = launch_many<EPI_WGRAD_UPD, OPT_SHB>(q, t, shape, c0.fine, s);
     else if (c0.upd_opt == OPT_ADAMW) e = launch_many<EPI_WGRAD_UPD, OPT_ADAMW>(q, t, shape, c0.fine, s);

@@ -1012,3 +1012,22 @@ def test_blocks_of_rows_through_all_layers(dims, act, bias, M, b):
         assert rep.guard_intact()
     finally:
         rep.close()
+
+
+# Weight gradients of long batches in slices of 256 x 256 tiles, all layers in one launch: two and four slices, the last one shorter and its
+# last k-tile cut, widths that leave most of a tile empty; the sums and the step as in every other form.
+@pytest.mark.parametrize("dims,M,b,opt", [((784, 512, 10), 12, 4001, W.OPT_ADAMW), ((784, 256, 256, 10), 8, 4090, W.OPT_SHB),
+                                          ((776, 504, 264, 2), 8, 3900, W.OPT_SGD)])
+def test_weight_gradients_in_slices_of_large_tiles(dims, M, b, opt):
+    A = _A()
+    w = W.Workload("slices", dims, W.ACT_RELU, True, W.PREC_BF16, N=512, M=M, H=1, rounds=1, b0=b, b_cap=b, opt=opt, lr=0.02, momentum=0.9,
+                   test=W.TEST_NORM, data="teacher_mlp", seed=61)
+    X, y = W.make_dataset(w)
+    rep = A.Replicas.from_workload(w, X, y, W.make_x0(w))
+    try:
+        rep.profile_enable(True)
+        rep.local_step(W.step_indices(w, 0, 0, b), w.lr)
+        assert [n for n in rep.profile_read() if n.startswith("gemm_wgrad_")] == ["gemm_wgrad_256x256_L0"]
+    finally:
+        rep.close()
+    test_weight_gradient_launches_of_long_batches(dims, M, b, opt, 0)
