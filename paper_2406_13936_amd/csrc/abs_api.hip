@@ -52,7 +52,7 @@ struct Plan {
   size_t o_qpart[MAXL] = {0}, o_partials = 0, o_stats = 0, o_cw = 0, o_colpart = 0, o_rows = 0, o_sqwave = 0, o_idx = 0, o_scal = 0, o_mean = 0;
   size_t o_kpart_l[MAXL + 1] = {0};    // per layer: partial products of a split weight-gradient reduction
   size_t kpart_floats_l[MAXL + 1] = {0};
-  bool softmax_step = false;           // fp32 without hidden layers: a step may be one launch (softmax_step.hip)
+  int softmax_chunks = 0;              // fp32 without hidden layers: chunks to a replica that the scratch of softmax_step.hip holds (0: not taken)
   size_t o_spart = 0, o_ssums = 0, o_count = 0;
   size_t o_chain = 0;                  // arrivals of the tiles of a chained launch, zero between launches
   int chain_words = 0, chain_max = 0;  // words to a chain, and chains
@@ -181,11 +181,10 @@ void make_plan(const abs_config *c, long long N, Plan &pl) {
   pl.o_cw = take((2 * (size_t)cross_worker_blocks(pl.Ppad) + 8) * 8);
   pl.o_idx = take((size_t)pl.M * pl.cap * sizeof(int32_t));      // inputs of replayed (graph) steps
   pl.o_scal = take(256);
-  if (!pl.bf16 && pl.L == 1 && softmax_step_fits(pl.dims[1], pl.dims[0], 2)) {
-    pl.softmax_step = true;
-    const size_t chunks = std::min<size_t>(SOFTMAX_STEP_CHUNKS, softmax_step_chunks(pl.dims[0], std::max(pl.cap, 64)));
-    pl.o_spart = take((size_t)pl.M * std::min<size_t>(chunks * softmax_step_part_floats(pl.dims[1], pl.dims[0]), SOFTMAX_STEP_PARTS) * sizeof(float));
-    pl.o_ssums = take((size_t)pl.M * chunks * 4 * sizeof(double));
+  if (!pl.bf16 && pl.L == 1) pl.softmax_chunks = softmax_step_max_chunks(pl.dims[1], pl.dims[0], pl.cap);
+  if (pl.softmax_chunks > 0) {
+    pl.o_spart = take((size_t)pl.M * pl.softmax_chunks * softmax_step_part_floats(pl.dims[1], pl.dims[0]) * sizeof(float));
+    pl.o_ssums = take((size_t)pl.M * pl.softmax_chunks * 4 * sizeof(double));
   }
   pl.o_count = take((size_t)pl.M * 16 * sizeof(int));         // arrivals of work-groups, zero between launches
   if (pl.bf16 && pl.L >= 2 && pl.L <= SmallChain::MAXL) {
@@ -759,7 +758,7 @@ static abs_status softmax_step(abs_ctx *c, const int32_t *idx_dev, int ldi, int 
   p.do_q = pl.want_ip ? 1 : 0;
   p.n_out = c->at<float>(pl.o_nout); p.q_out = c->at<float>(pl.o_qout); p.sNg = pl.cap;
   p.D = c->at<float>(pl.o_Dl[1]); p.sDg = (long long)pl.cap * pl.ld[1]; p.ldd = pl.ld[1];
-  p.part = c->at<float>(pl.o_spart); p.csums = c->at<double>(pl.o_ssums); p.count = c->at<int>(pl.o_count);
+  p.part = c->at<float>(pl.o_spart); p.csums = c->at<double>(pl.o_ssums); p.count = c->at<int>(pl.o_count); p.max_chunks = pl.softmax_chunks;
   p.stats = c->at<double>(pl.o_stats); p.stats_host = c->host_stats_dev;
   if (p.stats_host) { c->ticket += 1.0; p.ticket = c->ticket; c->ticket_live = true; }
   // counted as the two contractions that it is, the time in proportion to their bytes (operands; signals, index, label, norm and
@@ -802,7 +801,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
     rows = rows_dev;
     if (M >= 8) gperm = rows_dev + M;
   }
-  if (pl.softmax_step && ph.whole() && softmax_step_fits(pl.dims[1], pl.dims[0], b))
+  if (pl.softmax_chunks > 0 && ph.whole() && softmax_step_fits(pl.dims[1], pl.dims[0], b))
     return softmax_step(c, idx_dev, ldi, b, b_host, rows, lr, ph);
   int an_parts[MAXL + 1], dn_parts[MAXL + 2];
   for (int l = 0; l <= MAXL; ++l) an_parts[l] = dn_parts[l] = 1;

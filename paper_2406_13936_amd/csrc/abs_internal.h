@@ -196,12 +196,15 @@ struct SoftmaxStepP {
   float *D; long long sDg; int ldd;      // scratch: signals [g][i][ldd], ldd >= K (do_q over several chunks)
   float *part; double *csums; int *count;   // scratch of several chunks: [g][chunk][part_ld], [g][chunk][4], and 16 ints per group that
                                             //   are zero before the first launch and after each
+  int max_chunks;                           // chunks to a group that part and csums hold
   double *stats, *stats_host, ticket;
   int chunks, part_ld;                   // set by the launcher
 };
 enum { SOFTMAX_STEP_CHUNKS = 32, SOFTMAX_STEP_PARTS = 1 << 19 };     // chunks, and floats of partial gradients, to a group
 inline int softmax_step_part_floats(int K, int d) { return (K * d + K + 63) / 64 * 64; }
 int softmax_step_chunks(int d, int b);
+// The most chunks that a step of up to cap samples takes (a longer batch may take fewer: chunk_of), 0 where none is taken
+int softmax_step_max_chunks(int K, int d, int cap);
 bool softmax_step_fits(int K, int d, int b);
 hipError_t launch_softmax_step(SoftmaxStepP p, hipStream_t s);
 

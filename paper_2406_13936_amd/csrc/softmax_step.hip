@@ -469,6 +469,13 @@ bool softmax_step_fits(int K, int d, int b) {
          (long long)softmax_step_chunks(d, b) * softmax_step_part_floats(K, d) <= SOFTMAX_STEP_PARTS;
 }
 
+int softmax_step_max_chunks(int K, int d, int cap) {
+  int most = 0;
+  for (int b = 2; b <= std::min(cap, 64 * SOFTMAX_STEP_CHUNKS); ++b)            // (no chunk is longer than 64)
+    if (softmax_step_fits(K, d, b)) most = std::max(most, softmax_step_chunks(d, b));
+  return most;
+}
+
 hipError_t launch_softmax_step(SoftmaxStepP p, hipStream_t s) {
   if (!softmax_step_fits(p.K, p.d, p.b) || p.K < 2 || p.d < 1 || p.b < 1 || p.groups < 1 || p.groups > 65535 || p.N < 1 || p.ldi < p.b ||
       !p.X || !p.y || !p.idx || !p.upd_x || !p.grad || !p.stats || (p.opt != OPT_SGD && !p.upd_v) || (p.opt == OPT_ADAMW && !p.upd_m) ||
@@ -477,7 +484,7 @@ hipError_t launch_softmax_step(SoftmaxStepP p, hipStream_t s) {
     return hipErrorInvalidValue;
   p.chunks = softmax_step_chunks(p.d, p.b);
   p.part_ld = softmax_step_part_floats(p.K, p.d);
-  if (p.chunks > 1 && (!p.part || !p.csums || !p.count || (p.do_q && !p.D))) return hipErrorInvalidValue;
+  if (p.chunks > 1 && (p.chunks > p.max_chunks || !p.part || !p.csums || !p.count || (p.do_q && !p.D))) return hipErrorInvalidValue;
   hipError_t e;
   switch (p.opt) {
     case OPT_SGD: e = launch1<OPT_SGD>(p, s); break;

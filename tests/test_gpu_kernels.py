@@ -894,6 +894,41 @@ def test_one_launch_of_a_net_without_hidden_layers(dims, sizes, opt):
         rep.close()
 
 
+# Batches below the cap that take more of its chunks than the cap itself: 16 samples each up to 128 of them, 32 or 64 beside that, so the
+# scratch of a replica is not the cap's; single sizes and workers with batches of their own, one context through all of them.
+@pytest.mark.parametrize("dims,cap,steps,opt", [
+    ((784, 10), 130, ([65] * 4, [113] * 4, [128] * 4, [130] * 4, [16] * 4), W.OPT_SHB),
+    ((512, 10), 150, ([64] * 3, [65] * 3, [128] * 3, [129] * 3, [128, 150, 17]), W.OPT_SGD),
+    ((1024, 16), 224, ([97] * 2, [128, 65], [129] * 2, [128] * 2, [224] * 2), W.OPT_SGD)])
+def test_one_launch_of_batches_below_the_cap(dims, cap, steps, opt):
+    A = _A()
+    M = len(steps[0])
+    w = W.Workload("below", dims, W.ACT_NONE, True, W.PREC_F32, N=2048, M=M, H=1, rounds=1, b0=16, b_cap=cap, opt=opt, lr=0.05, momentum=0.9,
+                   test=W.TEST_IP, theta=0.9, data="teacher_mlp", seed=67)
+    X, y = W.make_dataset(w)
+    x0 = W.make_x0(w)
+    rep = A.Replicas.from_workload(w, X, y, x0)
+    try:
+        orc = O.Replicas(O.Net(w.dims, w.act, True), x0, X, y, M, opt=opt, momentum=w.momentum, want_ip=True)
+        for h, sizes in enumerate(steps):
+            rows = [W.batch_indices(w.seed, h, 0, m, s, w.N) for m, s in enumerate(sizes)]
+            if len(set(sizes)) > 1:
+                rep.local_step_ragged(rows, w.lr)
+            else:
+                rep.local_step(np.stack(rows), w.lr)
+            _check_fp32_step(rep, w, orc, rows, range(M))
+            res = rep.inner_product_test(0.9)
+            for m in range(M):                       # (as above)
+                s, (n, q) = orc.stats[m], rep.get_per_sample(m, sizes[m], want_q=True)
+                np.testing.assert_allclose(n, s["n"], rtol=1e-4, atol=1e-6 * s["n"].max())
+                np.testing.assert_allclose(q, s["q"], rtol=1e-3, atol=1e-5 * np.abs(s["q"]).max())
+                for got, want in ((res[m].sum_sq, s["S1"]), (res[m].loss_sum, s["loss_sum"]), (res[m].sum_q2, s["S3"]), (res[m].sum_q, s["S4"])):
+                    assert abs(got - want) <= 1e-4 * abs(want), (h, m, got, want)
+        assert rep.guard_intact()
+    finally:
+        rep.close()
+
+
 # Replays of a captured step of that kind, where a replica's work-groups count their arrivals: bit for bit the direct steps.
 def test_replayed_steps_of_a_net_without_hidden_layers():
     import torch
