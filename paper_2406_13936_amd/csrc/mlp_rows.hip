@@ -570,23 +570,32 @@ template <int NT> hipError_t launch_rows(const MlpRows &c, hipStream_t s) {
 
 // The fewer rows to a block the more CUs have one, and all of them stream the weights, which is what the time goes by: 16 rows while that
 // makes one round of 256 CUs, then 32, then 64; of 32 rows of layers up to 256 two blocks fit a CU, which suits
-// all larger batches better.  Fewer blocks than the first line leave CUs idle that tiles of 32 x 32 outputs would use; beyond 512 blocks of
-// 32 rows a wide layer's tiles of 128 or 256 rows read the weights less often (784-512-512-10, 8 replicas, b = 4096: 248 us per step
-// in tiles, 250 in blocks of 64, 303 in blocks of 32).  About 300 nets of 128 to 512 wide hidden layers, 1 to 16 replicas, b = 64 to
-// 4096, time of a step against tiles: layers up to 256, from 140 blocks of 16 rows on 0.75 to 0.98 (one 1.03); wider ones, 216 to
-// 256 blocks of 16 rows 0.83 to 1.03, then blocks of 32 0.81 to 0.96, of 64 0.84 to 0.94.  For example, us per step:
-// 784-512-512-10, 8 replicas, b = 1000 120 -> 104, 784-160-160-160-3 (GELU), 7 replicas, b = 479 87 -> 69,
+// all larger batches better.  Fewer blocks than the first line leave CUs idle that tiles of 32 x 32 outputs would use; more than one round
+// of a wide layer's blocks reads the weights more often than tiles of 128 or 256 rows do (784-512-512-10, 8 replicas, b = 4096: 248 us per
+// step in tiles, 250 in blocks of 64, 303 in blocks of 32).
+// Time of a step against tiles, about 1300 nets of 8 to 896 inputs and one to three hidden layers of 8 to 512, 1 to 600 replicas, b = 2 to 8192:
+//   16 rows, and 32 up to 256 blocks: 0.73 to 1.03, on average 0.91 (one 1.07: 464-112-114, 1 replica, b = 2283);
+//   64 rows in one round, layers up to 256: 0.71 to 1.03, on average 0.91; in two rounds up to 1.25 (400-56-272-64-18, 133 replicas, b = 77);
+//   64 rows, wider layers: from 192 blocks on 0.83 to 1.00; fewer of them with 800 and more inputs and hidden units 0.87 to 1.00, with less
+//     0.93 to 1.06: half the CUs idle, and little for each to load;
+//   32 rows, 257 to 768 blocks: 0.76 to 1.02, except where replicas of less than half a block make them mostly empty (up to 1.10); more of
+//     them with hidden layers of 128 and more 0.78 to 1.01, of less up to 1.05 to 1024 and beyond 0.90 to 1.37 (16-56-8-8-4, 31 replicas,
+//     b = 3547 192 -> 261 us): narrow layers leave most wavefronts without columns, and a round of blocks then costs what its barriers do,
+//     while tiles cost by the widths.
+// For example, us per step: 784-512-512-10, 8 replicas, b = 1000 120 -> 104, 784-160-160-160-3 (GELU), 7 replicas, b = 479 87 -> 69,
 // 784-328-328-328-34 (GELU), 16 replicas, b = 669 198 -> 166.
 int mlp_rows_block(int L, const int *dims, int b, int groups, long long N) {
   if (L < 2 || L > MlpRows::MAXL || dims[L] > MAX_CLASSES || dims[0] > MAX_IN || N * dims[0] * 2 >= (1LL << 30)) return 0;
-  int width = 0;
-  for (int l = 1; l < L; ++l) width = dims[l] > width ? dims[l] : width;
+  int width = 0, sum = 0;
+  for (int l = 1; l < L; ++l) { width = dims[l] > width ? dims[l] : width; sum += dims[l]; }
   auto blocks = [&](int rows) { return (long long)((b + rows - 1) / rows) * groups; };
-  if (width > 64 * WAVES || blocks(16) < (width <= 32 * WAVES ? 140 : 216)) return 0;
+  const bool wide = width > 32 * WAVES;
+  if (width > 64 * WAVES || blocks(16) < (wide ? 216 : 140)) return 0;
   if (blocks(16) <= 256) return 16;
   if (blocks(32) <= 256) return 32;
-  if (blocks(32) <= 512) return 64;
-  return width <= 32 * WAVES ? 32 : 0;
+  if (blocks(64) <= 256) return !wide || blocks(64) >= 192 || dims[0] + sum >= 800 ? 64 : 0;
+  if (wide || (long long)b * groups < 16 * blocks(32)) return 0;
+  return blocks(32) <= 768 || sum >= 128 * (L - 1) ? 32 : 0;
 }
 
 hipError_t launch_mlp_rows(MlpRows &c, hipStream_t s) {

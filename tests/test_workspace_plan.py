@@ -31,3 +31,21 @@ def test_the_chunks_reserved_for_a_cap_cover_every_batch_up_to_it():
                 if fits(K, d, b):
                     need = max(need, chunks(d, b))
                 assert most(K, d, b) == need, (K, d, b)
+
+
+# Which launches take blocks of rows through all layers (mlp_rows.hip), and how many rows to a block: up to 512 wide hidden layers, 128 classes,
+# 896 inputs, four layers; the tiles' are many rows of narrow layers and blocks that would be mostly empty or leave most CUs idle
+@pytest.mark.parametrize("dims,M,b,rows", [
+    ((784, 512, 512, 10), 8, 501, 16), ((784, 512, 512, 10), 8, 1000, 32), ((784, 512, 512, 10), 8, 2048, 64), ((784, 512, 512, 10), 8, 4096, 0),
+    ((784, 256, 256, 10), 8, 4096, 32), ((784, 264, 10), 8, 431, 16), ((784, 264, 10), 8, 416, 0), ((8, 8, 2), 14, 145, 16), ((8, 8, 2), 14, 144, 0),
+    ((896, 256, 128), 16, 160, 16), ((904, 256, 128), 16, 160, 0), ((896, 256, 129), 16, 160, 0), ((784, 520, 10), 16, 256, 0),
+    ((784, 64, 64, 64, 10), 16, 160, 16), ((784, 64, 64, 64, 64, 10), 16, 160, 0), ((784, 10), 16, 160, 0),
+    ((16, 56, 8, 8, 4), 24, 1024, 32), ((16, 56, 8, 8, 4), 24, 1025, 0), ((16, 56, 8, 8, 4), 31, 3547, 0), ((32, 40, 40, 16), 25, 4883, 0),
+    ((64, 32, 224, 10), 16, 4096, 32), ((64, 32, 216, 10), 16, 4096, 0), ((64, 128, 10), 32, 8192, 32),
+    # 64 rows in one round only; replicas of less than half a block; half a round of wide layers behind few inputs
+    ((264, 64, 10), 30, 517, 32), ((264, 64, 10), 28, 517, 64), ((400, 56, 272, 64, 18), 133, 77, 0), ((56, 16, 109), 273, 3, 0),
+    ((56, 16, 109), 300, 15, 0), ((56, 16, 109), 300, 16, 32), ((8, 360, 104, 3), 14, 740, 0), ((8, 360, 104, 3), 16, 740, 64),
+    ((48, 288, 78), 14, 640, 0), ((784, 512, 512, 10), 8, 1025, 64)])
+def test_which_steps_take_blocks_of_rows(dims, M, b, rows):
+    f = B.load_library()["_ZN4absk14mlp_rows_blockEiPKiiix"]
+    assert f(len(dims) - 1, (C.c_int * len(dims))(*dims), b, M, C.c_longlong(60000)) == rows
