@@ -189,7 +189,7 @@ void make_plan(const abs_config *c, long long N, Plan &pl) {
   pl.o_count = take((size_t)pl.M * 16 * sizeof(int));         // arrivals of work-groups, zero between launches
   if (pl.bf16 && pl.L >= 2 && pl.L <= SmallChain::MAXL) {
     pl.chain_words = small_chain_words(pl.L, pl.dims.data());
-    pl.chain_max = (int)std::min<long long>((long long)pl.M * ((pl.cap + 31) / 32), 512);     // (512 tiles of 32 x 32 in the first pass at most)
+    pl.chain_max = (int)std::min<long long>((long long)pl.M * ((pl.cap + 31) / 32), SmallChain::MAX_CHAINS);
     pl.o_chain = take((size_t)pl.chain_max * pl.chain_words * sizeof(int));
   }
   pl.o_mean = take((size_t)pl.Ppad * sizeof(float));          // the mean between the two passes of a large average
@@ -836,9 +836,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
     int ride = gather_rides(isb, L, b, pl.dims.data(), M, c->N, b_host);
     bool head_fused = gemm_head_fits(isb, b, pl.dims[L], M);
     // all passes on 32-row tiles: one launch for them
-    bool chained = (long long)M * ((b + 31) / 32) <= pl.chain_max && ride == 1 && head_fused;
-    for (int l = 1; l < L && chained; ++l)
-      chained = gemm_bf16_tile_shape(EPI_FWD_ACT, b, pl.dims[l], M, b_host) == 5 && gemm_bf16_tile_shape(EPI_BWD, b, pl.dims[l], M, b_host) == 5;
+    const bool chained = pl.bf16 && (long long)M * ((b + 31) / 32) <= pl.chain_max && small_chain_fits(L, pl.dims.data(), b, M, c->N, b_host);
     // or blocks of rows, each on its own way through all layers
     const int block = pl.bf16 && !chained && !b_host ? mlp_rows_block(L, pl.dims.data(), b, M, c->N) : 0;
     const bool gather_apart = block && !ride;               // (the gather counts as the launch that it would be)

@@ -135,7 +135,7 @@ hipError_t launch_gemm_small(const GemmP &p, int epi, hipStream_t s);
 // logits with the head, backward-data of layers L .. 2, and the gather.  count: `words` ints (small_chain_words) for each replica and 32
 // rows, zero before the first launch and after each.
 struct SmallChain {
-  enum { MAXL = 4 };
+  enum { MAXL = 4, MAX_CHAINS = 224 };
   int L, words;
   int *count;
   int end[2 * MAXL - 2], chains;                 // set by the launcher: tiles of a chain up to and with each pass (logits with layer L's backward-data)
@@ -144,6 +144,7 @@ struct SmallChain {
 };
 static_assert(sizeof(SmallChain) <= 4096, "kernel arguments");
 int small_chain_words(int L, const int *dims);
+bool small_chain_fits(int L, const int *dims, int b, int groups, long long N, const int *rows_host);       // (bf16) where that is the way
 hipError_t launch_small_chain(SmallChain &c, hipStream_t s);
 // ---- mlp_rows.hip ------------------------------------------------------------
 // The same passes with a block of `rows` rows of one replica to a work-group, which walks all layers (p, gather as in SmallChain; one row

@@ -49,3 +49,15 @@ def test_the_chunks_reserved_for_a_cap_cover_every_batch_up_to_it():
 def test_which_steps_take_blocks_of_rows(dims, M, b, rows):
     f = B.load_library()["_ZN4absk14mlp_rows_blockEiPKiiix"]
     assert f(len(dims) - 1, (C.c_int * len(dims))(*dims), b, M, C.c_longlong(60000)) == rows
+
+
+# Which steps take forward, head and backward-data in one launch of chains (gemm_small.hip): two to four layers whose launches are all 32-row
+# tiles, up to 224 blocks of 32 rows, which more of them are slower in
+@pytest.mark.parametrize("dims,M,b,taken", [
+    ((784, 512, 512, 10), 8, 32, 1), ((784, 512, 512, 10), 8, 64, 1), ((784, 512, 512, 10), 8, 501, 0), ((8, 8, 2), 2, 2, 1), ((72, 40, 32), 3, 65, 1), ((72, 40, 33), 3, 65, 0),
+    ((264, 72, 104, 17), 2, 96, 1), ((40, 1096, 64, 8, 5), 2, 40, 1), ((1096, 136, 520, 10), 1, 66, 1), ((40, 24, 24, 24, 24, 6), 2, 33, 0),
+    ((8, 2), 4, 32, 0), ((16, 48, 10), 224, 4, 1), ((16, 48, 10), 225, 4, 0), ((56, 16, 10), 486, 6, 0), ((56, 16, 10), 112, 33, 1), ((56, 16, 10), 113, 33, 0)])
+def test_which_steps_take_chains_of_tiles(dims, M, b, taken):
+    f = B.load_library()["_ZN4absk16small_chain_fitsEiPKiiixS1_"]
+    f.restype = C.c_bool
+    assert f(len(dims) - 1, (C.c_int * len(dims))(*dims), b, M, C.c_longlong(60000), None) == bool(taken)
