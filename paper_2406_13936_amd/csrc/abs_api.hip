@@ -181,7 +181,7 @@ void make_plan(const abs_config *c, long long N, Plan &pl) {
   pl.o_cw = take((2 * (size_t)cross_worker_blocks(pl.Ppad) + 8) * 8);
   pl.o_idx = take((size_t)pl.M * pl.cap * sizeof(int32_t));      // inputs of replayed (graph) steps
   pl.o_scal = take(256);
-  if (!pl.bf16 && pl.L == 1) pl.softmax_chunks = softmax_step_max_chunks(pl.dims[1], pl.dims[0], pl.cap);
+  if (!pl.bf16 && pl.L == 1) pl.softmax_chunks = softmax_step_max_chunks(pl.dims[1], pl.dims[0], pl.cap, pl.M);
   if (pl.softmax_chunks > 0) {
     pl.o_spart = take((size_t)pl.M * pl.softmax_chunks * softmax_step_part_floats(pl.dims[1], pl.dims[0]) * sizeof(float));
     pl.o_ssums = take((size_t)pl.M * pl.softmax_chunks * 4 * sizeof(double));
@@ -801,7 +801,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
     rows = rows_dev;
     if (M >= 8) gperm = rows_dev + M;
   }
-  if (pl.softmax_chunks > 0 && ph.whole() && softmax_step_fits(pl.dims[1], pl.dims[0], b))
+  if (pl.softmax_chunks > 0 && ph.whole() && softmax_step_fits(pl.dims[1], pl.dims[0], b, M))
     return softmax_step(c, idx_dev, ldi, b, b_host, rows, lr, ph);
   int an_parts[MAXL + 1], dn_parts[MAXL + 2];
   for (int l = 0; l <= MAXL; ++l) an_parts[l] = dn_parts[l] = 1;

@@ -205,8 +205,8 @@ enum { SOFTMAX_STEP_CHUNKS = 32, SOFTMAX_STEP_PARTS = 1 << 19 };     // chunks, 
 inline int softmax_step_part_floats(int K, int d) { return (K * d + K + 63) / 64 * 64; }
 int softmax_step_chunks(int d, int b);
 // The most chunks that a step of up to cap samples takes (a longer batch may take fewer: chunk_of), 0 where none is taken
-int softmax_step_max_chunks(int K, int d, int cap);
-bool softmax_step_fits(int K, int d, int b);
+int softmax_step_max_chunks(int K, int d, int cap, int groups);
+bool softmax_step_fits(int K, int d, int b, int groups);
 hipError_t launch_softmax_step(SoftmaxStepP p, hipStream_t s);
 
 // ---- gram_ip.hip -----------------------------------------------------------

@@ -464,20 +464,31 @@ int softmax_step_chunks(int d, int b) { return (b + chunk_of(d, b) - 1) / chunk_
 // 15.8, b = 512 36.5 -> 23.0; 64-2, 1 replica, b = 257 32.5 -> 19.6; 256-2, 16, b = 1024 65.9 -> 34.7; 1024-10, 16, b = 512 110 -> 41;
 // with inner products 784-10, 16, b = 1024 165 -> 87, 1024-16, 4, b = 512 58.9 -> 53.5, 1024-16, 1, b = 512 56.0 -> 55.4.  At the line
 // both cost the same: 1024-16, 16, b = 1024 134 and 137.
-bool softmax_step_fits(int K, int d, int b) {
-  return K <= KC && d <= 2048 && softmax_step_chunks(d, b) <= SOFTMAX_STEP_CHUNKS &&
-         (long long)softmax_step_chunks(d, b) * softmax_step_part_floats(K, d) <= SOFTMAX_STEP_PARTS;
+// Time of a step against the general launches, 1060 nets of 1 to 2048 features, 1 to 600 replicas, b = 2 to 1024:
+//   one work-group to a replica 0.17 to 0.99, on average 0.62;
+//   several, up to 768 in all 0.35 to 0.99, with 256 and more features 0.36 to 1.01 up to 2048: beyond, waves of work-groups come one after
+//     the other for few products each (23-6, 540 replicas, b = 588 273 -> 552 us; 1210-11, 307, b = 467 955 -> 1333);
+//   except that with fewer than 8 replicas the last work-group of each adds the partial gradients while other CUs idle: beyond 320 k floats of
+//     them, and beyond 8192 parameters where rows are not whole 16-byte pieces, 0.74 to 1.28 (1511-16, 1 replica, b = 199 38.8 -> 49.8).
+bool softmax_step_fits(int K, int d, int b, int groups) {
+  if (K > KC || d > 2048) return false;
+  const int chunks = softmax_step_chunks(d, b);
+  const long long parts = (long long)chunks * softmax_step_part_floats(K, d);
+  if (chunks > SOFTMAX_STEP_CHUNKS || parts > SOFTMAX_STEP_PARTS) return false;
+  if (chunks == 1) return true;
+  if ((long long)chunks * groups > (d < 256 ? 768 : 2048)) return false;
+  return groups >= 8 || (d & 3 ? K * d <= 8192 : parts <= 320 * 1024);
 }
 
-int softmax_step_max_chunks(int K, int d, int cap) {
+int softmax_step_max_chunks(int K, int d, int cap, int groups) {
   int most = 0;
   for (int b = 2; b <= std::min(cap, 64 * SOFTMAX_STEP_CHUNKS); ++b)            // (no chunk is longer than 64)
-    if (softmax_step_fits(K, d, b)) most = std::max(most, softmax_step_chunks(d, b));
+    if (softmax_step_fits(K, d, b, groups)) most = std::max(most, softmax_step_chunks(d, b));
   return most;
 }
 
 hipError_t launch_softmax_step(SoftmaxStepP p, hipStream_t s) {
-  if (!softmax_step_fits(p.K, p.d, p.b) || p.K < 2 || p.d < 1 || p.b < 1 || p.groups < 1 || p.groups > 65535 || p.N < 1 || p.ldi < p.b ||
+  if (!softmax_step_fits(p.K, p.d, p.b, p.groups) || p.K < 2 || p.d < 1 || p.b < 1 || p.groups < 1 || p.groups > 65535 || p.N < 1 || p.ldi < p.b ||
       !p.X || !p.y || !p.idx || !p.upd_x || !p.grad || !p.stats || (p.opt != OPT_SGD && !p.upd_v) || (p.opt == OPT_ADAMW && !p.upd_m) ||
       (reinterpret_cast<uintptr_t>(p.X) & 15) || (reinterpret_cast<uintptr_t>(p.upd_x) & 15) || (reinterpret_cast<uintptr_t>(p.grad) & 15) ||
       (p.sPg & 3) || p.ldd < p.K)

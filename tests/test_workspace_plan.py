@@ -23,14 +23,28 @@ def test_the_workspace_never_shrinks_as_the_cap_grows(dims):
 
 def test_the_chunks_reserved_for_a_cap_cover_every_batch_up_to_it():
     lib = B.load_library()
-    chunks, fits, most = (lib["_ZN4absk" + n] for n in ("19softmax_step_chunksEii", "17softmax_step_fitsEiii", "23softmax_step_max_chunksEiii"))
+    chunks, fits, most = (lib["_ZN4absk" + n] for n in ("19softmax_step_chunksEii", "17softmax_step_fitsEiiii", "23softmax_step_max_chunksEiiii"))
+    fits.restype = C.c_bool
     for d in [1, 3, 255, 256, 257, 511, 512, 513, 640, 784, 1000, 1023, 1024, 1025, 1536, 2047, 2048, 2049]:
-        for K in (2, 10, 16, 17):
+        for K, M in ((2, 1), (10, 4), (16, 40), (16, 1), (3, 300), (17, 4)):
             need = 0
             for b in range(2, 1101):
-                if fits(K, d, b):
+                if fits(K, d, b, M):
                     need = max(need, chunks(d, b))
-                assert most(K, d, b) == need, (K, d, b)
+                assert most(K, d, b, M) == need, (K, d, b)
+
+
+# Which fp32 steps without hidden layers take one launch: up to 16 classes, 2048 features and 32 chunks; several chunks not for many small
+# replicas nor where one work-group would add up many partial gradients of few replicas
+@pytest.mark.parametrize("d,K,M,b,taken", [
+    (256, 10, 4, 16, 1), (256, 10, 4, 512, 1), (784, 10, 4, 128, 1), (784, 16, 1, 1024, 0), (784, 16, 8, 1024, 1), (1, 2, 600, 64, 1), (1, 2, 600, 65, 0), (1, 17, 1, 2, 0),
+    (2048, 16, 1, 16, 1), (2049, 2, 1, 16, 0), (64, 2, 384, 40, 1), (64, 2, 256, 96, 1), (64, 2, 257, 96, 0), (256, 2, 257, 96, 1), (256, 2, 682, 96, 1),
+    (256, 2, 683, 96, 0), (23, 6, 540, 588, 0), (1511, 16, 1, 199, 0), (1511, 16, 8, 199, 1), (1511, 5, 1, 199, 1), (954, 11, 1, 58, 0), (954, 8, 1, 58, 1),
+    (1372, 13, 2, 288, 1), (1372, 13, 2, 289, 0), (100, 7, 3, 1024, 1), (100, 7, 3, 1025, 0)])
+def test_which_fp32_steps_take_one_launch(d, K, M, b, taken):
+    f = B.load_library()["_ZN4absk17softmax_step_fitsEiiii"]
+    f.restype = C.c_bool
+    assert f(K, d, b, M) == bool(taken)
 
 
 # Which launches take blocks of rows through all layers (mlp_rows.hip), and how many rows to a block: up to 512 wide hidden layers, 128 classes,
