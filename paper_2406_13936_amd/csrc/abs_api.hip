@@ -309,13 +309,15 @@ WgradPlan plan_wgrad(const Plan &pl, int b, int fused, const int *b_host) {
   int large = 0;
   double large_cost = 0.0;
   const double best = std::min(std::min(whole_f, whole_c), std::min(sliced[0], sliced[1]));
-  // Or slices of 256 x 256 tiles, all layers in one launch: a CU takes in about 45 bytes per ns whatever the tile, and these want a third
-  // of the operands' bytes of 64 x 128 ones (1.5 us per k-tile and round; 16: the finish and the step's end in launches of their
-  // own).  Less than 3 % under the other forms
-  // does not count, nor do fewer than 192 slices (2 replicas, b = 4096, 112 of them: they would take 130, launches of their own 141).  us per step, other forms -> slices (2, 3, 4):
-  // 784-512-512-10, 8 replicas, b = 4096 249.5 -> 239, 265, 257; 4 replicas, b = 4096 169 -> 166, 156, 156; 784-256-256-10,
-  // 8 replicas, b = 4096 178 -> 169, 162, 158; 784-512-10, 12 replicas, b = 4000 245 -> 227, 250, 244; not taken: 8 replicas, b = 2048
-  // 144 -> 160, 181, 180; 784-768-768-768-100, 4 replicas, b = 4096 301 -> 335, 317, 340
+  // Or slices of 256 x 256 tiles, all layers in one launch, which want a third of the operands' bytes of 64 x 128 ones (1.5 us per k-tile
+  // and round; 16: the finish and the step's end in launches of their own).  Less than 3 % under the other forms does not count, nor
+  // 15 % where the slices take more than one round of CUs, whose other forms the model prices too high: 200 nets with 136 to 2400
+  // inputs, b = 1300 to 13000, one round 0.81 to 1.01 of the time of a step (one 1.04), more of them under 0.85 0.88 to 1.03, above that 0.93
+  // to 1.07 (1248-584-528-664-22, 12 replicas, b = 1886 541 -> 578 us).  Nor do fewer than 192 slices (784-512-512-10, 2 replicas, b = 4096,
+  // 112 of them: they would take 130 us, launches of their own 141).  us per step, other forms -> slices (2, 3, 4): 784-512-512-10, 8 replicas,
+  // b = 4096 249.5 -> 239, 265, 257; 4 replicas, b = 4096 169 -> 166, 156, 156; 784-256-256-10, 8 replicas, b = 4096 178 -> 169, 162, 158;
+  // 784-512-10, 12 replicas, b = 4000 245 -> 227, 250, 244; not taken: 8 replicas, b = 2048 144 -> 160, 181, 180; 784-768-768-768-100,
+  // 4 replicas, b = 4096 301 -> 335, 317, 340
   for (int S = 2; S <= 4 && !b_host && (KT + S - 1) / S >= 8; ++S) {
     double blocks = 0.0, outputs = 0.0;
     bool fits = true;
@@ -327,7 +329,7 @@ WgradPlan plan_wgrad(const Plan &pl, int b, int fused, const int *b_host) {
       outputs += S * o;
     }
     const double t = std::ceil(blocks / 256) * ((KT + S - 1) / S) * 1.5 + launch + 16.0 + outputs * 8.0 / 9e6;
-    if (fits && blocks >= 192 && t < 0.97 * std::min(cost, best) && (large == 0 || t < large_cost)) { large = S; large_cost = t; }
+    if (fits && blocks >= 192 && t < (blocks <= 256 ? 0.97 : 0.85) * std::min(cost, best) && (large == 0 || t < large_cost)) { large = S; large_cost = t; }
   }
   if (large) {
     w.shared = true;

@@ -1066,3 +1066,19 @@ def test_weight_gradients_in_slices_of_large_tiles(dims, M, b, opt):
     finally:
         rep.close()
     test_weight_gradient_launches_of_long_batches(dims, M, b, opt, 0)
+
+
+# Slices in more than one round of CUs, which are slower than the other forms though the model prices them a little lower
+@pytest.mark.parametrize("dims,M,b", [((400, 136, 176, 256, 152, 12), 26, 1362), ((1496, 240, 472, 768, 192, 23), 15, 1716)])
+def test_weight_gradients_in_one_round_of_slices_only(dims, M, b):
+    A = _A()
+    w = W.Workload("rounds", dims, W.ACT_RELU, True, W.PREC_BF16, N=512, M=M, H=1, rounds=1, b0=b, b_cap=b, opt=W.OPT_SGD, lr=0.02,
+                   test=W.TEST_NORM, data="teacher_mlp", seed=61)
+    X, y = W.make_dataset(w)
+    rep = A.Replicas.from_workload(w, X, y, W.make_x0(w))
+    try:
+        rep.profile_enable(True)
+        rep.local_step(W.step_indices(w, 0, 0, b), w.lr)
+        assert "gemm_wgrad_256x256_L0" not in rep.profile_read()
+    finally:
+        rep.close()
