@@ -382,6 +382,9 @@ struct abs_ctx {
   long long N = 0;
   double *host_stats = nullptr;     // pinned, M*8 + 8 doubles
   double *host_stats_dev = nullptr; // the same memory as the device sees it (the statistics kernel writes there)
+  int chain_polls = SmallChain::POLLS;
+  // Word of the pinned block that a launch sets when one of its waits gave up (offset in doubles, of host_stats and host_stats_dev)
+  size_t failed_at() const { return (size_t)pl.M * 8 + 4; }
   double ticket = 0.0;              // number of the last statistics launch that mirrors its sums (exact in a double)
   bool ticket_live = false;         // that launch carried the ticket as a kernel argument (not a replayed graph)
   long long t = 0;                  // local steps taken (Adam bias correction)
@@ -521,6 +524,13 @@ void ceil_ratio(double num, double den, int b, double &ratio, long long &T) {
   T = c > 9.0e18 ? (long long)9e18 : (c < -9.0e18 ? (long long)-9e18 : (long long)c);
 }
 
+// After the steps taken so far have ended: whether a launch of one of them gave up waiting for its own tiles (it then went on with what was in
+// memory).  What the replicas hold is no step's result any more, so this stays for the life of the context.
+abs_status check_waits(abs_ctx *c) {
+  const volatile int *failed = reinterpret_cast<const int *>(c->host_stats + c->failed_at());
+  return *failed ? cfail(c, ABS_EHIP, "a launch gave up waiting for its own tiles: the results of its step are not valid") : ABS_OK;
+}
+
 abs_status read_stats(abs_ctx *c) {
   if (!c->have_stats) return cfail(c, ABS_ESTATE, "no local step has been taken yet");
   if (!c->host_stats_dev)
@@ -535,13 +545,13 @@ abs_status read_stats(abs_ctx *c) {
     for (unsigned spin = 0;; ++spin) {
       bool done = true;
       for (int m = 0; m < c->pl.M && done; ++m) done = h[m * 8 + 7] == c->ticket;
-      if (done) { std::atomic_thread_fence(std::memory_order_acquire); return ABS_OK; }
+      if (done) { std::atomic_thread_fence(std::memory_order_acquire); return check_waits(c); }
       if ((spin & 63) == 63 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(20)) break;
       __builtin_ia32_pause();
     }
   }
   HIPCHK(c, hipStreamSynchronize(c->stream));      // the statistics kernel has written the pinned mirror itself
-  return ABS_OK;
+  return check_waits(c);
 }
 
 // No exception leaves the library: host allocations (vectors, strings) are the only throwing operations.
@@ -838,7 +848,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
     int ride = gather_rides(isb, L, b, pl.dims.data(), M, c->N, b_host);
     bool head_fused = gemm_head_fits(isb, b, pl.dims[L], M);
     // all passes on 32-row tiles: one launch for them
-    const bool chained = pl.bf16 && (long long)M * ((b + 31) / 32) <= pl.chain_max && small_chain_fits(L, pl.dims.data(), b, M, c->N, b_host);
+    const bool chained = pl.bf16 && c->host_stats_dev && (long long)M * ((b + 31) / 32) <= pl.chain_max && small_chain_fits(L, pl.dims.data(), b, M, c->N, b_host);
     // or blocks of rows, each on its own way through all layers
     const int block = pl.bf16 && !chained && !b_host ? mlp_rows_block(L, pl.dims.data(), b, M, c->N) : 0;
     const bool gather_apart = block && !ride;               // (the gather counts as the launch that it would be)
@@ -950,6 +960,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
         SmallChain ch;
         std::memset(&ch, 0, sizeof(ch));
         ch.L = L; ch.words = pl.chain_words; ch.count = c->at<int>(pl.o_chain); ch.gather = ga;
+        ch.polls = c->chain_polls; ch.failed = reinterpret_cast<int *>(c->host_stats_dev + c->failed_at());
         std::copy(passes.begin(), passes.end(), ch.p);
         HIPCHK(c, launch_small_chain(ch, s));
       } else {
@@ -1514,6 +1525,7 @@ abs_status abs_cross_worker_test(abs_ctx *c, double eta, abs_test_result *out) t
   double *h = c->host_stats + (size_t)pl.M * 8;
   HIPCHK(c, hipMemcpyAsync(h, cw, 2 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
+  { abs_status ws = check_waits(c); if (ws != ABS_OK) return ws; }
   abs_test_result r;
   std::memset(&r, 0, sizeof(r));
   const int b = c->last_b, M = pl.M;
@@ -1588,6 +1600,7 @@ abs_status abs_get_opt_state(abs_ctx *c, int m, int which, float *out_host) try 
     return cfail(c, ABS_EINVAL, "this optimizer keeps no such state vector");
   std::vector<float> in(c->pl.Ppad);
   HIPCHK(c, hipStreamSynchronize(c->stream));
+  { abs_status ws = check_waits(c); if (ws != ABS_OK) return ws; }
   HIPCHK(c, hipMemcpy(in.data(), c->at<float>(which == 0 ? c->pl.o_v : c->pl.o_m) + (size_t)m * c->pl.Ppad,
                       c->pl.Ppad * sizeof(float), hipMemcpyDeviceToHost));
   to_external(c->pl, c->cfg.has_bias != 0, in.data(), out_host);
@@ -1599,6 +1612,7 @@ abs_status abs_get_params(abs_ctx *c, int m, float *out_host) try {
   if (m < 0 || m >= c->pl.M) return cfail(c, ABS_EINVAL, "replica index out of range");
   std::vector<float> in(c->pl.Ppad);
   HIPCHK(c, hipStreamSynchronize(c->stream));
+  { abs_status ws = check_waits(c); if (ws != ABS_OK) return ws; }
   HIPCHK(c, hipMemcpy(in.data(), c->at<float>(c->pl.o_xm) + (size_t)m * c->pl.Ppad, c->pl.Ppad * sizeof(float), hipMemcpyDeviceToHost));
   to_external(c->pl, c->cfg.has_bias != 0, in.data(), out_host);
   return ABS_OK;
@@ -1611,6 +1625,7 @@ abs_status abs_get_grad(abs_ctx *c, int m, float *out_host) try {
   { abs_status ms = materialize_grad(c); if (ms != ABS_OK) return ms; }
   std::vector<float> in(c->pl.Ppad);
   HIPCHK(c, hipStreamSynchronize(c->stream));
+  { abs_status ws = check_waits(c); if (ws != ABS_OK) return ws; }
   HIPCHK(c, hipMemcpy(in.data(), c->at<float>(c->pl.o_grad) + (size_t)m * c->pl.Ppad, c->pl.Ppad * sizeof(float), hipMemcpyDeviceToHost));
   to_external(c->pl, c->cfg.has_bias != 0, in.data(), out_host);
   return ABS_OK;
@@ -1637,6 +1652,7 @@ abs_status abs_get_per_sample(abs_ctx *c, int m, float *n_host, float *q_host) t
   if (!c->have_stats) return cfail(c, ABS_ESTATE, "no local step has been taken yet");
   if (q_host && !c->pl.want_ip) return cfail(c, ABS_ESTATE, "stats_mask lacks ABS_STATS_IP");
   HIPCHK(c, hipStreamSynchronize(c->stream));
+  { abs_status ws = check_waits(c); if (ws != ABS_OK) return ws; }
   HIPCHK(c, hipMemcpy(n_host, c->at<float>(c->pl.o_nout) + (size_t)m * c->pl.cap, (size_t)(c->last_ps >= 0 ? c->last_ps : c->last_bm[m]) * sizeof(float), hipMemcpyDeviceToHost));
   if (q_host)
     HIPCHK(c, hipMemcpy(q_host, c->at<float>(c->pl.o_qout) + (size_t)m * c->pl.cap, (size_t)(c->last_ps >= 0 ? c->last_ps : c->last_bm[m]) * sizeof(float), hipMemcpyDeviceToHost));
@@ -1850,3 +1866,5 @@ abs_status abs_average_bf16(void *params_dev, int M, int64_t n, void *scratch_de
 } catch (...) { return on_exception(); }
 
 }  // extern "C"
+
+void absk::set_chain_polls(abs_ctx *c, int polls) { c->chain_polls = polls; }

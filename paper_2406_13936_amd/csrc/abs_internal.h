@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+struct abs_ctx;
+
 namespace absk {
 
 typedef uint16_t bf16_t;   // raw bfloat16 bits in memory
@@ -136,14 +138,16 @@ hipError_t launch_gemm_small(const GemmP &p, int epi, hipStream_t s);
 // rows, zero before the first launch and after each.
 struct SmallChain {
   enum { MAXL = 4, MAX_CHAINS = 224 };
-  int L, words;
-  int *count;
+  enum { POLLS = 1 << 22 };                      // of a tile's wait, at about a microsecond each: only a mistake in here lets it last that long
+  int L, words, polls;
+  int *count, *failed;                           // failed (pinned host memory, as the device sees it): set to 1 if a wait gave up
   int end[2 * MAXL - 2], chains;                 // set by the launcher: tiles of a chain up to and with each pass (logits with layer L's backward-data)
   GatherP gather;
   GemmP p[2 * MAXL - 1];
 };
 static_assert(sizeof(SmallChain) <= 4096, "kernel arguments");
 int small_chain_words(int L, const int *dims);
+void set_chain_polls(abs_ctx *c, int polls);       // (for tests of a wait that gives up)
 bool small_chain_fits(int L, const int *dims, int b, int groups, long long N, const int *rows_host);       // (bf16) where that is the way
 hipError_t launch_small_chain(SmallChain &c, hipStream_t s);
 // ---- mlp_rows.hip ------------------------------------------------------------

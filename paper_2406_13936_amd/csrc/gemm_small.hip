@@ -40,9 +40,9 @@ __device__ __forceinline__ uint4 ld_agent(const bf16_t *p) {
 }
 
 // A tile of a chain (small_chain_kernel) waits until the `want` words at wait are set before it reads what other tiles of the same
-// launch wrote, and sets *done behind its own outputs.  Both sides go past the XCDs' L2 (agent scope).
-struct ChainLink { int *wait, want, *done; };
-constexpr int CHAIN_POLLS = 1 << 22;
+// launch wrote, and sets *done behind its own outputs.  Both sides go past the XCDs' L2 (agent scope).  After `polls` of them it gives up,
+// says so in *failed (host memory, which every read-back looks at) and goes on, so that the launch ends whatever happens.
+struct ChainLink { int *wait, want, *done, polls, *failed; };
 
 template <bool BT, int EPI> struct SmallTile {
   static constexpr int NJ = BT ? 2 : 1;                   // accumulator tiles of 32 x 32 per wave
@@ -51,15 +51,17 @@ template <bool BT, int EPI> struct SmallTile {
   static constexpr int LDS = 4 * 32 * RLD;
 };
 
-__device__ __forceinline__ void chain_wait(const int *at, int want) {
+__device__ __forceinline__ void chain_wait(const ChainLink &link) {
   if (threadIdx.x < 64) {
-    // (what it waits for was numbered before this tile and is running or done: the bound is never reached)
-    for (int n = 0; n < CHAIN_POLLS; ++n) {
+    // (what it waits for was numbered before this tile and is running or done)
+    int n = 0;
+    for (; n < link.polls; ++n) {
       int set = 1;
-      for (int i = threadIdx.x; i < want; i += 64) set &= __hip_atomic_load(at + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      for (int i = threadIdx.x; i < link.want; i += 64) set &= __hip_atomic_load(link.wait + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (__ballot(set == 0) == 0) break;
       __builtin_amdgcn_s_sleep(1);
     }
+    if (n == link.polls && threadIdx.x == 0) __hip_atomic_store(link.failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();                           // (loads of the weights stay in flight)
@@ -267,7 +269,7 @@ __device__ __forceinline__ void small_tile(const GemmP &p, const int g, const in
     if (CHAIN && GA == 0 && first) {                      // the weights are under way while it waits for the signals
 #pragma unroll
       for (int i = 0; i < D * KS; ++i) load_b1(i / KS, i % KS);
-      chain_wait(link.wait, link.want);
+      chain_wait(link);
       load_e();
 #pragma unroll
       for (int i = 0; i < D * KS; ++i) load_a1(i / KS, i % KS);
@@ -413,7 +415,7 @@ __device__ __forceinline__ void head_bwd_tile(const GemmP &pz, const GemmP &p, c
     for (int i = 0; i < D * KS; ++i) fb[i] = __builtin_amdgcn_raw_buffer_load_b128(rb, at(i) + half * 8 < K ? zrow + (uint32_t)at(i) * 2u : OOB, 0, 0);
     if (first) {
       label = min(max(pz.head.y[min(max(id, 0), pz.head.N - 1)], 0), classes - 1);
-      chain_wait(link.wait, link.want);
+      chain_wait(link);
       if (ACT != ACT_NONE && mr < Md && nc < p.Nd) ew = ld_agent(static_cast<const bf16_t *>(p.E) + (long long)g * p.sEg + (long long)mr * p.lde + nc);
       first = false;
     }
@@ -490,7 +492,7 @@ __global__ void __launch_bounds__(256, 2) small_chain_kernel(const SmallChain c)
     while (id >= c.end[ph]) ++ph;                          // uniform
     const int before = ph > 0 ? c.end[ph - 1] : 0, before2 = ph > 1 ? c.end[ph - 2] : 0, tn = id - before;
     int *const set = words + 32;                           // a word per tile
-    const ChainLink link = {set + before2, before - before2, ph < passes - 1 ? set + id : nullptr};
+    const ChainLink link = {set + before2, before - before2, ph < passes - 1 ? set + id : nullptr, c.polls, c.failed};
     const GemmP &p = c.p[ph < L ? ph : ph + 1];
     if (ph == 0) small_tile<false, EPI_FWD_ACT, ACT, 2, true>(p, g, tm, tn, red, link, src);
     else if (ph < L - 1) small_tile<false, EPI_FWD_ACT, ACT, 0, true>(p, g, tm, tn, red, link);
@@ -587,7 +589,7 @@ bool small_chain_fits(int L, const int *dims, int b, int groups, long long N, co
 
 hipError_t launch_small_chain(SmallChain &c, hipStream_t s) {
   const int L = c.L, n = 2 * L - 1;
-  if (L < 2 || L > SmallChain::MAXL || !c.count) return hipErrorInvalidValue;
+  if (L < 2 || L > SmallChain::MAXL || !c.count || !c.failed) return hipErrorInvalidValue;
   const int Md = c.p[0].Md, groups = c.p[0].groups, act = c.p[0].act;
   int tiles = 0;
   for (int i = 0; i < n; ++i) {

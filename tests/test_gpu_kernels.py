@@ -1008,6 +1008,33 @@ def test_passes_in_one_launch(dims, act, steps):
             twin.close()
 
 
+# A wait inside such a launch that gives up (no poll allowed, so that every tile reads what is there) is no step: every read-back says so, for the
+# context that it happened in.
+def test_a_wait_that_gives_up_is_an_error():
+    A = _A()
+    w = W.Workload("wait", (72, 40, 5), W.ACT_RELU, True, W.PREC_BF16, N=512, M=2, H=1, rounds=1, b0=33, b_cap=33, opt=W.OPT_SHB, lr=0.02,
+                   momentum=0.9, test=W.TEST_IP, theta=0.9, data="teacher_mlp", seed=71)
+    X, y = W.make_dataset(w)
+    x0 = W.make_x0(w)
+    rep, other = (A.Replicas.from_workload(w, X, y, x0) for _ in range(2))
+    try:
+        for r in (rep, other):
+            r.local_step(W.step_indices(w, 0, 0, 33), w.lr)
+            r.inner_product_test(w.theta)
+        rep._lib["_ZN4absk15set_chain_pollsEP7abs_ctxi"](rep._ctx, 0)
+        for r in (rep, other):
+            r.local_step(W.step_indices(w, 1, 0, 33), w.lr)
+        for call in (lambda r: r.inner_product_test(w.theta), lambda r: r.norm_test(0.5), lambda r: r.get_params(0), lambda r: r.get_grad(1),
+                     lambda r: r.get_opt_state(0), lambda r: r.get_per_sample(0, 33), lambda r: r.cross_worker_test(0.5)):
+            with pytest.raises(A.AbsError, match="gave up waiting"):
+                call(rep)
+            call(other)
+        assert rep.guard_intact()
+    finally:
+        rep.close()
+        other.close()
+
+
 # All passes of a block of rows in one work-group: blocks of 16, 32 and 64 rows, layers up to 256 and up to 512, last blocks of one row and
 # full ones, the widest inputs and the most classes, widths that fill no whole wavefront, no activation and no biases, indices outside the
 # dataset; and the first nets beyond (904 inputs, 129 classes, a layer of 520).  No ReLU where a layer of 24 takes in 500: a unit within an
