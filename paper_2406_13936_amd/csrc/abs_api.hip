@@ -364,7 +364,7 @@ static const char *const kTagNames[T_GEMM0 + T_GEMM_KINDS] = {
   "gemm_wgrad_128x64", "gemm_wgrad_128x128", "gemm_wgrad_256x256", "gemm_wgrad_64x256", "gemm_wgrad_64x128", "gemm_wgrad_128x256",
   "gemm_ipdot_128x64", "gemm_ipdot_128x128", "gemm_ipdot_256x256", "gemm_ipdot_64x256", "gemm_ipdot_64x128", ""};
 
-struct ProfRec { int tag; hipEvent_t e0, e1; double flops, bytes, share; };
+struct ProfRec { int tag; hipEvent_t e0, e1; double flops, bytes, share; size_t timed; };     // timed: the record whose events bracket the launch
 
 struct abs_ctx {
   bool prof_on = false;            // launches are being bracketed right now
@@ -447,23 +447,32 @@ void to_external(const Plan &pl, bool has_bias, const float *in, float *ext) {
   }
 }
 
-// Optional event bracket around one launch (profiling on: two hipEventRecord calls).  share: of a launch that is the work of two
-// classes, the part of its time that counts for this one.
+// Optional event bracket around one launch (profiling on: two hipEventRecord calls).  A launch that is the work of several classes has a
+// record of each, which takes part of its time in proportion to their bytes.
+struct ProfPart { int tag; double flops, bytes; };
 struct ProfScope {
-  abs_ctx *c; size_t r = 0; bool on = false;       // (its number: records of scopes inside this one may move the pool)
-  ProfScope(abs_ctx *ctx, int tag, double flops, double bytes, double share = 1.0) : c(ctx) {
-    if (!c->prof_on) return;
-    if (c->prof_used == c->prof_recs.size()) {
-      ProfRec n{};
-      if (hipEventCreate(&n.e0) != hipSuccess) return;
-      if (hipEventCreate(&n.e1) != hipSuccess) { (void)hipEventDestroy(n.e0); return; }
-      c->prof_recs.push_back(n);
+  abs_ctx *c; size_t r = 0; bool on = false;       // (its number: further records may move the pool)
+  ProfScope(abs_ctx *ctx, int tag, double flops, double bytes) : c(ctx) {
+    const ProfPart part = {tag, flops, bytes};
+    if (c->prof_on) open(&part, 1);
+  }
+  ProfScope(abs_ctx *ctx, const ProfPart *parts, size_t n) : c(ctx) { if (c->prof_on) open(parts, n); }
+  void open(const ProfPart *parts, size_t n) {
+    while (c->prof_recs.size() < c->prof_used + n) {
+      ProfRec rec{};
+      if (hipEventCreate(&rec.e0) != hipSuccess) return;
+      if (hipEventCreate(&rec.e1) != hipSuccess) { (void)hipEventDestroy(rec.e0); return; }
+      c->prof_recs.push_back(rec);
     }
-    r = c->prof_used++;
-    on = true;
-    ProfRec &rec = c->prof_recs[r];
-    rec.tag = tag; rec.flops = flops; rec.bytes = bytes; rec.share = share;
-    (void)hipEventRecord(rec.e0, c->stream);
+    double bytes = 0.0;
+    for (size_t i = 0; i < n; ++i) bytes += parts[i].bytes;
+    r = c->prof_used;
+    for (size_t i = 0; i < n; ++i) {
+      ProfRec &rec = c->prof_recs[c->prof_used++];
+      rec.tag = parts[i].tag; rec.flops = parts[i].flops; rec.bytes = parts[i].bytes; rec.share = n == 1 ? 1.0 : parts[i].bytes / bytes; rec.timed = r;
+    }
+    on = n > 0;
+    if (on) (void)hipEventRecord(c->prof_recs[r].e0, c->stream);
   }
   ~ProfScope() { if (on) (void)hipEventRecord(c->prof_recs[r].e1, c->stream); }
   ProfScope(const ProfScope &) = delete;
@@ -699,7 +708,7 @@ abs_status abs_profile_read(abs_ctx *c, int max_entries, abs_profile_entry *out,
   for (size_t i = 0; i < c->prof_used; ++i) {
     ProfRec &r = c->prof_recs[i];
     float ms = 0.0f;
-    HIPCHK(c, hipEventElapsedTime(&ms, r.e0, r.e1));
+    HIPCHK(c, hipEventElapsedTime(&ms, c->prof_recs[r.timed].e0, c->prof_recs[r.timed].e1));
     c->prof_ms[r.tag] += ms * r.share; c->prof_flops[r.tag] += r.flops; c->prof_bytes[r.tag] += r.bytes;
     c->prof_calls[r.tag] += 1;
   }
@@ -779,8 +788,8 @@ static abs_status softmax_step(abs_ctx *c, const int32_t *idx_dev, int ldi, int 
   const double fb = pl.M * (((double)b + p.K) * p.d * 4 + b * (pl.ld[1] * 4.0 + 16)), wb = pl.M * (((double)p.K + p.d) * b * 4 + Kd * (state + 4));
   const double flops = 2.0 * Kd * b * pl.M;
   {
-    ProfScope pf(c, T_GEMM0 + (EPI_LOGITS * 6 + 1) * T_LAYERS + 1, flops, fb, fb / (fb + wb));
-    ProfScope pw(c, T_GEMM0 + (EPI_WGRAD * 6 + 1) * T_LAYERS + 1, flops, wb, wb / (fb + wb));
+    const ProfPart parts[2] = {{T_GEMM0 + (EPI_LOGITS * 6 + 1) * T_LAYERS + 1, flops, fb}, {T_GEMM0 + (EPI_WGRAD * 6 + 1) * T_LAYERS + 1, flops, wb}};
+    ProfScope ps_(c, parts, 2);
     HIPCHK(c, launch_softmax_step(p, c->stream));
   }
   note_step(c, b, b_host);
@@ -945,17 +954,13 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
     if (chained || block) {
       // each pass counts as the class that it would be apart, with a share of the time by its bytes
       auto epi = [&](int i) { return i < L - 1 ? EPI_FWD_ACT : i == L - 1 ? EPI_LOGITS : EPI_BWD; };
-      std::unique_ptr<ProfScope> scopes[2 * SmallChain::MAXL - 1];
-      const double gathered = gather_apart ? 2.0 * M * b * pl.dims[0] * pl.esz : 0.0;
-      double bytes = gathered;
-      for (int i = 0; i < 2 * L - 1; ++i) bytes += gemm_bytes(c, passes[i], epi(i));
-      std::unique_ptr<ProfScope> gather_scope;
-      if (gather_apart && c->prof_on) gather_scope.reset(new ProfScope(c, T_GATHER, 0.0, gathered, gathered / bytes));
+      std::vector<ProfPart> parts;
+      if (gather_apart && c->prof_on) parts.push_back({T_GATHER, 0.0, 2.0 * M * b * pl.dims[0] * pl.esz});
       for (int i = 0; i < 2 * L - 1 && c->prof_on; ++i) {
-        const double own = gemm_bytes(c, passes[i], epi(i));
         const int shape = gemm_bf16_tile_shape(epi(i), b, passes[i].Nd, M, b_host);
-        scopes[i].reset(new ProfScope(c, T_GEMM0 + (epi(i) * 6 + shape) * T_LAYERS + (i < L ? i + 1 : 2 * L - i), gemm_flops(passes[i]), own, own / bytes));
+        parts.push_back({T_GEMM0 + (epi(i) * 6 + shape) * T_LAYERS + (i < L ? i + 1 : 2 * L - i), gemm_flops(passes[i]), gemm_bytes(c, passes[i], epi(i))});
       }
+      ProfScope ps_(c, parts.data(), parts.size());
       if (chained) {
         SmallChain ch;
         std::memset(&ch, 0, sizeof(ch));

@@ -1109,3 +1109,24 @@ def test_weight_gradients_in_one_round_of_slices_only(dims, M, b):
         assert "gemm_wgrad_256x256_L0" not in rep.profile_read()
     finally:
         rep.close()
+
+
+# A launch that is the work of several classes is timed once, and its time goes to them by their bytes
+@pytest.mark.parametrize("dims,prec,M,b,n", [((256, 10), W.PREC_F32, 4, 64, 2), ((784, 512, 512, 10), W.PREC_BF16, 2, 32, 5), ((784, 512, 512, 10), W.PREC_BF16, 8, 501, 5),
+                                             ((784, 256, 256, 10), W.PREC_BF16, 16, 600, 6)])
+def test_profile_shares_the_time_of_a_launch_by_bytes(dims, prec, M, b, n):
+    A = _A()
+    w = W.Workload("shares", dims, W.ACT_RELU, True, prec, N=1024, M=M, H=1, rounds=1, b0=b, b_cap=b, opt=W.OPT_SGD, lr=0.02, test=W.TEST_NORM,
+                   data="teacher_mlp", seed=73)
+    X, y = W.make_dataset(w)
+    rep = A.Replicas.from_workload(w, X, y, W.make_x0(w))
+    try:
+        rep.profile_enable(True)
+        for h in range(3):
+            rep.local_step(W.step_indices(w, h, 0, b), w.lr)
+        shared = {k: v for k, v in rep.profile_read().items() if k == "gather_rows" or k.startswith(("gemm_fwd_", "gemm_logits_", "gemm_bwd_")) or prec == W.PREC_F32}
+        assert len(shared) == n and all(v["calls"] == 3 and v["total_ms"] > 0 for v in shared.values())
+        rate = [v["total_ms"] / v["bytes"] for v in shared.values()]
+        assert max(rate) <= min(rate) * (1 + 1e-9)
+    finally:
+        rep.close()
