@@ -509,8 +509,8 @@ double gemm_flops(const std::vector<GemmP> &v) { double s = 0.0; for (const Gemm
 double gemm_bytes(const abs_ctx *c, const std::vector<GemmP> &v, int epi) { double s = 0.0; for (const GemmP &p : v) s += gemm_bytes(c, p, epi); return s; }
 
 hipError_t gemm(abs_ctx *c, const GemmP &p, int epi, int layer) {
-  int shape = !c->pl.bf16 ? 1 : p.fine == 2 ? 2 : p.fine ? 4 : (epi == EPI_WGRAD ? gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr, p.rows_host)
-                                                                : gemm_bf16_tile_shape(epi, p.Md, p.Nd, p.groups, p.rows_host));
+  const int shape = !c->pl.bf16 ? 1 : epi == EPI_WGRAD ? gemm_bf16_wgrad_tile(gemm_bf16_wgrad_shape(p.Md, p.Nd, p.Kd, p.groups, p.upd_x != nullptr, p.rows_host), p.fine)
+                                                       : gemm_bf16_tile_shape(epi, p.Md, p.Nd, p.groups, p.rows_host);
   ProfScope ps(c, T_GEMM0 + (epi * 6 + shape) * T_LAYERS + layer, gemm_flops(p), gemm_bytes(c, p, epi));
   return c->pl.bf16 ? launch_gemm_bf16(p, epi, c->stream) : launch_gemm_f32(p, epi, c->stream);
 }
@@ -1135,14 +1135,14 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
         const std::vector<GemmP> &v = many[sh][u];
         if (v.empty()) continue;
         if (!tail_taken && (v.size() > 1 || sh) && v[0].fine < 2 && (cf.n == 0 || (u == 1) == fused)) {
-          ProfScope ps_(c, T_GEMM0 + (EPI_WGRAD * 6 + (sh ? 3 : v[0].fine == 2 ? 2 : v[0].fine ? 4 : 1)) * T_LAYERS + (v.size() == 1 ? many_layer[sh][u] : 0),
+          ProfScope ps_(c, T_GEMM0 + (EPI_WGRAD * 6 + gemm_bf16_wgrad_tile(sh ? 3 : 1, v[0].fine)) * T_LAYERS + (v.size() == 1 ? many_layer[sh][u] : 0),
                         gemm_flops(v), gemm_bytes(c, v, EPI_WGRAD) + cf_bytes + (tail.st.nb_done > 0 ? sample_bytes(tail.st) : 0.0));
           HIPCHK(c, launch_wgrad_many(v.data(), (int)v.size(), sh ? 3 : 1, s, &tail));
           tail_taken = true;
           continue;
         }
         if (v.size() == 1) { HIPCHK(c, gemm(c, v[0], EPI_WGRAD, many_layer[sh][u])); continue; }   // (may take a deeper ring)
-        ProfScope ps_(c, T_GEMM0 + (EPI_WGRAD * 6 + (sh ? 3 : v[0].fine == 2 ? 2 : v[0].fine ? 4 : 1)) * T_LAYERS, gemm_flops(v), gemm_bytes(c, v, EPI_WGRAD));
+        ProfScope ps_(c, T_GEMM0 + (EPI_WGRAD * 6 + gemm_bf16_wgrad_tile(sh ? 3 : 1, v[0].fine)) * T_LAYERS, gemm_flops(v), gemm_bytes(c, v, EPI_WGRAD));
         HIPCHK(c, launch_wgrad_many(v.data(), (int)v.size(), sh ? 3 : 1, s));
       }
     if (kf.n > 0) {                        // all split reductions of the step in one launch

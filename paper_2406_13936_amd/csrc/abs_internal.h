@@ -173,6 +173,8 @@ bool gemm_head_fits(int is_bf16, int Md, int Nd, int groups);
 // fused != 0: the launch carries the optimizer step in its epilogue (GemmP::upd_x), which keeps medium batches on
 // 128x128 tiles, or 5 = 128x256 tiles of eight wavefronts.
 int gemm_bf16_wgrad_shape(int Md, int Nd, int Kd, int groups, int fused, const int *rows_host);
+// The tile that such a launch takes with GemmP::fine: the shape, or of shape 1 also 4 = 64x128 (1) and 2 = 256x256 (2).
+inline int gemm_bf16_wgrad_tile(int shape, int fine) { return shape != 1 || !fine ? shape : fine == 2 ? 2 : 4; }
 // Number of upd_sq slots (fused: with the optimizer step in the epilogue) or sq64 slots an EPI_WGRAD launch writes per group.
 int gemm_bf16_upd_slots(int Md, int Nd, int Kd, int groups, int fused, int fine, const int *rows_host);
 // fp32 SIMT family (gemm_f32.hip); EPI_IPDOT is not offered (U is materialised instead).

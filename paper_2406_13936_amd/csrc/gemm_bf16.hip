@@ -1403,8 +1403,8 @@ int gemm_bf16_wgrad_shape(int Md, int Nd, int Kd, int groups, int fused, const i
 }
 
 int gemm_bf16_upd_slots(int Md, int Nd, int Kd, int groups, int fused, int fine, const int *rows_host) {
-  const int bm[6] = {128, fine ? 64 : 128, 256, 64, 0, 128}, bn[6] = {64, 128, 256, 256, 1, 256}, nw[6] = {4, 4, 8, 4, 0, 8};
-  const int sh = gemm_bf16_wgrad_shape(Md, Nd, Kd, groups, fused, rows_host);
+  const int bm[6] = {128, 128, 256, 64, 64, 128}, bn[6] = {64, 128, 256, 256, 128, 256}, nw[6] = {4, 4, 8, 4, 4, 8};
+  const int sh = gemm_bf16_wgrad_tile(gemm_bf16_wgrad_shape(Md, Nd, Kd, groups, fused, rows_host), fine);
   return ((Md + bm[sh] - 1) / bm[sh]) * ((Nd + bn[sh] - 1) / bn[sh]) * nw[sh];
 }
 

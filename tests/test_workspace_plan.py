@@ -75,3 +75,14 @@ def test_which_steps_take_chains_of_tiles(dims, M, b, taken):
     f = B.load_library()["_ZN4absk16small_chain_fitsEiPKiiixS1_"]
     f.restype = C.c_bool
     assert f(len(dims) - 1, (C.c_int * len(dims))(*dims), b, M, C.c_longlong(60000), None) == bool(taken)
+
+
+# Partial sums of squares that a weight gradient's launch leaves, a slot to each wavefront of each of its tiles: tiles of 128 x 128, 64 x 128
+# and, by GemmP::fine, 256 x 256 outputs
+@pytest.mark.parametrize("fine,tile,waves", [(0, (128, 128), 4), (1, (64, 128), 4), (2, (256, 256), 8)])
+def test_slots_of_weight_gradient_tiles(fine, tile, waves):
+    lib = B.load_library()
+    shape, slots = (lib["_ZN4absk" + n] for n in ("21gemm_bf16_wgrad_shapeEiiiiiPKi", "19gemm_bf16_upd_slotsEiiiiiiPKi"))
+    for Md, Nd in ((512, 512), (128, 128), (520, 136), (264, 784)):
+        assert shape(Md, Nd, 4096, 8, 0, None) == 1
+        assert slots(Md, Nd, 4096, 8, 0, fine, None) == -(-Md // tile[0]) * -(-Nd // tile[1]) * waves, (Md, Nd)
