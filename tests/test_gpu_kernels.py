@@ -1076,6 +1076,62 @@ def test_blocks_of_rows_through_all_layers(dims, act, bias, M, b):
         rep.close()
 
 
+# The same launches in replayed steps (bit for bit the direct ones, sizes in turns), in the micro-batches of a larger step, and under inner
+# products from Gram matrices (up to b = 256) and from the batch gradient; tolerances as accumulated steps have them, twice that for squares.
+@pytest.mark.parametrize("dims,act,bias,sizes,micro,total", [((136, 72, 40, 10), W.ACT_GELU, True, (330, 150), 150, 449),
+                                                             ((264, 312, 10), W.ACT_NONE, False, (330, 224), 224, 448)])
+def test_blocks_of_rows_replayed_and_in_micro_batches(dims, act, bias, sizes, micro, total):
+    import ctypes as C
+    import torch
+    A = _A()
+    M, cap = 16, max(sizes)
+    w = W.Workload("rows", dims, act, bias, W.PREC_BF16, N=1024, M=M, H=1, rounds=1, b0=cap, b_cap=cap, opt=W.OPT_SHB, lr=0.02, momentum=0.9,
+                   test=W.TEST_IP, theta=0.9, data="teacher_mlp", seed=79)
+    X, y = W.make_dataset(w)
+    x0 = W.make_x0(w)
+    orc = O.Replicas(O.Net(w.dims, w.act, bias), x0, X, y, M, opt=w.opt, momentum=w.momentum, mixed=True, want_ip=True, gram_max_b=256)
+
+    def check(r, b, stored):
+        res = r.inner_product_test(w.theta)
+        for m in range(M):
+            s, (n, q) = orc.stats[m], r.get_per_sample(m, stored, want_q=True)
+            np.testing.assert_allclose(n, s["n"][:stored], rtol=2e-2, atol=2e-3 * s["n"].max())
+            np.testing.assert_allclose(q, s["q"][:stored], rtol=2e-2, atol=2e-3 * np.abs(s["q"]).max())
+            for k, got, want in ((1, res[m].sum_sq, s["S1"]), (1, res[m].gbar_sq, s["S2"]), (1, res[m].sum_q, s["S4"]), (2, res[m].sum_q2, s["S3"]),
+                                 (1, res[m].loss_sum, s["loss_sum"])):
+                assert abs(got - want) <= k * 2e-3 * abs(want), (b, m, got, want)
+            grad = r.get_grad(m).astype(np.float64)
+            assert np.linalg.norm(grad - orc.grads[m]) <= 2e-3 * np.linalg.norm(orc.grads[m]), (b, m)
+
+    with torch.cuda.stream(torch.cuda.Stream()):
+        ref, rep = (A.Replicas.from_workload(w, X, y, x0) for _ in range(2))
+        try:
+            rows = rep._lib["_ZN4absk14mlp_rows_blockEiPKiiix"]
+            assert all(rows(len(dims) - 1, (C.c_int * len(dims))(*dims), b, M, C.c_longlong(w.N)) for b in (*sizes, micro, total % micro or micro))
+            for h, b in enumerate(sizes * 4):
+                idx = W.step_indices(w, h, 0, b)
+                (t1, _), (t2, _) = ref.upload_indices(idx), rep.upload_indices(idx)
+                ref.local_step_dev(t1, b, w.lr)
+                rep.local_step_graphed_dev(t2, b, w.lr)
+                if h < 2:
+                    orc.local_step(idx, w.lr)
+                    check(ref, b, b)
+                for g1, g2 in zip(ref.inner_product_test(w.theta), rep.inner_product_test(w.theta)):
+                    assert (g1.sum_sq, g1.gbar_sq, g1.sum_q, g1.sum_q2, g1.loss_sum) == (g2.sum_sq, g2.gbar_sq, g2.sum_q, g2.sum_q2, g2.loss_sum), h
+                assert all(np.array_equal(ref.get_params(m), rep.get_params(m)) for m in range(M)), h
+            assert rep.graph_count() == 2
+            for m in range(M):
+                orc.x[m] = rep.get_params(m).astype(np.float64)
+            idx = W.step_indices(w, 9, 0, total)
+            rep.local_step_accumulated(idx, micro, w.lr)
+            orc.local_step(idx, w.lr)
+            check(rep, total, cap // micro * micro)          # (whole micro-batches that fit the cap are stored)
+            assert ref.guard_intact() and rep.guard_intact()
+        finally:
+            ref.close()
+            rep.close()
+
+
 # Weight gradients of long batches in slices of 256 x 256 tiles, all layers in one launch: two and four slices, the last one shorter and its
 # last k-tile cut, widths that leave most of a tile empty; the sums and the step as in every other form.
 @pytest.mark.parametrize("dims,M,b,opt", [((784, 512, 10), 12, 4001, W.OPT_ADAMW), ((784, 256, 256, 10), 8, 4090, W.OPT_SHB),
