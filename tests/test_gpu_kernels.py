@@ -1008,6 +1008,36 @@ def test_passes_in_one_launch(dims, act, steps):
             twin.close()
 
 
+# One replica more and the passes are launches of their own (225 and 226 blocks of 32 rows): the others' results are bit for bit the same.
+@pytest.mark.parametrize("dims,act,M,b", [((16, 48, 10), W.ACT_RELU, 224, 4), ((72, 40, 32), W.ACT_GELU, 112, 33)])
+def test_passes_in_one_launch_are_bitwise_the_launches_apart(dims, act, M, b):
+    import ctypes as C
+    A = _A()
+    got = []
+    for groups in (M, M + 1):
+        w = W.Workload("apart", dims, act, True, W.PREC_BF16, N=512, M=groups, H=1, rounds=1, b0=b, b_cap=b, opt=W.OPT_SHB, lr=0.02, momentum=0.9,
+                       test=W.TEST_IP, theta=0.9, data="teacher_mlp", seed=83)
+        X, y = W.make_dataset(w)
+        rep = A.Replicas.from_workload(w, X, y, W.make_x0(w))
+        try:
+            sizes = [b - m % 3 for m in range(groups)]       # (workers with batches of their own take no blocks of rows)
+            host, net = (C.c_int * groups)(*sizes), (C.c_int * len(dims))(*dims)
+            fits, shape = rep._lib["_ZN4absk16small_chain_fitsEiPKiiixS1_"], rep._lib["_ZN4absk20gemm_bf16_tile_shapeEiiiiPKi"]
+            fits.restype = C.c_bool
+            assert fits(len(dims) - 1, net, b, groups, C.c_longlong(w.N), host) == (groups == M)
+            assert all(shape(0, b, d, groups, host) == 5 for d in dims[1:-1])
+            for h in range(3):
+                rep.local_step_ragged([W.batch_indices(w.seed, h, 0, m, n, w.N) for m, n in enumerate(sizes)], w.lr)
+            res = rep.inner_product_test(w.theta)
+            got.append([((r.sum_sq, r.sum_q, r.sum_q2, r.loss_sum), rep.get_per_sample(m, sizes[m], want_q=True), rep.get_grad(m), rep.get_params(m))
+                        for m, r in enumerate(res[:M])])
+        finally:
+            rep.close()
+    for m, (a, c) in enumerate(zip(*got)):
+        assert a[0] == c[0], m
+        assert all(np.array_equal(u, v) for u, v in zip((*a[1], *a[2:]), (*c[1], *c[2:]))), m
+
+
 # A wait inside such a launch that gives up (no poll allowed, so that every tile reads what is there) is no step: every read-back says so, for the
 # context that it happened in.
 def test_a_wait_that_gives_up_is_an_error():
