@@ -322,7 +322,8 @@ abs_status abs_average_bf16_static(void *params_dev, int M, int64_t n, void *hip
  * for the bandwidth-bound kernels).  Bias gradients and per-sample statistics in front of the weight
  * gradients count in that launch, time and bytes.  A batch gather beside a contraction of the forward
  * pass has no entry: its time is part of that launch's, its bytes (two rows per sample) of no entry.
- * Passes that share one launch count as the classes that they would be apart, the time by their bytes.
+ * Passes that share one launch count as the classes that they would be apart (their names have the tile that each would take), the
+ * launch's time by their bytes: the sum over them is measured, their own times and rates are not.
  *   out : host.
  */
 typedef struct {

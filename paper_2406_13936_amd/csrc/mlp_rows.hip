@@ -582,6 +582,7 @@ template <int NT> hipError_t launch_rows(const MlpRows &c, hipStream_t s) {
 //     them with hidden layers of 128 and more 0.78 to 1.01, of less up to 1.05 to 1024 and beyond 0.90 to 1.37 (16-56-8-8-4, 31 replicas,
 //     b = 3547 192 -> 261 us): narrow layers leave most wavefronts without columns, and a round of blocks then costs what its barriers do,
 //     while tiles cost by the widths.
+// Inputs end at 896, 784 to the next 128: registers and LDS would hold 1024, which nothing has measured.
 // For example, us per step: 784-512-512-10, 8 replicas, b = 1000 120 -> 104, 784-160-160-160-3 (GELU), 7 replicas, b = 479 87 -> 69,
 // 784-328-328-328-34 (GELU), 16 replicas, b = 669 198 -> 166.
 int mlp_rows_block(int L, const int *dims, int b, int groups, long long N) {

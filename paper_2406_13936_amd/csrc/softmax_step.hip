@@ -427,8 +427,10 @@ __global__ void __launch_bounds__(NT) softmax_step_kernel(const SoftmaxStepP p) 
 // Samples to a work-group: the whole batch while one can hold it, else 32: 64 make the loads of the rows longer, 16 the sum over the
 // chunks.  us per step, 64 -> 32 -> 16: 256-10, 4 replicas, b = 512 23.2 -> 23.0 -> 24.9; 512-2, 4, b = 100 27.1 -> 23.0; 256-16, 16,
 // b = 512 27.7 (32) -> 38.2; 512-10, 8, b = 512 29.2 (32) -> 34.0.  Long rows in a few chunks are still faster in 16: 784-16, 4
-// replicas, b = 100 41.2 -> 36.1; 1024-16, 8, b = 100 51.4 -> 44.8; 512-10, 4, b = 100 25.9 -> 24.2.  (1024 and more features: 16 is
-// what fits.)
+// replicas, b = 100 41.2 -> 36.1; 1024-16, 8, b = 100 51.4 -> 44.8; 512-10, 4, b = 100 25.9 -> 24.2.  (Beyond 1024 features 16 is what fits.)
+// Up to 128 of them, since the sum takes eight chunks at a time: 512, 640, 784 and 1024 features, 1 to 16 replicas, 32 -> 16: b = 65 6 to 14 %
+// faster, b = 128 6 to 13 % (784-10, 8 replicas 24.8 -> 22.1 and 25.3 -> 22.7), b = 129 1 % faster to 6 % slower (25.0 -> 25.0; 1024-16, 16
+// replicas 32.6 -> 34.5).
 int chunk_of(int d, int b) {
   if (b <= 16 || d > 1024 || (d >= 512 && b > 64 && b <= 128)) return 16;
   return b > 32 && b <= 64 && d <= 512 ? 64 : 32;
