@@ -578,17 +578,20 @@ template <int NT> hipError_t launch_rows(const MlpRows &c, hipStream_t s) {
 //   64 rows in one round, layers up to 256: 0.71 to 1.03, on average 0.91; in two rounds up to 1.25 (400-56-272-64-18, 133 replicas, b = 77);
 //   64 rows, wider layers: from 192 blocks on 0.83 to 1.00; fewer of them with 800 and more inputs and hidden units 0.87 to 1.00, with less
 //     0.93 to 1.06: half the CUs idle, and little for each to load;
-//   32 rows, 257 to 768 blocks: 0.76 to 1.02, except where replicas of less than half a block make them mostly empty (up to 1.10); more of
-//     them with hidden layers of 128 and more 0.78 to 1.01, of less up to 1.05 to 1024 and beyond 0.90 to 1.37 (16-56-8-8-4, 31 replicas,
-//     b = 3547 192 -> 261 us): narrow layers leave most wavefronts without columns, and a round of blocks then costs what its barriers do,
-//     while tiles cost by the widths.
+//   32 rows, 257 to 768 blocks: 0.74 to 1.02 (one 1.04: 56-56-84, 21 replicas, b = 945), except where replicas of less than half a block make
+//     them mostly empty (up to 1.10);
+//   more of them: a round costs what its barriers do however few wavefronts have columns, or rows of the head, while tiles cost by the widths and
+//     get better with every round.  490 nets: with hidden layers of 128 on average, each from 64, to 1536 blocks and 64 classes 0.77 to 1.00, from 320
+//     inputs, whose gather is spared, to 2048 and 96 classes 0.77 to 1.00, both 0.90 on average (220 nets outside the fit 0.91, at most 1.03); narrower layers up to 1.37 (16-56-8-8-4, 31
+//     replicas, b = 3547 192 -> 261 us), one of them among wide ones up to 1.06, more classes up to 1.13 (32-168-107, 11 replicas, b = 5369
+//     141 -> 159), more blocks up to 1.26 (32-152-40-256-103, 95 replicas, b = 4599 1133 -> 1424).
 // Inputs end at 896, 784 to the next 128: registers and LDS would hold 1024, which nothing has measured.
 // For example, us per step: 784-512-512-10, 8 replicas, b = 1000 120 -> 104, 784-160-160-160-3 (GELU), 7 replicas, b = 479 87 -> 69,
 // 784-328-328-328-34 (GELU), 16 replicas, b = 669 198 -> 166.
 int mlp_rows_block(int L, const int *dims, int b, int groups, long long N) {
   if (L < 2 || L > MlpRows::MAXL || dims[L] > MAX_CLASSES || dims[0] > MAX_IN || N * dims[0] * 2 >= (1LL << 30)) return 0;
-  int width = 0, sum = 0;
-  for (int l = 1; l < L; ++l) { width = dims[l] > width ? dims[l] : width; sum += dims[l]; }
+  int width = 0, sum = 0, narrowest = 64 * WAVES;
+  for (int l = 1; l < L; ++l) { width = dims[l] > width ? dims[l] : width; narrowest = dims[l] < narrowest ? dims[l] : narrowest; sum += dims[l]; }
   auto blocks = [&](int rows) { return (long long)((b + rows - 1) / rows) * groups; };
   const bool wide = width > 32 * WAVES;
   if (width > 64 * WAVES || blocks(16) < (wide ? 216 : 140)) return 0;
@@ -596,7 +599,10 @@ int mlp_rows_block(int L, const int *dims, int b, int groups, long long N) {
   if (blocks(32) <= 256) return 32;
   if (blocks(64) <= 256) return !wide || blocks(64) >= 192 || dims[0] + sum >= 800 ? 64 : 0;
   if (wide || (long long)b * groups < 16 * blocks(32)) return 0;
-  return blocks(32) <= 768 || sum >= 128 * (L - 1) ? 32 : 0;
+  if (blocks(32) <= 768) return 32;
+  if (sum < 128 * (L - 1) || narrowest < 64) return 0;
+  const bool deep = dims[0] >= 320;
+  return blocks(32) <= (deep ? 2048 : 1536) && dims[L] <= (deep ? 96 : 64) ? 32 : 0;
 }
 
 hipError_t launch_mlp_rows(MlpRows &c, hipStream_t s) {

@@ -55,7 +55,12 @@ def test_which_fp32_steps_take_one_launch(d, K, M, b, taken):
     ((896, 256, 128), 16, 160, 16), ((904, 256, 128), 16, 160, 0), ((896, 256, 129), 16, 160, 0), ((784, 520, 10), 16, 256, 0),
     ((784, 64, 64, 64, 10), 16, 160, 16), ((784, 64, 64, 64, 64, 10), 16, 160, 0), ((784, 10), 16, 160, 0),
     ((16, 56, 8, 8, 4), 24, 1024, 32), ((16, 56, 8, 8, 4), 24, 1025, 0), ((16, 56, 8, 8, 4), 31, 3547, 0), ((32, 40, 40, 16), 25, 4883, 0),
-    ((64, 32, 224, 10), 16, 4096, 32), ((64, 32, 216, 10), 16, 4096, 0), ((64, 128, 10), 32, 8192, 32),
+    ((64, 32, 224, 10), 16, 1500, 32), ((64, 32, 224, 10), 16, 4096, 0), ((64, 128, 10), 32, 8192, 0),
+    # many of 32 rows: each hidden layer from 64, 128 on average, then to 1536 of them and 64 classes, from 320 inputs to 2048 and 96
+    ((56, 128, 240, 40, 35), 20, 2902, 0), ((24, 64, 208, 112, 54), 39, 6218, 0), ((32, 152, 40, 256, 103), 95, 4599, 0), ((896, 248, 248, 8, 6), 35, 1726, 0),
+    ((64, 64, 192, 64), 48, 1024, 32), ((64, 64, 192, 64), 48, 1025, 0), ((64, 64, 184, 64), 48, 1024, 0), ((64, 56, 200, 64), 48, 1024, 0),
+    ((64, 64, 192, 65), 48, 1024, 0), ((320, 64, 192, 96), 64, 1024, 32), ((312, 64, 192, 64), 64, 1024, 0), ((320, 64, 192, 97), 64, 1024, 0),
+    ((320, 64, 192, 96), 64, 1025, 0), ((64, 64, 192, 65), 24, 1024, 32),
     # 64 rows in one round only; replicas of less than half a block; half a round of wide layers behind few inputs
     ((264, 64, 10), 30, 517, 32), ((264, 64, 10), 28, 517, 64), ((400, 56, 272, 64, 18), 133, 77, 0), ((56, 16, 109), 273, 3, 0),
     ((56, 16, 109), 300, 15, 0), ((56, 16, 109), 300, 16, 32), ((8, 360, 104, 3), 14, 740, 0), ((8, 360, 104, 3), 16, 740, 64),
