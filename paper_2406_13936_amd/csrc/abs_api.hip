@@ -822,7 +822,7 @@ static abs_status local_step_impl(abs_ctx *c, const int32_t *idx_dev, int ldi, i
     rows = rows_dev;
     if (M >= 8) gperm = rows_dev + M;
   }
-  if (pl.softmax_chunks > 0 && ph.whole() && softmax_step_fits(pl.dims[1], pl.dims[0], b, M))
+  if (pl.softmax_chunks > 0 && ph.whole() && softmax_step_taken(pl.dims[1], pl.dims[0], b, M, pl.want_ip))
     return softmax_step(c, idx_dev, ldi, b, b_host, rows, lr, ph);
   int an_parts[MAXL + 1], dn_parts[MAXL + 2];
   for (int l = 0; l <= MAXL; ++l) an_parts[l] = dn_parts[l] = 1;

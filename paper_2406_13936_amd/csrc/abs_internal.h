@@ -213,6 +213,7 @@ int softmax_step_chunks(int d, int b);
 // The most chunks that a step of up to cap samples takes (a longer batch may take fewer: chunk_of), 0 where none is taken
 int softmax_step_max_chunks(int K, int d, int cap, int groups);
 bool softmax_step_fits(int K, int d, int b, int groups);
+bool softmax_step_taken(int K, int d, int b, int groups, int ip);        // and where it is the faster way (ip: with inner products)
 hipError_t launch_softmax_step(SoftmaxStepP p, hipStream_t s);
 
 // ---- gram_ip.hip -----------------------------------------------------------

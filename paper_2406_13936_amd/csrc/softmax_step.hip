@@ -467,7 +467,7 @@ int softmax_step_chunks(int d, int b) { return (b + chunk_of(d, b) - 1) / chunk_
 // with inner products 784-10, 16, b = 1024 165 -> 87, 1024-16, 4, b = 512 58.9 -> 53.5, 1024-16, 1, b = 512 56.0 -> 55.4.  At the line
 // both cost the same: 1024-16, 16, b = 1024 134 and 137.
 // Time of a step against the general launches, 1060 nets of 1 to 2048 features, 1 to 600 replicas, b = 2 to 1024:
-//   one work-group to a replica 0.17 to 0.99, on average 0.62;
+//   one work-group to a replica 0.17 to 0.99, on average 0.62 (many replicas of few features: softmax_step_taken);
 //   several, up to 768 in all 0.35 to 0.99, with 256 and more features 0.36 to 1.01 up to 2048: beyond, waves of work-groups come one after
 //     the other for few products each (23-6, 540 replicas, b = 588 273 -> 552 us; 1210-11, 307, b = 467 955 -> 1333);
 //   except that with fewer than 8 replicas the last work-group of each adds the partial gradients while other CUs idle: beyond 320 k floats of
@@ -480,6 +480,14 @@ bool softmax_step_fits(int K, int d, int b, int groups) {
   if (chunks == 1) return true;
   if ((long long)chunks * groups > (d < 256 ? 768 : 2048)) return false;
   return groups >= 8 || (d & 3 ? K * d <= 8192 : parts <= 320 * 1024);
+}
+
+// Many replicas of one work-group each come one round of CUs after the other, each with a way to the host of its own sums at its end, which the
+// general launches have once.  Step and test, 80 nets of 1 to 1038 features, 62 to 1420 replicas, b = 2 to 62, without inner products: from
+// 96 features 0.41 to 0.92 of the time; less of them with up to 384 replicas 0.63 to 1.03, with 385 to 620 0.92 to 1.10, beyond 1.01 to 1.13
+// (7-14, 743 replicas, b = 10 96.6 -> 108.7 us; steps without a test 46.8 -> 44).  With inner products, four to five general launches, 0.73 at most.
+bool softmax_step_taken(int K, int d, int b, int groups, int ip) {
+  return softmax_step_fits(K, d, b, groups) && (ip || d >= 96 || groups <= 384);
 }
 
 int softmax_step_max_chunks(int K, int d, int cap, int groups) {

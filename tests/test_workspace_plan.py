@@ -91,3 +91,13 @@ def test_slots_of_weight_gradient_tiles(fine, tile, waves):
     for Md, Nd in ((512, 512), (128, 128), (520, 136), (264, 784)):
         assert shape(Md, Nd, 4096, 8, 0, None) == 1
         assert slots(Md, Nd, 4096, 8, 0, fine, None) == -(-Md // tile[0]) * -(-Nd // tile[1]) * waves, (Md, Nd)
+
+
+# Replicas of one work-group each and few features: more than 384 of them are faster in the general launches, except with inner products
+@pytest.mark.parametrize("d,K,M,b,ip,taken", [
+    (7, 14, 743, 10, 0, 0), (7, 14, 743, 10, 1, 1), (30, 4, 500, 8, 0, 0), (95, 2, 385, 64, 0, 0), (95, 2, 384, 64, 0, 1), (96, 2, 5000, 64, 0, 1),
+    (2, 10, 4, 16, 0, 1), (64, 2, 384, 40, 0, 1), (64, 2, 385, 40, 0, 0), (64, 2, 256, 96, 0, 1), (1, 2, 600, 65, 1, 0), (17, 17, 4, 16, 1, 0)])
+def test_which_replicas_of_one_work_group_take_one_launch(d, K, M, b, ip, taken):
+    f = B.load_library()["_ZN4absk18softmax_step_takenEiiiii"]
+    f.restype = C.c_bool
+    assert f(K, d, b, M, ip) == bool(taken)
